@@ -163,10 +163,14 @@ int hdc_binarize_classical(hdc_ctx *ctx, const int32_t *acc_dev, const int64_t *
  * training.  Samples whose label is outside [0, C) are skipped.  The sequential
  * dependency between samples is the method's; one call is one dependency chain.
  * epochs >= 0; lr is the paper's learning rate gamma.  Beyond D = 32768 the call runs
- * hdc_train_online_batched with batches of one sample (the same method, three launches per sample).
- * Where the fastest kernel applies (C <= 12 with D <= 4096, or C <= 6 with D <= 10240) the first
- * call allocates 64 MB of context-owned scratch unless hdc_reserve has done so (HDC_ENOMEM if
- * that fails); later calls only enqueue on `stream`.  Other shapes allocate nothing.
+ * hdc_train_online_batched with batches of one sample (the same method).
+ * Up to C = 64 and D = 65535, calls of more than a few samples are worked off in blocks of 256
+ * samples: the chain is walked on the samples' scalar products with one another and the dot
+ * products with the rows at the block's start, then the updates are applied to the rows one by one.
+ * The cosines then leave out the fp32 rounding of the updates since the block's start (an error of
+ * about 1e-8, below what float(1 - cos) keeps).  The first call allocates context-owned scratch
+ * (11 MB + 16384 rows, at most 64 MB of them) unless hdc_reserve has done so (HDC_ENOMEM if that
+ * fails); later calls only enqueue on `stream`.
  */
 int hdc_train_online(hdc_ctx *ctx, const uint32_t *hv_dev, const int32_t *labels_dev, int64_t N,
                      int32_t epochs, float lr, float *acc_dev, void *stream);
@@ -180,7 +184,8 @@ int hdc_train_online(hdc_ctx *ctx, const uint32_t *hv_dev, const int32_t *labels
  *   delta[c] = sum over the batch of  +float(1 - cos_y) * s         for c == y
  *                                     -float(lr*(1 - cos_pred)) * s for c == pred != y
  * (fp64 sums) and acc[c] = float(double(acc[c]) + delta[c]), one rounding per element and
- * batch.  batch >= 1; a batch larger than N is one batch per epoch.  Other arguments, layout
+ * batch.  batch >= 1; a batch larger than N is one batch per epoch.  Small batches (up to 85 samples,
+ * C <= 64, D <= 65535) are worked off several at a time as described for hdc_train_online.  Other arguments, layout
  * and the treatment of out-of-range labels are those of hdc_train_online.  The first call,
  * and a call that needs more scratch than any before it (larger batch), allocates device
  * memory owned by the context (HDC_ENOMEM if that fails) and therefore synchronises the
@@ -257,7 +262,7 @@ int hdc_set_label_check(hdc_ctx *ctx, int enable);
  * Allocate now what entry points otherwise allocate at their first call (and which makes that
  * call synchronise the device): after hdc_reserve has covered the sizes that are used, no entry
  * point allocates, frees or synchronises.  `what` is a mask of
- *   HDC_RESERVE_ONLINE          the 64 MB of hdc_train_online's fast path
+ *   HDC_RESERVE_ONLINE          the scratch of hdc_train_online
  *   HDC_RESERVE_ONLINE_BATCHED  hdc_train_online_batched for batches of up to max_batch samples
  *   HDC_RESERVE_SEARCH_COSINE   hdc_search_cosine for calls of up to max_queries queries
  *   HDC_RESERVE_ENCODE_SPARSE   hdc_encode_sparse (its derived tables are computed on `stream`)

@@ -89,6 +89,17 @@ struct hdc_ctx_impl {
     size_t ob_meta_bytes;
     bool ob_attr_set;     // dynamic-LDS limit of the backward kernel raised
 
+    // Scratch of the block-wise online trainer (online_chain.hip), allocated on its first call.
+    int16_t *oc_gram_d;   // [blocks][10][64][64] scalar products of the samples of a block
+    size_t oc_gram_bytes;
+    uint64_t *oc_col_d;   // [ceil(D/64)][samples] 64-bit lane masks, dimension group major
+    size_t oc_col_bytes;
+    double *oc_part_d;    // [slices][C][256] partial dot products of a block
+    size_t oc_part_bytes;
+    void *oc_rec_d;       // [256] weight records of a block
+    size_t oc_rec_bytes;
+    bool oc_attr_set[6];  // dynamic-LDS limit of online_chain_kernel raised, by variant
+
     // hdc_encode_sparse (allocated and derived on its first call)
     bool sp_ready;
     uint32_t *sp_b_d;       // [slices][Fp][64] item ^ level 0 (of the compact tables when `compact`)

@@ -2,7 +2,9 @@
 //
 // The method is a dependency chain over the samples: every step needs the class
 // accumulators left by the step before (Sec. VI-D2 notes that this rules out parallelism over
-// the samples).  What
+// the samples).  Calls of more than a few samples walk it in blocks (online_chain.hip); the kernels
+// here walk it sample by sample: for the shortest calls, and for class counts and dimensions
+// the blocks do not take.  What
 // is parallel is the work inside one step - C dot products over D dimensions and at most two
 // row updates - so one persistent workgroup of 1024 threads walks the chain and spreads the
 // D dimensions over its lanes.  Thread t owns dimensions t, t+1024, ... in every phase, so a
@@ -11,6 +13,7 @@
 // or two rows that changed).  Dot products and norms are summed in fp64, the weights are
 // rounded once to fp32 and each accumulator element takes one fp32 add per update.
 #include "hdc_internal.h"
+#include "online_weight.h"
 
 namespace hdc {
 
@@ -538,10 +541,13 @@ __global__ __launch_bounds__(kOnlineThreads) void online_bits_kernel(const uint3
     tbits[(int64_t)blockIdx.x * kOnlineThreads + tid] = word;
 }
 
-constexpr int64_t kOnlineChunk = 16384;   // samples whose per-thread bit words are prepared at a time (64 MB)
+// Steps (samples x epochs) up to which a call is walked sample by sample where a kernel for it exists:
+// 12 us + 3.6 us a step at C = 6, D = 10000 against 32 us for a first block of up to 64 samples.
+constexpr int64_t kShortSteps = 6;
+constexpr int64_t kOnlineChunk = 8;   // samples whose per-thread bit words are prepared at a time (32 KB)
 
-// The per-thread sample words of the LDS variant of hdc_train_online (64 MB; a no-op when there).
-int reserve_online(hdc_ctx_impl *c) {
+// The per-thread sample words of online_lds_kernel (a no-op when there).
+static int reserve_words(hdc_ctx_impl *c) {
     if (c->on_bits_d) return HDC_OK;
     HDC_HIP(hipSetDevice(c->device));
     const hipError_t e = hipMalloc(reinterpret_cast<void **>(&c->on_bits_d),
@@ -552,6 +558,15 @@ int reserve_online(hdc_ctx_impl *c) {
     }
     HDC_HIP(e);
     return HDC_OK;
+}
+
+int reserve_online(hdc_ctx_impl *c) {
+    if (c->p.D > 32 * kOnlineThreads) {
+        const int rc = reserve_online_batched(c, 1);
+        if (rc != HDC_OK) return rc;
+    }
+    const int rc = online_chain_takes(c) ? reserve_online_chain(c) : HDC_OK;
+    return rc != HDC_OK ? rc : reserve_words(c);
 }
 
 template <int CMAX, int KPT>
@@ -566,7 +581,7 @@ static int launch_online_lds(hdc_ctx_impl *c, const uint32_t *hv, const int32_t 
         c->on_attr_set[CMAX] = true;
     }
     {
-        const int rc = reserve_online(c);
+        const int rc = reserve_words(c);
         if (rc != HDC_OK) return rc;
     }
     // A set that fits one chunk is prepared once and walked `epochs` times by one launch; a
@@ -599,32 +614,23 @@ static int launch_online_reg(hdc_ctx_impl *c, const uint32_t *hv, const int32_t 
 int launch_train_online(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *labels, int64_t N,
                         int32_t epochs, float lr, float *acc, hipStream_t s) {
     const int C = c->p.C;
-    // a thread keeps its sample bits in one word: beyond 32768 dimensions the batched trainer runs
-    // with batches of one sample, which is the same method (slower: three launches per sample)
-    if (c->p.D > 32 * kOnlineThreads) return launch_train_online_batched(c, hv, labels, N, epochs, lr, 1, acc, s);
-    // Register-resident kernel when C x (dimensions per thread) fits the register file.
     const int kpt = (c->p.D + kOnlineThreads - 1) / kOnlineThreads;
+    const bool blocks = online_chain_takes(c), brief = N * epochs <= kShortSteps;
+    // a thread keeps its sample bits in one word: beyond 32768 dimensions the batched trainer runs
+    // with batches of one sample, which is the same method (in blocks, from four samples on)
+    if (kpt > 32) return launch_train_online_batched(c, hv, labels, N, epochs, lr, 1, acc, s);
 #define HDC_ONLINE_LDS_CASE(CM, KP) \
-    if (C <= CM && kpt <= KP) return launch_online_lds<CM, KP>(c, hv, labels, N, epochs, lr, acc, s)
+    if (brief && C <= CM && kpt <= KP) return launch_online_lds<CM, KP>(c, hv, labels, N, epochs, lr, acc, s)
     HDC_ONLINE_LDS_CASE(8, 2);
     HDC_ONLINE_LDS_CASE(4, 4);
     HDC_ONLINE_LDS_CASE(12, 4);
     HDC_ONLINE_LDS_CASE(2, 10);
     HDC_ONLINE_LDS_CASE(6, 10);
 #undef HDC_ONLINE_LDS_CASE
-#define HDC_ONLINE_CASE(CM, KP) \
-    if (C <= CM && kpt <= KP) return launch_online_reg<CM, KP>(c, hv, labels, N, epochs, lr, acc, s)
-    HDC_ONLINE_CASE(8, 1);
-    HDC_ONLINE_CASE(32, 1);
-    HDC_ONLINE_CASE(80, 1);
-    HDC_ONLINE_CASE(8, 2);
-    HDC_ONLINE_CASE(40, 2);
-    HDC_ONLINE_CASE(4, 4);
-    HDC_ONLINE_CASE(20, 4);
-    HDC_ONLINE_CASE(2, 10);
-    HDC_ONLINE_CASE(6, 10);
-    HDC_ONLINE_CASE(2, 16);
-#undef HDC_ONLINE_CASE
+    if (brief && C <= 2 && kpt <= 16) return launch_online_reg<2, 16>(c, hv, labels, N, epochs, lr, acc, s);
+    if (blocks) return launch_online_chain(c, hv, labels, N, epochs, lr, 1, true, acc, s);
+    // more than 64 classes: in registers while they fit, else with the accumulators in memory
+    if (C <= 80 && kpt <= 1) return launch_online_reg<80, 1>(c, hv, labels, N, epochs, lr, acc, s);
     const size_t lds = (size_t)(2 + kOnlineWaves) * (C < 2 ? 2 : C) * sizeof(double);
     auto kern = online_kernel;
     if (lds > 64 * 1024)

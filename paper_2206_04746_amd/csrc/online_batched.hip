@@ -13,18 +13,12 @@
 #include <type_traits>
 
 #include "hdc_internal.h"
+#include "online_weight.h"
 
 namespace hdc {
 
 typedef const uint32_t __attribute__((address_space(4))) *kptr_u32;
 
-// One record per sample of the batch, written by the weights step, read by the backward step.
-struct OnlineWeight {
-    int32_t y;      // label, or -1: sample skipped
-    int32_t pred;   // predicted class if it differs from y, else -1
-    float w_y;      // float(1 - cos_y)
-    float w_p;      // float(lr * (1 - cos_pred))
-};
 typedef const OnlineWeight __attribute__((address_space(4))) *kptr_w;
 
 constexpr int kFwdWaves = 4;     // waves per forward block
@@ -788,22 +782,6 @@ __global__ __launch_bounds__(256) void cosine_finish_kernel(
 }
 
 // ---- host side ---------------------------------------------------------------------------------
-template <typename T>
-static int grow(T **p, size_t *have, size_t want) {
-    if (*have >= want) return HDC_OK;
-    if (*p) HDC_HIP(hipFree(*p));   // waits for the device: nothing still reads the old buffer
-    *p = nullptr;
-    *have = 0;
-    const hipError_t e = hipMalloc(reinterpret_cast<void **>(p), want + 256);
-    if (e == hipErrorOutOfMemory) {
-        (void)hipGetLastError();
-        return HDC_ENOMEM;
-    }
-    HDC_HIP(e);
-    *have = want;
-    return HDC_OK;
-}
-
 // Width of the dense coefficient rows of the backward step, 0 = none (LDS sums).
 static int bwd_dense_width(int C) { return C <= 2 ? 2 : C <= 4 ? 4 : C <= 8 ? 8 : C <= 16 ? 16 : 0; }
 
@@ -949,7 +927,7 @@ static int launch_fwd(hdc_ctx_impl *c, const FwdShape &f, const uint32_t *rows, 
     return HDC_OK;
 }
 
-static int launch_norm(hdc_ctx_impl *c, const float *acc, int G, hipStream_t s) {
+int launch_norm(hdc_ctx_impl *c, const float *acc, int G, hipStream_t s) {
     hipLaunchKernelGGL(online_norm_kernel, dim3((unsigned)G, (unsigned)((c->p.C + 3) / 4)), dim3(256), 0, s, acc,
                        c->p.D, c->p.C, G, c->ob_norm_d);
     HDC_HIP(hipGetLastError());
@@ -958,7 +936,7 @@ static int launch_norm(hdc_ctx_impl *c, const float *acc, int G, hipStream_t s) 
 
 // Scratch of hdc_train_online_batched for batches of up to `batch` samples (grown if smaller; a
 // no-op, without any synchronisation, when it is there already).
-int reserve_online_batched(hdc_ctx_impl *c, int64_t batch) {
+static int reserve_pieces(hdc_ctx_impl *c, int64_t batch) {
     const int C = c->p.C, D = c->p.D;
     const int G = (D + kWave - 1) / kWave;
     const FwdShape f = fwd_shape(C, G);
@@ -986,6 +964,13 @@ int reserve_online_batched(hdc_ctx_impl *c, int64_t batch) {
     return rc;
 }
 
+// What hdc_train_online_batched may need for batches of up to `batch` samples: a call works in pieces of
+// a batch or, where that is faster, in blocks of several.
+int reserve_online_batched(hdc_ctx_impl *c, int64_t batch) {
+    const int rc = online_chain_takes(c) ? reserve_online_chain(c) : HDC_OK;
+    return rc != HDC_OK ? rc : reserve_pieces(c, batch);
+}
+
 // Scratch of hdc_search_cosine for calls of up to `queries` queries.
 int reserve_search_cosine(hdc_ctx_impl *c, int64_t queries) {
     const int C = c->p.C, G = (c->p.D + kWave - 1) / kWave;
@@ -1003,12 +988,13 @@ int launch_train_online_batched(hdc_ctx_impl *c, const uint32_t *hv, const int32
     const int G = (D + kWave - 1) / kWave;
     const FwdShape f = fwd_shape(C, G);
     if (batch > N) batch = N;
+    if (online_chain_takes(c) && online_chain_pays(N, batch)) return launch_online_chain(c, hv, labels, N, epochs, lr, batch, false, acc, s);
 
     // A batch is worked off in pieces of at most `sb` samples (forward, weights, backward each);
     // sb bounds the scratch: partial dot products and transposed masks.
     const int64_t sb = fwd_sub_batch(f, C, batch);
     const int cb = bwd_dense_width(C);
-    int rc = reserve_online_batched(c, batch);
+    int rc = reserve_pieces(c, batch);
     if (rc != HDC_OK) return rc;
     if (!c->ob_attr_set) {
         const void *kernels[] = {reinterpret_cast<const void *>(online_bwd_kernel<0>),

@@ -1,0 +1,725 @@
+// Online training, per sample and in small batches, as a few parallel steps per block of up to 256
+// samples (arXiv 2206.04746, Sec. III Eqs. 2-3, caption of Fig. 1; Sec. VI-D2 for batches).
+//
+// The method is a dependency chain: a sample's cosines need the class rows as the sample (or batch)
+// before left them.  But a row only ever moves along samples, so within a block of samples
+//     <acc_c before m, s_m> = <acc_c at the block's start, s_m> + sum over earlier n of k_n,c <s_n, s_m>
+// and the whole chain can be walked on the scalar products of the samples with one another, which
+// do not depend on the rows.  Four kernels:
+//   online_gram_kernel   once per call: <s_n, s_m> of all pairs of a block (XOR + popcount)
+//   online_dots_kernel   per block: <acc_c, s_m> against the rows at the block's start (fp64)
+//   online_chain_kernel  per block, one workgroup: cosines, predictions and weights of all samples
+//   online_rows_kernel   per block: the updates applied to the rows element by element, in sample
+//                        order, one fp32 rounding per update (per batch: one per batch), and the rows'
+//                        new squared norms
+// The dot products stay fp64 sums of the same fp32 rows and fp32 weights.  Inside a block they leave
+// out the fp32 rounding of the updates made since the block began: at most 2^-24 of an element per
+// update, which moves a cosine by some 1e-8 (measured at 561 features, 6 classes, D = 10000: median
+// 5e-9, largest 3e-8), below the 6e-8 to which the weight made from it is rounded.
+//
+// Walking the chain sample after sample on one workgroup took 3.6 us per sample (two block barriers
+// and a block-wide sum for each).
+#include <algorithm>
+
+#include "hdc_internal.h"
+#include "online_weight.h"
+
+namespace hdc {
+
+constexpr int kChainBlock = 256;                    // most samples of a block
+constexpr int kSub = 64;                            // samples of a sub-block: one per lane
+constexpr int kSubs = kChainBlock / kSub;
+constexpr int kTile = kSub * kSub;                  // products of one pair of sub-blocks
+constexpr int kTiles = kSubs * (kSubs + 1) / 2;     // pairs (a, b), a <= b, at b (b + 1) / 2 + a
+constexpr int64_t kGramSamples = 16384;             // samples whose products are held at a time
+constexpr int64_t kGramBlocks = kGramSamples / (kChainBlock / 2 + 1) + 2;   // a block has more than 128 samples
+constexpr int kChainMaxWaves = 16;
+constexpr int kSlices = 10;                         // most slices the dimensions are split into
+
+// ---- the samples' bits, dimension group by dimension group ----------------------------------------
+// col[g][n] = bits 64 g .. 64 g + 63 of sample n: the steps below work on one group of all samples of a
+// block, which row by row would be 8 bytes out of every 4 W (the rows step took 16 us like that, most of
+// it in these loads).  A block turns 64 samples x 16 groups through LDS.  grid (sample tiles, group tiles)
+constexpr int kColGroups = 16;
+__global__ __launch_bounds__(256) void online_columns_kernel(const uint32_t *__restrict__ hv, int64_t N, int W, int G,
+                                                             int64_t ld, uint64_t *__restrict__ col) {
+    __shared__ uint32_t tile[kSub][2 * kColGroups + 1];
+    const int t = threadIdx.x;
+    const int64_t n0 = (int64_t)blockIdx.x * kSub;
+    const int g0 = blockIdx.y * kColGroups;
+#pragma unroll
+    for (int r = 0; r < kSub / 8; ++r) {
+        const int sm = r * 8 + (t >> 5), w = 2 * g0 + (t & 31);
+        tile[sm][t & 31] = (n0 + sm < N && w < W) ? hv[(n0 + sm) * W + w] : 0u;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kColGroups / 4; ++i) {
+        const int gg = (t >> 6) + 4 * i, sm = t & 63;
+        if (g0 + gg < G)
+            col[(int64_t)(g0 + gg) * ld + n0 + sm] = (uint64_t)tile[sm][2 * gg] | ((uint64_t)tile[sm][2 * gg + 1] << 32);
+    }
+}
+
+// ---- products of the samples of a block ---------------------------------------------------------
+// grid (pair (a, b) of sub-blocks, block).  <s_n, s_m> = D - 2 popcount(h_n ^ h_m) is stored as
+// (D >> 1) - popcount, which fits 16 bits up to D = 65535.  popcount(h_n ^ h_m) = |h_n| + |h_m| - 2 <h_n, h_m>,
+// the last term a product of 0/1 vectors on 4-bit floats: a nibble with one bit set is worth 0.5, 1 or 2,
+// so the bits stay where they are in one operand and carry the reciprocal in the other (search_mfma.hip
+// tells the whole of it); a step is 64 dimensions, a word per lane.  The eight waves split the dimensions
+// and add up 64 x 64 whole numbers in LDS.  7352 samples at D = 10000: XOR and popcount on the
+// vector unit took 59 us, this 15.
+constexpr int kGramWaves = 8, kGramPitch = kSub + 8;   // (the two halves of a wave add to different banks)
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+
+__global__ __launch_bounds__(kGramWaves *kWave) void online_gram_kernel(const uint64_t *__restrict__ col, int64_t ld,
+                                                                        int64_t N, int D, int G, int block,
+                                                                        int16_t *__restrict__ gram) {
+    __shared__ int sum[kSub][kGramPitch];
+    __shared__ int ones[2][kSub];
+    int b = 0;
+    while ((b + 1) * (b + 2) / 2 <= (int)blockIdx.x) ++b;
+    const int a = (int)blockIdx.x - b * (b + 1) / 2;
+    const int64_t n0 = (int64_t)blockIdx.y * block;
+    const int nb = (int)(N - n0 < block ? N - n0 : block);
+    if (b * kSub >= nb) return;
+    const int t = threadIdx.x, lane = t & (kWave - 1), wave = t >> 6;
+    const int r = lane & 31, half = lane >> 5;   // this lane's sample of a tile of 32, and its word of a group
+    for (int i = t; i < kSub * kGramPitch; i += kGramWaves * kWave) (&sum[0][0])[i] = 0;
+    if (t < 2 * kSub) (&ones[0][0])[t] = 0;
+    const uint32_t *src[4];   // rows a 64 + r, + 32; columns b 64 + r, + 32
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int n = min((i < 2 ? a : b) * kSub + 32 * (i & 1) + r, nb - 1);
+        src[i] = reinterpret_cast<const uint32_t *>(col + n0 + n) + half;
+    }
+    v16f dot[2][2] = {};
+    int pop[4] = {0, 0, 0, 0};
+    constexpr int U = 4;   // groups a trip; those past the last read as zeros
+    for (int g0 = wave; g0 < G; g0 += U * kGramWaves) {
+        uint32_t x[U][4];
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) x[k][i] = src[i][2 * (int64_t)min(g0 + k * kGramWaves, G - 1) * ld];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            v8i op[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                x[k][i] = g0 + k * kGramWaves < G ? x[k][i] : 0u;
+                pop[i] += __popc(x[k][i]);
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const uint32_t u = x[k][i], v = x[k][2 + i];
+                op[i] = v8i{(int)(u & 0x11111111u), (int)(u & 0x22222222u), (int)(u & 0x44444444u),
+                            (int)((u >> 1) & 0x44444444u), 0, 0, 0, 0};
+                op[2 + i] = v8i{(int)((v << 2) & 0x44444444u), (int)(v & 0x22222222u), (int)((v >> 2) & 0x11111111u),
+                                (int)((v >> 3) & 0x11111111u), 0, 0, 0, 0};
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    dot[i][j] =
+                        __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(op[i], op[2 + j], dot[i][j], 4, 4, 0, 0, 0, 0);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) atomicAdd(&ones[i >> 1][32 * (i & 1) + r], pop[i]);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int k = 0; k < 16; ++k)   // register k: row 8 (k / 4) + 4 half + k % 4, column r
+                atomicAdd(&sum[32 * i + 8 * (k / 4) + 4 * half + k % 4][32 * j + r], (int)dot[i][j][k]);
+    __syncthreads();
+    int16_t *out = gram + ((int64_t)blockIdx.y * kTiles + blockIdx.x) * kTile;
+    for (int i = t; i < kTile; i += kGramWaves * kWave) {
+        const int u = i / kSub, v = i % kSub;
+        out[i] = (int16_t)((D >> 1) - ones[0][u] - ones[1][v] + 2 * sum[u][v]);
+    }
+}
+
+// ---- dot products against the rows at the block's start -----------------------------------------
+// grid (slices of the dimensions, tiles of 16 samples, tiles of 16 classes), 8 waves a block that
+// split the slice.  On the matrix cores in fp64: their rate equals the vector unit's on this chip, but
+// the sum over the dimensions comes with the instruction, where the vector form spends a cross-lane
+// sum per (sample, class).  Any assignment of dimensions to the instruction's K positions will
+// do as long as both operands agree: lane 16 q + i takes dimensions 16 q .. 16 q + 15 of a group of
+// 64, so that it loads 64 consecutive bytes of row i and 16 bits of sample i.  Output
+// part[slice][class][sample].
+constexpr int kDotWaves = 8;
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+__global__ __launch_bounds__(kDotWaves *kWave) void online_dots_kernel(const uint64_t *__restrict__ col,
+                                                                       int64_t ld, int nb,
+                                                                       const float *__restrict__ acc, int D, int C,
+                                                                       int slice, double *__restrict__ part) {
+    __shared__ double red[kDotWaves][256];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    const int q = lane >> 4, i = lane & 15;
+    int n = blockIdx.y * 16 + i;
+    n = n < nb ? n : nb - 1;
+    const int c = blockIdx.z * 16 + i;
+    const uint16_t *h = reinterpret_cast<const uint16_t *>(col) + 4 * (int64_t)n + q;   // this lane's 16 bits of a group
+    const float *row = acc + (int64_t)(c < C ? c : C - 1) * D;
+    const int span = slice / kDotWaves;   // a multiple of 64
+    const int lo = blockIdx.x * slice + wave * span;
+    const int hi = lo + span < D ? lo + span : D;
+    f64x4 sum = {0.0, 0.0, 0.0, 0.0};
+    for (int d0 = lo; d0 < hi; d0 += kWave) {
+        const int d = d0 + 16 * q;
+        const uint32_t inv = ~(uint32_t)h[(int64_t)(d0 >> 6) * ld * 4];   // bit k: the sign of dimension d + k
+        float x[16];
+        if (d + 16 <= D) {
+            __builtin_memcpy(x, row + d, sizeof(x));
+        } else {
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const float v = row[d + k < D ? d + k : D - 1];
+                x[k] = d + k < D ? v : 0.0f;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const int hi32 = (int)(((inv << (31 - k)) & 0x80000000u) | 0x3FF00000u);
+            sum = __builtin_amdgcn_mfma_f64_16x16x4f64(__hiloint2double(hi32, 0), (double)x[k], sum, 0, 0, 0);
+        }
+    }
+    // register r of lane 16 q + i: sample 4 r + q, class i
+#pragma unroll
+    for (int r = 0; r < 4; ++r) red[wave][(4 * r + q) * 16 + i] = sum[r];
+    __syncthreads();
+    const int t = threadIdx.x;
+    if (t < 256) {
+        const int cc = blockIdx.z * 16 + (t >> 4), m = blockIdx.y * 16 + (t & 15);
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < kDotWaves; ++w) s += red[w][(t & 15) * 16 + (t >> 4)];
+        if (cc < C) part[((int64_t)blockIdx.x * C + cc) * kChainBlock + m] = s;
+    }
+}
+
+// ---- the chain -----------------------------------------------------------------------------------
+__device__ __forceinline__ float lane_f32(float v, int i) {
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i));
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xF, ROWS == 0xF);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xF, ROWS == 0xF);
+    return v + __hiloint2double(hi, lo);
+}
+// Inclusive sum over the lanes: four shifts within a row of 16, then the row totals.
+__device__ __forceinline__ double lane_prefix(double v) {
+    v = dpp_add<0x111, 0xF>(v);   // row_shr:1
+    v = dpp_add<0x112, 0xF>(v);
+    v = dpp_add<0x114, 0xF>(v);
+    v = dpp_add<0x118, 0xF>(v);
+    v = dpp_add<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
+    v = dpp_add<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
+    return v;
+}
+__device__ __forceinline__ double lane_f64(double v, int i) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), i),
+                            __builtin_amdgcn_readlane(__double2loint(v), i));
+}
+// The value of the lane before (lane 0: zero).
+__device__ __forceinline__ double lane_before(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xF, 0xF, true);   // wave_shr:1
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xF, 0xF, true);
+    return __hiloint2double(hi, lo);
+}
+
+// One workgroup; wave w has classes w CPW .. w CPW + CPW - 1, lane m of it sample m of the sub-block.
+//
+// Sub-block after sub-block: the samples' weights k_n,c (nonzero for the label's class and a wrong
+// prediction's) are found as the fixed point of
+//     dot_m,c  = D0_m,c + sum over n < m of k_n,c <s_n, s_m>
+//     |acc_c|^2 before m = its value at the sub-block's start + sum over n < m of 2 k_n,c dot_n,c + k_n,c^2 D
+//     cosines, prediction, k_m,.
+// by plain iteration from k = 0.  It is triangular - pass t leaves the first t samples final - so the
+// fixed point is unique, is what the walk sample by sample gives, and at most 64 passes reach it;
+// because one sample moves the cosines of the others little, four or five do (the last one only
+// finds that no weight changed in any bit), 8 to 18 in the first few sub-blocks of a zero model.  A pass
+// costs about two samples of a walk.  In batches (BATCH) only samples of earlier batches count
+// for dot and norm of a sample; the number of batch starts in a sub-block bounds the passes.
+//
+// What bounds it is latency, so: everything that comes from memory is asked for at the start, by
+// sixteen waves (those without classes leave then); a wave sums over the samples that name its class
+// only (a ballot lists them) and keeps their products in registers from pass to pass, for as
+// long as the list is the same; the best cosine of each wave meets the others' in LDS, where every wave
+// takes the same decision for all 64 samples: one barrier a pass (two LDS areas in turn).
+template <int CPW, bool BATCH>
+__global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
+    const int16_t *__restrict__ gram, const double *__restrict__ part, int slices, int nb, int batch,
+    const int32_t *__restrict__ labels, const double *__restrict__ normpart, int G, int C, int D, float lr,
+    double inv_root_d, OnlineWeight *__restrict__ out) {
+    constexpr int kKept = CPW == 1 ? 24 : CPW == 2 ? 12 : 4;   // list entries of a class whose products stay in registers
+    extern __shared__ __align__(16) int16_t prod[];   // the tiles of the block's sub-blocks
+    __shared__ double s_best[2][kChainMaxWaves][kSub];
+    __shared__ double s_cosy[2][kSub];
+    __shared__ int s_pred[CPW > 1 ? 2 : 1][CPW > 1 ? kChainMaxWaves : 1][kSub];
+    __shared__ OnlineWeight s_rec[kChainBlock];
+    __shared__ uint2 s_list[kChainMaxWaves][kChainBlock];   // a wave's own: weight and place of the samples that name its class
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int subs = (nb + kSub - 1) / kSub;
+    const int used = (C + CPW - 1) / CPW;   // waves that have classes
+    constexpr int kCopies = kTiles * kTile * 2 / 16 / (kChainMaxWaves * kWave);
+    uint4 copy[kCopies];
+    const int units = subs * (subs + 1) / 2 * (kTile * 2 / 16);
+#pragma unroll
+    for (int u = 0; u < kCopies; ++u)
+        copy[u] = reinterpret_cast<const uint4 *>(gram)[min(tid + u * kChainMaxWaves * kWave, units - 1)];
+    double nrm[CPW], nrm_fb[CPW];   // squared norms before the sub-block; and where the batch that runs into it began
+    double start[CPW][kSubs];       // dot products against the rows at the block's start
+    int label[kSubs];
+#pragma unroll
+    for (int j = 0; j < kSubs; ++j) {
+        const int y = labels[min(j * kSub + lane, nb - 1)];
+        label[j] = j * kSub + lane < nb && y >= 0 && y < C ? y : -1;
+    }
+#pragma unroll
+    for (int k = 0; k < CPW; ++k) {
+        const int c = wave * CPW + k;
+        nrm[k] = nrm_fb[k] = 0.0;
+#pragma unroll
+        for (int j = 0; j < kSubs; ++j) start[k][j] = 0.0;
+        if (c < C) {
+            double s = 0.0;
+            for (int g0 = 0; g0 < G; g0 += 4 * kWave) {
+                double p[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) p[i] = normpart[(int64_t)c * G + min(g0 + i * kWave + lane, G - 1)];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s += g0 + i * kWave + lane < G ? p[i] : 0.0;
+            }
+            double x[kSlices][kSubs];
+#pragma unroll
+            for (int i = 0; i < kSlices; ++i)
+#pragma unroll
+                for (int j = 0; j < kSubs; ++j)
+                    x[i][j] = part[((int64_t)min(i, slices - 1) * C + c) * kChainBlock + j * kSub + lane];
+#pragma unroll
+            for (int i = 0; i < kSlices; ++i)
+#pragma unroll
+                for (int j = 0; j < kSubs; ++j) start[k][j] += i < slices ? x[i][j] : 0.0;
+            nrm[k] = nrm_fb[k] = lane_f64(lane_prefix(s), kWave - 1);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < kCopies; ++u)
+        if (tid + u * kChainMaxWaves * kWave < units)
+            reinterpret_cast<uint4 *>(prod)[tid + u * kChainMaxWaves * kWave] = copy[u];
+    __syncthreads();
+    if (wave >= used) return;   // (an ended wave takes no part in later barriers)
+    const int odd = D & 1;
+    const double dd = (double)D;
+
+    // adds w_i <s_i, s_lane> over the listed samples i < lane of the diagonal tile to `all`, and to `some` where i < lim
+    auto walk = [&](uint64_t list, double w, const int16_t *tile, int lim, double &all, double &some) {
+        constexpr int U = 8;   // entries at a time; past the list's end weight 0
+        while (list) {
+            int at[U], g[U];
+            double v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                at[u] = (__ffsll((long long)list) - 1) & (kSub - 1);
+                const double x = lane_f64(w, at[u]);
+                v[u] = list ? x : 0.0;
+                list &= list - 1;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) g[u] = 2 * (int)tile[at[u] * kSub + lane] + odd;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (BATCH) some = fma(v[u], (double)(at[u] < lim ? g[u] : 0), some);
+                all = fma(v[u], (double)(at[u] < lane ? g[u] : 0), all);
+            }
+        }
+    };
+
+    int buf = 0;
+    for (int j = 0; j < subs; ++j) {
+        const int m0 = j * kSub, m = m0 + lane;
+        int y = label[0];
+        const int fb = BATCH ? m / batch * batch : m;   // first sample that does not count for this one
+        int passes = kSub;
+        if (BATCH) passes = 1 + (m0 + kSub - 1) / batch - m0 / batch;
+        double d0[CPW], d0_all[CPW];
+#pragma unroll
+        for (int k = 0; k < CPW; ++k) d0[k] = d0_all[k] = start[k][0];
+#pragma unroll
+        for (int i = 0; i + 1 < kSubs; ++i) {   // the next sub-block's move up
+            label[i] = label[i + 1];
+#pragma unroll
+            for (int k = 0; k < CPW; ++k) start[k][i] = start[k][i + 1];
+        }
+        // What the sub-blocks before this one add: their entries of the class side by side in the
+        // wave's own list, then eight at a time (every lane reads the same entry and its own product).
+        if (j > 0) {
+            const int16_t *tiles = prod + j * (j + 1) / 2 * kTile + lane;   // row n of tile a is row a 64 + n here
+#pragma unroll
+            for (int k = 0; k < CPW; ++k) {
+                const int c = wave * CPW + k;
+                int entries = 0;
+                for (int a = 0; a < j; ++a) {
+                    const OnlineWeight r = s_rec[a * kSub + lane];
+                    const float w = r.y == c ? r.w_y : r.pred == c ? -r.w_p : 0.0f;
+                    const uint64_t list = __ballot(w != 0.0f);
+                    const int at = entries + __popcll(list & ((1ull << lane) - 1));
+                    if (w != 0.0f) s_list[wave][at] = make_uint2(__float_as_uint(w), (uint32_t)(a * kSub + lane));
+                    entries += __popcll(list);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                for (int e = 0; e < entries; e += 8) {
+                    uint2 x[8];
+                    int g[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) x[u] = s_list[wave][min(e + u, entries - 1)];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) g[u] = 2 * (int)tiles[x[u].y * kSub] + odd;
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const double v = e + u < entries ? (double)__uint_as_float(x[u].x) : 0.0;
+                        if (BATCH) d0[k] = fma(v, (double)((int)x[u].y < fb ? g[u] : 0), d0[k]);
+                        d0_all[k] = fma(v, (double)g[u], d0_all[k]);
+                    }
+                }
+                if (!BATCH) d0[k] = d0_all[k];
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();   // the list is rewritten for the next class
+            }
+        }
+        const int16_t *diag = prod + (j * (j + 1) / 2 + j) * kTile;
+        float wy = 0.0f, wp = 0.0f;
+        int pred = -1;
+        double before[CPW] = {}, total[CPW] = {};   // what the sub-block adds to the squared norms, before each sample and in all
+        uint64_t known[CPW] = {};      // the list whose first products are kept: entry u is sample at[][u]
+        int at[CPW][kKept] = {};
+        double kept[CPW][kKept] = {};
+        auto norms = [&](int k, double &dot) {
+            const int c = wave * CPW + k;
+            const float wf = y == c ? wy : pred == c ? -wp : 0.0f;
+            const double w = (double)wf;
+            const uint64_t list = __ballot(wf != 0.0f);
+            const int entries = __popcll(list);
+            double all = d0_all[k], all1 = 0.0;
+            dot = d0[k];
+            uint64_t rest = list;
+            const bool renew = list != known[k];
+            known[k] = list;
+#pragma unroll
+            for (int q = 0; q < kKept; q += 4) {
+                if (entries > q) {   // uniform, like renew
+                    if (renew) {
+#pragma unroll
+                        for (int u = q; u < q + 4; ++u) {
+                            at[k][u] = (__ffsll((long long)rest) - 1) & (kSub - 1);   // past the end the last sample: nobody comes after it
+                            rest &= rest - 1;
+                        }
+#pragma unroll
+                        for (int u = q; u < q + 4; ++u) {
+                            const int g = 2 * (int)diag[at[k][u] * kSub + lane] + odd;
+                            kept[k][u] = (double)(at[k][u] < lane ? g : 0);
+                        }
+                    }
+#pragma unroll
+                    for (int u = q; u < q + 4; ++u) {
+                        const double v = lane_f64(w, at[k][u]);
+                        if (BATCH) dot = fma(v, at[k][u] < fb - m0 ? kept[k][u] : 0.0, dot);
+                        if (u & 1)
+                            all1 = fma(v, kept[k][u], all1);
+                        else
+                            all = fma(v, kept[k][u], all);
+                    }
+                }
+            }
+            all += all1;
+            if (entries > kKept) {
+                rest = list;
+#pragma unroll
+                for (int u = 0; u < kKept; ++u) rest &= rest - 1;
+                walk(rest, w, diag, fb - m0, all, dot);
+            }
+            if (!BATCH) dot = all;
+            const double sum = lane_prefix(wf != 0.0f ? w * (2.0 * all + w * dd) : 0.0);
+            before[k] = lane_before(sum);
+            total[k] = lane_f64(sum, kWave - 1);
+        };
+        bool settled = false;
+        for (int pass = 1; !settled && pass <= passes; ++pass) {
+            double best = -4.0;
+            int arg = 0;
+#pragma unroll
+            for (int k = 0; k < CPW; ++k) {
+                const int c = wave * CPW + k;
+                if (c < C) {
+                    double dot;
+                    norms(k, dot);
+                    double nn = nrm[k] + before[k];
+                    if (BATCH) nn = fb >= m0 ? nrm[k] + __shfl(before[k], fb - m0, kWave) : nrm_fb[k];
+                    double r = __builtin_amdgcn_rsq(nn);
+                    r = r * fma(-0.5 * nn * r, r, 1.5);
+                    r = r * fma(-0.5 * nn * r, r, 1.5);
+                    const double cs = nn > 0.0 ? dot * r * inv_root_d : 0.0;
+                    if (y == c) s_cosy[buf][lane] = cs;
+                    if (cs > best) {
+                        best = cs;
+                        arg = c;
+                    }
+                }
+            }
+            s_best[buf][wave][lane] = best;
+            if constexpr (CPW > 1) s_pred[buf][wave][lane] = arg;
+            __syncthreads();
+            const double cos_y = s_cosy[buf][lane];
+            best = -4.0;
+            arg = 0;
+            for (int w0 = 0; w0 < used; w0 += 8) {   // eight waves' bests at a time (the last one repeats: it cannot win twice)
+                double v[8];
+                int p[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    p[u] = min(w0 + u, used - 1);
+                    v[u] = s_best[buf][p[u]][lane];
+                    if constexpr (CPW > 1) p[u] = s_pred[buf][p[u]][lane];
+                }
+                const double top = fmax(fmax(fmax(v[0], v[1]), fmax(v[2], v[3])), fmax(fmax(v[4], v[5]), fmax(v[6], v[7])));
+                int first = p[7];
+#pragma unroll
+                for (int u = 6; u >= 0; --u) first = v[u] == top ? p[u] : first;
+                if (top > best) {
+                    best = top;
+                    arg = first;
+                }
+            }
+            float wy1 = 0.0f, wp1 = 0.0f;
+            int pred1 = -1;
+            if (y >= 0) {
+                wy1 = (float)(1.0 - cos_y);
+                if (arg != y) {
+                    pred1 = arg;
+                    wp1 = (float)((double)lr * (1.0 - best));
+                }
+            }
+            settled = __ballot(wy1 != wy || wp1 != wp || pred1 != pred) == 0;
+            wy = wy1;
+            wp = wp1;
+            pred = pred1;
+            buf ^= 1;
+        }
+#pragma unroll
+        for (int k = 0; k < CPW; ++k) {
+            double dot;
+            if (!settled) norms(k, dot);   // the last pass used the weights of the one before
+            if (BATCH) {
+                const int next = (m0 + kSub) / batch * batch;   // where the next sub-block's first batch begins
+                if (next >= m0 && next < m0 + kSub) nrm_fb[k] = nrm[k] + lane_f64(before[k], next - m0);
+            }
+            nrm[k] += total[k];
+            if (BATCH && (m0 + kSub) % batch == 0) nrm_fb[k] = nrm[k];
+        }
+        if (wave == 0) {
+            const OnlineWeight r = {y, pred, wy, wp};
+            s_rec[m] = r;
+            if (m < nb) out[m] = r;
+        }
+        __syncthreads();
+    }
+}
+
+// ---- the rows ------------------------------------------------------------------------------------
+// A block per group of 64 dimensions, waves deal the classes among them.  A lane keeps one element of
+// a row in a register and takes the updates that name its class in sample order: the listed samples'
+// weight and 64 bits come by lane reads, so nothing in the loop waits for memory.  Per sample one fp32
+// add (the method's rounding); in batches an fp64 sum per batch and one rounding.
+template <bool BATCH>
+__global__ __launch_bounds__(kChainMaxWaves *kWave) void online_rows_kernel(
+    const uint64_t *__restrict__ col, int64_t ld, int nb, int batch, const OnlineWeight *__restrict__ recs, float *acc,
+    int D, int C, int G, double *__restrict__ normpart) {
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
+    const int g = blockIdx.x, d = g * kWave + lane;
+    OnlineWeight rec[kSubs];
+    uint64_t bits[kSubs];
+#pragma unroll
+    for (int j = 0; j < kSubs; ++j) {
+        const int n = min(j * kSub + lane, nb - 1);
+        rec[j] = recs[n];
+        bits[j] = col[(int64_t)g * ld + n];
+    }
+    for (int c = wave; c < C; c += nw) {
+        float a = d < D ? acc[(int64_t)c * D + d] : 0.0f;
+        double delta = 0.0;
+        int end = batch;   // first sample of the next batch
+#pragma unroll
+        for (int j = 0; j < kSubs; ++j) {
+            const OnlineWeight r = rec[j];
+            const int lo = (int)(uint32_t)bits[j], hi = (int)(uint32_t)(bits[j] >> 32);
+            const float w = r.y == c ? r.w_y : r.pred == c ? -r.w_p : 0.0f;
+            uint64_t list = __ballot(w != 0.0f && j * kSub + lane < nb);
+            while (list) {
+                constexpr int U = 4;   // entries at a time; past the list's end weight 0
+                float x[U];
+                int n[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int i = list ? __builtin_ctzll(list) : 0;
+                    const float v = list ? lane_f32(w, i) : 0.0f;
+                    n[u] = list ? j * kSub + i : 0;
+                    const uint64_t mask = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(lo, i) |
+                                          (uint64_t)(uint32_t)__builtin_amdgcn_readlane(hi, i) << 32;
+                    int flip;   // the sign bit where the sample's bit is clear
+                    asm("v_cndmask_b32_e64 %0, %1, 0, %2" : "=v"(flip) : "v"((int)0x80000000u), "s"(mask));
+                    x[u] = __int_as_float(__float_as_int(v) ^ flip);
+                    list &= list - 1;
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if constexpr (BATCH) {
+                        if (n[u] >= end) {   // uniform
+                            a = (float)((double)a + delta);
+                            delta = 0.0;
+                            end = (n[u] / batch + 1) * batch;
+                        }
+                        delta += (double)x[u];
+                    } else {
+                        a = __fadd_rn(a, x[u]);
+                    }
+                }
+            }
+        }
+        if (BATCH) a = (float)((double)a + delta);
+        double q = 0.0;
+        if (d < D) {
+            acc[(int64_t)c * D + d] = a;
+            q = (double)a * (double)a;
+        }
+        q = lane_prefix(q);
+        if (lane == kWave - 1) normpart[(int64_t)c * G + g] = q;
+    }
+}
+
+// ---- host side -------------------------------------------------------------------------------------
+static int chain_slice(int D) {   // dimensions of a slice: up to ten slices, whole groups of 64 per wave
+    int s = (D + kSlices - 1) / kSlices;
+    s = (s + kDotWaves * kWave - 1) / (kDotWaves * kWave) * (kDotWaves * kWave);
+    return s;
+}
+
+// Samples whose products and columns are held at a time: the columns stay within 64 MB.
+static int64_t held_samples(int G) {
+    const int64_t fit = ((int64_t)64 << 20) / ((int64_t)G * (int64_t)sizeof(uint64_t)) / kSub * kSub;
+    return fit < kGramSamples ? fit : kGramSamples;
+}
+
+bool online_chain_takes(const hdc_ctx_impl *c) { return c->p.C <= 4 * kChainMaxWaves && c->p.D <= 65535; }
+
+// A block of up to 256 samples costs about what two batches cost the other way (three launches a
+// batch; 37 us a block against 18 us a batch at C = 6, D = 10000), and the call two more: batches of up to 85.
+bool online_chain_pays(int64_t N, int64_t batch) {
+    if (batch > kChainBlock) return false;
+    const int64_t block = kChainBlock / batch * batch;
+    return (N + batch - 1) / batch >= 2 * ((N + block - 1) / block) + 2;
+}
+
+int reserve_online_chain(hdc_ctx_impl *c) {
+    const int C = c->p.C, D = c->p.D;
+    const int G = (D + kWave - 1) / kWave, slice = chain_slice(D), slices = (D + slice - 1) / slice;
+    HDC_HIP(hipSetDevice(c->device));
+    int rc = grow(&c->oc_col_d, &c->oc_col_bytes, (size_t)G * held_samples(G) * sizeof(uint64_t));
+    if (rc == HDC_OK) rc = grow(&c->oc_gram_d, &c->oc_gram_bytes, (size_t)kGramBlocks * kTiles * kTile * sizeof(int16_t));
+    if (rc == HDC_OK) rc = grow(&c->oc_part_d, &c->oc_part_bytes, (size_t)slices * C * kChainBlock * sizeof(double));
+    if (rc == HDC_OK) rc = grow(&c->oc_rec_d, &c->oc_rec_bytes, (size_t)kChainBlock * sizeof(OnlineWeight));
+    if (rc == HDC_OK) rc = grow(&c->ob_norm_d, &c->ob_norm_bytes, (size_t)C * G * sizeof(double));
+    return rc;
+}
+
+template <int CPW, bool BATCH>
+static int launch_chain(hdc_ctx_impl *c, const int16_t *gram, int slices, int nb, int batch, const int32_t *labels,
+                        int G, float lr, hipStream_t s) {
+    auto kern = online_chain_kernel<CPW, BATCH>;
+    const int slot = (CPW == 1 ? 0 : CPW == 2 ? 2 : 4) + (BATCH ? 1 : 0);
+    if (!c->oc_attr_set[slot]) {
+        HDC_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    kTiles * kTile * (int)sizeof(int16_t)));
+        c->oc_attr_set[slot] = true;
+    }
+    const int subs = (nb + kSub - 1) / kSub;
+    ProfScope prof(c, BATCH ? HDC_K_ONLINE_FWD : HDC_K_ONLINE, s);
+    hipLaunchKernelGGL(kern, dim3(1), dim3(kChainMaxWaves * kWave),
+                       (size_t)(subs * (subs + 1) / 2) * kTile * sizeof(int16_t), s, gram, c->oc_part_d, slices, nb,
+                       batch, labels, c->ob_norm_d, G, c->p.C, c->p.D, lr, 1.0 / sqrt((double)c->p.D),
+                       static_cast<OnlineWeight *>(c->oc_rec_d));
+    HDC_HIP(hipGetLastError());
+    return HDC_OK;
+}
+
+template <bool BATCH>
+static int walk_blocks(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *labels, int64_t N, int32_t epochs, float lr,
+                       int batch, float *acc, hipStream_t s) {
+    const int C = c->p.C, D = c->p.D, W = c->W;
+    const int G = (D + kWave - 1) / kWave, slice = chain_slice(D), slices = (D + slice - 1) / slice;
+    int rc = reserve_online_chain(c);
+    if (rc == HDC_OK) rc = launch_norm(c, acc, G, s);
+    if (rc != HDC_OK) return rc;
+    const int block = kChainBlock / batch * batch;   // whole batches
+    const int64_t held = held_samples(G) / block * block, ld = held_samples(G);
+    for (int32_t e = 0; e < epochs; ++e)
+        for (int64_t h0 = 0; h0 < N; h0 += held) {
+            const int64_t hn = N - h0 < held ? N - h0 : held;
+            if (e == 0 || N > held) {   // a set that fits is multiplied out once for all epochs
+                hipLaunchKernelGGL(online_columns_kernel,
+                                   dim3((unsigned)((hn + kSub - 1) / kSub), (unsigned)((G + kColGroups - 1) / kColGroups)),
+                                   dim3(256), 0, s, hv + h0 * W, hn, W, G, ld, c->oc_col_d);
+                HDC_HIP(hipGetLastError());
+                if (hn > 1) {
+                    const unsigned blocks = (unsigned)((hn + block - 1) / block);
+                    const int subs = (int)((std::min<int64_t>(hn, block) + kSub - 1) / kSub);
+                    hipLaunchKernelGGL(online_gram_kernel, dim3((unsigned)(subs * (subs + 1) / 2), blocks),
+                                       dim3(kGramWaves * kWave), 0, s, c->oc_col_d, ld, hn, D, G, block, c->oc_gram_d);
+                }
+                HDC_HIP(hipGetLastError());
+            }
+            for (int64_t b0 = 0; b0 < hn; b0 += block) {
+                const int nb = (int)(hn - b0 < block ? hn - b0 : block);
+                const uint64_t *col = c->oc_col_d + b0;
+                const int32_t *lab = labels + h0 + b0;
+                const int16_t *gram = c->oc_gram_d + b0 / block * kTiles * kTile;
+                hipLaunchKernelGGL(online_dots_kernel,
+                                   dim3((unsigned)slices, (unsigned)((nb + 15) / 16), (unsigned)((C + 15) / 16)),
+                                   dim3(kDotWaves * kWave), 0, s, col, ld, nb, acc, D, C, slice, c->oc_part_d);
+                HDC_HIP(hipGetLastError());
+                if (C <= kChainMaxWaves)
+                    rc = launch_chain<1, BATCH>(c, gram, slices, nb, batch, lab, G, lr, s);
+                else if (C <= 2 * kChainMaxWaves)
+                    rc = launch_chain<2, BATCH>(c, gram, slices, nb, batch, lab, G, lr, s);
+                else
+                    rc = launch_chain<4, BATCH>(c, gram, slices, nb, batch, lab, G, lr, s);
+                if (rc != HDC_OK) return rc;
+                const unsigned waves = (unsigned)(C < 4 ? 4 : C < kChainMaxWaves ? C : kChainMaxWaves);
+                hipLaunchKernelGGL(online_rows_kernel<BATCH>, dim3((unsigned)G), dim3(waves * kWave), 0, s, col, ld,
+                                   nb, batch, static_cast<const OnlineWeight *>(c->oc_rec_d), acc, D, C, G,
+                                   c->ob_norm_d);
+                HDC_HIP(hipGetLastError());
+            }
+        }
+    return HDC_OK;
+}
+
+int launch_online_chain(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *labels, int64_t N, int32_t epochs,
+                        float lr, int64_t batch, bool per_sample, float *acc, hipStream_t s) {
+    return per_sample ? walk_blocks<false>(c, hv, labels, N, epochs, lr, 1, acc, s)
+                      : walk_blocks<true>(c, hv, labels, N, epochs, lr, (int)batch, acc, s);
+}
+
+}  // namespace hdc

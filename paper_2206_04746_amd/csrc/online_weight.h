@@ -1,0 +1,46 @@
+// What the online trainers' translation units share (online.hip, online_batched.hip, online_chain.hip).
+#pragma once
+
+#include "hdc_internal.h"
+
+namespace hdc {
+
+// One record per sample, written by the step that takes the decisions, read by the one that
+// updates the rows.
+struct OnlineWeight {
+    int32_t y;      // label, or -1: sample skipped
+    int32_t pred;   // predicted class if it differs from y, else -1
+    float w_y;      // float(1 - cos_y)
+    float w_p;      // float(lr * (1 - cos_pred))
+};
+
+// A context-owned buffer of at least `want` bytes; a no-op when it is that large already.
+template <typename T>
+int grow(T **p, size_t *have, size_t want) {
+    if (*have >= want) return HDC_OK;
+    if (*p) HDC_HIP(hipFree(*p));   // waits for the device: nothing still reads the old buffer
+    *p = nullptr;
+    *have = 0;
+    const hipError_t e = hipMalloc(reinterpret_cast<void **>(p), want + 256);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        return HDC_ENOMEM;
+    }
+    HDC_HIP(e);
+    *have = want;
+    return HDC_OK;
+}
+
+// Squared-norm partials of the rows into ob_norm_d (online_batched.hip).
+int launch_norm(hdc_ctx_impl *c, const float *acc, int G, hipStream_t s);
+
+// The block-wise walk of the chain (online_chain.hip): models it takes, batch sizes at which it is the
+// faster way, its scratch, the call (per_sample: hdc_train_online's arithmetic, else
+// hdc_train_online_batched's).
+bool online_chain_takes(const hdc_ctx_impl *c);
+bool online_chain_pays(int64_t N, int64_t batch);
+int reserve_online_chain(hdc_ctx_impl *c);
+int launch_online_chain(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *labels, int64_t N, int32_t epochs,
+                        float lr, int64_t batch, bool per_sample, float *acc, hipStream_t s);
+
+}  // namespace hdc

@@ -1,0 +1,92 @@
+"""Online training in blocks of samples (csrc/online_chain.hip) against the CPU oracle, at the sizes where
+the blocks, sub-blocks, classes per wave and dimension groups change."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+import oracle  # noqa: E402
+from workloads import make_workload  # noqa: E402
+
+from test_gpu_online_batched import clustered  # noqa: E402
+from test_gpu_parity import dev_u32, make_ctx  # noqa: E402
+
+# A weight is rounded to 24 bits; cosines that leave out the rows' rounding inside a block move it by a last
+# bit (at most 2^-23 for weights below 2) now and then.  An element is a sum of n such weights, so it is off by
+# n 2^-23 at the very most, whatever its own size (an element next to zero by as much as a large one: hence the
+# bound against the largest), which for n <= 300 per class and rows of size sqrt(n) is 2e-6.
+TOL = 2e-6
+
+
+def off(acc, want):
+    return float(np.max(np.abs(acc.cpu().numpy() - want)) / np.max(np.abs(want)))
+
+
+# short calls on either side of the walk by samples (6 steps); one sub-block and its edges; one block and its
+# edges; several blocks; classes at one, two and four to a wave; one class; odd D, the smallest and largest D
+SHAPES = [(1000, 5, 6), (1000, 5, 7), (2049, 3, 63), (2049, 3, 64), (10000, 6, 65), (1000, 2, 255), (1000, 16, 256),
+          (1001, 17, 257), (640, 32, 300), (640, 33, 300), (512, 64, 600), (100, 1, 300), (65535, 2, 70), (63, 2, 130)]
+
+
+@pytest.mark.parametrize("batch", [0, 1, 7, 64, 85])   # 0: hdc_train_online
+@pytest.mark.parametrize("D,C,N", SHAPES)
+def test_blocks_match_the_oracle(D, C, N, batch):
+    rng = np.random.default_rng(D + 100 * C + N)
+    wl = make_workload(1, D=D, C=C, F=3, L=2)
+    hv, y = clustered(rng, N, D, C)
+    y[N // 2] = C                                  # out of range: skipped
+    hv[N - 1], y[N - 1] = hv[0], y[0]              # the same sample twice
+    ctx = make_ctx(wl)
+    hvd, yd = dev_u32(hv), torch.from_numpy(y).cuda()
+    acc = torch.zeros((C, D), dtype=torch.float32, device="cuda")
+    for calls in (1, 2):                           # the second call goes on from the rows of the first
+        if batch:
+            ctx.hdc_train_online_batched(hvd, yd, acc, batch, epochs=2, lr=0.5)
+            want = oracle.train_online_batched(hv, y, D, C, batch, epochs=2 * calls, lr=0.5)
+        else:
+            ctx.hdc_train_online(hvd, yd, acc, epochs=2, lr=0.5)
+            want = oracle.train_online(hv, y, D, C, epochs=2 * calls, lr=0.5)
+        assert off(acc, want) < TOL
+    ctx.close()
+
+
+def test_more_samples_than_are_held_at_a_time():
+    D, C, N = 96, 3, 16384 + 300                   # the sample products of 16384 rows are held at a time
+    rng = np.random.default_rng(1)
+    wl = make_workload(1, D=D, C=C, F=3, L=2)
+    hv, y = clustered(rng, N, D, C)
+    ctx = make_ctx(wl)
+    hvd, yd = dev_u32(hv), torch.from_numpy(y).cuda()
+    for batch in (8, 60):
+        acc = torch.zeros((C, D), dtype=torch.float32, device="cuda")
+        ctx.hdc_train_online_batched(hvd, yd, acc, batch, epochs=2, lr=1.0)
+        assert off(acc, oracle.train_online_batched(hv, y, D, C, batch, epochs=2, lr=1.0)) < 1e-5   # n <= 11000: sqrt(n) 2^-23
+    ctx.close()
+
+
+def test_blocks_replayed_from_a_graph():
+    D, C, N = 10000, 6, 600
+    rng = np.random.default_rng(2)
+    wl = make_workload(1, D=D, C=C, F=3, L=2)
+    hv, y = clustered(rng, N, D, C)
+    ctx = make_ctx(wl)
+    hvd, yd = dev_u32(hv), torch.from_numpy(y).cuda()
+    acc = torch.zeros((C, D), dtype=torch.float32, device="cuda")
+    eager = torch.zeros_like(acc)
+    ctx.hdc_train_online(hvd, yd, eager, epochs=1, lr=1.0)     # scratch and attributes are set up here
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        acc.zero_()
+        ctx.hdc_train_online(hvd, yd, acc, epochs=1, lr=1.0)
+    for k in range(3):
+        hvd.copy_(hvd.roll(17, dims=0))
+        yd.copy_(yd.roll(17, dims=0))
+        graph.replay()
+        eager.zero_()
+        ctx.hdc_train_online(hvd, yd, eager, epochs=1, lr=1.0)
+        torch.cuda.synchronize()
+        assert torch.equal(acc, eager), k
+    ctx.close()
