@@ -106,16 +106,22 @@ def _check(code: int) -> None:
 def _dev(t: Optional[torch.Tensor], dtype: torch.dtype, shape=None) -> Optional[int]:
     if t is None:
         return None
-    if not (t.is_cuda and t.is_contiguous() and t.dtype == dtype):
+    if not (t.is_cuda and t.is_contiguous() and t.dtype is dtype):
         raise TypeError(f"expected a contiguous CUDA tensor of {dtype}, got {t.dtype} on {t.device}")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape:
         raise ValueError(f"expected shape {tuple(shape)}, got {tuple(t.shape)}")
     return t.data_ptr()
 
 
+# torch.cuda.current_stream() builds a Stream object: 2.7 us, most of a call's host time beside the
+# launches; the handle alone, from the functions it is built on, takes 0.2 us.
+_current_device, _current_handle = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+
+
 def _stream(stream) -> int:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream if hasattr(s, "cuda_stream") else int(s)
+    if stream is None:
+        return _current_handle(_current_device())
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
 def _host(a, dtype) -> np.ndarray:
