@@ -313,6 +313,10 @@ int reserve_sparse(hdc_ctx_impl *c, hipStream_t s) {
 }
 
 int launch_encode_sparse(hdc_ctx_impl *c, const void *feats, int64_t N, uint32_t *hv, hipStream_t s) {
+    {
+        int rc = HDC_OK;   // a few samples: launches are what counts, listed features or not
+        if (try_encode_few(c, feats, N, hv, s, &rc)) return rc;
+    }
     int P;
     uint32_t bias;
     majority_planes(c, &P, &bias);
