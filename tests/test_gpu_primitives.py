@@ -19,7 +19,8 @@ def ctx_for(D, C=2):
     return make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
 
 
-# D % 16 == 0 takes the vector path when the matrix is 16-byte aligned; the others the byte path
+# D % 16 == 0 takes whole aligned chunks when the matrix is 16-byte aligned, else chunks at any address;
+# matrices below 16 bytes (pack) and rows below 16 bytes (unpack) go byte by byte
 @pytest.mark.parametrize("D,N", [(10000, 700), (10016, 33), (1, 5), (31, 9), (32, 8), (33, 70), (4097, 41),
                                  (16, 1000), (48, 257), (32768, 19)])
 def test_pack_and_unpack_bit_exact(D, N):
@@ -42,8 +43,31 @@ def test_pack_and_unpack_bit_exact(D, N):
     ctx.close()
 
 
+# rows that end inside a chunk, chunks over two rows, the matrix's first and last pieces of a line, blocks
+# that start inside a row; nothing outside the matrix is written
+@pytest.mark.parametrize("off", [0, 1, 8, 15])
+@pytest.mark.parametrize("D,N", [(3, 4), (5, 900), (15, 1), (17, 1), (17, 777), (31, 130), (47, 300), (64, 70), (999, 41),
+                                 (10001, 11), (20013, 3)])
+def test_pack_and_unpack_any_size_and_address(D, N, off):
+    rng = np.random.default_rng(D * 31 + N)
+    bits = rng.integers(0, 2, size=(N, D), dtype=np.uint8)
+    ctx = ctx_for(D)
+    buf = torch.full((N * D + off + 40,), 9, dtype=torch.uint8, device="cuda")   # what surrounds the matrix: ones
+    view = buf[off:off + N * D].view(N, D)
+    view.copy_(torch.from_numpy(bits * 255))
+    hv = torch.full((N + 1, ctx.W), -1, dtype=torch.int32, device="cuda")
+    ctx.hdc_pack(view, hv[:N])
+    buf.fill_(9)
+    ctx.hdc_unpack(hv[:N], view)
+    torch.cuda.synchronize()
+    assert np.array_equal(host_u32(hv[:N].contiguous()), oracle.pack(bits)) and bool((hv[N] == -1).all())
+    assert np.array_equal(view.cpu().numpy(), bits)
+    assert bool((buf[:off] == 9).all()) and bool((buf[off + N * D:] == 9).all())
+    ctx.close()
+
+
 def test_pack_and_unpack_unaligned_matrix():
-    # a byte matrix that starts 1 byte into an allocation: the byte path, same result
+    # a byte matrix that starts 1 byte into an allocation: same result
     D, N = 10000, 50
     rng = np.random.default_rng(1)
     bits = rng.integers(0, 2, size=(N, D), dtype=np.uint8)
