@@ -16,6 +16,8 @@
 // out the fp32 rounding of the updates made since the block began: at most 2^-24 of an element per
 // update, which moves a cosine by some 1e-8 (measured at 561 features, 6 classes, D = 10000: median
 // 5e-9, largest 3e-8), below the 6e-8 to which the weight made from it is rounded.
+// The rows after training are as far from the method in 64 bits as the sample-by-sample kernels leave
+// them: relative 2-norm 5.89e-7 both (6 classes, D = 10000, 3000 samples), 1.65e-7 both (26, 1024, 1500).
 //
 // Walking the chain sample after sample on one workgroup took 3.6 us per sample (two block barriers
 // and a block-wide sum for each).
