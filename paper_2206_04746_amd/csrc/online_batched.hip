@@ -54,12 +54,11 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
 }
 
 // +1.0 in the lanes whose bit of the 64-bit mask is set, -1.0 in the others.  The mask lives
-// in a scalar register pair, which is the form v_cndmask takes its lane select in.
+// in a scalar register pair, which is the form v_cndmask takes its lane select in.  (By the builtin and
+// not by inline assembly: where the pair comes from vector registers - a lane read, a spilled scalar
+// coming back - the select has to wait two states for it, and only the compiler can see that.)
 __device__ __forceinline__ double lane_sign(uint64_t mask) {
-    int hi;
-    const int neg = (int)0xBFF00000u, pos = 0x3FF00000;
-    asm("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(hi) : "v"(neg), "v"(pos), "s"(mask));
-    return __hiloint2double(hi, 0);
+    return __hiloint2double(__builtin_amdgcn_inverse_ballot_w64(mask) ? 0x3FF00000 : (int)0xBFF00000u, 0);
 }
 
 // mem += v on an LDS double that only this lane touches; nothing is returned, so the wave does

@@ -580,9 +580,7 @@ __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_rows_kernel(
                     n[u] = list ? j * kSub + i : 0;
                     const uint64_t mask = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(lo, i) |
                                           (uint64_t)(uint32_t)__builtin_amdgcn_readlane(hi, i) << 32;
-                    int flip;   // the sign bit where the sample's bit is clear
-                    asm("v_cndmask_b32_e64 %0, %1, 0, %2" : "=v"(flip) : "v"((int)0x80000000u), "s"(mask));
-                    x[u] = __int_as_float(__float_as_int(v) ^ flip);
+                    x[u] = __builtin_amdgcn_inverse_ballot_w64(mask) ? v : -v;   // (waits for the lane reads; inline assembly would not)
                     list &= list - 1;
                 }
 #pragma unroll
