@@ -168,9 +168,11 @@ int hdc_binarize_classical(hdc_ctx *ctx, const int32_t *acc_dev, const int64_t *
  * samples: the chain is walked on the samples' scalar products with one another and the dot
  * products with the rows at the block's start, then the updates are applied to the rows one by one.
  * The cosines then leave out the fp32 rounding of the updates since the block's start (an error of
- * about 1e-8, below what float(1 - cos) keeps).  The first call allocates context-owned scratch
- * (11 MB + 16384 rows, at most 64 MB of them) unless hdc_reserve has done so (HDC_ENOMEM if that
- * fails); later calls only enqueue on `stream`.
+ * about 1e-8, below what float(1 - cos) keeps).  The first call, whatever its size, allocates
+ * context-owned scratch (11 MB + 16384 rows, at most 64 MB of them) unless hdc_reserve has done so;
+ * later calls only enqueue on `stream`.  Where the scratch cannot be had - memory is short, or the
+ * first call is being captured into a graph - and D <= 32768, the call goes sample by sample
+ * without any, which is slower; beyond D = 32768 that is HDC_ENOMEM or HDC_EHIP.
  */
 int hdc_train_online(hdc_ctx *ctx, const uint32_t *hv_dev, const int32_t *labels_dev, int64_t N,
                      int32_t epochs, float lr, float *acc_dev, void *stream);
@@ -186,10 +188,10 @@ int hdc_train_online(hdc_ctx *ctx, const uint32_t *hv_dev, const int32_t *labels
  * (fp64 sums) and acc[c] = float(double(acc[c]) + delta[c]), one rounding per element and
  * batch.  batch >= 1; a batch larger than N is one batch per epoch.  Small batches (up to 85 samples,
  * C <= 64, D <= 65535) are worked off several at a time as described for hdc_train_online.  Other arguments, layout
- * and the treatment of out-of-range labels are those of hdc_train_online.  The first call,
- * and a call that needs more scratch than any before it (larger batch), allocates device
- * memory owned by the context (HDC_ENOMEM if that fails) and therefore synchronises the
- * device; later calls only enqueue on `stream`.
+ * and the treatment of out-of-range labels are those of hdc_train_online.  The first call, and one
+ * with a larger batch (min(batch, N)) than any before it, allocates device memory owned by the
+ * context (HDC_ENOMEM if that fails) and therefore synchronises the device; other calls only
+ * enqueue on `stream`, whichever way they are worked off.
  */
 int hdc_train_online_batched(hdc_ctx *ctx, const uint32_t *hv_dev, const int32_t *labels_dev,
                              int64_t N, int32_t epochs, float lr, int64_t batch, float *acc_dev,

@@ -61,7 +61,8 @@ struct hdc_ctx_impl {
     int64_t perm_rows;
     uint32_t *partial_d;  // [partial_items][Wp * 16] per-block partial counts, two u16 per dword
     int64_t partial_items;
-    uint32_t *on_bits_d;  // [16384][1024] per-thread sample bits of hdc_train_online (first call or hdc_reserve allocates)
+    uint32_t *on_bits_d;  // [8][1024] per-thread sample bits of online_lds_kernel, allocated with the block-wise trainer's scratch
+    size_t on_bits_bytes;
     bool check_labels;    // hdc_set_label_check: training calls refuse labels outside [0, C)
     unsigned long long *bad_labels_d;   // [1] counter of count_bad_labels
 
@@ -87,9 +88,12 @@ struct hdc_ctx_impl {
     size_t ob_lw_bytes;
     uint32_t *ob_meta_d;  // [3 C + 1 + rows] entries / first share row / share rows per class, row counter, work list
     size_t ob_meta_bytes;
+    int64_t ob_blocks_batch;   // largest batch of a call in blocks for which the scratch above has been asked for
     bool ob_attr_set;     // dynamic-LDS limit of the backward kernel raised
 
-    // Scratch of the block-wise online trainer (online_chain.hip), allocated on its first call.
+    // Scratch of the block-wise online trainer (online_chain.hip), allocated at the first call of either
+    // online trainer, whatever its size, so that later ones only enqueue.
+    bool oc_ready;        // all of it is there
     int16_t *oc_gram_d;   // [blocks][10][64][64] scalar products of the samples of a block
     size_t oc_gram_bytes;
     uint64_t *oc_col_d;   // [ceil(D/64)][samples] 64-bit lane masks, dimension group major

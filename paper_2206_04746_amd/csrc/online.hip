@@ -3,9 +3,8 @@
 // The method is a dependency chain over the samples: every step needs the class
 // accumulators left by the step before (Sec. VI-D2 notes that this rules out parallelism over
 // the samples).  Calls of more than a few samples walk it in blocks (online_chain.hip); the kernels
-// here walk it sample by sample: for the shortest calls, and for class counts and dimensions
-// the blocks do not take.  What
-// is parallel is the work inside one step - C dot products over D dimensions and at most two
+// here walk it sample by sample: for the shortest calls, for class counts and dimensions the blocks do
+// not take, and for calls whose scratch cannot be had.  What is parallel is the work inside one step - C dot products over D dimensions and at most two
 // row updates - so one persistent workgroup of 1024 threads walks the chain and spreads the
 // D dimensions over its lanes.  Thread t owns dimensions t, t+1024, ... in every phase, so a
 // thread only ever re-reads accumulator elements it wrote itself; the only communication per
@@ -544,31 +543,15 @@ __global__ __launch_bounds__(kOnlineThreads) void online_bits_kernel(const uint3
 // Steps (samples x epochs) up to which a call is walked sample by sample where a kernel for it exists:
 // 12 us + 3.6 us a step at C = 6, D = 10000 against 32 us for a first block of up to 64 samples.
 constexpr int64_t kShortSteps = 6;
-constexpr int64_t kOnlineChunk = 8;   // samples whose per-thread bit words are prepared at a time (32 KB)
+static_assert(kShortSteps * kOnlineThreads <= kOnlineWords, "the words of every sample of a short call");
 
-// The per-thread sample words of online_lds_kernel (a no-op when there).
-static int reserve_words(hdc_ctx_impl *c) {
-    if (c->on_bits_d) return HDC_OK;
-    HDC_HIP(hipSetDevice(c->device));
-    const hipError_t e = hipMalloc(reinterpret_cast<void **>(&c->on_bits_d),
-                                   (size_t)kOnlineChunk * kOnlineThreads * sizeof(uint32_t));
-    if (e == hipErrorOutOfMemory) {
-        (void)hipGetLastError();
-        return HDC_ENOMEM;
-    }
-    HDC_HIP(e);
-    return HDC_OK;
-}
-
+// What hdc_train_online may need; a no-op when it is there.
 int reserve_online(hdc_ctx_impl *c) {
-    if (c->p.D > 32 * kOnlineThreads) {
-        const int rc = reserve_online_batched(c, 1);
-        if (rc != HDC_OK) return rc;
-    }
-    const int rc = online_chain_takes(c) ? reserve_online_chain(c) : HDC_OK;
-    return rc != HDC_OK ? rc : reserve_words(c);
+    if (c->p.D > 32 * kOnlineThreads) return reserve_online_batched(c, 1);
+    return online_chain_takes(c) ? reserve_online_chain(c) : HDC_OK;
 }
 
+// (at most kShortSteps samples, their words' memory there: online_chain_ready)
 template <int CMAX, int KPT>
 static int launch_online_lds(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *labels, int64_t N,
                              int32_t epochs, float lr, float *acc, hipStream_t s) {
@@ -580,23 +563,11 @@ static int launch_online_lds(hdc_ctx_impl *c, const uint32_t *hv, const int32_t 
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         c->on_attr_set[CMAX] = true;
     }
-    {
-        const int rc = reserve_words(c);
-        if (rc != HDC_OK) return rc;
-    }
-    // A set that fits one chunk is prepared once and walked `epochs` times by one launch; a
-    // longer one is walked chunk by chunk, every epoch (the accumulators rest in memory between
-    // launches, which changes nothing: they are fp32 there and in the registers).
-    const bool one = N <= kOnlineChunk;
-    for (int32_t e = 0; e < (one ? 1 : epochs); ++e)
-        for (int64_t n0 = 0; n0 < N; n0 += kOnlineChunk) {
-            const int64_t n = N - n0 < kOnlineChunk ? N - n0 : kOnlineChunk;
-            hipLaunchKernelGGL(online_bits_kernel, dim3((unsigned)n), dim3(kOnlineThreads), 0, s, hv + n0 * c->W,
-                               labels + n0, c->p.C, c->p.D, c->W, c->on_bits_d);
-            ProfScope prof(c, HDC_K_ONLINE, s);
-            hipLaunchKernelGGL(kern, dim3(1), dim3(kOnlineThreads), lds, s, c->on_bits_d, n, one ? (int)epochs : 1,
-                               lr, acc, c->p.D, c->p.C, 1.0 / sqrt((double)c->p.D));
-        }
+    hipLaunchKernelGGL(online_bits_kernel, dim3((unsigned)N), dim3(kOnlineThreads), 0, s, hv, labels, c->p.C, c->p.D,
+                       c->W, c->on_bits_d);
+    ProfScope prof(c, HDC_K_ONLINE, s);
+    hipLaunchKernelGGL(kern, dim3(1), dim3(kOnlineThreads), lds, s, c->on_bits_d, N, (int)epochs, lr, acc, c->p.D,
+                       c->p.C, 1.0 / sqrt((double)c->p.D));
     HDC_HIP(hipGetLastError());
     return HDC_OK;
 }
@@ -615,22 +586,32 @@ int launch_train_online(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *labe
                         int32_t epochs, float lr, float *acc, hipStream_t s) {
     const int C = c->p.C;
     const int kpt = (c->p.D + kOnlineThreads - 1) / kOnlineThreads;
-    const bool blocks = online_chain_takes(c), brief = N * epochs <= kShortSteps;
     // a thread keeps its sample bits in one word: beyond 32768 dimensions the batched trainer runs
     // with batches of one sample, which is the same method (in blocks, from four samples on)
     if (kpt > 32) return launch_train_online_batched(c, hv, labels, N, epochs, lr, 1, acc, s);
+    const bool brief = N * epochs <= kShortSteps;
+    int rc;
+    const bool blocks = online_chain_ready(c, s, &rc);
+    if (rc != HDC_OK) return rc;
 #define HDC_ONLINE_LDS_CASE(CM, KP) \
-    if (brief && C <= CM && kpt <= KP) return launch_online_lds<CM, KP>(c, hv, labels, N, epochs, lr, acc, s)
+    if (blocks && brief && C <= CM && kpt <= KP) return launch_online_lds<CM, KP>(c, hv, labels, N, epochs, lr, acc, s)
     HDC_ONLINE_LDS_CASE(8, 2);
     HDC_ONLINE_LDS_CASE(4, 4);
     HDC_ONLINE_LDS_CASE(12, 4);
     HDC_ONLINE_LDS_CASE(2, 10);
     HDC_ONLINE_LDS_CASE(6, 10);
 #undef HDC_ONLINE_LDS_CASE
-    if (brief && C <= 2 && kpt <= 16) return launch_online_reg<2, 16>(c, hv, labels, N, epochs, lr, acc, s);
-    if (blocks) return launch_online_chain(c, hv, labels, N, epochs, lr, 1, true, acc, s);
-    // more than 64 classes: in registers while they fit, else with the accumulators in memory
-    if (C <= 80 && kpt <= 1) return launch_online_reg<80, 1>(c, hv, labels, N, epochs, lr, acc, s);
+    if (blocks && !(brief && C <= 2 && kpt <= 16)) return launch_online_chain(c, hv, labels, N, epochs, lr, 1, true, acc, s);
+    // Sample by sample without any scratch: more than 64 classes, and calls for which the blocks' scratch
+    // cannot be had (a first call under capture).  In registers while the rows fit, else in memory.
+#define HDC_ONLINE_CASE(CM, KP) \
+    if (C <= CM && kpt <= KP) return launch_online_reg<CM, KP>(c, hv, labels, N, epochs, lr, acc, s)
+    HDC_ONLINE_CASE(32, 1);
+    HDC_ONLINE_CASE(80, 1);
+    HDC_ONLINE_CASE(40, 2);
+    HDC_ONLINE_CASE(20, 4);
+    HDC_ONLINE_CASE(2, 16);
+#undef HDC_ONLINE_CASE
     const size_t lds = (size_t)(2 + kOnlineWaves) * (C < 2 ? 2 : C) * sizeof(double);
     auto kern = online_kernel;
     if (lds > 64 * 1024)

@@ -987,13 +987,25 @@ int launch_train_online_batched(hdc_ctx_impl *c, const uint32_t *hv, const int32
     const int G = (D + kWave - 1) / kWave;
     const FwdShape f = fwd_shape(C, G);
     if (batch > N) batch = N;
-    if (online_chain_takes(c) && online_chain_pays(N, batch)) return launch_online_chain(c, hv, labels, N, epochs, lr, batch, false, acc, s);
+    int rc = HDC_OK;
+    if (online_chain_pays(N, batch) && online_chain_ready(c, s, &rc)) {
+        // a shorter call with the same batch goes in pieces: their scratch, too, belongs to this call
+        if (batch > c->ob_blocks_batch && !stream_captured(s)) {
+            rc = reserve_pieces(c, batch);
+            if (rc != HDC_OK && rc != HDC_ENOMEM) return rc;
+            c->ob_blocks_batch = batch;
+        }
+        return launch_online_chain(c, hv, labels, N, epochs, lr, batch, false, acc, s);
+    }
+    if (rc != HDC_OK) return rc;
 
     // A batch is worked off in pieces of at most `sb` samples (forward, weights, backward each);
     // sb bounds the scratch: partial dot products and transposed masks.
     const int64_t sb = fwd_sub_batch(f, C, batch);
     const int cb = bwd_dense_width(C);
-    int rc = reserve_pieces(c, batch);
+    rc = reserve_pieces(c, batch);
+    if (rc != HDC_OK) return rc;
+    (void)online_chain_ready(c, s, &rc);   // (a longer call, or smaller batches, go in blocks)
     if (rc != HDC_OK) return rc;
     if (!c->ob_attr_set) {
         const void *kernels[] = {reinterpret_cast<const void *>(online_bwd_kernel<0>),

@@ -633,6 +633,7 @@ bool online_chain_pays(int64_t N, int64_t batch) {
 }
 
 int reserve_online_chain(hdc_ctx_impl *c) {
+    if (c->oc_ready) return HDC_OK;
     const int C = c->p.C, D = c->p.D;
     const int G = (D + kWave - 1) / kWave, slice = chain_slice(D), slices = (D + slice - 1) / slice;
     HDC_HIP(hipSetDevice(c->device));
@@ -640,8 +641,25 @@ int reserve_online_chain(hdc_ctx_impl *c) {
     if (rc == HDC_OK) rc = grow(&c->oc_gram_d, &c->oc_gram_bytes, (size_t)kGramBlocks * kTiles * kTile * sizeof(int16_t));
     if (rc == HDC_OK) rc = grow(&c->oc_part_d, &c->oc_part_bytes, (size_t)slices * C * kChainBlock * sizeof(double));
     if (rc == HDC_OK) rc = grow(&c->oc_rec_d, &c->oc_rec_bytes, (size_t)kChainBlock * sizeof(OnlineWeight));
+    if (rc == HDC_OK) rc = grow(&c->on_bits_d, &c->on_bits_bytes, (size_t)kOnlineWords * sizeof(uint32_t));
     if (rc == HDC_OK) rc = grow(&c->ob_norm_d, &c->ob_norm_bytes, (size_t)C * G * sizeof(double));
+    c->oc_ready = rc == HDC_OK;
+    if (rc == HDC_ENOMEM) {   // all or nothing: what is left of the memory is for the other ways
+        (void)hipFree(c->oc_col_d);
+        (void)hipFree(c->oc_gram_d);
+        c->oc_col_d = nullptr;
+        c->oc_gram_d = nullptr;
+        c->oc_col_bytes = c->oc_gram_bytes = 0;
+    }
     return rc;
+}
+
+bool online_chain_ready(hdc_ctx_impl *c, hipStream_t s, int *rc) {
+    *rc = HDC_OK;
+    if (!online_chain_takes(c)) return false;
+    if (!c->oc_ready && !stream_captured(s)) *rc = reserve_online_chain(c);
+    if (*rc == HDC_ENOMEM) *rc = HDC_OK;
+    return c->oc_ready;
 }
 
 template <int CPW, bool BATCH>
@@ -669,8 +687,7 @@ static int walk_blocks(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *label
                        int batch, float *acc, hipStream_t s) {
     const int C = c->p.C, D = c->p.D, W = c->W;
     const int G = (D + kWave - 1) / kWave, slice = chain_slice(D), slices = (D + slice - 1) / slice;
-    int rc = reserve_online_chain(c);
-    if (rc == HDC_OK) rc = launch_norm(c, acc, G, s);
+    int rc = launch_norm(c, acc, G, s);
     if (rc != HDC_OK) return rc;
     const int block = kChainBlock / batch * batch;   // whole batches
     const int64_t held = held_samples(G) / block * block, ld = held_samples(G);

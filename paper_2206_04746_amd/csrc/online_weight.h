@@ -34,12 +34,24 @@ int grow(T **p, size_t *have, size_t want) {
 // Squared-norm partials of the rows into ob_norm_d (online_batched.hip).
 int launch_norm(hdc_ctx_impl *c, const float *acc, int G, hipStream_t s);
 
+// Whether the stream is being captured into a graph (or cannot tell): nothing may be allocated then.
+inline bool stream_captured(hipStream_t s) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    const bool known = hipStreamIsCapturing(s, &status) == hipSuccess;
+    if (!known) (void)hipGetLastError();
+    return !known || status != hipStreamCaptureStatusNone;
+}
+
 // The block-wise walk of the chain (online_chain.hip): models it takes, batch sizes at which it is the
-// faster way, its scratch, the call (per_sample: hdc_train_online's arithmetic, else
-// hdc_train_online_batched's).
+// faster way, its scratch (with the words of online_lds_kernel), the call (per_sample: hdc_train_online's
+// arithmetic, else hdc_train_online_batched's).
+constexpr int64_t kOnlineWords = 8 * 1024;   // samples x threads whose bit words online_lds_kernel is handed (32 KB)
 bool online_chain_takes(const hdc_ctx_impl *c);
 bool online_chain_pays(int64_t N, int64_t batch);
 int reserve_online_chain(hdc_ctx_impl *c);
+// Whether a call may go in blocks: a model they take, their scratch there or to be had.  False without an
+// error (*rc HDC_OK) while the stream is captured or memory is short: such a call goes another way.
+bool online_chain_ready(hdc_ctx_impl *c, hipStream_t s, int *rc);
 int launch_online_chain(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *labels, int64_t N, int32_t epochs,
                         float lr, int64_t batch, bool per_sample, float *acc, hipStream_t s);
 
