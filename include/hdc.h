@@ -115,8 +115,8 @@ int hdc_encode(hdc_ctx *ctx, const void *feats_dev, int64_t N, uint32_t *hv_dev,
  * not in bin 0; only the latter are bundled, at about 1.5 times the cost of a feature in
  * hdc_encode, so the call pays off when fewer than about 60 % of a sample's features leave bin 0
  * (80 % of the pixels of a digit image are background) and costs at most about half as much again
- * when they all do.  The first call allocates scratch (4 bytes per feature for 65536 samples) and
- * derives three tables on `stream`.  Arguments and errors as hdc_encode.
+ * when they all do.  The first call, whatever its size, allocates scratch (4 bytes per feature for
+ * 65536 samples) and derives three tables on `stream`.  Arguments and errors as hdc_encode.
  */
 int hdc_encode_sparse(hdc_ctx *ctx, const void *feats_dev, int64_t N, uint32_t *hv_dev, void *stream);
 

@@ -313,14 +313,18 @@ int reserve_sparse(hdc_ctx_impl *c, hipStream_t s) {
 }
 
 int launch_encode_sparse(hdc_ctx_impl *c, const void *feats, int64_t N, uint32_t *hv, hipStream_t s) {
-    {
-        int rc = HDC_OK;   // a few samples: launches are what counts, listed features or not
-        if (try_encode_few(c, feats, N, hv, s, &rc)) return rc;
-    }
     int P;
     uint32_t bias;
     majority_planes(c, &P, &bias);
-    const int prc = prepare_sparse(c, P, bias, s);
+    // A few samples need no scratch (launches are what counts there, listed features or not), but the
+    // first call allocates it whatever its size, so that later ones only enqueue.
+    int prc = c->sp_ready || stream_captured(s) ? HDC_OK : prepare_sparse(c, P, bias, s);
+    if (prc != HDC_OK && prc != HDC_ENOMEM) return prc;
+    {
+        int rc = HDC_OK;
+        if (try_encode_few(c, feats, N, hv, s, &rc)) return rc;
+    }
+    prc = prepare_sparse(c, P, bias, s);
     if (prc != HDC_OK) return prc;
     const bool compact = c->compact;
     if (compact && c->Wc == 0) return launch_encode(c, feats, N, hv, s);

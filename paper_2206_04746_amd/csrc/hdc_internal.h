@@ -183,6 +183,14 @@ int hip_fail(hipError_t e, const char *what);
         if (e__ != hipSuccess) return ::hdc::hip_fail(e__, #call); \
     } while (0)
 
+// Whether the stream is being captured into a graph (or cannot tell): nothing may be allocated then.
+inline bool stream_captured(hipStream_t s) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    const bool known = hipStreamIsCapturing(s, &status) == hipSuccess;
+    if (!known) (void)hipGetLastError();
+    return !known || status != hipStreamCaptureStatusNone;
+}
+
 // Kernel launchers (one per translation unit); all only enqueue on `s`.
 int launch_encode(hdc_ctx_impl *c, const void *feats, int64_t N, uint32_t *hv, hipStream_t s);
 int launch_encode_sparse(hdc_ctx_impl *c, const void *feats, int64_t N, uint32_t *hv, hipStream_t s);

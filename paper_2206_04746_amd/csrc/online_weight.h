@@ -34,14 +34,6 @@ int grow(T **p, size_t *have, size_t want) {
 // Squared-norm partials of the rows into ob_norm_d (online_batched.hip).
 int launch_norm(hdc_ctx_impl *c, const float *acc, int G, hipStream_t s);
 
-// Whether the stream is being captured into a graph (or cannot tell): nothing may be allocated then.
-inline bool stream_captured(hipStream_t s) {
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    const bool known = hipStreamIsCapturing(s, &status) == hipSuccess;
-    if (!known) (void)hipGetLastError();
-    return !known || status != hipStreamCaptureStatusNone;
-}
-
 // The block-wise walk of the chain (online_chain.hip): models it takes, batch sizes at which it is the
 // faster way, its scratch (with the words of online_lds_kernel), the call (per_sample: hdc_train_online's
 // arithmetic, else hdc_train_online_batched's).

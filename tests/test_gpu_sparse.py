@@ -122,6 +122,25 @@ def test_sparse_encode_chunked_stream_and_agreement_with_dense():
     ctx.close()
 
 
+def test_sparse_encode_captured_after_a_short_first_call():
+    # the first call, however few its samples, leaves later ones nothing to allocate
+    wl = make_workload(3, F=100, L=32, D=1000, n_train=3000)
+    x, _ = wl.train(3000)
+    ctx = _ctx(wl)
+    assert np.array_equal(_sparse(ctx, x[:2]), _oracle(wl, x[:2]))
+    xd = torch.from_numpy(x).cuda()
+    hv = torch.empty((3000, ctx.W), dtype=torch.int32, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ctx.hdc_encode_sparse(xd, hv)
+    want = _oracle(wl, x)
+    for _ in range(3):
+        hv.fill_(-1)
+        graph.replay()
+        assert np.array_equal(hv.cpu().numpy().view(np.uint32), want)
+    ctx.close()
+
+
 def test_sparse_encode_argument_errors():
     from paper_2206_04746_amd import binding
     wl = make_workload(1, n_train=8)
