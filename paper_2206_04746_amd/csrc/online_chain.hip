@@ -41,10 +41,12 @@ constexpr int kSlices = 10;                         // most slices the dimension
 // ---- the samples' bits, dimension group by dimension group ----------------------------------------
 // col[g][n] = bits 64 g .. 64 g + 63 of sample n: the steps below work on one group of all samples of a
 // block, which row by row would be 8 bytes out of every 4 W (the rows step took 16 us like that, most of
-// it in these loads).  A block turns 64 samples x 16 groups through LDS.  grid (sample tiles, group tiles)
+// it in these loads).  Bits past D are dropped here: the products count every bit of a word.  A block
+// turns 64 samples x 16 groups through LDS.  grid (sample tiles, group tiles)
 constexpr int kColGroups = 16;
-__global__ __launch_bounds__(256) void online_columns_kernel(const uint32_t *__restrict__ hv, int64_t N, int W, int G,
-                                                             int64_t ld, uint64_t *__restrict__ col) {
+__global__ __launch_bounds__(256) void online_columns_kernel(const uint32_t *__restrict__ hv, int64_t N, int W,
+                                                             uint32_t last_mask, int G, int64_t ld,
+                                                             uint64_t *__restrict__ col) {
     __shared__ uint32_t tile[kSub][2 * kColGroups + 1];
     const int t = threadIdx.x;
     const int64_t n0 = (int64_t)blockIdx.x * kSub;
@@ -52,7 +54,8 @@ __global__ __launch_bounds__(256) void online_columns_kernel(const uint32_t *__r
 #pragma unroll
     for (int r = 0; r < kSub / 8; ++r) {
         const int sm = r * 8 + (t >> 5), w = 2 * g0 + (t & 31);
-        tile[sm][t & 31] = (n0 + sm < N && w < W) ? hv[(n0 + sm) * W + w] : 0u;
+        const uint32_t x = (n0 + sm < N && w < W) ? hv[(n0 + sm) * W + w] : 0u;
+        tile[sm][t & 31] = w == W - 1 ? x & last_mask : x;
     }
     __syncthreads();
 #pragma unroll
@@ -697,7 +700,7 @@ static int walk_blocks(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *label
             if (e == 0 || N > held) {   // a set that fits is multiplied out once for all epochs
                 hipLaunchKernelGGL(online_columns_kernel,
                                    dim3((unsigned)((hn + kSub - 1) / kSub), (unsigned)((G + kColGroups - 1) / kColGroups)),
-                                   dim3(256), 0, s, hv + h0 * W, hn, W, G, ld, c->oc_col_d);
+                                   dim3(256), 0, s, hv + h0 * W, hn, W, c->last_word_mask, G, ld, c->oc_col_d);
                 HDC_HIP(hipGetLastError());
                 if (hn > 1) {
                     const unsigned blocks = (unsigned)((hn + block - 1) / block);

@@ -52,6 +52,26 @@ def test_blocks_match_the_oracle(D, C, N, batch):
     ctx.close()
 
 
+@pytest.mark.parametrize("batch", [0, 16])
+def test_bits_past_the_last_dimension_are_ignored(batch):
+    D, C, N = 1001, 4, 300
+    hv, y = clustered(np.random.default_rng(4), N, D, C)
+    dirty = hv.copy()
+    dirty[::3, -1] |= np.uint32(0xffffffff) << np.uint32(D % 32)
+    ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
+    yd = torch.from_numpy(y).cuda()
+    rows = []
+    for h in (hv, dirty):
+        acc = torch.zeros((C, D), dtype=torch.float32, device="cuda")
+        if batch:
+            ctx.hdc_train_online_batched(dev_u32(h), yd, acc, batch, epochs=2, lr=1.0)
+        else:
+            ctx.hdc_train_online(dev_u32(h), yd, acc, epochs=2, lr=1.0)
+        rows.append(acc.cpu())
+    assert torch.equal(rows[0], rows[1])
+    ctx.close()
+
+
 def test_more_samples_than_are_held_at_a_time():
     D, C, N = 96, 3, 16384 + 300                   # the sample products of 16384 rows are held at a time
     rng = np.random.default_rng(1)
