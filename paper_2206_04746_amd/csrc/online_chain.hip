@@ -241,6 +241,82 @@ __device__ __forceinline__ double lane_before(double v) {
     return __hiloint2double(hi, lo);
 }
 
+__device__ __forceinline__ double refined_rsq(double nn) {
+    double r = __builtin_amdgcn_rsq(nn);
+    r = r * fma(-0.5 * nn * r, r, 1.5);
+    return r * fma(-0.5 * nn * r, r, 1.5);
+}
+
+// The samples of a block one after another: a wave's lanes deal the samples before among them for each of
+// its classes, and the decision is taken class by class, as in the kernels that walk sample by sample
+// (BATCH: as in the batched trainer, which passes over classes whose cosine is no number).  cosv: [C] in LDS.
+template <int CPW, bool BATCH>
+__device__ __noinline__ void walk_block(const int16_t *prod, const double *__restrict__ part, int slices, int nb, int batch,
+                           const int32_t *__restrict__ labels, const double *__restrict__ normpart, int G, int C, int D,
+                           float lr, double inv_root_d, OnlineWeight *rec, double *cosv) {
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    double nrm[CPW], frozen[CPW];   // squared norms now, and where the batch began
+    for (int k = 0; k < CPW; ++k) {
+        const int c = wave * CPW + k;
+        double s = 0.0;
+        for (int g = lane; g < G && c < C; g += kWave) s += normpart[(int64_t)c * G + g];
+        nrm[k] = frozen[k] = lane_f64(lane_prefix(s), kWave - 1);
+    }
+    for (int m = 0; m < nb; ++m) {
+        const int first = BATCH ? m / batch * batch : m, b = m / kSub;
+        const int16_t *tiles = prod + b * (b + 1) / 2 * kTile + m % kSub;   // row n is product (n, m)
+        int y = labels[m];
+        y = y >= 0 && y < C ? y : -1;
+        double all[CPW];
+        __syncthreads();   // the record before is there, cosv has been read
+#pragma unroll
+        for (int k = 0; k < CPW; ++k) {
+            const int c = wave * CPW + k;
+            if (first == m) frozen[k] = nrm[k];
+            if (c >= C) continue;
+            double start = 0.0, old = 0.0, own = 0.0;
+            for (int i = 0; i < slices; ++i) start += part[((int64_t)i * C + c) * kChainBlock + m];
+            for (int n = lane; n < m; n += kWave) {
+                const OnlineWeight r = rec[n];
+                const double g = (double)(2 * (int)tiles[n * kSub] + (D & 1));
+                const double term = r.y == c ? (double)r.w_y * g : r.pred == c ? -(double)r.w_p * g : 0.0;
+                (n < first ? old : own) += term;
+            }
+            const double dot = start + lane_f64(lane_prefix(old), kWave - 1);
+            all[k] = dot + lane_f64(lane_prefix(own), kWave - 1);
+            const double nn = frozen[k];
+            if (lane == 0) cosv[c] = nn <= 0.0 ? 0.0 : dot * refined_rsq(nn) * inv_root_d;
+        }
+        __syncthreads();
+        int pred = BATCH ? -1 : 0;
+        double best = BATCH ? -2.0 : cosv[0];
+        for (int c = BATCH ? 0 : 1; c < C; ++c) {
+            const double v = cosv[c];
+            if (v > best) {
+                best = v;
+                pred = c;
+            }
+        }
+        OnlineWeight r = {y, -1, 0.0f, 0.0f};
+        if (y >= 0) {
+            r.w_y = (float)(1.0 - cosv[y]);
+            if (pred >= 0 && pred != y) {
+                r.pred = pred;
+                r.w_p = (float)((double)lr * (1.0 - best));
+            }
+        }
+        if (tid == 0) rec[m] = r;
+#pragma unroll
+        for (int k = 0; k < CPW; ++k) {
+            const int c = wave * CPW + k;
+            const double w = r.y == c ? (double)r.w_y : r.pred == c ? -(double)r.w_p : 0.0;
+            if (c < C && (r.y == c || r.pred == c)) nrm[k] += w * (2.0 * all[k] + w * (double)D);
+        }
+    }
+    __syncthreads();
+}
+
 // One workgroup; wave w has classes w CPW .. w CPW + CPW - 1, lane m of it sample m of the sub-block.
 //
 // Sub-block after sub-block: the samples' weights k_n,c (nonzero for the label's class and a wrong
@@ -260,6 +336,11 @@ __device__ __forceinline__ double lane_before(double v) {
 // only (a ballot lists them) and keeps their products in registers from pass to pass, for as
 // long as the list is the same; the best cosine of each wave meets the others' in LDS, where every wave
 // takes the same decision for all 64 samples: one barrier a pass (two LDS areas in turn).
+//
+// Rows or weights that are infinite or no numbers: the passes add samples that do not count with factor
+// zero, which is no longer nothing then, and the order of the classes matters to a comparison.  A block that
+// starts from such rows is walked sample by sample (walk_block), and so is every block if the learning rate
+// could make a weight overflow; else a weight, at most 2 or twice the rate, stays finite.
 template <int CPW, bool BATCH>
 __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
     const int16_t *__restrict__ gram, const double *__restrict__ part, int slices, int nb, int batch,
@@ -271,6 +352,7 @@ __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
     __shared__ double s_cosy[2][kSub];
     __shared__ int s_pred[CPW > 1 ? 2 : 1][CPW > 1 ? kChainMaxWaves : 1][kSub];
     __shared__ OnlineWeight s_rec[kChainBlock];
+    __shared__ int s_odd[kChainMaxWaves];   // a wave's rows are not finite
     __shared__ uint2 s_list[kChainMaxWaves][kChainBlock];   // a wave's own: weight and place of the samples that name its class
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -285,6 +367,7 @@ __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
     double nrm[CPW], nrm_fb[CPW];   // squared norms before the sub-block; and where the batch that runs into it began
     double start[CPW][kSubs];       // dot products against the rows at the block's start
     int label[kSubs];
+    bool odd_rows = false;
 #pragma unroll
     for (int j = 0; j < kSubs; ++j) {
         const int y = labels[min(j * kSub + lane, nb - 1)];
@@ -316,14 +399,21 @@ __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
 #pragma unroll
                 for (int j = 0; j < kSubs; ++j) start[k][j] += i < slices ? x[i][j] : 0.0;
             nrm[k] = nrm_fb[k] = lane_f64(lane_prefix(s), kWave - 1);
+            odd_rows |= !(nrm[k] < __builtin_inf());
         }
     }
+    if (lane == 0) s_odd[wave] = odd_rows;
 #pragma unroll
     for (int u = 0; u < kCopies; ++u)
         if (tid + u * kChainMaxWaves * kWave < units)
             reinterpret_cast<uint4 *>(prod)[tid + u * kChainMaxWaves * kWave] = copy[u];
     __syncthreads();
     if (wave >= used) return;   // (an ended wave takes no part in later barriers)
+    if (__builtin_expect(__ballot(lane < used && s_odd[lane]) != 0 || !(fabsf(lr) < 1e30f), 0)) {   // the same in every wave
+        walk_block<CPW, BATCH>(prod, part, slices, nb, batch, labels, normpart, G, C, D, lr, inv_root_d, s_rec, s_cosy[0]);
+        for (int n = tid; n < nb; n += used * kWave) out[n] = s_rec[n];
+        return;
+    }
     const int odd = D & 1;
     const double dd = (double)D;
 
@@ -472,10 +562,7 @@ __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
                     norms(k, dot);
                     double nn = nrm[k] + before[k];
                     if (BATCH) nn = fb >= m0 ? nrm[k] + __shfl(before[k], fb - m0, kWave) : nrm_fb[k];
-                    double r = __builtin_amdgcn_rsq(nn);
-                    r = r * fma(-0.5 * nn * r, r, 1.5);
-                    r = r * fma(-0.5 * nn * r, r, 1.5);
-                    const double cs = nn > 0.0 ? dot * r * inv_root_d : 0.0;
+                    const double cs = nn > 0.0 ? dot * refined_rsq(nn) * inv_root_d : 0.0;
                     if (y == c) s_cosy[buf][lane] = cs;
                     if (cs > best) {
                         best = cs;

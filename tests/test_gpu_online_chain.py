@@ -72,6 +72,39 @@ def test_bits_past_the_last_dimension_are_ignored(batch):
     ctx.close()
 
 
+NAN, INF = float("nan"), float("inf")
+
+
+# rows that are no numbers or infinite from the start, and weights that get there in the middle of a block
+@pytest.mark.parametrize("batch", [0, 24])
+@pytest.mark.parametrize("row,value,lr", [(0, NAN, 1.0), (2, NAN, 1.0), (0, INF, 1.0), (1, -INF, 0.5), (-1, NAN, 1.0), (1, 0.0, INF),
+                                          (1, 0.0, NAN), (0, 0.0, -INF)])
+@pytest.mark.parametrize("C", [3, 20, 40])
+def test_rows_and_weights_that_are_not_finite(C, row, value, lr, batch):
+    D, N = 200, 300
+    hv, y = clustered(np.random.default_rng(5), N, D, C)
+    start = np.random.default_rng(6).normal(size=(C, D)).astype(np.float32)
+    if value != 0.0:
+        start[row if row >= 0 else slice(None), 7] = value
+    ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
+    hvd, yd, acc = dev_u32(hv), torch.from_numpy(y).cuda(), torch.from_numpy(start.copy()).cuda()
+    if batch:    # (against calls of one batch each, which do not go in blocks: the oracle takes class 0 here as well)
+        ctx.hdc_train_online_batched(hvd, yd, acc, batch, epochs=1, lr=lr)
+        single = torch.from_numpy(start.copy()).cuda()
+        for n in range(0, N, batch):
+            ctx.hdc_train_online_batched(hvd[n:n + batch], yd[n:n + batch], single, batch, epochs=1, lr=lr)
+        want = single.cpu().numpy()
+    else:
+        ctx.hdc_train_online(hvd, yd, acc, epochs=1, lr=lr)
+        want = oracle.train_online(hv, y, D, C, epochs=1, lr=lr, acc=start.copy())
+    got = acc.cpu().numpy()
+    assert np.array_equal(np.isfinite(got), np.isfinite(want)) and np.array_equal(np.isnan(got), np.isnan(want))
+    ok = np.isfinite(want)
+    assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
+    assert np.max(np.abs(got[ok] - want[ok]), initial=0.0) <= TOL * max(1.0, float(np.max(np.abs(want[ok]), initial=0.0)))
+    ctx.close()
+
+
 def test_more_samples_than_are_held_at_a_time():
     D, C, N = 96, 3, 16384 + 300                   # the sample products of 16384 rows are held at a time
     rng = np.random.default_rng(1)
