@@ -61,7 +61,7 @@ struct hdc_ctx_impl {
     int64_t perm_rows;
     uint32_t *partial_d;  // [partial_items][Wp * 16] per-block partial counts, two u16 per dword
     int64_t partial_items;
-    uint32_t *on_bits_d;  // [8][1024] per-thread sample bits of online_lds_kernel, allocated with the block-wise trainer's scratch
+    uint32_t *on_bits_d;  // [14][1024] per-thread sample bits of online_lds_kernel, allocated with the block-wise trainer's scratch
     size_t on_bits_bytes;
     bool check_labels;    // hdc_set_label_check: training calls refuse labels outside [0, C)
     unsigned long long *bad_labels_d;   // [1] counter of count_bad_labels

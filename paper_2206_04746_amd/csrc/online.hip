@@ -540,10 +540,8 @@ __global__ __launch_bounds__(kOnlineThreads) void online_bits_kernel(const uint3
     tbits[(int64_t)blockIdx.x * kOnlineThreads + tid] = word;
 }
 
-// Steps (samples x epochs) up to which a call is walked sample by sample where a kernel for it exists:
-// 12 us + 3.6 us a step at C = 6, D = 10000 against 32 us for a first block of up to 64 samples.
-constexpr int64_t kShortSteps = 6;
-static_assert(kShortSteps * kOnlineThreads <= kOnlineWords, "the words of every sample of a short call");
+constexpr int64_t kMostSteps = 14;   // of a call of online_lds_kernel
+static_assert(kMostSteps * kOnlineThreads <= kOnlineWords, "the words of every sample of a short call");
 
 // What hdc_train_online may need; a no-op when it is there.
 int reserve_online(hdc_ctx_impl *c) {
@@ -551,7 +549,7 @@ int reserve_online(hdc_ctx_impl *c) {
     return online_chain_takes(c) ? reserve_online_chain(c) : HDC_OK;
 }
 
-// (at most kShortSteps samples, their words' memory there: online_chain_ready)
+// (at most kMostSteps samples, their words' memory there: online_chain_ready)
 template <int CMAX, int KPT>
 static int launch_online_lds(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *labels, int64_t N,
                              int32_t epochs, float lr, float *acc, hipStream_t s) {
@@ -589,27 +587,38 @@ int launch_train_online(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *labe
     // a thread keeps its sample bits in one word: beyond 32768 dimensions the batched trainer runs
     // with batches of one sample, which is the same method (in blocks, from four samples on)
     if (kpt > 32) return launch_train_online_batched(c, hv, labels, N, epochs, lr, 1, acc, s);
-    const bool brief = N * epochs <= kShortSteps;
+    const int64_t steps = N * epochs;
     int rc;
     const bool blocks = online_chain_ready(c, s, &rc);
     if (rc != HDC_OK) return rc;
-#define HDC_ONLINE_LDS_CASE(CM, KP) \
-    if (blocks && brief && C <= CM && kpt <= KP) return launch_online_lds<CM, KP>(c, hv, labels, N, epochs, lr, acc, s)
-    HDC_ONLINE_LDS_CASE(8, 2);
-    HDC_ONLINE_LDS_CASE(4, 4);
-    HDC_ONLINE_LDS_CASE(12, 4);
-    HDC_ONLINE_LDS_CASE(2, 10);
-    HDC_ONLINE_LDS_CASE(6, 10);
+    // Up to some number of steps the walk by samples is the faster way: 5 to 15 us and a step of 1.5 us (C = 1),
+    // 2.1 (C = 6, D = 1000), 2.9 (C = 6, D = 4000), 2.8 (C = 3, D = 10000) or 3.7 us (C = 6, D = 10000), against 24
+    // to 33 us of a first block.  The line of each variant lies where the two meet (11 steps against a block:
+    // C = 3, D = 1000 24.4 and 28.4 us, C = 6, D = 2000 29.6 and 27.9, C = 1, D = 10000 25.7 and 30.2; 6 steps:
+    // C = 6, D = 4000 27.7 and 27.6, C = 3, D = 10000 30.1 and 31.0, C = 6, D = 10000 36.4 and 30.9).
+#define HDC_ONLINE_LDS_CASE(CM, KP, STEPS) \
+    if (blocks && C <= CM && kpt <= KP && steps <= (STEPS)) return launch_online_lds<CM, KP>(c, hv, labels, N, epochs, lr, acc, s)
+    HDC_ONLINE_LDS_CASE(8, 2, kMostSteps - C * 3 / 4);
+    HDC_ONLINE_LDS_CASE(4, 4, kMostSteps - C * 3 / 4);
+    HDC_ONLINE_LDS_CASE(12, 4, 6);
+    HDC_ONLINE_LDS_CASE(2, 10, C == 1 ? kMostSteps : 12);
+    HDC_ONLINE_LDS_CASE(6, 10, 8 - C * 2 / 3);
 #undef HDC_ONLINE_LDS_CASE
-    if (blocks && !(brief && C <= 2 && kpt <= 16)) return launch_online_chain(c, hv, labels, N, epochs, lr, 1, true, acc, s);
-    // Sample by sample without any scratch: more than 64 classes, and calls for which the blocks' scratch
+    // The one-launch kernels below: with up to two classes to D = 16384 the same (46 us for six steps against 52),
+    // one step of up to 20 classes to D = 4096 and 32 to 1024 (36 to 44 us alone, against 40 to 49 of the blocks' five
+    // launches), two of up to 16 to D = 4096 (45 against 47 at 13), two of one class beyond (55 against 62 at D = 32000).
+    const bool one_launch = (C <= 2 && kpt > 10 && kpt <= 16 && steps <= 6) || (C == 1 && kpt > 16 && steps <= 2) ||
+                            (C > 12 && steps == 1 && ((C <= 20 && kpt <= 4) || (C <= 32 && kpt <= 1))) ||
+                            (C > 12 && C <= 16 && steps == 2 && kpt > 2 && kpt <= 4);
+    if (blocks && !one_launch) return launch_online_chain(c, hv, labels, N, epochs, lr, 1, true, acc, s);
+    // Sample by sample without any scratch: also more than 64 classes, and calls for which the blocks' scratch
     // cannot be had (a first call under capture).  In registers while the rows fit, else in memory.
 #define HDC_ONLINE_CASE(CM, KP) \
     if (C <= CM && kpt <= KP) return launch_online_reg<CM, KP>(c, hv, labels, N, epochs, lr, acc, s)
+    HDC_ONLINE_CASE(20, 4);
     HDC_ONLINE_CASE(32, 1);
     HDC_ONLINE_CASE(80, 1);
     HDC_ONLINE_CASE(40, 2);
-    HDC_ONLINE_CASE(20, 4);
     HDC_ONLINE_CASE(2, 16);
 #undef HDC_ONLINE_CASE
     const size_t lds = (size_t)(2 + kOnlineWaves) * (C < 2 ? 2 : C) * sizeof(double);

@@ -37,7 +37,7 @@ int launch_norm(hdc_ctx_impl *c, const float *acc, int G, hipStream_t s);
 // The block-wise walk of the chain (online_chain.hip): models it takes, batch sizes at which it is the
 // faster way, its scratch (with the words of online_lds_kernel), the call (per_sample: hdc_train_online's
 // arithmetic, else hdc_train_online_batched's).
-constexpr int64_t kOnlineWords = 8 * 1024;   // samples x threads whose bit words online_lds_kernel is handed (32 KB)
+constexpr int64_t kOnlineWords = 14 * 1024;   // samples x threads whose bit words online_lds_kernel is handed (56 KB)
 bool online_chain_takes(const hdc_ctx_impl *c);
 bool online_chain_pays(int64_t N, int64_t batch);
 int reserve_online_chain(hdc_ctx_impl *c);
