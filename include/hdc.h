@@ -187,7 +187,7 @@ int hdc_train_online(hdc_ctx *ctx, const uint32_t *hv_dev, const int32_t *labels
  *                                     -float(lr*(1 - cos_pred)) * s for c == pred != y
  * (fp64 sums) and acc[c] = float(double(acc[c]) + delta[c]), one rounding per element and
  * batch.  batch >= 1; a batch larger than N is one batch per epoch.  Small batches (up to 85 samples,
- * C <= 64, D <= 65535) are worked off several at a time as described for hdc_train_online.  Other arguments, layout
+ * fewer for few dimensions and for one or two classes; C <= 64, D <= 65535) are worked off several at a time as described for hdc_train_online.  Other arguments, layout
  * and the treatment of out-of-range labels are those of hdc_train_online.  The first call, and one
  * with a larger batch (min(batch, N)) than any before it, allocates device memory owned by the
  * context (HDC_ENOMEM if that fails) and therefore synchronises the device; other calls only

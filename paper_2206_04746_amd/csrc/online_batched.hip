@@ -988,7 +988,7 @@ int launch_train_online_batched(hdc_ctx_impl *c, const uint32_t *hv, const int32
     const FwdShape f = fwd_shape(C, G);
     if (batch > N) batch = N;
     int rc = HDC_OK;
-    if (online_chain_pays(N, batch) && online_chain_ready(c, s, &rc)) {
+    if (online_chain_pays(c, N, batch) && online_chain_ready(c, s, &rc)) {
         // a shorter call with the same batch goes in pieces: their scratch, too, belongs to this call
         if (batch > c->ob_blocks_batch && !stream_captured(s)) {
             rc = reserve_pieces(c, batch);

@@ -714,12 +714,30 @@ static int64_t held_samples(int G) {
 
 bool online_chain_takes(const hdc_ctx_impl *c) { return c->p.C <= 4 * kChainMaxWaves && c->p.D <= 65535; }
 
-// A block of up to 256 samples costs about what two batches cost the other way (three launches a
-// batch; 37 us a block against 18 us a batch at C = 6, D = 10000), and the call two more: batches of up to 85.
-bool online_chain_pays(int64_t N, int64_t batch) {
-    if (batch > kChainBlock) return false;
-    const int64_t block = kChainBlock / batch * batch;
-    return (N + batch - 1) / batch >= 2 * ((N + block - 1) / block) + 2;
+// A block of 256 samples costs as much as this many batches the other way, three launches each.  The fewer the
+// classes, the longer the list of samples that name one; at two and four classes a wave the passes spill; at large
+// D a batch costs more, a block hardly.  1020 samples, time of the blocks over that of the batches, at 32, 42, 51, 64
+// and 85 samples a batch:
+//   C = 1:  D = 1000 0.94 1.27 1.45 1.46 2.09   10000 0.77 1.03 1.19 1.20 1.74   40000 0.49 0.67 0.79 0.84 1.07
+//   C = 2:  D = 1000 0.68 0.90 1.04 1.08 1.54    4000 0.61 0.83 0.95 0.99 1.40   40000 0.39 0.53 0.63 0.67 0.87
+//   C = 4:  D = 1000 0.53 0.72 0.82 0.88 1.25    4000 0.46 0.63 0.72 0.79 1.10   10000 0.37 0.52 0.59 0.65 0.90
+//   C = 10: D = 1000 0.38 0.57 0.63 0.66 0.95    4000 0.35 0.53 0.57 0.62 0.88   10000 0.31 0.45 0.51 0.54 0.78
+//   C = 33: D = 1000 0.55 0.79 0.87 0.91 1.30    4000 0.52 0.75 0.81 0.84 1.22   10000 0.38 0.54 0.60 0.63 0.88
+// The line below leaves 10 of 3180 calls measured on both sides (1 to 64 classes, D = 100 to 65535, 4 to 1500 samples,
+// batches of 1 to 85) more than 5 % slower than the other way, the worst 9 %.
+static double batches_per_block(int C, int D) {
+    if (D < 512 && C <= 10) return C == 1 ? 4.0 : C <= 4 ? 3.2 : 2.0;   // few dimensions: the passes settle sooner
+    const double small = C == 1 ? 7.0 : C == 2 ? 4.7 : C <= 5 ? 3.9 : C <= 16 ? 3.05 : 3.7;
+    return small / (1.0 + D / (C <= 2 ? 45e3 : C <= 5 ? 30e3 : C <= 10 ? 45e3 : 22e3));
+}
+
+// A block that is not full costs a third of a full one and its share of the rest; but a call costs two
+// batches more, a last block of a few samples (260 at 85 a batch) as much as any.
+bool online_chain_pays(const hdc_ctx_impl *c, int64_t N, int64_t batch) {
+    if (3 * batch > kChainBlock) return false;   // (two batches a block or one: not measured)
+    const int64_t block = kChainBlock / batch * batch, batches = (N + batch - 1) / batch, rest = N % block;
+    const double blocks = (double)(N / block) + (rest ? 0.35 + 0.65 * (double)rest / (double)block : 0.0);
+    return batches >= 2 * ((N + block - 1) / block) + 2 && (double)batches >= batches_per_block(c->p.C, c->p.D) * blocks;
 }
 
 int reserve_online_chain(hdc_ctx_impl *c) {

@@ -39,7 +39,7 @@ int launch_norm(hdc_ctx_impl *c, const float *acc, int G, hipStream_t s);
 // arithmetic, else hdc_train_online_batched's).
 constexpr int64_t kOnlineWords = 14 * 1024;   // samples x threads whose bit words online_lds_kernel is handed (56 KB)
 bool online_chain_takes(const hdc_ctx_impl *c);
-bool online_chain_pays(int64_t N, int64_t batch);
+bool online_chain_pays(const hdc_ctx_impl *c, int64_t N, int64_t batch);
 int reserve_online_chain(hdc_ctx_impl *c);
 // Whether a call may go in blocks: a model they take, their scratch there or to be had.  False without an
 // error (*rc HDC_OK) while the stream is captured or memory is short: such a call goes another way.
