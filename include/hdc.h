@@ -304,10 +304,11 @@ typedef enum {
     HDC_K_ENCODE = 0,     /* bind + bundle + majority kernel of hdc_encode */
     HDC_K_QUANTIZE = 1,   /* bin-index kernel of hdc_encode */
     HDC_K_ACCUMULATE = 2, /* per-class vertical count kernel of hdc_train_classical */
-    HDC_K_ONLINE = 3,     /* sequential updater of hdc_train_online */
+    HDC_K_ONLINE = 3,     /* sequential updater of hdc_train_online: one entry a call, all its kernels where it goes in
+                             blocks; in hdc_train_online_batched the weights of a block of small batches */
     HDC_K_SEARCH = 4,     /* Hamming distance + argmin kernel of hdc_search */
-    HDC_K_ONLINE_FWD = 5, /* partial dot products of hdc_train_online_batched */
-    HDC_K_ONLINE_BWD = 6, /* batch sum + accumulator update of hdc_train_online_batched */
+    HDC_K_ONLINE_FWD = 5, /* partial dot products of hdc_train_online_batched, by batch or block */
+    HDC_K_ONLINE_BWD = 6, /* batch sums + accumulator update of hdc_train_online_batched, by batch or block */
     HDC_K_ENCODE_CONTRACT = 7, /* the contraction form of hdc_encode (quantises, bundles and spreads in one kernel) */
     HDC_K_ENCODE_WIDE = 8,     /* the contraction form of hdc_encode for long streams (jobs of 64 or 128 samples) */
     HDC_K_COUNT = 9

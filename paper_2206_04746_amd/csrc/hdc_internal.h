@@ -162,9 +162,9 @@ struct ProfScope {
     int id;
     hipStream_t s;
     bool live;
-    ProfScope(hdc_ctx_impl *ctx, int kernel_id, hipStream_t stream)
+    ProfScope(hdc_ctx_impl *ctx, int kernel_id, hipStream_t stream, bool wanted = true)
         : c(ctx), id(kernel_id), s(stream), live(false) {
-        if (c->prof_on && c->prof_ev[id] && c->prof_used[id] < HDC_PROFILE_SLOTS) {
+        if (wanted && c->prof_on && c->prof_ev[id] && c->prof_used[id] < HDC_PROFILE_SLOTS) {
             live = hipEventRecord(c->prof_ev[id][2 * c->prof_used[id]], s) == hipSuccess;
         }
     }

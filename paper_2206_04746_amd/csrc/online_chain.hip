@@ -781,7 +781,7 @@ static int launch_chain(hdc_ctx_impl *c, const int16_t *gram, int slices, int nb
         c->oc_attr_set[slot] = true;
     }
     const int subs = (nb + kSub - 1) / kSub;
-    ProfScope prof(c, BATCH ? HDC_K_ONLINE_FWD : HDC_K_ONLINE, s);
+    ProfScope prof(c, HDC_K_ONLINE, s, BATCH);
     hipLaunchKernelGGL(kern, dim3(1), dim3(kChainMaxWaves * kWave),
                        (size_t)(subs * (subs + 1) / 2) * kTile * sizeof(int16_t), s, gram, c->oc_part_d, slices, nb,
                        batch, labels, c->ob_norm_d, G, c->p.C, c->p.D, lr, 1.0 / sqrt((double)c->p.D),
@@ -795,6 +795,7 @@ static int walk_blocks(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *label
                        int batch, float *acc, hipStream_t s) {
     const int C = c->p.C, D = c->p.D, W = c->W;
     const int G = (D + kWave - 1) / kWave, slice = chain_slice(D), slices = (D + slice - 1) / slice;
+    ProfScope walk(c, HDC_K_ONLINE, s, !BATCH);   // a walk by samples as a whole; of batches each block's three steps
     int rc = launch_norm(c, acc, G, s);
     if (rc != HDC_OK) return rc;
     const int block = kChainBlock / batch * batch;   // whole batches
@@ -820,9 +821,12 @@ static int walk_blocks(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *label
                 const uint64_t *col = c->oc_col_d + b0;
                 const int32_t *lab = labels + h0 + b0;
                 const int16_t *gram = c->oc_gram_d + b0 / block * kTiles * kTile;
-                hipLaunchKernelGGL(online_dots_kernel,
-                                   dim3((unsigned)slices, (unsigned)((nb + 15) / 16), (unsigned)((C + 15) / 16)),
-                                   dim3(kDotWaves * kWave), 0, s, col, ld, nb, acc, D, C, slice, c->oc_part_d);
+                {
+                    ProfScope prof(c, HDC_K_ONLINE_FWD, s, BATCH);
+                    hipLaunchKernelGGL(online_dots_kernel,
+                                       dim3((unsigned)slices, (unsigned)((nb + 15) / 16), (unsigned)((C + 15) / 16)),
+                                       dim3(kDotWaves * kWave), 0, s, col, ld, nb, acc, D, C, slice, c->oc_part_d);
+                }
                 HDC_HIP(hipGetLastError());
                 if (C <= kChainMaxWaves)
                     rc = launch_chain<1, BATCH>(c, gram, slices, nb, batch, lab, G, lr, s);
@@ -832,6 +836,7 @@ static int walk_blocks(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *label
                     rc = launch_chain<4, BATCH>(c, gram, slices, nb, batch, lab, G, lr, s);
                 if (rc != HDC_OK) return rc;
                 const unsigned waves = (unsigned)(C < 4 ? 4 : C < kChainMaxWaves ? C : kChainMaxWaves);
+                ProfScope prof(c, HDC_K_ONLINE_BWD, s, BATCH);
                 hipLaunchKernelGGL(online_rows_kernel<BATCH>, dim3((unsigned)G), dim3(waves * kWave), 0, s, col, ld,
                                    nb, batch, static_cast<const OnlineWeight *>(c->oc_rec_d), acc, D, C, G,
                                    c->ob_norm_d);

@@ -143,3 +143,31 @@ def test_blocks_replayed_from_a_graph():
         torch.cuda.synchronize()
         assert torch.equal(acc, eager), k
     ctx.close()
+
+
+# samples, batch (0: hdc_train_online) -> entries of the counters online, online_fwd, online_bwd; a call in batches
+# that goes in blocks has as many of each as it has blocks, one that does not has none of the first
+@pytest.mark.parametrize("D,C,N,batch,blocks", [
+    (1000, 5, 600, 0, 0), (1000, 5, 600, 8, 3), (1000, 5, 32, 8, 1), (1000, 5, 24, 8, None), (1000, 5, 600, 86, None),
+    (1000, 1, 510, 85, None), (1000, 1, 1020, 42, None), (1000, 1, 1024, 32, 4), (20000, 1, 1020, 42, 5), (1000, 17, 510, 85, None),
+    (10000, 17, 510, 85, 2), (1000, 8, 510, 85, 2), (4000, 33, 1020, 85, None), (4000, 33, 1024, 64, 4), (1000, 65, 600, 8, None),
+    (65535, 3, 1020, 85, 4)])
+def test_which_calls_go_in_blocks_and_what_the_counters_say(D, C, N, batch, blocks):
+    ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
+    hvd = torch.zeros((N, ctx.W), dtype=torch.int32, device="cuda")
+    yd = torch.zeros(N, dtype=torch.int32, device="cuda")
+    acc = torch.zeros((C, D), dtype=torch.float32, device="cuda")
+    ctx.hdc_profile_enable(True)
+    if batch:
+        ctx.hdc_train_online_batched(hvd, yd, acc, batch, epochs=1, lr=1.0)
+    else:
+        ctx.hdc_train_online(hvd, yd, acc, epochs=1, lr=1.0)
+    (ms, n), (fwd_ms, fwd), (bwd_ms, bwd) = (ctx.hdc_profile_read(k) for k in ("online", "online_fwd", "online_bwd"))
+    if not batch:
+        assert (n, fwd, bwd) == (1, 0, 0) and ms > 0
+    elif blocks:
+        assert (n, fwd, bwd) == (blocks, blocks, blocks) and min(ms, fwd_ms, bwd_ms) > 0
+    else:
+        batches = -(-N // batch)
+        assert n == 0 and fwd == batches and bwd >= batches and min(fwd_ms, bwd_ms) > 0
+    ctx.close()
