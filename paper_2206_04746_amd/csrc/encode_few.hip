@@ -131,12 +131,15 @@ static int launch_few(hdc_ctx_impl *c, const void *feats, int N, uint32_t *hv, i
     return HDC_OK;
 }
 
-bool try_encode_few(hdc_ctx_impl *c, const void *feats, int64_t N, uint32_t *hv, hipStream_t s, int *rc) {
+bool try_encode_few(hdc_ctx_impl *c, const void *feats, int64_t N, uint32_t *hv, bool sparse, hipStream_t s, int *rc) {
     // A block costs about 1.1 ns + 6.8 ns per thousand features of the chip's time (31 to 784 features,
     // D = 2048 to 20000), the other kernels 7 us more than this one's launch: below that sum.
     // From 1024 samples on a matrix kernel takes any model that it can, with one launch more.
     const int64_t blocks = (int64_t)((c->W + kFewWords - 1) / kFewWords) * N;
     if (N >= 1024 || blocks * (c->p.F + 160) > 1 << 20) return false;
+    // The sparse encoder's two launches take 8.6 us whatever they find: a model of a few features is there
+    // sooner (F = 3, bytes, unrelated levels: 6400 blocks 10.9 us, 4800 blocks 9.1; at F = 64 4680 blocks 8.6).
+    if (sparse && blocks > 4400) return false;
     int P;
     uint32_t bias;
     majority_planes(c, &P, &bias);

@@ -322,7 +322,7 @@ int launch_encode_sparse(hdc_ctx_impl *c, const void *feats, int64_t N, uint32_t
     if (prc != HDC_OK && prc != HDC_ENOMEM) return prc;
     {
         int rc = HDC_OK;
-        if (try_encode_few(c, feats, N, hv, s, &rc)) return rc;
+        if (try_encode_few(c, feats, N, hv, true, s, &rc)) return rc;
     }
     prc = prepare_sparse(c, P, bias, s);
     if (prc != HDC_OK) return prc;

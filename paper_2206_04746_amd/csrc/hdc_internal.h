@@ -231,7 +231,7 @@ bool try_encode_contract(hdc_ctx_impl *c, const void *feats, int64_t N, uint32_t
 int prepare_wide(hdc_ctx_impl *c, const uint32_t *item, const uint32_t *level, const uint32_t *tie);
 bool try_encode_wide(hdc_ctx_impl *c, const void *feats, int64_t N, uint32_t *hv, hipStream_t s, int *rc);
 // Encoding of a few samples in one launch (encode_few.hip); same conventions.
-bool try_encode_few(hdc_ctx_impl *c, const void *feats, int64_t N, uint32_t *hv, hipStream_t s, int *rc);
+bool try_encode_few(hdc_ctx_impl *c, const void *feats, int64_t N, uint32_t *hv, bool sparse, hipStream_t s, int *rc);
 // Hamming search on the matrix cores for long query streams with 9..31 classes; false when the
 // shape is not its own (then nothing was launched and *rc is untouched).
 bool try_search_mfma(hdc_ctx_impl *c, const uint32_t *hv, int64_t N, const uint32_t *class_hv,
