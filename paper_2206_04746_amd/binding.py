@@ -114,8 +114,10 @@ def _dev(t: Optional[torch.Tensor], dtype: torch.dtype, shape=None) -> Optional[
 
 
 # torch.cuda.current_stream() builds a Stream object: 2.7 us, most of a call's host time beside the
-# launches; the handle alone, from the functions it is built on, takes 0.2 us.
-_current_device, _current_handle = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+# launches; the handle alone, from the functions it is built on, takes 0.2 us.  A torch without those
+# (they are not part of its public interface; a build for the CPU has neither) is asked the long way.
+_current_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
+_current_handle = getattr(torch._C, "_cuda_getCurrentRawStream", lambda device: torch.cuda.current_stream(device).cuda_stream)
 
 
 def _stream(stream) -> int:

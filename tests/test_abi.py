@@ -38,6 +38,23 @@ def test_status_texts_and_version():
     assert re.fullmatch(r"\d+\.\d+\.\d+", binding.version())
 
 
+def test_binding_imports_and_finds_the_stream_without_private_names_of_torch(monkeypatch):
+    import importlib.util
+    import types
+
+    import torch
+
+    for name in ("_cuda_getDevice", "_cuda_getCurrentRawStream"):
+        monkeypatch.delattr(torch._C, name, raising=False)
+    spec = importlib.util.spec_from_file_location("binding_again", os.path.join(ROOT, "paper_2206_04746_amd", "binding.py"))
+    binding = importlib.util.module_from_spec(spec)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: types.SimpleNamespace(cuda_stream=1000 + device))
+    spec.loader.exec_module(binding)
+    assert binding._stream(None) == 1003
+    assert binding._stream(17) == 17 and binding._stream(types.SimpleNamespace(cuda_stream=5)) == 5
+
+
 def test_product_package_does_not_import_the_oracle():
     pkg = os.path.join(ROOT, "paper_2206_04746_amd")
     for dirpath, _, files in os.walk(pkg):
