@@ -13,10 +13,12 @@ from workloads import make_workload  # noqa: E402
 from test_gpu_online_batched import clustered  # noqa: E402
 from test_gpu_parity import dev_u32, make_ctx  # noqa: E402
 
-# A weight is rounded to 24 bits; cosines that leave out the rows' rounding inside a block move it by a last
-# bit (at most 2^-23 for weights below 2) now and then.  An element is a sum of n such weights, so it is off by
-# n 2^-23 at the very most, whatever its own size (an element next to zero by as much as a large one: hence the
-# bound against the largest), which for n <= 300 per class and rows of size sqrt(n) is 2e-6.
+# A block's cosines leave out the fp32 rounding of the updates made since it began: u updates that name a row,
+# each off by at most 2^-24 of its elements, and the signs of those errors as good as random, so a cosine by about
+# sqrt(u) 2^-24 (measured, rows from zero: up to 3e-7 over D = 33 to 4096, 1 to 16 classes, samples 2 to 35 %
+# from their prototype; u 2^-24 at the very most).  A weight moves by as much.  An element is a sum of n
+# such weights of random sign: sqrt(n) 3e-7, whatever its own size (an element next to zero by as much as a large
+# one: hence the bound against the largest), which against rows of size sqrt(n) is 3e-7.  Seven times that.
 TOL = 2e-6
 
 
@@ -24,8 +26,9 @@ def off(acc, want):
     return float(np.max(np.abs(acc.cpu().numpy() - want)) / np.max(np.abs(want)))
 
 
-# short calls on either side of the walk by samples (6 steps); one sub-block and its edges; one block and its
-# edges; several blocks; classes at one, two and four to a wave; one class; odd D, the smallest and largest D
+# a few samples (fewer than a batch's dozen go sample by sample: test_gpu_online_short.py); one sub-block and its
+# edges; one block and its edges; several blocks; classes at one, two and four to a wave; one class; odd D, the
+# smallest and largest D
 SHAPES = [(1000, 5, 6), (1000, 5, 7), (2049, 3, 63), (2049, 3, 64), (10000, 6, 65), (1000, 2, 255), (1000, 16, 256),
           (1001, 17, 257), (640, 32, 300), (640, 33, 300), (512, 64, 600), (100, 1, 300), (65535, 2, 70), (63, 2, 130)]
 
@@ -50,6 +53,30 @@ def test_blocks_match_the_oracle(D, C, N, batch):
             want = oracle.train_online(hv, y, D, C, epochs=2 * calls, lr=0.5)
         assert off(acc, want) < TOL
     ctx.close()
+
+
+# Samples close to their prototypes (weights next to zero, and the roundings of a row's updates alike), and rows that
+# are large to begin with.  What a cosine leaves out is at most half a unit of every element for each of the u <= 256
+# updates of the row in the block, u 2^-24 of the row, and a weight moves by as much; N weights of random sign, and
+# an element's own rounding.
+@pytest.mark.parametrize("batch", [0, 20])
+@pytest.mark.parametrize("size", [0.0, 1.0, 1e3, 1e6])
+@pytest.mark.parametrize("D,C,flip", [(64, 1, 0.05), (100, 2, 0.02), (1024, 5, 0.02), (1000, 17, 0.1), (4096, 3, 0.35)])
+def test_similar_samples_and_large_rows(D, C, flip, size, batch):
+    rng = np.random.default_rng(D + C)
+    N = 700
+    hv, y = clustered(rng, N, D, C, flip)
+    start = (size * rng.normal(size=(C, D))).astype(np.float32)
+    ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
+    acc = torch.from_numpy(start.copy()).cuda()
+    if batch:
+        ctx.hdc_train_online_batched(dev_u32(hv), torch.from_numpy(y).cuda(), acc, batch, epochs=1, lr=1.0)
+        want = oracle.train_online_batched(hv, y, D, C, batch, epochs=1, lr=1.0, acc=start)
+    else:
+        ctx.hdc_train_online(dev_u32(hv), torch.from_numpy(y).cuda(), acc, epochs=1, lr=1.0)
+        want = oracle.train_online(hv, y, D, C, epochs=1, lr=1.0, acc=start)
+    ctx.close()
+    assert np.max(np.abs(acc.cpu().numpy() - want)) <= np.sqrt(N) * 256 * 2.0 ** -24 + 2 * np.spacing(np.abs(want).max())
 
 
 @pytest.mark.parametrize("batch", [0, 16])

@@ -48,7 +48,8 @@ def rand_hv(rng, N, D):
 
 
 # ------------------------------------------------------------------------------ encode
-# small batches take the feature-split launch, the 14000-sample cases the unsplit one
+# calls of the configurations: the contraction from 1024 samples on, below that the feature-split launch (the vector
+# encoders on models the contraction does not take are in test_gpu_encode_vector.py)
 @pytest.mark.parametrize("cfg,n", [(1, 2000), (2, 1500), (3, 1200), (4, 1000), (5, 1100), (5, 14000), (3, 14001)])
 def test_encode_configs_bit_exact(cfg, n):
     wl = make_workload(cfg)
@@ -83,9 +84,9 @@ def test_encode_ragged_shapes_bit_exact(D, F, L, N):
     ctx.close()
 
 
-# few samples: the waves of a block share one sample (16 waves each up to 256 sample-slices, 8 up
-# to 2048, one-sample units beyond); feature counts chosen to need 8, 10, 12 and 16 count planes
-# and half-block counts that do not divide by the waves
+# few samples: one launch while blocks x (features + 160) stays below 2^20; beyond, the waves of a block share
+# one sample (here from 85 samples of 617 features on, and of any number of 5000 features); feature counts
+# chosen to need 8, 10, 12 and 16 count planes
 @pytest.mark.parametrize("D,F,L,N", [
     (10000, 617, 64, 1), (10000, 617, 64, 2), (10000, 617, 64, 85), (10000, 617, 64, 86),
     (10000, 617, 64, 682), (10000, 617, 64, 683), (10000, 100, 16, 40), (10000, 1100, 7, 30),
@@ -321,9 +322,9 @@ def rel_err(got, want):
 @pytest.mark.parametrize("D,C,N,epochs,lr", [(1024, 5, 600, 2, 1.0), (10000, 6, 1500, 3, 1.0),
                                              (10000, 26, 300, 1, 0.5), (33, 1, 20, 2, 1.0),
                                              (2049, 3, 100, 1, 0.0), (32768, 2, 40, 1, 1.0),
-                                             # more samples than one prepared chunk (16384), two epochs
+                                             # more samples than are held at a time (16384), two epochs
                                              (1024, 3, 20000, 2, 1.0),
-                                             # 12 < C: the kernel with a butterfly per value; C > 80: accumulators in memory
+                                             # two classes a wave of the blocks; C > 64: sample by sample, accumulators in memory
                                              (1024, 20, 300, 1, 1.0), (512, 100, 120, 1, 1.0)])
 def test_online_training_matches_oracle(D, C, N, epochs, lr):
     rng = np.random.default_rng(D + C + N)
