@@ -6,18 +6,22 @@
 //     <acc_c before m, s_m> = <acc_c at the block's start, s_m> + sum over earlier n of k_n,c <s_n, s_m>
 // and the whole chain can be walked on the scalar products of the samples with one another, which
 // do not depend on the rows.  Four kernels:
-//   online_gram_kernel   once per call: <s_n, s_m> of all pairs of a block (XOR + popcount)
+//   online_gram_kernel   once per call: <s_n, s_m> of all pairs of a block
 //   online_dots_kernel   per block: <acc_c, s_m> against the rows at the block's start (fp64)
 //   online_chain_kernel  per block, one workgroup: cosines, predictions and weights of all samples
 //   online_rows_kernel   per block: the updates applied to the rows element by element, in sample
 //                        order, one fp32 rounding per update (per batch: one per batch), and the rows'
 //                        new squared norms
 // The dot products stay fp64 sums of the same fp32 rows and fp32 weights.  Inside a block they leave
-// out the fp32 rounding of the updates made since the block began: at most 2^-24 of an element per
-// update, which moves a cosine by some 1e-8 (measured at 561 features, 6 classes, D = 10000: median
-// 5e-9, largest 3e-8), below the 6e-8 to which the weight made from it is rounded.
-// The rows after training are as far from the method in 64 bits as the sample-by-sample kernels leave
-// them: relative 2-norm 5.89e-7 both (6 classes, D = 10000, 3000 samples), 1.65e-7 both (26, 1024, 1500).
+// out the fp32 rounding of the u updates of a row made since the block began: at most 2^-24 of an element each,
+// so u 2^-24 of a cosine at the very most and about sqrt(u) 2^-24 as a rule: largest 3e-8 at 561 features, 6
+// classes, D = 10000; 3e-7 over D = 33 to 4096, 1 to 16 classes and samples 2 to 35 % from their prototype; 3e-6
+// where rows of size 1e6 are trained on; up to 4e-4 for a cosine or two where samples drive a row through zero.
+// That is no distance from the method: against the method in 64 bits the walk by samples, which rounds the rows at
+// every step, is as far off (largest over those models, walk and blocks: cosines 2.8e-7 and 3.4e-7, rows relative
+// 2-norm 1.4e-6 and 1.3e-6 from zero rows; 1.4e-5 and 1.2e-5, 2.9e-5 both from rows of 1e6; 5.6e-4 and 2.1e-4,
+// 5.3e-6 and 5.4e-6 through zero).  But the two forms may part where two cosines agree that closely, also where samples that repeat
+// make rows proportional.
 //
 // Walking the chain sample after sample on one workgroup took 3.6 us per sample (two block barriers
 // and a block-wide sum for each).
