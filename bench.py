@@ -247,7 +247,7 @@ def main() -> int:
         "value": round(value, 1), "unit": "samples/s", "n_gpus": 1, "steps": K, "warmup": Wm,
         "ms_per_step": round(ms_per_step, 4), "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "u32", "data": "synthetic",
-        "config": {"workload": f"configs[4]: long-term-EEG-shaped classical HDC, D=10000, F=342 fp32, L=64, C=2, "
+        "config": {"workload": f"long-term-EEG-shaped classical HDC, D=10000, F=342 fp32, L=64, C=2, "
                                f"{N} windows (1 % positive, lognormal per channel) in {len(chunks)} chunks of "
                                f"{CHUNK_WINDOWS}",
                    "step": "per chunk: encode + train_classical; binarize; per chunk: search"},
@@ -325,7 +325,7 @@ def secondary(torch, binding, make_workload, K):
     t_train = float(np.median([e[0].elapsed_time(e[1]) for e in ev]))
     t_enc_s = float(np.median([e[1].elapsed_time(e[2]) for e in ev]))
     t_search = float(np.median([e[2].elapsed_time(e[3]) for e in ev]))
-    res = {"workload": "configs[1]: D=10000, F=617 fp32, L=64, C=26, 6238 train / 1559 test",
+    res = {"workload": "spoken-letter shape: D=10000, F=617 fp32, L=64, C=26, 6238 train / 1559 test",
            "steps": K, "ms_per_step": round(ms_per_step, 4),
            "encoded_plus_trained_samples_per_s": round(ntr / (t_train * 1e-3), 1),
            "queries_per_s": round(nte / (t_search * 1e-3), 1),
@@ -704,7 +704,7 @@ def cpu_baseline(wl):
     finally:
         _omp_threads(cores)
     return {"value": round(n_all / dt, 1), "unit": "samples/s", "cores": cores, "kind": "oracle",
-            "sample": f"first {n_all} of the 5,000,000 windows of configs[4]: oracle encode + train_classical + "
+            "sample": f"first {n_all} of the 5,000,000 windows of the EEG-shaped stream: oracle encode + train_classical + "
                       f"binarize ({dt:.1f} s); search of the same windows: {n_all / ds:.0f} queries/s",
             "queries_per_s": round(n_all / ds, 1),
             "one_thread": {"value": round(n_one / dt1, 1), "queries_per_s": round(n_one / ds1, 1),

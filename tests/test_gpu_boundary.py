@@ -140,7 +140,7 @@ def test_reserved_calls_are_captured_without_a_call_before():
 
 def test_search_of_one_chunk_beside_the_encoding_of_the_next_on_two_streams():
     """hdc_search uses no scratch of the context, so with one context the search of chunk k may run
-    on one stream while chunk k + 1 is encoded on another (the long stream of configs[4] invites
+    on one stream while chunk k + 1 is encoded on another (a long stream invites
     that): the rows and predictions equal those of the same calls made one after the other."""
     wl = make_workload(5)
     from paper_2206_04746_amd import binding
