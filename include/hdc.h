@@ -167,14 +167,14 @@ int hdc_binarize_classical(hdc_ctx *ctx, const int32_t *acc_dev, const int64_t *
  * Up to C = 64 and D = 65535, calls of more than a few samples are worked off in blocks of 256
  * samples: the chain is walked on the samples' scalar products with one another and the dot
  * products with the rows at the block's start, then the updates are applied to the rows one by one.
- * The cosines then leave out the fp32 rounding of the u <= 256 updates of a row since the block's
- * start: at most u * 2^-24, as a rule sqrt(u) * 2^-24 (largest seen 3e-8 at D = 10000, 6 classes;
+ * The cosines then leave out the fp32 rounding of the u <= 512 updates of a row since the start of
+ * the block or the one before: at most u * 2^-24, as a rule sqrt(u) * 2^-24 (largest seen 3e-8 at D = 10000, 6 classes;
  * 3e-7 over D = 33 to 4096 from zero rows; 3e-6 from rows of size 1e6; more while samples drive a
  * row through zero).  They are no further from the
  * method in 64 bits for it, but a prediction between cosines that agree this closely (rows that
  * repeated samples have made proportional, for instance) may be another one than a walk by samples
  * takes.  The first call, whatever its size, allocates
- * context-owned scratch (11 MB + 16384 rows, at most 64 MB of them) unless hdc_reserve has done so;
+ * context-owned scratch (19 MB + 16384 rows, at most 64 MB of them) unless hdc_reserve has done so;
  * later calls only enqueue on `stream`.  Where the scratch cannot be had - memory is short, or the
  * first call is being captured into a graph - and D <= 32768, the call goes sample by sample
  * without any, which is slower; beyond D = 32768 that is HDC_ENOMEM or HDC_EHIP.

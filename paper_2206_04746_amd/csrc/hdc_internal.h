@@ -102,7 +102,15 @@ struct hdc_ctx_impl {
     size_t oc_part_bytes;
     void *oc_rec_d;       // [256] weight records of a block
     size_t oc_rec_bytes;
-    bool oc_attr_set[6];  // dynamic-LDS limit of online_chain_kernel raised, by variant
+    void *oc_order_d;     // [blocks] online_wide_kernel's rows by wave
+    size_t oc_order_bytes;
+    int16_t *oc_image_d;  // [blocks][8][12][64][8] and the products of those rows
+    size_t oc_image_bytes;
+    int16_t *oc_pairs_d;  // [blocks][4][4][64][64] products of a block's samples with the next one's
+    size_t oc_pairs_bytes;
+    double *oc_norm_d;    // [C][ceil(D/64)] the other squared-norm partials, and [C] what a block adds to them
+    size_t oc_norm_bytes;
+    bool oc_attr_set[8];  // dynamic-LDS limit of online_chain_kernel / online_wide_kernel raised, by variant
 
     // hdc_encode_sparse (allocated and derived on its first call)
     bool sp_ready;

@@ -12,20 +12,25 @@
 //   online_rows_kernel   per block: the updates applied to the rows element by element, in sample
 //                        order, one fp32 rounding per update (per batch: one per batch), and the rows'
 //                        new squared norms
+// Per-sample calls of up to 16 classes take online_wide_kernel for the chain, which walks the block as a whole, with the
+// row updates of the block before as its other workgroups (wide_takes, walk_wide).
 // The dot products stay fp64 sums of the same fp32 rows and fp32 weights.  Inside a block they leave
-// out the fp32 rounding of the u updates of a row made since the block began: at most 2^-24 of an element each,
+// out the fp32 rounding of the u updates of a row made since the block began (walk_wide: since the one before did): at most 2^-24 of an element each,
 // so u 2^-24 of a cosine at the very most and about sqrt(u) 2^-24 as a rule: largest 3e-8 at 561 features, 6
 // classes, D = 10000; 3e-7 over D = 33 to 4096, 1 to 16 classes and samples 2 to 35 % from their prototype; 3e-6
 // where rows of size 1e6 are trained on; up to 4e-4 for a cosine or two where samples drive a row through zero.
 // That is no distance from the method: against the method in 64 bits the walk by samples, which rounds the rows at
 // every step, is as far off (largest over those models, walk and blocks: cosines 2.8e-7 and 3.4e-7, rows relative
 // 2-norm 1.4e-6 and 1.3e-6 from zero rows; 1.4e-5 and 1.2e-5, 2.9e-5 both from rows of 1e6; 5.6e-4 and 2.1e-4,
-// 5.3e-6 and 5.4e-6 through zero).  But the two forms may part where two cosines agree that closely, also where samples that repeat
+// 5.3e-6 and 5.4e-6 through zero; walk_wide on the GPU, 1 to 16 classes, D = 1000 to 12000, 1000 to 1500 samples: rows
+// 1.43e-7 to 5.47e-7 where blocks that begin from their own rows are 1.42e-7 to 5.46e-7 off, largest differences alike
+// in four digits).  But the two forms may part where two cosines agree that closely, also where samples that repeat
 // make rows proportional.
 //
 // Walking the chain sample after sample on one workgroup took 3.6 us per sample (two block barriers
 // and a block-wide sum for each).
 #include <algorithm>
+#include <type_traits>
 
 #include "hdc_internal.h"
 #include "online_weight.h"
@@ -38,19 +43,126 @@ constexpr int kSubs = kChainBlock / kSub;
 constexpr int kTile = kSub * kSub;                  // products of one pair of sub-blocks
 constexpr int kTiles = kSubs * (kSubs + 1) / 2;     // pairs (a, b), a <= b, at b (b + 1) / 2 + a
 constexpr int64_t kGramSamples = 16384;             // samples whose products are held at a time
+constexpr int64_t kWideSamples = 8192;              // ... where blocks are walked as a whole, which takes three times the memory
+constexpr int64_t kWideBlocks = kWideSamples / kChainBlock;
 constexpr int64_t kGramBlocks = kGramSamples / (kChainBlock / 2 + 1) + 2;   // a block has more than 128 samples
 constexpr int kChainMaxWaves = 16;
 constexpr int kSlices = 10;                         // most slices the dimensions are split into
+
+// ---- the order of a block's products in online_wide_kernel (below) --------------------------------
+constexpr int kWideWaves = 8, kWideRows = 96, kWideClasses = 16;   // rows of a wave: room for
+constexpr int kNoSample = kChainBlock;   // its weight is zero
+// Groups of rows: 640 rows and the filling of 4 C classes are 184 groups of four at most (8 classes), 352 of two (16).
+__host__ __device__ constexpr int wide_group(int C) { return C <= 8 ? 4 : 2; }
+__host__ __device__ constexpr int wide_rows(int GR) { return GR == 4 ? 92 : 88; }   // of a wave, therefore
+// Places in LDS for sums over a wave's rows from its first one on, one for every run of groups of a class in a wave.
+// The last two: one that holds zero, one nobody reads.
+__host__ __device__ constexpr int wide_places(int C) { return kSubs * C + kWideWaves + 2; }
+
+struct WideOrder {                       // of a block, from its labels
+    uint16_t src[kWideWaves][kWideRows]; // a wave's rows: sample, kNoSample where a class is filled up
+    uint16_t to[kWideWaves][kSub];       // places of its groups' sums
+    uint16_t sum[kWideClasses][kSubs][8];// a class's sum in a target sub-block: that of place [0] less that of place [1], and those of
+                                         // [2] to [5] in the waves it goes on in; [6]: it goes on in more than one
+    uint16_t row[kSubs][kChainBlock];    // 96 wave + row of a sample in a target sub-block's list, ~0: none
+    int32_t rows;                        // of a wave: at least 64, so that a list of 256 touches no more than five waves
+    int32_t pad[3];
+};
+
+// A wave's rows as they lie in memory: [wave][row / 8][lane][row % 8], 16 bytes a lane and load.
+constexpr int kWideImage = kWideWaves * kWideRows * kSub;
+__host__ __device__ constexpr int wide_place(int row, int lane) {   // row: 96 wave + its row
+    return ((row >> 3) * kSub + lane) * 8 + (row & 7);
+}
+
+// Sum over the lanes up to this one.
+__device__ __forceinline__ int lane_sum(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);    // row_shr:1, 2, 4, 8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15, 31
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);
+    return v;
+}
+
+// Writes the order of one block (256 threads).  A list: the samples of a class among those up to the end of a target
+// sub-block; lists stand at C j + c, their groups one after another are dealt to the waves in equal numbers.
+__device__ void write_order(const int32_t *__restrict__ labels, int nb, int C, WideOrder *__restrict__ out) {
+    __shared__ WideOrder o;
+    __shared__ int cnt[kSubs][kWideClasses];
+    __shared__ int first[kSubs * kWideClasses], run[kSubs * kWideClasses];   // a list's first group and run
+    const int t = threadIdx.x, lane = t & (kWave - 1), a = t >> 6;
+    const int GR = wide_group(C), zero = wide_places(C) - 2, lists = kSubs * C;
+    int y = t < nb ? labels[t] : -1;
+    y = y >= 0 && y < C ? y : -1;
+    int rank = 0;
+    for (int c = 0; c < C; ++c) {
+        const uint64_t m = __ballot(y == c);
+        if (y == c) rank = __popcll(m & ((1ull << lane) - 1));
+        if (lane == 0) cnt[a][c] = __popcll(m);
+    }
+    for (int i = t; i < kWideWaves * kWideRows; i += kChainBlock) (&o.src[0][0])[i] = kNoSample;
+    for (int i = t; i < kSubs * kChainBlock; i += kChainBlock) (&o.row[0][0])[i] = 0xFFFF;
+    for (int i = t; i < kWideWaves * kSub; i += kChainBlock) (&o.to[0][0])[i] = (uint16_t)(zero + 1);
+    __syncthreads();
+    if (a == 0) {   // a lane to a list
+        const int j = lane / C, c = lane % C;
+        int groups = 0;
+        if (lane < lists)
+            for (int i = 0; i <= j; ++i) groups += cnt[i][c];
+        groups = (groups + GR - 1) / GR;
+        const int end = lane_sum(groups), g0 = end - groups;
+        const int per = max((__builtin_amdgcn_readlane(end, kWave - 1) + kWideWaves - 1) / kWideWaves, kSub / GR);   // groups of a wave
+        const int w0 = g0 / per, w1 = groups ? (end - 1) / per : w0 - 1, runs = w1 - w0 + 1;
+        const int r0 = lane_sum(runs) - runs;
+        if (lane < lists) {
+            first[lane] = g0;
+            run[lane] = r0;
+            uint16_t *sum = o.sum[c][j];
+            sum[0] = (uint16_t)(runs ? r0 : zero);
+            sum[1] = (uint16_t)(runs && g0 % per ? r0 - 1 : zero);   // (the run before it in the wave)
+            for (int i = 2; i < 6; ++i) sum[i] = (uint16_t)(runs >= i ? r0 + i - 1 : zero);
+            sum[6] = runs > 2;
+            sum[7] = 0;
+        }
+        if (lane == 0) o.rows = per * GR;
+    }
+    __syncthreads();
+    if (y >= 0) {
+        const int per = o.rows / GR;
+        int r = rank;
+        for (int i = 0; i < a; ++i) r += cnt[i][y];
+        for (int j = a; j < kSubs; ++j) {
+            const int list = j * C + y, g = first[list] + r / GR, w = g / per, u = g % per * GR + r % GR;
+            o.src[w][u] = (uint16_t)t;
+            o.row[j][t] = (uint16_t)(w * kWideRows + u);
+            o.to[w][g % per] = (uint16_t)(run[list] + w - first[list] / per);
+        }
+    }
+    __syncthreads();
+    for (int i = t; i < (int)(sizeof(WideOrder) / 4); i += kChainBlock)
+        reinterpret_cast<uint32_t *>(out)[i] = reinterpret_cast<const uint32_t *>(&o)[i];
+}
 
 // ---- the samples' bits, dimension group by dimension group ----------------------------------------
 // col[g][n] = bits 64 g .. 64 g + 63 of sample n: the steps below work on one group of all samples of a
 // block, which row by row would be 8 bytes out of every 4 W (the rows step took 16 us like that, most of
 // it in these loads).  Bits past D are dropped here: the products count every bit of a word.  A block
-// turns 64 samples x 16 groups through LDS.  grid (sample tiles, group tiles)
+// turns 64 samples x 16 groups through LDS.  grid (sample tiles, group tiles, and where there are orders to
+// write a row more: block after block of samples)
 constexpr int kColGroups = 16;
+template <bool WIDE>
 __global__ __launch_bounds__(256) void online_columns_kernel(const uint32_t *__restrict__ hv, int64_t N, int W,
                                                              uint32_t last_mask, int G, int64_t ld,
-                                                             uint64_t *__restrict__ col) {
+                                                             uint64_t *__restrict__ col,
+                                                             const int32_t *__restrict__ labels, int C,
+                                                             WideOrder *__restrict__ order) {
+    if (WIDE && (int)blockIdx.y * kColGroups >= G) {
+        const int64_t n = (int64_t)blockIdx.x * kChainBlock;
+        if (n < N) write_order(labels + n, (int)(N - n < kChainBlock ? N - n : kChainBlock), C, order + blockIdx.x);
+        return;
+    }
     __shared__ uint32_t tile[kSub][2 * kColGroups + 1];
     const int t = threadIdx.x;
     const int64_t n0 = (int64_t)blockIdx.x * kSub;
@@ -71,7 +183,7 @@ __global__ __launch_bounds__(256) void online_columns_kernel(const uint32_t *__r
 }
 
 // ---- products of the samples of a block ---------------------------------------------------------
-// grid (pair (a, b) of sub-blocks, block).  <s_n, s_m> = D - 2 popcount(h_n ^ h_m) is stored as
+// grid (pair (a, b) of sub-blocks, then the pairs of a block with the next one if they are wanted, block).  <s_n, s_m> = D - 2 popcount(h_n ^ h_m) is stored as
 // (D >> 1) - popcount, which fits 16 bits up to D = 65535.  popcount(h_n ^ h_m) = |h_n| + |h_m| - 2 <h_n, h_m>,
 // the last term a product of 0/1 vectors on 4-bit floats: a nibble with one bit set is worth 0.5, 1 or 2,
 // so the bits stay where they are in one operand and carry the reciprocal in the other (search_mfma.hip
@@ -81,17 +193,27 @@ __global__ __launch_bounds__(256) void online_columns_kernel(const uint32_t *__r
 constexpr int kGramWaves = 8, kGramPitch = kSub + 8;   // (the two halves of a wave add to different banks)
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+template <bool WIDE>
 __global__ __launch_bounds__(kGramWaves *kWave) void online_gram_kernel(const uint64_t *__restrict__ col, int64_t ld,
                                                                         int64_t N, int D, int G, int block,
-                                                                        int16_t *__restrict__ gram) {
+                                                                        int16_t *__restrict__ gram,
+                                                                        const WideOrder *__restrict__ order,
+                                                                        int16_t *__restrict__ image, int16_t *__restrict__ pairs) {
     __shared__ int sum[kSub][kGramPitch];
     __shared__ int ones[2][kSub];
-    int b = 0;
-    while ((b + 1) * (b + 2) / 2 <= (int)blockIdx.x) ++b;
-    const int a = (int)blockIdx.x - b * (b + 1) / 2;
-    const int64_t n0 = (int64_t)blockIdx.y * block;
-    const int nb = (int)(N - n0 < block ? N - n0 : block);
+    const bool pair = WIDE && (int)blockIdx.x >= kTiles;   // sub-block a of this block, b of the next one
+    int a, b = 0;
+    if (pair) {
+        a = ((int)blockIdx.x - kTiles) / kSubs;
+        b = ((int)blockIdx.x - kTiles) % kSubs;
+    } else {
+        while ((b + 1) * (b + 2) / 2 <= (int)blockIdx.x) ++b;
+        a = (int)blockIdx.x - b * (b + 1) / 2;
+    }
+    const int64_t n0 = (int64_t)blockIdx.y * block, m0 = n0 + (pair ? block : 0);   // first sample of the rows' block, of the columns'
+    const int nb = (int)(N - m0 < block ? N - m0 : block);
     if (b * kSub >= nb) return;
     const int t = threadIdx.x, lane = t & (kWave - 1), wave = t >> 6;
     const int r = lane & 31, half = lane >> 5;   // this lane's sample of a tile of 32, and its word of a group
@@ -100,8 +222,8 @@ __global__ __launch_bounds__(kGramWaves *kWave) void online_gram_kernel(const ui
     const uint32_t *src[4];   // rows a 64 + r, + 32; columns b 64 + r, + 32
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const int n = min((i < 2 ? a : b) * kSub + 32 * (i & 1) + r, nb - 1);
-        src[i] = reinterpret_cast<const uint32_t *>(col + n0 + n) + half;
+        const int n = (i < 2 ? a : b) * kSub + 32 * (i & 1) + r;
+        src[i] = reinterpret_cast<const uint32_t *>(col + (i < 2 ? n0 : m0) + (pair && i < 2 ? n : min(n, nb - 1))) + half;   // (a block with a next one is full)
     }
     v16f dot[2][2] = {};
     int pop[4] = {0, 0, 0, 0};
@@ -147,15 +269,23 @@ __global__ __launch_bounds__(kGramWaves *kWave) void online_gram_kernel(const ui
             for (int k = 0; k < 16; ++k)   // register k: row 8 (k / 4) + 4 half + k % 4, column r
                 atomicAdd(&sum[32 * i + 8 * (k / 4) + 4 * half + k % 4][32 * j + r], (int)dot[i][j][k]);
     __syncthreads();
-    int16_t *out = gram + ((int64_t)blockIdx.y * kTiles + blockIdx.x) * kTile;
+    int16_t *out = pair ? pairs + ((int64_t)blockIdx.y * kSubs * kSubs + ((int)blockIdx.x - kTiles)) * kTile
+                        : gram + ((int64_t)blockIdx.y * kTiles + blockIdx.x) * kTile;
     for (int i = t; i < kTile; i += kGramWaves * kWave) {
         const int u = i / kSub, v = i % kSub;
-        out[i] = (int16_t)((D >> 1) - ones[0][u] - ones[1][v] + 2 * sum[u][v]);
+        const int half = (D >> 1) - ones[0][u] - ones[1][v] + 2 * sum[u][v];
+        if (WIDE && !pair) {   // for online_wide_kernel the whole product (D <= 32767) where it counts, and it in the row that holds it
+            const int whole = a < b || u < v ? 2 * half + (D & 1) : 0, row = order[blockIdx.y].row[b][a * kSub + u];
+            out[i] = (int16_t)whole;
+            if (row != 0xFFFF) image[(int64_t)blockIdx.y * kWideImage + wide_place(row, v)] = (int16_t)whole;
+        } else {
+            out[i] = (int16_t)half;
+        }
     }
 }
 
 // ---- dot products against the rows at the block's start -----------------------------------------
-// grid (slices of the dimensions, tiles of 16 samples, tiles of 16 classes), 8 waves a block that
+// grid (slices of the dimensions and, where wanted, the block before; tiles of 16 samples; of 16 classes), 8 waves a block that
 // split the slice.  On the matrix cores in fp64: their rate equals the vector unit's on this chip, but
 // the sum over the dimensions comes with the instruction, where the vector form spends a cross-lane
 // sum per (sample, class).  Any assignment of dimensions to the instruction's K positions will
@@ -165,11 +295,37 @@ __global__ __launch_bounds__(kGramWaves *kWave) void online_gram_kernel(const ui
 constexpr int kDotWaves = 8;
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
+// One more slice where the rows do not yet hold the updates of the block before: what those add to 16 samples'
+// products, from the products of samples and that block's weights (lane 16 q + i: sample i, one of four samples before).
+__device__ __forceinline__ f64x4 add_block_before(const int16_t *__restrict__ pairs, const OnlineWeight *__restrict__ recs, int D, double *lds) {
+    static_assert(kDotWaves * kWave == 2 * kChainBlock, "a thread to half a row of 16");
+    int16_t(*g)[16] = reinterpret_cast<int16_t(*)[16]>(lds);                 // 8 KB
+    OnlineWeight *r = reinterpret_cast<OnlineWeight *>(lds + 1024);          // 4 KB
+    const int t = threadIdx.x, n0 = t >> 1, b = blockIdx.y / 4, v = 16 * (blockIdx.y % 4) + 8 * (t & 1);
+    *reinterpret_cast<u32x4 *>(&g[n0][8 * (t & 1)]) =
+        *reinterpret_cast<const u32x4 *>(pairs + (((n0 / kSub) * kSubs + b) * kSub + n0 % kSub) * kSub + v);
+    if (t < kChainBlock) r[t] = recs[t];
+    __syncthreads();
+    const int q = (t & (kWave - 1)) >> 4, i = t & 15, c = blockIdx.z * 16 + i;
+    f64x4 sum = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < kChainBlock / kDotWaves / 4; ++s) {
+        const int n = (t / kWave) * (kChainBlock / kDotWaves) + 4 * s + q;
+        const OnlineWeight w = r[n];
+        const float k = w.y == c ? w.w_y : w.pred == c ? -w.w_p : 0.0f;
+        sum = __builtin_amdgcn_mfma_f64_16x16x4f64((double)(2 * (int)g[n][i] + (D & 1)), (double)k, sum, 0, 0, 0);
+    }
+    __syncthreads();
+    return sum;
+}
+
 __global__ __launch_bounds__(kDotWaves *kWave) void online_dots_kernel(const uint64_t *__restrict__ col,
                                                                        int64_t ld, int nb,
                                                                        const float *__restrict__ acc, int D, int C,
-                                                                       int slice, double *__restrict__ part) {
-    __shared__ double red[kDotWaves][256];
+                                                                       int slice, int slices, const int16_t *__restrict__ pairs,
+                                                                       const OnlineWeight *__restrict__ recs,
+                                                                       double *__restrict__ part) {
+    __shared__ __align__(16) double red[kDotWaves][256];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
     const int q = lane >> 4, i = lane & 15;
     int n = blockIdx.y * 16 + i;
@@ -181,6 +337,7 @@ __global__ __launch_bounds__(kDotWaves *kWave) void online_dots_kernel(const uin
     const int lo = blockIdx.x * slice + wave * span;
     const int hi = lo + span < D ? lo + span : D;
     f64x4 sum = {0.0, 0.0, 0.0, 0.0};
+    if ((int)blockIdx.x == slices) sum = add_block_before(pairs, recs, D, &red[0][0]);   // (lo is past D)
     for (int d0 = lo; d0 < hi; d0 += kWave) {
         const int d = d0 + 16 * q;
         const uint32_t inv = ~(uint32_t)h[(int64_t)(d0 >> 6) * ld * 4];   // bit k: the sign of dimension d + k
@@ -255,17 +412,18 @@ __device__ __forceinline__ double refined_rsq(double nn) {
 // its classes, and the decision is taken class by class, as in the kernels that walk sample by sample
 // (BATCH: as in the batched trainer, which passes over classes whose cosine is no number).  cosv: [C] in LDS.
 template <int CPW, bool BATCH>
-__device__ __noinline__ void walk_block(const int16_t *prod, const double *__restrict__ part, int slices, int nb, int batch,
-                           const int32_t *__restrict__ labels, const double *__restrict__ normpart, int G, int C, int D,
-                           float lr, double inv_root_d, OnlineWeight *rec, double *cosv) {
+__device__ __noinline__ void walk_block(const int16_t *prod, bool halves, const double *__restrict__ part, int slices, int nb, int batch,
+                           const int32_t *__restrict__ labels, const double *__restrict__ normpart, const double *before,
+                           double *grown, int G, int C, int D, float lr, double inv_root_d, OnlineWeight *rec, double *cosv) {
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    double nrm[CPW], frozen[CPW];   // squared norms now, and where the batch began
+    double nrm[CPW], frozen[CPW], at_start[CPW];   // squared norms now, where the batch began, where the block did
     for (int k = 0; k < CPW; ++k) {
         const int c = wave * CPW + k;
         double s = 0.0;
         for (int g = lane; g < G && c < C; g += kWave) s += normpart[(int64_t)c * G + g];
-        nrm[k] = frozen[k] = lane_f64(lane_prefix(s), kWave - 1);
+        nrm[k] = frozen[k] = lane_f64(lane_prefix(s), kWave - 1) + (before && c < C ? before[c] : 0.0);
+        at_start[k] = nrm[k];
     }
     for (int m = 0; m < nb; ++m) {
         const int first = BATCH ? m / batch * batch : m, b = m / kSub;
@@ -283,7 +441,7 @@ __device__ __noinline__ void walk_block(const int16_t *prod, const double *__res
             for (int i = 0; i < slices; ++i) start += part[((int64_t)i * C + c) * kChainBlock + m];
             for (int n = lane; n < m; n += kWave) {
                 const OnlineWeight r = rec[n];
-                const double g = (double)(2 * (int)tiles[n * kSub] + (D & 1));
+                const double g = (double)(halves ? 2 * (int)tiles[n * kSub] + (D & 1) : (int)tiles[n * kSub]);
                 const double term = r.y == c ? (double)r.w_y * g : r.pred == c ? -(double)r.w_p * g : 0.0;
                 (n < first ? old : own) += term;
             }
@@ -318,6 +476,8 @@ __device__ __noinline__ void walk_block(const int16_t *prod, const double *__res
             if (c < C && (r.y == c || r.pred == c)) nrm[k] += w * (2.0 * all[k] + w * (double)D);
         }
     }
+    for (int k = 0; k < CPW && grown; ++k)
+        if (lane == 0 && wave * CPW + k < C) grown[wave * CPW + k] = nrm[k] - at_start[k];
     __syncthreads();
 }
 
@@ -414,7 +574,8 @@ __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
     __syncthreads();
     if (wave >= used) return;   // (an ended wave takes no part in later barriers)
     if (__builtin_expect(__ballot(lane < used && s_odd[lane]) != 0 || !(fabsf(lr) < 1e30f), 0)) {   // the same in every wave
-        walk_block<CPW, BATCH>(prod, part, slices, nb, batch, labels, normpart, G, C, D, lr, inv_root_d, s_rec, s_cosy[0]);
+        walk_block<CPW, BATCH>(prod, true, part, slices, nb, batch, labels, normpart, nullptr, nullptr, G, C, D, lr, inv_root_d, s_rec,
+                               s_cosy[0]);
         for (int n = tid; n < nb; n += used * kWave) out[n] = s_rec[n];
         return;
     }
@@ -639,12 +800,12 @@ __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
 // weight and 64 bits come by lane reads, so nothing in the loop waits for memory.  Per sample one fp32
 // add (the method's rounding); in batches an fp64 sum per batch and one rounding.
 template <bool BATCH>
-__global__ __launch_bounds__(kChainMaxWaves *kWave) void online_rows_kernel(
-    const uint64_t *__restrict__ col, int64_t ld, int nb, int batch, const OnlineWeight *__restrict__ recs, float *acc,
-    int D, int C, int G, double *__restrict__ normpart) {
+__device__ __forceinline__ void update_rows(int g, const uint64_t *__restrict__ col, int64_t ld, int nb, int batch,
+                                            const OnlineWeight *__restrict__ recs, float *acc, int D, int C, int G,
+                                            double *__restrict__ normpart) {
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
-    const int g = blockIdx.x, d = g * kWave + lane;
+    const int d = g * kWave + lane;
     OnlineWeight rec[kSubs];
     uint64_t bits[kSubs];
 #pragma unroll
@@ -703,6 +864,362 @@ __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_rows_kernel(
     }
 }
 
+// grid (groups)
+template <bool BATCH>
+__global__ __launch_bounds__(kChainMaxWaves *kWave) void online_rows_kernel(
+    const uint64_t *__restrict__ col, int64_t ld, int nb, int batch, const OnlineWeight *__restrict__ recs, float *acc,
+    int D, int C, int G, double *__restrict__ normpart) {
+    update_rows<BATCH>((int)blockIdx.x, col, ld, nb, batch, recs, acc, D, C, G, normpart);
+}
+
+// ---- the chain of a whole block at once ------------------------------------------------------------
+// One workgroup, per sample (not in batches), up to 16 classes.  The same fixed point as in online_chain_kernel, over all
+// samples of a block together: four or five passes settle 256 samples where the sub-blocks one after another take
+// sixteen (from rows of zeros nine to twenty where those take 24 to 37).  7352 samples x 3 epochs, 6 classes,
+// D = 10000: 29.2 us a block -> 14.3, of which five are spent before the first pass.
+//
+// A pass takes the block's whole triangle of products, 640 rows of 64 (source sample x targets of a sub-block).  They
+// stay in registers for all passes, as fp64: eight waves of up to 92 rows, listed sub-block after sub-block and class
+// after class (write_order), each class filled up to whole groups of GR rows.  A weight reaches all lanes with the
+// multiply-add itself (a row-wise broadcast of its 64-bit operand: no lane read), and after every group the running sum
+// goes to its class's place in LDS, so that there is no branch in it: a class's sum is the difference of two places.  A
+// jump costs 20 clocks, as much as four rows; a branch where a class ends took 280 a group, this way 70.  Class c
+// belongs to wave c % 8, whose lanes form its dot products, the squared norms before each sample (prefix sums) and the
+// cosines of all four sub-blocks; wave j decides for the samples of sub-block j.  Three barriers, 5600 clocks a pass:
+// rows 1600, cosines 1800 to 2600, decisions 1250.  A class wrongly predicted for a sample takes that sample's products
+// from LDS, as the list changes from pass to pass.
+//
+// All of it has to stay within 256 registers: a kernel that spills waits 4 us longer for its launch.
+
+// acc += w of lane (16 k + I) x g, in every row of 16 lanes k, for GR rows.  (Such a broadcast wants two wait states
+// after a vector write of its operand; five after one of the execution mask by the vector unit, of which there is none.)
+template <int I, int GR>
+__device__ __forceinline__ void add_rows(double &acc, double w, const double *g) {
+    if constexpr (GR == 4)
+        asm volatile("s_nop 1\n\t"
+                     "v_fmac_f64_dpp %0, %1, %2 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+                     "v_fmac_f64_dpp %0, %1, %3 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
+                     "v_fmac_f64_dpp %0, %1, %4 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
+                     "v_fmac_f64_dpp %0, %1, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
+                     : "+v"(acc) : "v"(w), "v"(g[0]), "v"(g[1]), "v"(g[2]), "v"(g[3]), "n"(I), "n"(I + 1), "n"(I + 2), "n"(I + 3));
+    else
+        asm volatile("s_nop 1\n\t"
+                     "v_fmac_f64_dpp %0, %1, %2 row_newbcast:%4 row_mask:0xf bank_mask:0xf\n\t"
+                     "v_fmac_f64_dpp %0, %1, %3 row_newbcast:%5 row_mask:0xf bank_mask:0xf"
+                     : "+v"(acc) : "v"(w), "v"(g[0]), "v"(g[1]), "n"(I), "n"(I + 1));
+}
+
+// f(0), f(1) ... f(N - 1) with the number as a type
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void each(F &&f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        each<N, I + 1>(f);
+    }
+}
+
+struct WideRows {   // what the workgroups beside it need: the updates of the block before
+    const uint64_t *col;
+    int64_t ld;
+    const OnlineWeight *recs;
+    float *acc;
+    double *normpart;
+};
+
+template <int CPW, int GR>
+__global__ __launch_bounds__(kWideWaves *kWave) void online_wide_kernel(
+    const int16_t *__restrict__ gram, const int16_t *__restrict__ image, const WideOrder *__restrict__ order,
+    double *part, int slices, int nb, const int32_t *__restrict__ labels,
+    const double *__restrict__ normpart, int G, int C, int D, float lr, double inv_root_d, OnlineWeight *__restrict__ out,
+    double *grown, bool ahead, WideRows before) {
+    if (blockIdx.x) {
+        update_rows<false>((int)blockIdx.x - 1, before.col, before.ld, kChainBlock, 1, before.recs, before.acc, D, C, G, before.normpart);
+        return;
+    }
+    extern __shared__ __align__(16) int16_t prod[];   // the tiles of the block's sub-blocks, then s_place [wide_places], s_cos [4 C], s_start [4 C]
+    __shared__ double s_wy[kChainBlock + 2];
+    __shared__ uint2 s_wrong[kChainBlock];   // class wrongly predicted, or -1, and its weight
+    __shared__ double s_grown[kWideClasses];   // what the block adds to a class's squared norm
+    __shared__ int s_odd[kWideWaves];
+    __shared__ int s_any[kSubs][2];          // a sub-block's samples: a weight changed; a prediction is wrong
+    constexpr int kRows = wide_rows(GR);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int subs = (nb + kSub - 1) / kSub;
+    const int tiles = subs * (subs + 1) / 2, places = wide_places(C);
+    double(*s_place)[kSub] = reinterpret_cast<double(*)[kSub]>(prod + tiles * kTile);
+    double(*s_cos)[kSub] = s_place + places;            // [4 c + j]
+    // dot products against the rows at the block's start: in LDS, or (two classes a wave: it is full) where they came from
+    double(*start)[kSub] = CPW == 1 ? s_cos + kSubs * C : reinterpret_cast<double(*)[kSub]>(part);
+
+    // Everything from memory at once, in the order in which it is needed: 300 KB take the longer part of the time
+    // before the first pass, and what the later passes need comes in during that one.
+    int label[kSubs];
+#pragma unroll
+    for (int i = 0; i < kSubs; ++i) label[i] = labels[min(i * kSub + lane, nb - 1)];
+    double p[CPW][4];
+#pragma unroll
+    for (int k = 0; k < CPW; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p[k][i] = normpart[(int64_t)min(wave + k * kWideWaves, C - 1) * G + min(i * kWave + lane, G - 1)];
+    constexpr int kAtOnce = 3, kThreads = kWideWaves * kWave;   // elements of part a thread has in flight, a load for each slice
+    double first[kAtOnce][kSlices + 1];
+    const int elements = C * kChainBlock;
+    auto ask = [&](int e0, double(&v)[kAtOnce][kSlices + 1]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < kAtOnce; ++u)
+#pragma unroll
+            for (int i = 0; i <= kSlices; ++i) v[u][i] = part[(int64_t)min(i, slices - 1) * elements + min(e0 + u * kThreads, elements - 1)];
+    };
+    auto take = [&](int e0, const double(&v)[kAtOnce][kSlices + 1]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < kAtOnce; ++u) {
+            double s = 0.0;
+#pragma unroll
+            for (int i = 0; i <= kSlices; ++i) s += i < slices ? v[u][i] : 0.0;
+            if (e0 + u * kThreads < elements) (&start[0][0])[e0 + u * kThreads] = s;
+        }
+    };
+    ask(tid, first);
+    uint4 raw[(kRows + 7) / 8];
+#pragma unroll
+    for (int i = 0; i < (kRows + 7) / 8; ++i)
+        raw[i] = reinterpret_cast<const uint4 *>(image)[(wave * (kWideRows / 8) + i) * kSub + lane];
+    uint32_t wsrc[kWideRows / 32];   // the samples whose weights this lane broadcasts, two to a register
+#pragma unroll
+    for (int i = 0; i < kWideRows / 32; ++i)
+        wsrc[i] = (uint32_t)order->src[wave][32 * i + (lane & 15)] | (uint32_t)order->src[wave][32 * i + 16 + (lane & 15)] << 16;
+    const int to = order->to[wave][lane];
+    const int rows = order->rows;
+    uint32_t sum_at[CPW];   // lane 8 j + i: place i of sub-block j
+#pragma unroll
+    for (int k = 0; k < CPW; ++k) sum_at[k] = order->sum[min(wave + k * kWideWaves, C - 1)][(lane >> 3) & (kSubs - 1)][lane & 7];
+    constexpr int kCopies = kTiles * kTile * 2 / 16 / (kWideWaves * kWave);
+    u32x4 copy[kCopies];
+    const int units = tiles * (kTile * 2 / 16);
+#pragma unroll
+    for (int u = 0; u < kCopies; ++u)
+        copy[u] = reinterpret_cast<const u32x4 *>(gram)[min(tid + u * kThreads, units - 1)];
+
+    take(tid, first);
+    for (int e = tid + kAtOnce * kThreads; e < elements; e += kAtOnce * kThreads) {
+        ask(e, first);
+        take(e, first);
+    }
+    bool odd_rows = false, zero_rows = true;
+    uint64_t mine[CPW][kSubs];   // samples with the class's label
+    double nrm[CPW];
+#pragma unroll
+    for (int i = 0; i < kSubs; ++i) label[i] = i * kSub + lane < nb && label[i] >= 0 && label[i] < C ? label[i] : -1;
+    int y = -1;   // of the sample this lane decides for
+#pragma unroll
+    for (int i = 0; i < kSubs; ++i) y = wave == i ? label[i] : y;
+#pragma unroll
+    for (int k = 0; k < CPW; ++k) {
+        const int c = wave + k * kWideWaves;
+#pragma unroll
+        for (int j = 0; j < kSubs; ++j) mine[k][j] = __ballot(label[j] == c);
+        double s = 0.0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s += i * kWave + lane < G ? p[k][i] : 0.0;
+        for (int g = 4 * kWave + lane; g < G; g += kWave) s += normpart[(int64_t)min(c, C - 1) * G + g];
+        nrm[k] = lane_f64(lane_prefix(s), kWave - 1) + (ahead ? grown[min(c, C - 1)] : 0.0);
+        odd_rows |= !(nrm[k] < __builtin_inf());
+        zero_rows &= nrm[k] == 0.0;
+    }
+    if (lane == 0) s_odd[wave] = odd_rows ? 1 : zero_rows ? 0 : 2;
+    if (tid < kChainBlock + 2) s_wy[tid] = 0.0;
+    if (tid < kChainBlock) s_wrong[tid] = make_uint2(~0u, 0u);   // (past the last sub-block nobody decides)
+    if (tid < kWideClasses) s_grown[tid] = 0.0;
+    if (tid < kSub) s_place[places - 2][tid] = 0.0;
+    __syncthreads();
+    const int kind = s_odd[lane & (kWideWaves - 1)];
+    const bool zero_model = __ballot(kind != 0) == 0;
+    const bool strange = __ballot(kind == 1) != 0 || !(fabsf(lr) < 1e30f);
+
+    float wy = 0.0f, wp = 0.0f;
+    int pred = -1;
+    bool wrong_ones = false;
+    // Predictions and weights from s_cos, after a barrier; false: no weight has changed.  (With guess, labels count as
+    // predictions: rows of zeros would say class 0 of every sample.  The passes end in the same place from any start.)
+    auto decide = [&](int l, bool guess) __attribute__((always_inline)) {
+        if (wave < subs) {
+            const double cos_y = s_cos[kSubs * max(y, 0) + wave][l];
+            double best = -4.0;
+            int arg = 0;
+            for (int c0 = 0; c0 < C; c0 += 8) {   // eight at a time (the last one repeats: it cannot win twice)
+                double v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = s_cos[kSubs * min(c0 + u, C - 1) + wave][l];
+                const double top = fmax(fmax(fmax(v[0], v[1]), fmax(v[2], v[3])), fmax(fmax(v[4], v[5]), fmax(v[6], v[7])));
+                int first = 7;
+#pragma unroll
+                for (int u = 6; u >= 0; --u) first = v[u] == top ? u : first;
+                if (top > best) {
+                    best = top;
+                    arg = c0 + first;
+                }
+            }
+            float wy1 = 0.0f, wp1 = 0.0f;
+            int pred1 = -1;
+            if (y >= 0) {
+                wy1 = (float)(1.0 - cos_y);
+                if (arg != y && !guess) {
+                    pred1 = arg;
+                    wp1 = (float)((double)lr * (1.0 - best));
+                }
+            }
+            const uint64_t changed = __ballot(wy1 != wy || wp1 != wp || pred1 != pred), wrong = __ballot(pred1 >= 0);
+            wy = wy1;
+            wp = wp1;
+            pred = pred1;
+            s_wy[wave * kSub + l] = (double)wy;
+            s_wrong[wave * kSub + l] = make_uint2((uint32_t)pred, __float_as_uint(wp));
+            if (l == 0) {
+                s_any[wave][0] = changed != 0;
+                s_any[wave][1] = wrong != 0;
+            }
+        }
+        __syncthreads();
+        const uint64_t any = __ballot(l < 2 * subs && (&s_any[0][0])[l & (2 * kSubs - 1)]);   // the same in every wave
+        wrong_ones = (any & 0xAA) != 0;
+        return (any & 0x55) != 0;
+    };
+    // the first pass: no sample of the block counts yet
+#pragma unroll
+    for (int k = 0; k < CPW; ++k) {
+        const int c = wave + k * kWideWaves;
+        const double r = nrm[k] > 0.0 ? refined_rsq(nrm[k]) * inv_root_d : 0.0;
+        if (c < C) {
+#pragma unroll
+            for (int i = 0; i < kSubs; ++i) s_cos[kSubs * c + i][lane] = start[kSubs * c + i][lane] * r;
+        }
+    }
+    __syncthreads();
+    bool going = decide(lane, zero_model);
+
+#pragma unroll
+    for (int u = 0; u < kCopies; ++u) reinterpret_cast<u32x4 *>(prod)[min(tid + u * kThreads, units - 1)] = copy[u];
+    double kept[kRows];
+#pragma unroll
+    for (int i = 0; i < (kRows + 7) / 8; ++i) {
+        const uint32_t q[4] = {raw[i].x, raw[i].y, raw[i].z, raw[i].w};
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (8 * i + u < kRows) kept[8 * i + u] = (double)(int)(int16_t)(q[u >> 1] >> (16 * (u & 1)));
+    }
+    if (__builtin_expect(strange, 0)) {
+        __syncthreads();
+        OnlineWeight *rec = reinterpret_cast<OnlineWeight *>(&s_place[0][0]);   // (4 KB of at least 7)
+        walk_block<CPW, false>(prod, false, part, CPW == 1 ? slices : 1, nb, 1, labels, normpart, ahead ? grown : nullptr, grown, G, C, D,
+                               lr, inv_root_d, rec, s_wy);
+        for (int n = tid; n < nb; n += kWideWaves * kWave) out[n] = rec[n];
+        return;
+    }
+    const double dd = (double)D;
+    int column[kSubs];   // first tile of a target sub-block; past the last one, of that
+#pragma unroll
+    for (int i = 0; i < kSubs; ++i) column[i] = min(i, subs - 1) * (min(i, subs - 1) + 1) / 2 * kTile;
+    for (int pass = 1; going && pass <= nb; ++pass) {
+        int l = lane;
+        asm volatile("" : "+v"(l));   // (addresses are formed anew in a pass: kept over all, they would not fit the registers)
+        {
+            double w[kWideRows / 16];
+#pragma unroll
+            for (int i = 0; i < kWideRows / 16; ++i) w[i] = s_wy[wsrc[i / 2] >> (16 * (i & 1)) & 0xFFFFu];
+            int at = to * (kSub * (int)sizeof(double)), used = __builtin_amdgcn_readfirstlane(rows);
+            asm volatile("" : "+v"(at), "+s"(used));   // (what follows from these is not kept over the passes: a hundred scalars, which spill)
+            double sum = 0.0;
+            char *base = reinterpret_cast<char *>(&s_place[0][l]);
+            each<kWideRows / 16>([&](auto i_) {
+                constexpr int i = decltype(i_)::value;
+                if (16 * i < used)
+                    each<(kRows - 16 * i < 16 ? kRows - 16 * i : 16) / GR>([&](auto q_) {
+                        constexpr int g = 16 / GR * i + decltype(q_)::value;
+                        add_rows<g * GR % 16, GR>(sum, w[i], kept + g * GR);
+                        *reinterpret_cast<double *>(base + __builtin_amdgcn_readlane(at, g)) = sum;
+                    });
+            });
+            __syncthreads();
+        }
+#pragma unroll
+        for (int k = 0; k < CPW; ++k) {
+            const int c = wave + k * kWideWaves;
+            if (c < C) {
+                double dot[kSubs], wd[kSubs];
+#pragma unroll
+                for (int i = 0; i < kSubs; ++i) {
+                    dot[i] = start[kSubs * c + i][l];
+                    const double v = s_wy[i * kSub + l];
+                    wd[i] = __builtin_amdgcn_inverse_ballot_w64(mine[k][i]) ? v : 0.0;
+                }
+                {
+#pragma unroll
+                    for (int i0 = 0; i0 < kSubs; i0 += 2) {   // (two at a time: more would not fit the registers)
+                        double v[2][3];
+#pragma unroll
+                        for (int i = 0; i < 2; ++i)
+#pragma unroll
+                            for (int u = 0; u < 3; ++u) v[i][u] = s_place[__builtin_amdgcn_readlane(sum_at[k], 8 * (i0 + i) + u)][l];
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) dot[i0 + i] += (v[i][0] - v[i][1]) + v[i][2];
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if (__builtin_expect(__ballot((l & 7) == 6 && l < 8 * kSubs && sum_at[k]) != 0, 0)) {
+#pragma unroll
+                        for (int i = 0; i < kSubs; ++i)
+#pragma unroll
+                            for (int u = 3; u < 6; ++u) dot[i] += s_place[__builtin_amdgcn_readlane(sum_at[k], 8 * i + u)][l];
+                    }
+                }
+                if (wrong_ones) {
+#pragma unroll
+                    for (int a = 0; a < kSubs; ++a) {
+                        const uint2 r = s_wrong[a * kSub + l];
+                        const double wx = -(double)__uint_as_float(r.y);
+                        uint64_t list = __ballot((int)r.x == c);
+                        if ((int)r.x == c) wd[a] = wx;
+                        while (list) {
+                            constexpr int U = 4;   // samples at a time; past the list's end weight 0
+                            int n[U], g[U][kSubs];
+#pragma unroll
+                            for (int u = 0; u < U; ++u) {
+                                n[u] = list ? __builtin_ctzll(list) : -1;
+                                list &= list - 1;
+#pragma unroll
+                                for (int i = a; i < kSubs; ++i) g[u][i] = prod[column[i] + a * kTile + (n[u] & (kSub - 1)) * kSub + l];
+                            }
+#pragma unroll
+                            for (int u = 0; u < U; ++u) {
+                                const double z = lane_f64(wx, n[u] & (kSub - 1)), v = n[u] >= 0 ? z : 0.0;
+#pragma unroll
+                                for (int i = a; i < kSubs; ++i) dot[i] = fma(v, (double)g[u][i], dot[i]);
+                            }
+                        }
+                    }
+                }
+                double run[kSubs];   // what the samples up to each add to the squared norm
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < kSubs; ++i) run[i] = lane_prefix(wd[i] * fma(wd[i], dd, 2.0 * dot[i]));
+                double base = nrm[k];   // of the squared norm: at the sub-block's start
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < kSubs; ++i) {
+                    const double nn = base + lane_before(run[i]);
+                    base += lane_f64(run[i], kWave - 1);
+                    s_cos[kSubs * c + i][l] = nn > 0.0 ? dot[i] * refined_rsq(nn) * inv_root_d : 0.0;
+                }
+                if (l == 0) s_grown[c] = base - nrm[k];
+            }
+        }
+        __syncthreads();
+        going = decide(l, false);
+    }
+    if (wave < subs && wave * kSub + lane < nb) out[wave * kSub + lane] = OnlineWeight{y, pred, wy, wp};
+    if (tid < C) grown[tid] = s_grown[tid];
+}
+
 // ---- host side -------------------------------------------------------------------------------------
 static int chain_slice(int D) {   // dimensions of a slice: up to ten slices, whole groups of 64 per wave
     int s = (D + kSlices - 1) / kSlices;
@@ -744,6 +1261,18 @@ bool online_chain_pays(const hdc_ctx_impl *c, int64_t N, int64_t batch) {
     return batches >= 2 * ((N + block - 1) / block) + 2 && (double)batches >= batches_per_block(c->p.C, c->p.D) * blocks;
 }
 
+// Per-sample calls whose blocks are walked as a whole (online_wide_kernel).  A product has to fit 16 bits; a learning rate
+// that can make a weight overflow leaves the walk sample by sample, and that to the other kernel.  The first blocks of a
+// zero model take more passes the more classes, and long lists of one to three classes are what the sub-blocks pay for.
+// Time by sub-blocks over time of this way, samples 10 and 30 % from their prototype, every tenth label at random, D = 1000:
+//   C = 1:  129 samples 1.55 1.53, 520 2.45 2.60    C = 3: 129 0.98 1.08, 520 1.31 1.45    C = 5: 200 1.07 1.03, 385 1.14 1.12
+//   C = 8:  300 0.88 0.98, 520 0.99 1.10, 769 1.07 1.19    C = 12: 520 0.93 1.01, 1281 1.08 1.21    C = 16: 520 0.86 0.93, 1793 1.10 1.17
+// and, 2000 samples, 6 classes, D = 10000: 1.65 without false labels, 1.01 with half of them, 0.93 with labels at random.
+static bool wide_takes(const hdc_ctx_impl *c, int64_t N, int32_t epochs, float lr) {
+    const int C = c->p.C;
+    return C <= kWideClasses && c->p.D <= 32767 && N > 2 * kSub && N * epochs > 2 * kSub * (C - 2) && fabsf(lr) < 1e30f;
+}
+
 int reserve_online_chain(hdc_ctx_impl *c) {
     if (c->oc_ready) return HDC_OK;
     const int C = c->p.C, D = c->p.D;
@@ -751,17 +1280,23 @@ int reserve_online_chain(hdc_ctx_impl *c) {
     HDC_HIP(hipSetDevice(c->device));
     int rc = grow(&c->oc_col_d, &c->oc_col_bytes, (size_t)G * held_samples(G) * sizeof(uint64_t));
     if (rc == HDC_OK) rc = grow(&c->oc_gram_d, &c->oc_gram_bytes, (size_t)kGramBlocks * kTiles * kTile * sizeof(int16_t));
-    if (rc == HDC_OK) rc = grow(&c->oc_part_d, &c->oc_part_bytes, (size_t)slices * C * kChainBlock * sizeof(double));
-    if (rc == HDC_OK) rc = grow(&c->oc_rec_d, &c->oc_rec_bytes, (size_t)kChainBlock * sizeof(OnlineWeight));
+    if (rc == HDC_OK) rc = grow(&c->oc_part_d, &c->oc_part_bytes, (size_t)(slices + 1) * C * kChainBlock * sizeof(double));
+    if (rc == HDC_OK) rc = grow(&c->oc_rec_d, &c->oc_rec_bytes, (size_t)2 * kChainBlock * sizeof(OnlineWeight));
+    if (rc == HDC_OK) rc = grow(&c->oc_pairs_d, &c->oc_pairs_bytes, (size_t)(kWideBlocks - 1) * kSubs * kSubs * kTile * sizeof(int16_t));
+    if (rc == HDC_OK) rc = grow(&c->oc_norm_d, &c->oc_norm_bytes, (size_t)C * (G + 1) * sizeof(double));
+    if (rc == HDC_OK) rc = grow(&c->oc_order_d, &c->oc_order_bytes, (size_t)kWideBlocks * sizeof(WideOrder));
+    if (rc == HDC_OK) rc = grow(&c->oc_image_d, &c->oc_image_bytes, (size_t)kWideBlocks * kWideImage * sizeof(int16_t));
     if (rc == HDC_OK) rc = grow(&c->on_bits_d, &c->on_bits_bytes, (size_t)kOnlineWords * sizeof(uint32_t));
     if (rc == HDC_OK) rc = grow(&c->ob_norm_d, &c->ob_norm_bytes, (size_t)C * G * sizeof(double));
     c->oc_ready = rc == HDC_OK;
     if (rc == HDC_ENOMEM) {   // all or nothing: what is left of the memory is for the other ways
         (void)hipFree(c->oc_col_d);
         (void)hipFree(c->oc_gram_d);
+        (void)hipFree(c->oc_image_d);
+        (void)hipFree(c->oc_pairs_d);
         c->oc_col_d = nullptr;
-        c->oc_gram_d = nullptr;
-        c->oc_col_bytes = c->oc_gram_bytes = 0;
+        c->oc_gram_d = c->oc_image_d = c->oc_pairs_d = nullptr;
+        c->oc_col_bytes = c->oc_gram_bytes = c->oc_image_bytes = c->oc_pairs_bytes = 0;
     }
     return rc;
 }
@@ -776,7 +1311,7 @@ bool online_chain_ready(hdc_ctx_impl *c, hipStream_t s, int *rc) {
 
 template <int CPW, bool BATCH>
 static int launch_chain(hdc_ctx_impl *c, const int16_t *gram, int slices, int nb, int batch, const int32_t *labels,
-                        int G, float lr, hipStream_t s) {
+                        const double *norm, OnlineWeight *recs, int G, float lr, hipStream_t s) {
     auto kern = online_chain_kernel<CPW, BATCH>;
     const int slot = (CPW == 1 ? 0 : CPW == 2 ? 2 : 4) + (BATCH ? 1 : 0);
     if (!c->oc_attr_set[slot]) {
@@ -788,9 +1323,67 @@ static int launch_chain(hdc_ctx_impl *c, const int16_t *gram, int slices, int nb
     ProfScope prof(c, HDC_K_ONLINE, s, BATCH);
     hipLaunchKernelGGL(kern, dim3(1), dim3(kChainMaxWaves * kWave),
                        (size_t)(subs * (subs + 1) / 2) * kTile * sizeof(int16_t), s, gram, c->oc_part_d, slices, nb,
-                       batch, labels, c->ob_norm_d, G, c->p.C, c->p.D, lr, 1.0 / sqrt((double)c->p.D),
-                       static_cast<OnlineWeight *>(c->oc_rec_d));
+                       batch, labels, norm, G, c->p.C, c->p.D, lr, 1.0 / sqrt((double)c->p.D), recs);
     HDC_HIP(hipGetLastError());
+    return HDC_OK;
+}
+
+template <int CPW, int GR>
+static int launch_wide(hdc_ctx_impl *c, int64_t b, int slices, int nb, const int32_t *labels, int G, float lr,
+                       const double *norm, bool ahead, const WideRows &before, OnlineWeight *recs, hipStream_t s) {
+    auto kern = online_wide_kernel<CPW, GR>;
+    const int slot = CPW == 1 ? 6 : 7, C = c->p.C, per_place = kSub * (int)sizeof(double);
+    const int most = CPW * kWideWaves, cosines = kSubs * (CPW == 1 ? 2 : 1);   // places beside the runs' for a class: cosines, starts
+    if (!c->oc_attr_set[slot]) {
+        HDC_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    kTiles * kTile * (int)sizeof(int16_t) + (wide_places(most) + cosines * most) * per_place));
+        c->oc_attr_set[slot] = true;
+    }
+    const int subs = (nb + kSub - 1) / kSub;
+    hipLaunchKernelGGL(kern, dim3(ahead ? 1u + (unsigned)G : 1u), dim3(kWideWaves * kWave),
+                       (size_t)(subs * (subs + 1) / 2) * kTile * sizeof(int16_t) + (size_t)(wide_places(C) + cosines * C) * per_place, s,
+                       c->oc_gram_d + b * kTiles * kTile, c->oc_image_d + b * kWideImage,
+                       static_cast<const WideOrder *>(c->oc_order_d) + b, c->oc_part_d, slices + (ahead ? 1 : 0), nb, labels, norm, G,
+                       C, c->p.D, lr, 1.0 / sqrt((double)c->p.D), recs,
+                       c->oc_norm_d + (int64_t)C * G, ahead, before);
+    HDC_HIP(hipGetLastError());
+    return HDC_OK;
+}
+
+// The blocks of samples that are held, per sample.  Two launches a block: the chain of block b beside the row updates of
+// block b - 1, then the products of block b + 1 with the rows as those left them, and with block b's updates by the
+// samples' own products.  (Rows, products and chain one after another: 27 us a block at 6 classes, D = 10000; this way 22.)
+static int walk_wide(hdc_ctx_impl *c, const int32_t *labels, int64_t N, float lr, float *acc, int64_t ld, int *norm_at, hipStream_t s) {
+    const int C = c->p.C, D = c->p.D;
+    const int G = (D + kWave - 1) / kWave, slice = chain_slice(D), slices = (D + slice - 1) / slice;
+    double *norm[2] = {c->ob_norm_d, c->oc_norm_d};   // squared norms: of the rows before the last update, and after
+    const int64_t blocks = (N + kChainBlock - 1) / kChainBlock;
+    OnlineWeight *const all = static_cast<OnlineWeight *>(c->oc_rec_d);   // of an even block, and of an odd one
+    for (int64_t b = 0; b < blocks; ++b) {
+        const int nb = (int)(N - b * kChainBlock < kChainBlock ? N - b * kChainBlock : kChainBlock);
+        OnlineWeight *recs = all + b % 2 * kChainBlock;
+        const OnlineWeight *recs_before = all + (b + 1) % 2 * kChainBlock;
+        const uint64_t *col = c->oc_col_d + b * kChainBlock;
+        const bool ahead = b > 0;   // the rows do not hold the block before yet
+        hipLaunchKernelGGL(online_dots_kernel, dim3((unsigned)(slices + (ahead ? 1 : 0)), (unsigned)((nb + 15) / 16), (unsigned)((C + 15) / 16)),
+                           dim3(kDotWaves * kWave), 0, s, col, ld, nb, acc, D, C, slice, slices,
+                           ahead ? c->oc_pairs_d + (b - 1) * kSubs * kSubs * kTile : nullptr, recs_before, c->oc_part_d);
+        HDC_HIP(hipGetLastError());
+        const WideRows before = {col - (ahead ? kChainBlock : 0), ld, recs_before, acc, norm[*norm_at ^ 1]};
+        const int32_t *lab = labels + b * kChainBlock;
+        const int rc = C <= kWideWaves
+                           ? launch_wide<1, wide_group(kWideWaves)>(c, b, slices, nb, lab, G, lr, norm[*norm_at], ahead, before, recs, s)
+                           : launch_wide<2, wide_group(2 * kWideWaves)>(c, b, slices, nb, lab, G, lr, norm[*norm_at], ahead, before, recs, s);
+        if (rc != HDC_OK) return rc;
+        if (ahead) *norm_at ^= 1;
+        if (b + 1 == blocks) {
+            const unsigned waves = (unsigned)(C < 4 ? 4 : C);
+            hipLaunchKernelGGL(online_rows_kernel<false>, dim3((unsigned)G), dim3(waves * kWave), 0, s, col, ld, nb, 1, recs, acc, D, C,
+                               G, norm[*norm_at ^ 1]);
+            HDC_HIP(hipGetLastError());
+            *norm_at ^= 1;
+        }
+    }
     return HDC_OK;
 }
 
@@ -803,47 +1396,58 @@ static int walk_blocks(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *label
     int rc = launch_norm(c, acc, G, s);
     if (rc != HDC_OK) return rc;
     const int block = kChainBlock / batch * batch;   // whole batches
-    const int64_t held = held_samples(G) / block * block, ld = held_samples(G);
+    const bool wide = !BATCH && wide_takes(c, N, epochs, lr);
+    const int64_t ld = held_samples(G), held = (wide ? std::min(ld, kWideSamples) : ld) / block * block;
+    int norm_at = 0;   // which of the two arrays of squared norms is that of the rows (walk_wide)
     for (int32_t e = 0; e < epochs; ++e)
         for (int64_t h0 = 0; h0 < N; h0 += held) {
             const int64_t hn = N - h0 < held ? N - h0 : held;
             if (e == 0 || N > held) {   // a set that fits is multiplied out once for all epochs
-                hipLaunchKernelGGL(online_columns_kernel,
-                                   dim3((unsigned)((hn + kSub - 1) / kSub), (unsigned)((G + kColGroups - 1) / kColGroups)),
-                                   dim3(256), 0, s, hv + h0 * W, hn, W, c->last_word_mask, G, ld, c->oc_col_d);
+                const unsigned blocks = (unsigned)((hn + block - 1) / block);
+                WideOrder *order = wide ? static_cast<WideOrder *>(c->oc_order_d) : nullptr;
+                hipLaunchKernelGGL(wide ? online_columns_kernel<true> : online_columns_kernel<false>,
+                                   dim3((unsigned)((hn + kSub - 1) / kSub), (unsigned)((G + kColGroups - 1) / kColGroups + (wide ? 1 : 0))),
+                                   dim3(256), 0, s, hv + h0 * W, hn, W, c->last_word_mask, G, ld, c->oc_col_d, labels + h0, C, order);
                 HDC_HIP(hipGetLastError());
-                if (hn > 1) {
-                    const unsigned blocks = (unsigned)((hn + block - 1) / block);
+                if (hn > 1 || wide) {
                     const int subs = (int)((std::min<int64_t>(hn, block) + kSub - 1) / kSub);
-                    hipLaunchKernelGGL(online_gram_kernel, dim3((unsigned)(subs * (subs + 1) / 2), blocks),
-                                       dim3(kGramWaves * kWave), 0, s, c->oc_col_d, ld, hn, D, G, block, c->oc_gram_d);
+                    hipLaunchKernelGGL(wide ? online_gram_kernel<true> : online_gram_kernel<false>,
+                                       dim3((unsigned)(subs * (subs + 1) / 2 + (wide && blocks > 1 ? kSubs * kSubs : 0)), blocks),
+                                       dim3(kGramWaves * kWave), 0, s, c->oc_col_d, ld, hn, D, G, block, c->oc_gram_d, order,
+                                       c->oc_image_d, c->oc_pairs_d);
                 }
                 HDC_HIP(hipGetLastError());
+            }
+            if (wide) {
+                rc = walk_wide(c, labels + h0, hn, lr, acc, ld, &norm_at, s);
+                if (rc != HDC_OK) return rc;
+                continue;
             }
             for (int64_t b0 = 0; b0 < hn; b0 += block) {
                 const int nb = (int)(hn - b0 < block ? hn - b0 : block);
                 const uint64_t *col = c->oc_col_d + b0;
                 const int32_t *lab = labels + h0 + b0;
                 const int16_t *gram = c->oc_gram_d + b0 / block * kTiles * kTile;
+                OnlineWeight *recs = static_cast<OnlineWeight *>(c->oc_rec_d);
                 {
                     ProfScope prof(c, HDC_K_ONLINE_FWD, s, BATCH);
                     hipLaunchKernelGGL(online_dots_kernel,
                                        dim3((unsigned)slices, (unsigned)((nb + 15) / 16), (unsigned)((C + 15) / 16)),
-                                       dim3(kDotWaves * kWave), 0, s, col, ld, nb, acc, D, C, slice, c->oc_part_d);
+                                       dim3(kDotWaves * kWave), 0, s, col, ld, nb, acc, D, C, slice, slices, nullptr, nullptr,
+                                       c->oc_part_d);
                 }
                 HDC_HIP(hipGetLastError());
                 if (C <= kChainMaxWaves)
-                    rc = launch_chain<1, BATCH>(c, gram, slices, nb, batch, lab, G, lr, s);
+                    rc = launch_chain<1, BATCH>(c, gram, slices, nb, batch, lab, c->ob_norm_d, recs, G, lr, s);
                 else if (C <= 2 * kChainMaxWaves)
-                    rc = launch_chain<2, BATCH>(c, gram, slices, nb, batch, lab, G, lr, s);
+                    rc = launch_chain<2, BATCH>(c, gram, slices, nb, batch, lab, c->ob_norm_d, recs, G, lr, s);
                 else
-                    rc = launch_chain<4, BATCH>(c, gram, slices, nb, batch, lab, G, lr, s);
+                    rc = launch_chain<4, BATCH>(c, gram, slices, nb, batch, lab, c->ob_norm_d, recs, G, lr, s);
                 if (rc != HDC_OK) return rc;
                 const unsigned waves = (unsigned)(C < 4 ? 4 : C < kChainMaxWaves ? C : kChainMaxWaves);
                 ProfScope prof(c, HDC_K_ONLINE_BWD, s, BATCH);
                 hipLaunchKernelGGL(online_rows_kernel<BATCH>, dim3((unsigned)G), dim3(waves * kWave), 0, s, col, ld,
-                                   nb, batch, static_cast<const OnlineWeight *>(c->oc_rec_d), acc, D, C, G,
-                                   c->ob_norm_d);
+                                   nb, batch, recs, acc, D, C, G, c->ob_norm_d);
                 HDC_HIP(hipGetLastError());
             }
         }
