@@ -94,22 +94,16 @@ struct hdc_ctx_impl {
     // Scratch of the block-wise online trainer (online_chain.hip), allocated at the first call of either
     // online trainer, whatever its size, so that later ones only enqueue.
     bool oc_ready;        // all of it is there
+    char *oc_mem_d;       // the allocation that holds what follows
+    size_t oc_mem_bytes;
     int16_t *oc_gram_d;   // [blocks][10][64][64] scalar products of the samples of a block
-    size_t oc_gram_bytes;
     uint64_t *oc_col_d;   // [ceil(D/64)][samples] 64-bit lane masks, dimension group major
-    size_t oc_col_bytes;
     double *oc_part_d;    // [slices][C][256] partial dot products of a block
-    size_t oc_part_bytes;
-    void *oc_rec_d;       // [256] weight records of a block
-    size_t oc_rec_bytes;
+    void *oc_rec_d;       // [2][256] weight records of a block, and of the one before
     void *oc_order_d;     // [blocks] online_wide_kernel's rows by wave
-    size_t oc_order_bytes;
     int16_t *oc_image_d;  // [blocks][8][12][64][8] and the products of those rows
-    size_t oc_image_bytes;
     int16_t *oc_pairs_d;  // [blocks][4][4][64][64] products of a block's samples with the next one's
-    size_t oc_pairs_bytes;
     double *oc_norm_d;    // [C][ceil(D/64)] the other squared-norm partials, and [C] what a block adds to them
-    size_t oc_norm_bytes;
     bool oc_attr_set[8];  // dynamic-LDS limit of online_chain_kernel / online_wide_kernel raised, by variant
 
     // hdc_encode_sparse (allocated and derived on its first call)

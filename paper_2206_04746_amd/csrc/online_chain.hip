@@ -42,10 +42,8 @@ constexpr int kSub = 64;                            // samples of a sub-block: o
 constexpr int kSubs = kChainBlock / kSub;
 constexpr int kTile = kSub * kSub;                  // products of one pair of sub-blocks
 constexpr int kTiles = kSubs * (kSubs + 1) / 2;     // pairs (a, b), a <= b, at b (b + 1) / 2 + a
-constexpr int64_t kGramSamples = 16384;             // samples whose products are held at a time
-constexpr int64_t kWideSamples = 8192;              // ... where blocks are walked as a whole, which takes three times the memory
-constexpr int64_t kWideBlocks = kWideSamples / kChainBlock;
-constexpr int64_t kGramBlocks = kGramSamples / (kChainBlock / 2 + 1) + 2;   // a block has more than 128 samples
+constexpr int64_t kHeldBlocks = 32;                 // blocks whose columns and products are held at a time
+constexpr float kTameRate = 1e30f;                  // a learning rate below which no weight overflows
 constexpr int kChainMaxWaves = 16;
 constexpr int kSlices = 10;                         // most slices the dimensions are split into
 
@@ -203,7 +201,7 @@ __global__ __launch_bounds__(kGramWaves *kWave) void online_gram_kernel(const ui
                                                                         int16_t *__restrict__ image, int16_t *__restrict__ pairs) {
     __shared__ int sum[kSub][kGramPitch];
     __shared__ int ones[2][kSub];
-    const bool pair = WIDE && (int)blockIdx.x >= kTiles;   // sub-block a of this block, b of the next one
+    const bool pair = (int)blockIdx.x >= kTiles;   // sub-block a of this block, b of the next one
     int a, b = 0;
     if (pair) {
         a = ((int)blockIdx.x - kTiles) / kSubs;
@@ -223,7 +221,7 @@ __global__ __launch_bounds__(kGramWaves *kWave) void online_gram_kernel(const ui
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int n = (i < 2 ? a : b) * kSub + 32 * (i & 1) + r;
-        src[i] = reinterpret_cast<const uint32_t *>(col + (i < 2 ? n0 : m0) + (pair && i < 2 ? n : min(n, nb - 1))) + half;   // (a block with a next one is full)
+        src[i] = reinterpret_cast<const uint32_t *>(col + (i < 2 ? n0 : m0) + (pair && i < 2 ? n : min(n, nb - 1))) + half;   // (a block with a next one is full; what is past it nobody asks for)
     }
     v16f dot[2][2] = {};
     int pop[4] = {0, 0, 0, 0};
@@ -297,14 +295,14 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 // One more slice where the rows do not yet hold the updates of the block before: what those add to 16 samples'
 // products, from the products of samples and that block's weights (lane 16 q + i: sample i, one of four samples before).
-__device__ __forceinline__ f64x4 add_block_before(const int16_t *__restrict__ pairs, const OnlineWeight *__restrict__ recs, int D, double *lds) {
+__device__ __forceinline__ f64x4 add_block_before(const int16_t *__restrict__ pairs, const OnlineWeight *__restrict__ recs, int before, int D, double *lds) {
     static_assert(kDotWaves * kWave == 2 * kChainBlock, "a thread to half a row of 16");
     int16_t(*g)[16] = reinterpret_cast<int16_t(*)[16]>(lds);                 // 8 KB
     OnlineWeight *r = reinterpret_cast<OnlineWeight *>(lds + 1024);          // 4 KB
     const int t = threadIdx.x, n0 = t >> 1, b = blockIdx.y / 4, v = 16 * (blockIdx.y % 4) + 8 * (t & 1);
     *reinterpret_cast<u32x4 *>(&g[n0][8 * (t & 1)]) =
         *reinterpret_cast<const u32x4 *>(pairs + (((n0 / kSub) * kSubs + b) * kSub + n0 % kSub) * kSub + v);
-    if (t < kChainBlock) r[t] = recs[t];
+    if (t < kChainBlock) r[t] = t < before ? recs[t] : OnlineWeight{-1, -1, 0.0f, 0.0f};
     __syncthreads();
     const int q = (t & (kWave - 1)) >> 4, i = t & 15, c = blockIdx.z * 16 + i;
     f64x4 sum = {0.0, 0.0, 0.0, 0.0};
@@ -323,7 +321,7 @@ __global__ __launch_bounds__(kDotWaves *kWave) void online_dots_kernel(const uin
                                                                        int64_t ld, int nb,
                                                                        const float *__restrict__ acc, int D, int C,
                                                                        int slice, int slices, const int16_t *__restrict__ pairs,
-                                                                       const OnlineWeight *__restrict__ recs,
+                                                                       const OnlineWeight *__restrict__ recs, int before,
                                                                        double *__restrict__ part) {
     __shared__ __align__(16) double red[kDotWaves][256];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
@@ -337,7 +335,7 @@ __global__ __launch_bounds__(kDotWaves *kWave) void online_dots_kernel(const uin
     const int lo = blockIdx.x * slice + wave * span;
     const int hi = lo + span < D ? lo + span : D;
     f64x4 sum = {0.0, 0.0, 0.0, 0.0};
-    if ((int)blockIdx.x == slices) sum = add_block_before(pairs, recs, D, &red[0][0]);   // (lo is past D)
+    if ((int)blockIdx.x == slices) sum = add_block_before(pairs, recs, before, D, &red[0][0]);   // (lo is past D)
     for (int d0 = lo; d0 < hi; d0 += kWave) {
         const int d = d0 + 16 * q;
         const uint32_t inv = ~(uint32_t)h[(int64_t)(d0 >> 6) * ld * 4];   // bit k: the sign of dimension d + k
@@ -371,7 +369,7 @@ __global__ __launch_bounds__(kDotWaves *kWave) void online_dots_kernel(const uin
     }
 }
 
-// ---- the chain -----------------------------------------------------------------------------------
+// ---- lanes ------------------------------------------------------------------------------------------
 __device__ __forceinline__ float lane_f32(float v, int i) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i));
 }
@@ -402,6 +400,95 @@ __device__ __forceinline__ double lane_before(double v) {
     return __hiloint2double(hi, lo);
 }
 
+// ---- the rows ------------------------------------------------------------------------------------
+// A block per group of 64 dimensions, waves deal the classes among them.  A lane keeps one element of
+// a row in a register and takes the updates that name its class in sample order: the listed samples'
+// weight and 64 bits come by lane reads, so nothing in the loop waits for memory.  Per sample one fp32
+// add (the method's rounding); in batches an fp64 sum per batch and one rounding.
+template <bool BATCH>
+__device__ __forceinline__ void update_rows(int g, const uint64_t *__restrict__ col, int64_t ld, int nb, int batch,
+                                            const OnlineWeight *__restrict__ recs, float *acc, int D, int C, int G,
+                                            double *__restrict__ normpart) {
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
+    const int d = g * kWave + lane;
+    OnlineWeight rec[kSubs];
+    uint64_t bits[kSubs];
+#pragma unroll
+    for (int j = 0; j < kSubs; ++j) {
+        const int n = min(j * kSub + lane, nb - 1);
+        rec[j] = recs[n];
+        bits[j] = col[(int64_t)g * ld + n];
+    }
+    for (int c = wave; c < C; c += nw) {
+        float a = d < D ? acc[(int64_t)c * D + d] : 0.0f;
+        double delta = 0.0;
+        int end = batch;   // first sample of the next batch
+#pragma unroll
+        for (int j = 0; j < kSubs; ++j) {
+            const OnlineWeight r = rec[j];
+            const int lo = (int)(uint32_t)bits[j], hi = (int)(uint32_t)(bits[j] >> 32);
+            const float w = r.y == c ? r.w_y : r.pred == c ? -r.w_p : 0.0f;
+            uint64_t list = __ballot(w != 0.0f && j * kSub + lane < nb);
+            while (list) {
+                constexpr int U = 4;   // entries at a time; past the list's end weight 0
+                float x[U];
+                int n[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int i = list ? __builtin_ctzll(list) : 0;
+                    const float v = list ? lane_f32(w, i) : 0.0f;
+                    n[u] = list ? j * kSub + i : 0;
+                    const uint64_t mask = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(lo, i) |
+                                          (uint64_t)(uint32_t)__builtin_amdgcn_readlane(hi, i) << 32;
+                    x[u] = __builtin_amdgcn_inverse_ballot_w64(mask) ? v : -v;   // (waits for the lane reads; inline assembly would not)
+                    list &= list - 1;
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if constexpr (BATCH) {
+                        if (n[u] >= end) {   // uniform
+                            a = (float)((double)a + delta);
+                            delta = 0.0;
+                            end = (n[u] / batch + 1) * batch;
+                        }
+                        delta += (double)x[u];
+                    } else {
+                        a = __fadd_rn(a, x[u]);
+                    }
+                }
+            }
+        }
+        if (BATCH) a = (float)((double)a + delta);
+        double q = 0.0;
+        if (d < D) {
+            acc[(int64_t)c * D + d] = a;
+            q = (double)a * (double)a;
+        }
+        q = lane_prefix(q);
+        if (lane == kWave - 1) normpart[(int64_t)c * G + g] = q;
+    }
+}
+
+// grid (groups)
+template <bool BATCH>
+__global__ __launch_bounds__(kChainMaxWaves *kWave) void online_rows_kernel(
+    const uint64_t *__restrict__ col, int64_t ld, int nb, int batch, const OnlineWeight *__restrict__ recs, float *acc,
+    int D, int C, int G, double *__restrict__ normpart) {
+    update_rows<BATCH>((int)blockIdx.x, col, ld, nb, batch, recs, acc, D, C, G, normpart);
+}
+
+// What a chain's launch needs to run the row updates of the block before beside it, a workgroup to a group of dimensions.
+struct BlockBefore {
+    const uint64_t *col;
+    int64_t ld;
+    int nb;
+    const OnlineWeight *recs;
+    float *acc;
+    double *normpart;
+};
+
+// ---- the chain -----------------------------------------------------------------------------------
 __device__ __forceinline__ double refined_rsq(double nn) {
     double r = __builtin_amdgcn_rsq(nn);
     r = r * fma(-0.5 * nn * r, r, 1.5);
@@ -509,7 +596,12 @@ template <int CPW, bool BATCH>
 __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
     const int16_t *__restrict__ gram, const double *__restrict__ part, int slices, int nb, int batch,
     const int32_t *__restrict__ labels, const double *__restrict__ normpart, int G, int C, int D, float lr,
-    double inv_root_d, OnlineWeight *__restrict__ out) {
+    double inv_root_d, OnlineWeight *__restrict__ out, double *grown, bool ahead, BlockBefore before_it) {
+    if (blockIdx.x) {
+        update_rows<BATCH>((int)blockIdx.x - 1, before_it.col, before_it.ld, before_it.nb, batch, before_it.recs, before_it.acc, D, C, G,
+                           before_it.normpart);
+        return;
+    }
     constexpr int kKept = CPW == 1 ? 24 : CPW == 2 ? 12 : 4;   // list entries of a class whose products stay in registers
     extern __shared__ __align__(16) int16_t prod[];   // the tiles of the block's sub-blocks
     __shared__ double s_best[2][kChainMaxWaves][kSub];
@@ -529,6 +621,7 @@ __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
     for (int u = 0; u < kCopies; ++u)
         copy[u] = reinterpret_cast<const uint4 *>(gram)[min(tid + u * kChainMaxWaves * kWave, units - 1)];
     double nrm[CPW], nrm_fb[CPW];   // squared norms before the sub-block; and where the batch that runs into it began
+    double at_start[CPW];           // before the block
     double start[CPW][kSubs];       // dot products against the rows at the block's start
     int label[kSubs];
     bool odd_rows = false;
@@ -540,7 +633,7 @@ __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
 #pragma unroll
     for (int k = 0; k < CPW; ++k) {
         const int c = wave * CPW + k;
-        nrm[k] = nrm_fb[k] = 0.0;
+        nrm[k] = nrm_fb[k] = at_start[k] = 0.0;
 #pragma unroll
         for (int j = 0; j < kSubs; ++j) start[k][j] = 0.0;
         if (c < C) {
@@ -552,17 +645,18 @@ __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
 #pragma unroll
                 for (int i = 0; i < 4; ++i) s += g0 + i * kWave + lane < G ? p[i] : 0.0;
             }
-            double x[kSlices][kSubs];
+            double x[kSlices + 1][kSubs];
 #pragma unroll
-            for (int i = 0; i < kSlices; ++i)
+            for (int i = 0; i <= kSlices; ++i)
 #pragma unroll
                 for (int j = 0; j < kSubs; ++j)
                     x[i][j] = part[((int64_t)min(i, slices - 1) * C + c) * kChainBlock + j * kSub + lane];
 #pragma unroll
-            for (int i = 0; i < kSlices; ++i)
+            for (int i = 0; i <= kSlices; ++i)
 #pragma unroll
                 for (int j = 0; j < kSubs; ++j) start[k][j] += i < slices ? x[i][j] : 0.0;
-            nrm[k] = nrm_fb[k] = lane_f64(lane_prefix(s), kWave - 1);
+            nrm[k] = nrm_fb[k] = lane_f64(lane_prefix(s), kWave - 1) + (ahead ? grown[c] : 0.0);
+            at_start[k] = nrm[k];
             odd_rows |= !(nrm[k] < __builtin_inf());
         }
     }
@@ -573,9 +667,9 @@ __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
             reinterpret_cast<uint4 *>(prod)[tid + u * kChainMaxWaves * kWave] = copy[u];
     __syncthreads();
     if (wave >= used) return;   // (an ended wave takes no part in later barriers)
-    if (__builtin_expect(__ballot(lane < used && s_odd[lane]) != 0 || !(fabsf(lr) < 1e30f), 0)) {   // the same in every wave
-        walk_block<CPW, BATCH>(prod, true, part, slices, nb, batch, labels, normpart, nullptr, nullptr, G, C, D, lr, inv_root_d, s_rec,
-                               s_cosy[0]);
+    if (__builtin_expect(__ballot(lane < used && s_odd[lane]) != 0 || !(fabsf(lr) < kTameRate), 0)) {   // the same in every wave
+        walk_block<CPW, BATCH>(prod, true, part, slices, nb, batch, labels, normpart, ahead ? grown : nullptr, grown, G, C, D, lr,
+                               inv_root_d, s_rec, s_cosy[0]);
         for (int n = tid; n < nb; n += used * kWave) out[n] = s_rec[n];
         return;
     }
@@ -792,84 +886,9 @@ __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
         }
         __syncthreads();
     }
-}
-
-// ---- the rows ------------------------------------------------------------------------------------
-// A block per group of 64 dimensions, waves deal the classes among them.  A lane keeps one element of
-// a row in a register and takes the updates that name its class in sample order: the listed samples'
-// weight and 64 bits come by lane reads, so nothing in the loop waits for memory.  Per sample one fp32
-// add (the method's rounding); in batches an fp64 sum per batch and one rounding.
-template <bool BATCH>
-__device__ __forceinline__ void update_rows(int g, const uint64_t *__restrict__ col, int64_t ld, int nb, int batch,
-                                            const OnlineWeight *__restrict__ recs, float *acc, int D, int C, int G,
-                                            double *__restrict__ normpart) {
-    const int tid = threadIdx.x, lane = tid & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
-    const int d = g * kWave + lane;
-    OnlineWeight rec[kSubs];
-    uint64_t bits[kSubs];
 #pragma unroll
-    for (int j = 0; j < kSubs; ++j) {
-        const int n = min(j * kSub + lane, nb - 1);
-        rec[j] = recs[n];
-        bits[j] = col[(int64_t)g * ld + n];
-    }
-    for (int c = wave; c < C; c += nw) {
-        float a = d < D ? acc[(int64_t)c * D + d] : 0.0f;
-        double delta = 0.0;
-        int end = batch;   // first sample of the next batch
-#pragma unroll
-        for (int j = 0; j < kSubs; ++j) {
-            const OnlineWeight r = rec[j];
-            const int lo = (int)(uint32_t)bits[j], hi = (int)(uint32_t)(bits[j] >> 32);
-            const float w = r.y == c ? r.w_y : r.pred == c ? -r.w_p : 0.0f;
-            uint64_t list = __ballot(w != 0.0f && j * kSub + lane < nb);
-            while (list) {
-                constexpr int U = 4;   // entries at a time; past the list's end weight 0
-                float x[U];
-                int n[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int i = list ? __builtin_ctzll(list) : 0;
-                    const float v = list ? lane_f32(w, i) : 0.0f;
-                    n[u] = list ? j * kSub + i : 0;
-                    const uint64_t mask = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(lo, i) |
-                                          (uint64_t)(uint32_t)__builtin_amdgcn_readlane(hi, i) << 32;
-                    x[u] = __builtin_amdgcn_inverse_ballot_w64(mask) ? v : -v;   // (waits for the lane reads; inline assembly would not)
-                    list &= list - 1;
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if constexpr (BATCH) {
-                        if (n[u] >= end) {   // uniform
-                            a = (float)((double)a + delta);
-                            delta = 0.0;
-                            end = (n[u] / batch + 1) * batch;
-                        }
-                        delta += (double)x[u];
-                    } else {
-                        a = __fadd_rn(a, x[u]);
-                    }
-                }
-            }
-        }
-        if (BATCH) a = (float)((double)a + delta);
-        double q = 0.0;
-        if (d < D) {
-            acc[(int64_t)c * D + d] = a;
-            q = (double)a * (double)a;
-        }
-        q = lane_prefix(q);
-        if (lane == kWave - 1) normpart[(int64_t)c * G + g] = q;
-    }
-}
-
-// grid (groups)
-template <bool BATCH>
-__global__ __launch_bounds__(kChainMaxWaves *kWave) void online_rows_kernel(
-    const uint64_t *__restrict__ col, int64_t ld, int nb, int batch, const OnlineWeight *__restrict__ recs, float *acc,
-    int D, int C, int G, double *__restrict__ normpart) {
-    update_rows<BATCH>((int)blockIdx.x, col, ld, nb, batch, recs, acc, D, C, G, normpart);
+    for (int k = 0; k < CPW; ++k)
+        if (lane == 0 && wave * CPW + k < C) grown[wave * CPW + k] = nrm[k] - at_start[k];
 }
 
 // ---- the chain of a whole block at once ------------------------------------------------------------
@@ -918,22 +937,14 @@ __device__ __forceinline__ void each(F &&f) {
     }
 }
 
-struct WideRows {   // what the workgroups beside it need: the updates of the block before
-    const uint64_t *col;
-    int64_t ld;
-    const OnlineWeight *recs;
-    float *acc;
-    double *normpart;
-};
-
 template <int CPW, int GR>
 __global__ __launch_bounds__(kWideWaves *kWave) void online_wide_kernel(
     const int16_t *__restrict__ gram, const int16_t *__restrict__ image, const WideOrder *__restrict__ order,
     double *part, int slices, int nb, const int32_t *__restrict__ labels,
     const double *__restrict__ normpart, int G, int C, int D, float lr, double inv_root_d, OnlineWeight *__restrict__ out,
-    double *grown, bool ahead, WideRows before) {
+    double *grown, bool ahead, BlockBefore before) {
     if (blockIdx.x) {
-        update_rows<false>((int)blockIdx.x - 1, before.col, before.ld, kChainBlock, 1, before.recs, before.acc, D, C, G, before.normpart);
+        update_rows<false>((int)blockIdx.x - 1, before.col, before.ld, before.nb, 1, before.recs, before.acc, D, C, G, before.normpart);
         return;
     }
     extern __shared__ __align__(16) int16_t prod[];   // the tiles of the block's sub-blocks, then s_place [wide_places], s_cos [4 C], s_start [4 C]
@@ -1035,7 +1046,7 @@ __global__ __launch_bounds__(kWideWaves *kWave) void online_wide_kernel(
     __syncthreads();
     const int kind = s_odd[lane & (kWideWaves - 1)];
     const bool zero_model = __ballot(kind != 0) == 0;
-    const bool strange = __ballot(kind == 1) != 0 || !(fabsf(lr) < 1e30f);
+    const bool strange = __ballot(kind == 1) != 0 || !(fabsf(lr) < kTameRate);
 
     float wy = 0.0f, wp = 0.0f;
     int pred = -1;
@@ -1227,10 +1238,10 @@ static int chain_slice(int D) {   // dimensions of a slice: up to ten slices, wh
     return s;
 }
 
-// Samples whose products and columns are held at a time: the columns stay within 64 MB.
+// Samples whose columns are held at a time: within 64 MB.
 static int64_t held_samples(int G) {
     const int64_t fit = ((int64_t)64 << 20) / ((int64_t)G * (int64_t)sizeof(uint64_t)) / kSub * kSub;
-    return fit < kGramSamples ? fit : kGramSamples;
+    return std::min(fit, kHeldBlocks * kChainBlock);
 }
 
 bool online_chain_takes(const hdc_ctx_impl *c) { return c->p.C <= 4 * kChainMaxWaves && c->p.D <= 65535; }
@@ -1270,7 +1281,7 @@ bool online_chain_pays(const hdc_ctx_impl *c, int64_t N, int64_t batch) {
 // and, 2000 samples, 6 classes, D = 10000: 1.65 without false labels, 1.01 with half of them, 0.93 with labels at random.
 static bool wide_takes(const hdc_ctx_impl *c, int64_t N, int32_t epochs, float lr) {
     const int C = c->p.C;
-    return C <= kWideClasses && c->p.D <= 32767 && N > 2 * kSub && N * epochs > 2 * kSub * (C - 2) && fabsf(lr) < 1e30f;
+    return C <= kWideClasses && c->p.D <= 32767 && N > 2 * kSub && N * epochs > 2 * kSub * (C - 2) && fabsf(lr) < kTameRate;
 }
 
 int reserve_online_chain(hdc_ctx_impl *c) {
@@ -1278,25 +1289,32 @@ int reserve_online_chain(hdc_ctx_impl *c) {
     const int C = c->p.C, D = c->p.D;
     const int G = (D + kWave - 1) / kWave, slice = chain_slice(D), slices = (D + slice - 1) / slice;
     HDC_HIP(hipSetDevice(c->device));
-    int rc = grow(&c->oc_col_d, &c->oc_col_bytes, (size_t)G * held_samples(G) * sizeof(uint64_t));
-    if (rc == HDC_OK) rc = grow(&c->oc_gram_d, &c->oc_gram_bytes, (size_t)kGramBlocks * kTiles * kTile * sizeof(int16_t));
-    if (rc == HDC_OK) rc = grow(&c->oc_part_d, &c->oc_part_bytes, (size_t)(slices + 1) * C * kChainBlock * sizeof(double));
-    if (rc == HDC_OK) rc = grow(&c->oc_rec_d, &c->oc_rec_bytes, (size_t)2 * kChainBlock * sizeof(OnlineWeight));
-    if (rc == HDC_OK) rc = grow(&c->oc_pairs_d, &c->oc_pairs_bytes, (size_t)(kWideBlocks - 1) * kSubs * kSubs * kTile * sizeof(int16_t));
-    if (rc == HDC_OK) rc = grow(&c->oc_norm_d, &c->oc_norm_bytes, (size_t)C * (G + 1) * sizeof(double));
-    if (rc == HDC_OK) rc = grow(&c->oc_order_d, &c->oc_order_bytes, (size_t)kWideBlocks * sizeof(WideOrder));
-    if (rc == HDC_OK) rc = grow(&c->oc_image_d, &c->oc_image_bytes, (size_t)kWideBlocks * kWideImage * sizeof(int16_t));
+    // one allocation (each takes half a millisecond), the parts at multiples of 256 bytes
+    struct { void **at; size_t bytes; } parts[] = {
+        {(void **)&c->oc_col_d, (size_t)G * held_samples(G) * sizeof(uint64_t)},
+        {(void **)&c->oc_gram_d, (size_t)kHeldBlocks * kTiles * kTile * sizeof(int16_t)},
+        {(void **)&c->oc_pairs_d, (size_t)(kHeldBlocks - 1) * kSubs * kSubs * kTile * sizeof(int16_t)},
+        {(void **)&c->oc_image_d, (size_t)kHeldBlocks * kWideImage * sizeof(int16_t)},
+        {(void **)&c->oc_order_d, (size_t)kHeldBlocks * sizeof(WideOrder)},
+        {(void **)&c->oc_part_d, (size_t)(slices + 1) * C * kChainBlock * sizeof(double)},
+        {(void **)&c->oc_rec_d, (size_t)2 * kChainBlock * sizeof(OnlineWeight)},
+        {(void **)&c->oc_norm_d, (size_t)C * (G + 1) * sizeof(double)},
+    };
+    size_t want = 0;
+    for (const auto &p : parts) want += (p.bytes + 255) / 256 * 256;
+    int rc = grow(&c->oc_mem_d, &c->oc_mem_bytes, want);
+    char *next = c->oc_mem_d;
+    for (const auto &p : parts) {
+        *p.at = next;
+        if (next) next += (p.bytes + 255) / 256 * 256;
+    }
     if (rc == HDC_OK) rc = grow(&c->on_bits_d, &c->on_bits_bytes, (size_t)kOnlineWords * sizeof(uint32_t));
     if (rc == HDC_OK) rc = grow(&c->ob_norm_d, &c->ob_norm_bytes, (size_t)C * G * sizeof(double));
     c->oc_ready = rc == HDC_OK;
     if (rc == HDC_ENOMEM) {   // all or nothing: what is left of the memory is for the other ways
-        (void)hipFree(c->oc_col_d);
-        (void)hipFree(c->oc_gram_d);
-        (void)hipFree(c->oc_image_d);
-        (void)hipFree(c->oc_pairs_d);
-        c->oc_col_d = nullptr;
-        c->oc_gram_d = c->oc_image_d = c->oc_pairs_d = nullptr;
-        c->oc_col_bytes = c->oc_gram_bytes = c->oc_image_bytes = c->oc_pairs_bytes = 0;
+        (void)hipFree(c->oc_mem_d);
+        c->oc_mem_d = nullptr;
+        c->oc_mem_bytes = 0;
     }
     return rc;
 }
@@ -1309,9 +1327,20 @@ bool online_chain_ready(hdc_ctx_impl *c, hipStream_t s, int *rc) {
     return c->oc_ready;
 }
 
+// A block's chain, with the row updates of the block before beside it if the rows do not hold those yet (ahead).
+struct ChainCall {
+    int64_t b;               // block of those that are held
+    int slices, nb, batch, G;
+    const int32_t *labels;
+    float lr;
+    const double *norm;      // squared-norm partials of the rows
+    bool ahead;
+    BlockBefore before;
+    OnlineWeight *recs;      // out
+};
+
 template <int CPW, bool BATCH>
-static int launch_chain(hdc_ctx_impl *c, const int16_t *gram, int slices, int nb, int batch, const int32_t *labels,
-                        const double *norm, OnlineWeight *recs, int G, float lr, hipStream_t s) {
+static int launch_chain(hdc_ctx_impl *c, const ChainCall &a, hipStream_t s) {
     auto kern = online_chain_kernel<CPW, BATCH>;
     const int slot = (CPW == 1 ? 0 : CPW == 2 ? 2 : 4) + (BATCH ? 1 : 0);
     if (!c->oc_attr_set[slot]) {
@@ -1319,18 +1348,17 @@ static int launch_chain(hdc_ctx_impl *c, const int16_t *gram, int slices, int nb
                                     kTiles * kTile * (int)sizeof(int16_t)));
         c->oc_attr_set[slot] = true;
     }
-    const int subs = (nb + kSub - 1) / kSub;
-    ProfScope prof(c, HDC_K_ONLINE, s, BATCH);
-    hipLaunchKernelGGL(kern, dim3(1), dim3(kChainMaxWaves * kWave),
-                       (size_t)(subs * (subs + 1) / 2) * kTile * sizeof(int16_t), s, gram, c->oc_part_d, slices, nb,
-                       batch, labels, norm, G, c->p.C, c->p.D, lr, 1.0 / sqrt((double)c->p.D), recs);
+    const int subs = (a.nb + kSub - 1) / kSub;
+    hipLaunchKernelGGL(kern, dim3(a.ahead ? 1u + (unsigned)a.G : 1u), dim3(kChainMaxWaves * kWave),
+                       (size_t)(subs * (subs + 1) / 2) * kTile * sizeof(int16_t), s, c->oc_gram_d + a.b * kTiles * kTile, c->oc_part_d,
+                       a.slices + (a.ahead ? 1 : 0), a.nb, a.batch, a.labels, a.norm, a.G, c->p.C, c->p.D, a.lr,
+                       1.0 / sqrt((double)c->p.D), a.recs, c->oc_norm_d + (int64_t)c->p.C * a.G, a.ahead, a.before);
     HDC_HIP(hipGetLastError());
     return HDC_OK;
 }
 
 template <int CPW, int GR>
-static int launch_wide(hdc_ctx_impl *c, int64_t b, int slices, int nb, const int32_t *labels, int G, float lr,
-                       const double *norm, bool ahead, const WideRows &before, OnlineWeight *recs, hipStream_t s) {
+static int launch_wide(hdc_ctx_impl *c, const ChainCall &a, hipStream_t s) {
     auto kern = online_wide_kernel<CPW, GR>;
     const int slot = CPW == 1 ? 6 : 7, C = c->p.C, per_place = kSub * (int)sizeof(double);
     const int most = CPW * kWideWaves, cosines = kSubs * (CPW == 1 ? 2 : 1);   // places beside the runs' for a class: cosines, starts
@@ -1339,47 +1367,66 @@ static int launch_wide(hdc_ctx_impl *c, int64_t b, int slices, int nb, const int
                                     kTiles * kTile * (int)sizeof(int16_t) + (wide_places(most) + cosines * most) * per_place));
         c->oc_attr_set[slot] = true;
     }
-    const int subs = (nb + kSub - 1) / kSub;
-    hipLaunchKernelGGL(kern, dim3(ahead ? 1u + (unsigned)G : 1u), dim3(kWideWaves * kWave),
+    const int subs = (a.nb + kSub - 1) / kSub;
+    hipLaunchKernelGGL(kern, dim3(a.ahead ? 1u + (unsigned)a.G : 1u), dim3(kWideWaves * kWave),
                        (size_t)(subs * (subs + 1) / 2) * kTile * sizeof(int16_t) + (size_t)(wide_places(C) + cosines * C) * per_place, s,
-                       c->oc_gram_d + b * kTiles * kTile, c->oc_image_d + b * kWideImage,
-                       static_cast<const WideOrder *>(c->oc_order_d) + b, c->oc_part_d, slices + (ahead ? 1 : 0), nb, labels, norm, G,
-                       C, c->p.D, lr, 1.0 / sqrt((double)c->p.D), recs,
-                       c->oc_norm_d + (int64_t)C * G, ahead, before);
+                       c->oc_gram_d + a.b * kTiles * kTile, c->oc_image_d + a.b * kWideImage,
+                       static_cast<const WideOrder *>(c->oc_order_d) + a.b, c->oc_part_d, a.slices + (a.ahead ? 1 : 0), a.nb, a.labels,
+                       a.norm, a.G, C, c->p.D, a.lr, 1.0 / sqrt((double)c->p.D), a.recs, c->oc_norm_d + (int64_t)C * a.G, a.ahead,
+                       a.before);
     HDC_HIP(hipGetLastError());
     return HDC_OK;
 }
 
-// The blocks of samples that are held, per sample.  Two launches a block: the chain of block b beside the row updates of
-// block b - 1, then the products of block b + 1 with the rows as those left them, and with block b's updates by the
-// samples' own products.  (Rows, products and chain one after another: 27 us a block at 6 classes, D = 10000; this way 22.)
-static int walk_wide(hdc_ctx_impl *c, const int32_t *labels, int64_t N, float lr, float *acc, int64_t ld, int *norm_at, hipStream_t s) {
+// The blocks of samples that are held.  Two launches a block: the chain of block b beside the row updates of block b - 1,
+// then the products of block b + 1 with the rows as those left them, and with block b's updates by the samples' own
+// products.  (Rows, products and chain one after another took 27 us a block instead of 22, per sample, 6 classes, D = 10000;
+// 36 instead of 30 in batches of 64.)  A learning rate that can make a weight overflow leaves that: each block after the rows.
+template <bool BATCH>
+static int walk_held(hdc_ctx_impl *c, const int32_t *labels, int64_t N, float lr, int batch, bool wide, float *acc, int64_t ld,
+                     int *norm_at, hipStream_t s) {
     const int C = c->p.C, D = c->p.D;
     const int G = (D + kWave - 1) / kWave, slice = chain_slice(D), slices = (D + slice - 1) / slice;
-    double *norm[2] = {c->ob_norm_d, c->oc_norm_d};   // squared norms: of the rows before the last update, and after
-    const int64_t blocks = (N + kChainBlock - 1) / kChainBlock;
+    const int block = kChainBlock / batch * batch;   // whole batches
+    double *norm[2] = {c->ob_norm_d, c->oc_norm_d};  // squared norms: of the rows before the last update, and after
+    const int64_t blocks = (N + block - 1) / block;
+    const bool beside = fabsf(lr) < kTameRate;
     OnlineWeight *const all = static_cast<OnlineWeight *>(c->oc_rec_d);   // of an even block, and of an odd one
     for (int64_t b = 0; b < blocks; ++b) {
-        const int nb = (int)(N - b * kChainBlock < kChainBlock ? N - b * kChainBlock : kChainBlock);
+        const int nb = (int)(N - b * block < block ? N - b * block : block);
         OnlineWeight *recs = all + b % 2 * kChainBlock;
         const OnlineWeight *recs_before = all + (b + 1) % 2 * kChainBlock;
-        const uint64_t *col = c->oc_col_d + b * kChainBlock;
-        const bool ahead = b > 0;   // the rows do not hold the block before yet
-        hipLaunchKernelGGL(online_dots_kernel, dim3((unsigned)(slices + (ahead ? 1 : 0)), (unsigned)((nb + 15) / 16), (unsigned)((C + 15) / 16)),
-                           dim3(kDotWaves * kWave), 0, s, col, ld, nb, acc, D, C, slice, slices,
-                           ahead ? c->oc_pairs_d + (b - 1) * kSubs * kSubs * kTile : nullptr, recs_before, c->oc_part_d);
+        const uint64_t *col = c->oc_col_d + b * block;
+        const bool ahead = beside && b > 0;   // the rows do not hold the block before yet
+        {
+            ProfScope prof(c, HDC_K_ONLINE_FWD, s, BATCH);
+            hipLaunchKernelGGL(online_dots_kernel,
+                               dim3((unsigned)(slices + (ahead ? 1 : 0)), (unsigned)((nb + 15) / 16), (unsigned)((C + 15) / 16)),
+                               dim3(kDotWaves * kWave), 0, s, col, ld, nb, acc, D, C, slice, slices,
+                               ahead ? c->oc_pairs_d + (b - 1) * kSubs * kSubs * kTile : nullptr, recs_before, block, c->oc_part_d);
+        }
         HDC_HIP(hipGetLastError());
-        const WideRows before = {col - (ahead ? kChainBlock : 0), ld, recs_before, acc, norm[*norm_at ^ 1]};
-        const int32_t *lab = labels + b * kChainBlock;
-        const int rc = C <= kWideWaves
-                           ? launch_wide<1, wide_group(kWideWaves)>(c, b, slices, nb, lab, G, lr, norm[*norm_at], ahead, before, recs, s)
-                           : launch_wide<2, wide_group(2 * kWideWaves)>(c, b, slices, nb, lab, G, lr, norm[*norm_at], ahead, before, recs, s);
-        if (rc != HDC_OK) return rc;
+        const ChainCall a = {b, slices, nb, batch, G, labels + b * block, lr, norm[*norm_at], ahead,
+                             {col - (ahead ? block : 0), ld, block, recs_before, acc, norm[*norm_at ^ 1]}, recs};
+        {
+            ProfScope prof(c, HDC_K_ONLINE, s, BATCH), with(c, HDC_K_ONLINE_BWD, s, BATCH && ahead);
+            int rc;
+            if (wide)
+                rc = C <= kWideWaves ? launch_wide<1, wide_group(kWideWaves)>(c, a, s) : launch_wide<2, wide_group(2 * kWideWaves)>(c, a, s);
+            else if (C <= kChainMaxWaves)
+                rc = launch_chain<1, BATCH>(c, a, s);
+            else if (C <= 2 * kChainMaxWaves)
+                rc = launch_chain<2, BATCH>(c, a, s);
+            else
+                rc = launch_chain<4, BATCH>(c, a, s);
+            if (rc != HDC_OK) return rc;
+        }
         if (ahead) *norm_at ^= 1;
-        if (b + 1 == blocks) {
-            const unsigned waves = (unsigned)(C < 4 ? 4 : C);
-            hipLaunchKernelGGL(online_rows_kernel<false>, dim3((unsigned)G), dim3(waves * kWave), 0, s, col, ld, nb, 1, recs, acc, D, C,
-                               G, norm[*norm_at ^ 1]);
+        if (!beside || b + 1 == blocks) {
+            const unsigned waves = (unsigned)(C < 4 ? 4 : C < kChainMaxWaves ? C : kChainMaxWaves);
+            ProfScope prof(c, HDC_K_ONLINE_BWD, s, BATCH);
+            hipLaunchKernelGGL(online_rows_kernel<BATCH>, dim3((unsigned)G), dim3(waves * kWave), 0, s, col, ld, nb, batch, recs, acc, D,
+                               C, G, norm[*norm_at ^ 1]);
             HDC_HIP(hipGetLastError());
             *norm_at ^= 1;
         }
@@ -1391,14 +1438,14 @@ template <bool BATCH>
 static int walk_blocks(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *labels, int64_t N, int32_t epochs, float lr,
                        int batch, float *acc, hipStream_t s) {
     const int C = c->p.C, D = c->p.D, W = c->W;
-    const int G = (D + kWave - 1) / kWave, slice = chain_slice(D), slices = (D + slice - 1) / slice;
+    const int G = (D + kWave - 1) / kWave;
     ProfScope walk(c, HDC_K_ONLINE, s, !BATCH);   // a walk by samples as a whole; of batches each block's three steps
     int rc = launch_norm(c, acc, G, s);
     if (rc != HDC_OK) return rc;
     const int block = kChainBlock / batch * batch;   // whole batches
     const bool wide = !BATCH && wide_takes(c, N, epochs, lr);
-    const int64_t ld = held_samples(G), held = (wide ? std::min(ld, kWideSamples) : ld) / block * block;
-    int norm_at = 0;   // which of the two arrays of squared norms is that of the rows (walk_wide)
+    const int64_t ld = held_samples(G), held = std::min(ld / block, kHeldBlocks) * block;
+    int norm_at = 0;   // which of the two arrays of squared norms is that of the rows
     for (int32_t e = 0; e < epochs; ++e)
         for (int64_t h0 = 0; h0 < N; h0 += held) {
             const int64_t hn = N - h0 < held ? N - h0 : held;
@@ -1412,44 +1459,14 @@ static int walk_blocks(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *label
                 if (hn > 1 || wide) {
                     const int subs = (int)((std::min<int64_t>(hn, block) + kSub - 1) / kSub);
                     hipLaunchKernelGGL(wide ? online_gram_kernel<true> : online_gram_kernel<false>,
-                                       dim3((unsigned)(subs * (subs + 1) / 2 + (wide && blocks > 1 ? kSubs * kSubs : 0)), blocks),
+                                       dim3((unsigned)(subs * (subs + 1) / 2 + (blocks > 1 ? (kTiles - subs * (subs + 1) / 2) + kSubs * kSubs : 0)), blocks),
                                        dim3(kGramWaves * kWave), 0, s, c->oc_col_d, ld, hn, D, G, block, c->oc_gram_d, order,
                                        c->oc_image_d, c->oc_pairs_d);
                 }
                 HDC_HIP(hipGetLastError());
             }
-            if (wide) {
-                rc = walk_wide(c, labels + h0, hn, lr, acc, ld, &norm_at, s);
-                if (rc != HDC_OK) return rc;
-                continue;
-            }
-            for (int64_t b0 = 0; b0 < hn; b0 += block) {
-                const int nb = (int)(hn - b0 < block ? hn - b0 : block);
-                const uint64_t *col = c->oc_col_d + b0;
-                const int32_t *lab = labels + h0 + b0;
-                const int16_t *gram = c->oc_gram_d + b0 / block * kTiles * kTile;
-                OnlineWeight *recs = static_cast<OnlineWeight *>(c->oc_rec_d);
-                {
-                    ProfScope prof(c, HDC_K_ONLINE_FWD, s, BATCH);
-                    hipLaunchKernelGGL(online_dots_kernel,
-                                       dim3((unsigned)slices, (unsigned)((nb + 15) / 16), (unsigned)((C + 15) / 16)),
-                                       dim3(kDotWaves * kWave), 0, s, col, ld, nb, acc, D, C, slice, slices, nullptr, nullptr,
-                                       c->oc_part_d);
-                }
-                HDC_HIP(hipGetLastError());
-                if (C <= kChainMaxWaves)
-                    rc = launch_chain<1, BATCH>(c, gram, slices, nb, batch, lab, c->ob_norm_d, recs, G, lr, s);
-                else if (C <= 2 * kChainMaxWaves)
-                    rc = launch_chain<2, BATCH>(c, gram, slices, nb, batch, lab, c->ob_norm_d, recs, G, lr, s);
-                else
-                    rc = launch_chain<4, BATCH>(c, gram, slices, nb, batch, lab, c->ob_norm_d, recs, G, lr, s);
-                if (rc != HDC_OK) return rc;
-                const unsigned waves = (unsigned)(C < 4 ? 4 : C < kChainMaxWaves ? C : kChainMaxWaves);
-                ProfScope prof(c, HDC_K_ONLINE_BWD, s, BATCH);
-                hipLaunchKernelGGL(online_rows_kernel<BATCH>, dim3((unsigned)G), dim3(waves * kWave), 0, s, col, ld,
-                                   nb, batch, recs, acc, D, C, G, c->ob_norm_d);
-                HDC_HIP(hipGetLastError());
-            }
+            rc = walk_held<BATCH>(c, labels + h0, hn, lr, batch, wide, acc, ld, &norm_at, s);
+            if (rc != HDC_OK) return rc;
         }
     return HDC_OK;
 }
