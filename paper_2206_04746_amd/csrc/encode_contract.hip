@@ -67,6 +67,7 @@ constexpr int kCtWaves = 8;        // waves per block at least (the kernel runs 
 constexpr int kCtPlanes = 8;      // most bit planes of a bin number: L <= 256 (a model has ceil(log2 L) of them)
 constexpr int kCtMaxSteps = 14;   // MFMAs per tile: 64 features each
 constexpr int kCtSamples = 32;    // samples per block and job
+constexpr size_t kCtLdsLimit = 160 * 1024;   // of a compute unit
 // A model with chains is taken while its tiles, a chain's counted one and a quarter times (most
 // bring a new threshold), are at most (24 + F / 34) / 10 times the tiles its varying dimensions
 // would fill: measured at D = 10000 on 65536 samples against the vector kernel, whose time grows
@@ -97,7 +98,7 @@ int prepare_contract(hdc_ctx_impl *c, const uint32_t *item, const uint32_t *leve
     c->ct_ready = false;
     c->ct_min_split = -1;
     if (!c->expand_d || L < 2 || L > (1 << kCtPlanes) || F > 64 * kCtMaxSteps || F < 4 || W > 4 * kCtWaves * kWave) return HDC_OK;   // four features per load; a thread per word of a quarter of a row at least
-    const int steps = ((F + 63) / 64 + 1) / 2 * 2;   // the kernel is built for even counts; a step past F meets zeros
+    const int steps = F <= 64 ? 1 : ((F + 63) / 64 + 1) / 2 * 2;   // the kernel is built for one and for even counts; a step past F meets zeros
     const ModelView model = {p.D, W, F, L, c->votes, item, level, tie};
     std::vector<std::vector<int>> by_tau;
     std::vector<FlipChain> chains;
@@ -442,6 +443,24 @@ constexpr int kCtSplitWork = 1024;         // MFMAs per 32 samples from which a 
 constexpr int64_t kCtMinSamples = 1024;        // models whose words are not split over blocks
 constexpr int64_t kCtMinSamplesSplit = 256;    // models whose words are
 
+// (one step counts as two: what a block does per tile beside its MFMAs is the same)
+static bool contract_splits(const hdc_ctx_impl *c) {
+    return c->ct_tiles[c->ct_min_split] * std::max(c->ct_steps, 2) >= kCtSplitWork;
+}
+
+static size_t contract_lds(const hdc_ctx_impl *c, int v, bool planes) {
+    return (size_t)kCtSamples * (c->ct_steps * 64 + 16) + (planes ? (size_t)c->ct_steps * 2 * kWave * 16 : 0) + (size_t)c->ct_range_max[v] * 32 * 4;
+}
+
+// Blocks of eight waves have at most 128 registers a lane: two share a compute unit where its LDS holds both.  A block
+// is a chain of phases that leave the unit idle in places (20000 samples, D = 10000, 64 levels: 200 features, one
+// block a unit 56.2 us, two 42.4; 31 features 46.6, two and one step instead of two 31.9).
+constexpr int kCtMostSharedSteps = 4;
+static int contract_per_unit(const hdc_ctx_impl *c, int v) {
+    return c->ct_steps <= kCtMostSharedSteps && 2 * (contract_lds(c, v, false) + 1024) <= kCtLdsLimit ? 2 : 1;
+}
+bool contract_shares_units(const hdc_ctx_impl *c) { return c->ct_ready && contract_per_unit(c, c->ct_min_split) == 2; }
+
 template <int KS, int NB, bool kU8, bool kChain>
 static int launch_contract(hdc_ctx_impl *c, const void *x, int64_t n, uint32_t *out, hipStream_t s) {
     // With few samples, several blocks per 32 of them, each with a range of the row's words -- where
@@ -449,21 +468,20 @@ static int launch_contract(hdc_ctx_impl *c, const void *x, int64_t n, uint32_t *
     // make more, emptier tiles: with 300 MFMAs per 32 samples the split was 8 % slower, with 1900 25 % faster).
     const int64_t jobs = (n + kCtSamples - 1) / kCtSamples;
     int v = jobs * 4 <= c->num_cus ? 2 : jobs * 2 <= c->num_cus ? 1 : 0;
-    if (c->ct_tiles[c->ct_min_split] * c->ct_steps < kCtSplitWork) v = 0;
+    if (!contract_splits(c)) v = 0;
     v = std::max(c->ct_min_split, std::min(v, c->ct_max_split));   // (wide rows are always split: a thread per word of a range)
     // Twelve waves where the tiles are most of the work (a third wave per SIMD fills more of the gaps
     // between matrix and vector instructions: 3 to 6 % on the 342- to 784-feature shapes), eight
     // for small models (100 features: 3 % slower with twelve).  The limits the host applies to the
     // tables are those of eight.
-    constexpr int NW = KS >= 6 ? 12 : kCtWaves;
+    constexpr int NW = KS > kCtMostSharedSteps ? 12 : kCtWaves;
     constexpr bool kPlanesInLds = KS > 10 || NW > 8;
     auto kern = encode_contract_kernel<KS, NB, kU8, NW, kChain>;
-    const size_t lds = (size_t)kCtSamples * (KS * 64 + 16) + (kPlanesInLds ? (size_t)KS * 2 * kWave * 16 : 0) +
-                       (size_t)c->ct_range_max[v] * 32 * 4;
+    const size_t lds = contract_lds(c, v, kPlanesInLds);
     if (lds > 64 * 1024)
         HDC_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     (int)lds));
-    const int64_t blocks = std::min<int64_t>(jobs << v, (int64_t)c->num_cus);
+    const int64_t blocks = std::min<int64_t>(jobs << v, (int64_t)c->num_cus * contract_per_unit(c, v));
     CtRanges rt;
     for (int r = 0; r <= 4; ++r) rt.t[r] = c->ct_range[v][r];
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(NW * kWave), lds, s, x, n, c->p.F, c->p.L, c->lo_d,
@@ -477,6 +495,7 @@ static int launch_contract(hdc_ctx_impl *c, const void *x, int64_t n, uint32_t *
 template <int NB, bool kU8, bool kChain>
 static int launch_contract_steps(hdc_ctx_impl *c, const void *x, int64_t n, uint32_t *out, hipStream_t s) {
     switch (c->ct_steps) {
+    case 1: return launch_contract<1, NB, kU8, kChain>(c, x, n, out, s);
     case 2: return launch_contract<2, NB, kU8, kChain>(c, x, n, out, s);
     case 4: return launch_contract<4, NB, kU8, kChain>(c, x, n, out, s);
     case 6: return launch_contract<6, NB, kU8, kChain>(c, x, n, out, s);
@@ -499,7 +518,7 @@ static int launch_contract_planes(hdc_ctx_impl *c, const void *x, int64_t n, uin
 // nothing was launched).
 bool try_encode_contract(hdc_ctx_impl *c, const void *feats, int64_t N, uint32_t *hv, hipStream_t s, int *rc) {
     if (!c->ct_ready) return false;
-    const bool splits = c->ct_max_split > 0 && c->ct_tiles[c->ct_min_split] * c->ct_steps >= kCtSplitWork;
+    const bool splits = c->ct_max_split > 0 && contract_splits(c);
     if (N < (splits ? kCtMinSamplesSplit : kCtMinSamples)) return false;
     ProfScope prof(c, HDC_K_ENCODE_CONTRACT, s);
     *rc = c->ct_chained ? launch_contract_planes<true>(c, feats, N, hv, s) : launch_contract_planes<false>(c, feats, N, hv, s);

@@ -228,6 +228,7 @@ int64_t classical_max_items(hdc_ctx_impl *c);
 // when the model or the call is not of its shape (then nothing was launched).
 int prepare_contract(hdc_ctx_impl *c, const uint32_t *item, const uint32_t *level, const uint32_t *tie);
 bool try_encode_contract(hdc_ctx_impl *c, const void *feats, int64_t N, uint32_t *hv, hipStream_t s, int *rc);
+bool contract_shares_units(const hdc_ctx_impl *c);   // two blocks of the contraction a compute unit
 // The contraction for long streams (encode_wide.hip); same conventions.  prepare_wide needs the
 // tables of prepare_compact.
 int prepare_wide(hdc_ctx_impl *c, const uint32_t *item, const uint32_t *level, const uint32_t *tie);

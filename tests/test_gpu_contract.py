@@ -196,6 +196,28 @@ def test_encode_tables_whose_every_dimension_flips_once_take_the_contraction():
     ctx.close()
 
 
+@pytest.mark.parametrize("cfg,D,F,L,N,circle", [
+    # one step of 64 features and both sides of it; blocks that share a compute unit, with one job each and with a second one
+    (2, 3000, 4, 16, 8257, False), (2, 3000, 64, 64, 8193, False), (2, 3000, 65, 64, 9001, False), (3, 2048, 49, 256, 16001, False),
+    (2, 1024, 63, 100, 16417, False), (2, 1000, 31, 2, 17003, False), (2, 2500, 256, 32, 17003, False), (2, 4000, 60, 8, 17003, True),
+    # columns of 32 samples that the LDS holds once a compute unit, not twice; rows split over blocks
+    (2, 32768, 40, 16, 4001, False), (2, 20000, 64, 64, 9001, False), (2, 16384, 129, 256, 8257, False),
+])
+def test_encode_contraction_of_few_features_with_two_blocks_a_compute_unit(cfg, D, F, L, N, circle):
+    wl = make_workload(cfg, seed=D + F + L, D=D, F=F, L=L, n_train=N)
+    if circle:
+        rng = np.random.default_rng(D + N)
+        step = rng.integers(1, L // 2 + 1, D)
+        wl.level = _levels_from_flips(rng, D, L, [(int(s), int(s) + L // 2) if s + L // 2 < L else (int(s),) for s in step])
+    x, _ = wl.train(N)
+    ctx = _ctx(wl)
+    ctx.hdc_profile_enable(True)
+    got = _encode(ctx, x)
+    assert ctx.hdc_profile_read("encode_contract")[1] == 1
+    assert np.array_equal(got, _oracle(wl, x))
+    ctx.close()
+
+
 def test_encode_contraction_many_samples_and_agreement_with_small_calls():
     # more samples than blocks in flight (several jobs per block); the same rows encoded in calls too
     # small for the contraction must give the same bits
