@@ -99,20 +99,23 @@ __device__ __forceinline__ void pin_schedule() { __builtin_amdgcn_sched_barrier(
 // (j, r) adds up value j of source lanes 16 r .. 16 r + 15 and two lane exchanges fold the four
 // r.  That is ~4 issue slots per value instead of ~20 for a butterfly per value.  The masks of
 // the next sample are loaded (scalar) while the current one computes.
+// With `normpart` the first tile's blocks leave the squared norms of the rows they have staged instead: a launch less for
+// cosine inference (with the partials of a cosine in flight together, below: 2947 queries, 6 classes, D = 10000, 27.7
+// -> 24.3 us a call).
 constexpr int kFwdVals = 16;                 // values reduced per trip = NS * CC
 constexpr int kFwdStride = kWave + 1;        // doubles per value row in the LDS tile (+1: banks)
 
 template <int CC, int KPT>
 __global__ __launch_bounds__(kFwdWaves *kWave) void online_fwd_kernel(
     const uint32_t *__restrict__ hv, int64_t nb, const float *__restrict__ acc, int D, int W, int C,
-    int spw, double *__restrict__ part) {
+    int spw, double *__restrict__ part, double *__restrict__ normpart) {
     constexpr int NS = kFwdVals / CC;
     __shared__ double xch[kFwdWaves][kFwdVals * kFwdStride];
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int slice = blockIdx.x;
     const int c0 = blockIdx.y * CC;
-    const int64_t n0 = ((int64_t)blockIdx.z * kFwdWaves + wave) * spw;
+    const int64_t n0 = ((int64_t)((int)blockIdx.z - (normpart ? 1 : 0)) * kFwdWaves + wave) * spw;
     const int64_t n1 = n0 + spw < nb ? n0 + spw : nb;
     double *buf = xch[wave];
 
@@ -145,6 +148,16 @@ __global__ __launch_bounds__(kFwdWaves *kWave) void online_fwd_kernel(
         for (int i = 0; i < kPerThread; ++i) stage[threadIdx.x + i * kFwdWaves * kWave] = x[i];
     }
     __syncthreads();
+    if (normpart && blockIdx.z == 0) {   // block-uniform; the arithmetic of online_norm_kernel
+        for (int i = wave; i < CC * KPT; i += kFwdWaves) {
+            const int j = i / KPT, g = g_base + i % KPT;
+            if (c0 + j >= C || g >= G || g < g_own) continue;
+            const double x = (double)stage[i * kWave + lane];
+            const double q = wave_sum_f64(x * x);
+            if (lane == 0) normpart[(int64_t)(c0 + j) * G + g] = q;
+        }
+        return;
+    }
     double v[CC][KPT];
 #pragma unroll
     for (int j = 0; j < CC; ++j)
@@ -221,6 +234,7 @@ __global__ __launch_bounds__(kFwdWaves *kWave) void online_fwd_kernel(
 // row), optionally stores it, and keeps its best; a butterfly over the group then leaves in every
 // lane the largest cosine and the lowest class that has it.  *cos_y receives cos of class y
 // (summed over the group: exactly one lane holds it).
+constexpr int kFinishLoads = 12;   // slice partials in flight together (D = 10000: 10 slices of 1024 dimensions)
 __device__ __forceinline__ void finish_cosines(const double *__restrict__ part, int slices, int64_t nb, int64_t n,
                                                bool live, int C, const double *nrm, double root_d, int cp, int lc,
                                                int y, float *cos_out, double *best_out, int *pred_out,
@@ -230,7 +244,15 @@ __device__ __forceinline__ void finish_cosines(const double *__restrict__ part, 
     if (live)
         for (int c = lc; c < C; c += cp) {
             double dot = 0.0;
-            for (int s = 0; s < slices; ++s) dot += part[((int64_t)s * nb + n) * C + c];
+            const double *at = part + n * C + c;
+            for (int s0 = 0; s0 < slices; s0 += kFinishLoads) {
+                double x[kFinishLoads];
+#pragma unroll
+                for (int i = 0; i < kFinishLoads; ++i) x[i] = at[(int64_t)min(s0 + i, slices - 1) * nb * C];
+#pragma unroll
+                for (int i = 0; i < kFinishLoads; ++i)
+                    if (s0 + i < slices) dot += x[i];   // uniform
+            }
             const double nn = nrm[c];
             const double cs = nn == 0.0 ? 0.0 : dot / (sqrt(nn) * root_d);
             if (cos_out) cos_out[n * C + c] = (float)cs;
@@ -908,20 +930,21 @@ static int64_t fwd_sub_batch(const FwdShape &f, int C, int64_t limit) {
 }
 
 static int launch_fwd(hdc_ctx_impl *c, const FwdShape &f, const uint32_t *rows, int64_t nb, const float *acc,
-                      hipStream_t s) {
+                      bool norms, hipStream_t s) {
     // about four waves per SIMD when there is that much work; whole trips per wave
     int64_t spw = (nb * f.slices * f.chunks + 4095) / 4096;
     spw = (spw + f.ns - 1) / f.ns * f.ns;
     if (spw > 64) spw = 64;
     const int64_t tiles = (nb + kFwdWaves * spw - 1) / (kFwdWaves * spw);
-    const dim3 grid((unsigned)f.slices, (unsigned)f.chunks, (unsigned)tiles);
+    const dim3 grid((unsigned)f.slices, (unsigned)f.chunks, (unsigned)(tiles + (norms ? 1 : 0)));
+    double *norm = norms ? c->ob_norm_d : nullptr;
     ProfScope prof(c, HDC_K_ONLINE_FWD, s);
     if (f.wide)
         hipLaunchKernelGGL((online_fwd_kernel<4, 8>), grid, dim3(kFwdWaves * kWave), 0, s, rows, nb, acc, c->p.D,
-                           c->W, c->p.C, (int)spw, c->ob_part_d);
+                           c->W, c->p.C, (int)spw, c->ob_part_d, norm);
     else
         hipLaunchKernelGGL((online_fwd_kernel<2, 16>), grid, dim3(kFwdWaves * kWave), 0, s, rows, nb, acc, c->p.D,
-                           c->W, c->p.C, (int)spw, c->ob_part_d);
+                           c->W, c->p.C, (int)spw, c->ob_part_d, norm);
     HDC_HIP(hipGetLastError());
     return HDC_OK;
 }
@@ -1029,7 +1052,7 @@ int launch_train_online_batched(hdc_ctx_impl *c, const uint32_t *hv, const int32
             for (int64_t s0 = 0; s0 < B; s0 += sb) {
                 const int64_t nb = s0 + sb < B ? sb : B - s0;
                 const uint32_t *rows = hv + (b0 + s0) * W;
-                rc = launch_fwd(c, f, rows, nb, acc, s);
+                rc = launch_fwd(c, f, rows, nb, acc, false, s);
                 if (rc != HDC_OK) return rc;
                 const int64_t ld_used = (nb + kTileSamples - 1) / kTileSamples * kTileSamples;
                 const int cp = cosine_group(C);
@@ -1058,12 +1081,10 @@ int launch_search_cosine(hdc_ctx_impl *c, const uint32_t *hv, int64_t N, const f
     const int64_t sb = fwd_sub_batch(f, C, N);
     int rc = reserve_search_cosine(c, N);
     if (rc != HDC_OK) return rc;
-    rc = launch_norm(c, acc, G, s);
-    if (rc != HDC_OK) return rc;
     const double root_d = sqrt((double)D);
     for (int64_t n0 = 0; n0 < N; n0 += sb) {
         const int64_t nb = n0 + sb < N ? sb : N - n0;
-        rc = launch_fwd(c, f, hv + n0 * W, nb, acc, s);
+        rc = launch_fwd(c, f, hv + n0 * W, nb, acc, n0 == 0, s);
         if (rc != HDC_OK) return rc;
         const int cp = cosine_group(C);
         hipLaunchKernelGGL(cosine_finish_kernel, dim3((unsigned)((nb + 256 / cp - 1) / (256 / cp))), dim3(256),

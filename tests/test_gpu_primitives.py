@@ -152,6 +152,26 @@ def test_cosine_inference_matches_oracle(D, C, N):
     ctx.close()
 
 
+@pytest.mark.parametrize("D", [1, 64, 511, 1025, 6144, 6145, 10000, 12288, 12289, 24641])
+@pytest.mark.parametrize("C", [2, 4, 7])
+def test_cosine_inference_at_the_edges_of_slices(D, C):
+    """Squared norms and partial sums by slices of 1024 (C = 2) or 512 dimensions, the last one shifted back; 12 partials
+    are added at a time.  fp64 sums of D terms, rounded to fp32 once."""
+    rng = np.random.default_rng(D + C)
+    N = 77
+    m = rng.standard_normal((C, D)).astype(np.float32) * 30
+    hv = pack_bits_lsb((rng.random((N, D)) < 0.5).astype(np.uint8))
+    ctx = ctx_for(D, C)
+    cos = torch.empty((N, C), dtype=torch.float32, device="cuda")
+    pred = torch.full((N,), -1, dtype=torch.int32, device="cuda")
+    for rows in (m, m * np.float32(0.5), m[::-1].copy()):     # other rows: no norm is left over from the call before
+        ctx.hdc_search_cosine(dev_u32(hv), torch.from_numpy(rows).cuda(), pred, cos)
+        torch.cuda.synchronize()
+        o_cos, _ = oracle.search_cosine(hv, rows, D)
+        assert np.max(np.abs(cos.cpu().numpy() - o_cos)) < 1.2e-7   # half an fp32 ulp of values below 1, and its tie
+    ctx.close()
+
+
 def test_cosine_inference_on_bipolar_rows_ranks_like_hamming():
     # class rows of +-1: cosine = 1 - 2 hamming / D exactly, so both searches agree bit for bit
     rng = np.random.default_rng(9)
