@@ -15,8 +15,8 @@
 // constant of the instruction) and the encoded bit is their sign: no per-sample count of U, no
 // start values, no compare.
 //
-// A block of eight waves takes a job of G groups of 32 samples (G = 4, or 2 where the LDS does not
-// hold four), a job after the other:
+// A block of eight waves takes a job of G groups of 32 samples (G = 4; four waves and G = 2 for models
+// of six steps of which the LDS does not hold four), a job after the other:
 //   Q  it loads and quantises the job (cache hits: the lines were touched while the previous
 //      job's rows were written), leaves the bin numbers in LDS a byte each, and turns them into
 //      bit planes over the features, [group][step] of 64 lanes x NB words, in LDS;
@@ -63,8 +63,7 @@ typedef uint32_t wd_u32x6 __attribute__((ext_vector_type(6)));
 typedef uint32_t wd_u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));   // a global load of 16 bytes at any word
 
 // Waves per block: two per group of a job.  Four groups: eight waves, a block per compute unit (two
-// waves per SIMD, 256 registers each).  Two groups: four waves, and two blocks per compute unit where
-// the LDS holds both, so that one block's tile phase fills the other's loads and stores.
+// waves per SIMD, 256 registers each).  Two groups: four waves.
 constexpr int wd_waves_of(int groups) { return 2 * groups; }
 // Tiles of 16 dimensions of one threshold a wave works on at a time: their model-side operands
 // stay in registers (4 a tile and matrix instruction of 128 feature slots).  Five tiles hold the
@@ -76,6 +75,18 @@ constexpr int wd_tiles_of(int steps) { return steps > 6 ? kWdTilesLong : kWdTile
 // Steps of 64 feature slots per tile at most, two to a matrix instruction.
 constexpr int kWdMaxSteps = 10;
 constexpr size_t kWdLdsLimit = 160 * 1024;
+// Models that are left to encode_contract.hip, whose blocks run two a compute unit up to four steps (microseconds
+// here / there, L = 64 unless said).
+// Two groups a job leave four waves alone on a unit: 65536 samples, D = 16384, 256 features 263 / 149, the same of 256
+// levels 397 / 187; tables that vary in every dimension, D = 10000, 31 features 162 / 96, 200 features 204 / 142; and
+// beyond six steps, where its blocks are one a unit.
+constexpr int kWdStepsOfTwo = 6;
+// Where the threshold needs slots that the last step does not have (128 or 256 features), a third or half of the matrix
+// instructions are for it.  From some number of varying dimensions on that is not made up for: 65536 samples, 256 features,
+// D = 9000 105 / 107, 10000 106 / 107 (262144 samples: 369 / 423), 11000 131 / 108, 13000 150 / 126; 128 features,
+// 10000 88 / 86, 14500 137 / 98; 256 levels, 256 features, 8500 175 / 172, 9300 206 / 175, 128 features, 8500 131 / 138,
+// 10000 162 / 140.
+constexpr int kWdMostExtra6 = 5400, kWdMostExtra8 = 4500;   // columns, up to 64 levels and beyond
 
 // ---- host: tables of the model (built in contract_tables.h) ------------------------------------
 template <typename T>
@@ -130,7 +141,8 @@ int prepare_wide(hdc_ctx_impl *c, const uint32_t *item, const uint32_t *level, c
     for (int g : {4, 2})
         if (!groups && wide_lds_bytes(steps, nb, g, ovs) + 64 <= kWdLdsLimit) groups = g;
     if (!groups) return HDC_OK;
-    if (steps > 6 && groups != 4) return HDC_OK;   // (measured: with two groups a job the other kernel is faster for such models)
+    if (groups != 4 && (steps != kWdStepsOfTwo || contract_shares_units(c))) return HDC_OK;
+    if (steps > std::max(c->ct_steps, 2) && ovs >= (nb == 6 ? kWdMostExtra6 : kWdMostExtra8) && contract_shares_units(c)) return HDC_OK;
     int rc = wd_upload(&c->wd_items_d, items);
     if (rc == HDC_OK) rc = wd_upload(&c->wd_bx_d, bx);
     if (rc == HDC_OK) rc = wd_upload(&c->wd_src_d, src2);
@@ -537,8 +549,7 @@ static int launch_wide(hdc_ctx_impl *c, const void *x, int64_t n, uint32_t *out,
         HDC_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     (int)lds));
     const int64_t jobs = (n + 32 * G - 1) / (32 * G);
-    const int per_cu = G == 2 && 2 * (lds + 1024) <= kWdLdsLimit ? 2 : 1;
-    const int64_t blocks = std::min<int64_t>(jobs, (int64_t)c->num_cus * per_cu);
+    const int64_t blocks = std::min<int64_t>(jobs, (int64_t)c->num_cus);
     // Start offsets between blocks (see the kernel): a sixteenth of a job's time per step, eight steps, from ten
     // jobs per block on.  A job takes about 3.2 times what its matrix instructions take alone
     // (7.6 ns each, four SIMDs).
@@ -554,14 +565,15 @@ static int launch_wide(hdc_ctx_impl *c, const void *x, int64_t n, uint32_t *out,
     return HDC_OK;
 }
 
-template <int NB, bool kU8, int G>
+template <int NB, bool kU8>
 static int launch_wide_steps(hdc_ctx_impl *c, const void *x, int64_t n, uint32_t *out, hipStream_t s) {
+    if (c->wd_groups == 2) return launch_wide<kWdStepsOfTwo, NB, kU8, 2>(c, x, n, out, s);
     switch (c->wd_steps) {
-    case 2: return launch_wide<2, NB, kU8, G>(c, x, n, out, s);
-    case 4: return launch_wide<4, NB, kU8, G>(c, x, n, out, s);
-    case 6: return launch_wide<6, NB, kU8, G>(c, x, n, out, s);
-    case 8: return launch_wide<8, NB, kU8, G>(c, x, n, out, s);
-    default: return launch_wide<10, NB, kU8, G>(c, x, n, out, s);
+    case 2: return launch_wide<2, NB, kU8, 4>(c, x, n, out, s);
+    case 4: return launch_wide<4, NB, kU8, 4>(c, x, n, out, s);
+    case 6: return launch_wide<6, NB, kU8, 4>(c, x, n, out, s);
+    case 8: return launch_wide<8, NB, kU8, 4>(c, x, n, out, s);
+    default: return launch_wide<10, NB, kU8, 4>(c, x, n, out, s);
     }
 }
 
@@ -575,13 +587,8 @@ bool try_encode_wide(hdc_ctx_impl *c, const void *feats, int64_t N, uint32_t *hv
     if (jobs < c->num_cus || jobs * 10 < rounds * c->num_cus * 7) return false;
     ProfScope prof(c, HDC_K_ENCODE_WIDE, s);
     const bool u8 = c->p.feat_dtype == HDC_U8;
-    if (c->wd_groups == 4) {
-        if (c->wd_nb == 6) *rc = u8 ? launch_wide_steps<6, true, 4>(c, feats, N, hv, s) : launch_wide_steps<6, false, 4>(c, feats, N, hv, s);
-        else *rc = u8 ? launch_wide_steps<8, true, 4>(c, feats, N, hv, s) : launch_wide_steps<8, false, 4>(c, feats, N, hv, s);
-    } else {
-        if (c->wd_nb == 6) *rc = u8 ? launch_wide_steps<6, true, 2>(c, feats, N, hv, s) : launch_wide_steps<6, false, 2>(c, feats, N, hv, s);
-        else *rc = u8 ? launch_wide_steps<8, true, 2>(c, feats, N, hv, s) : launch_wide_steps<8, false, 2>(c, feats, N, hv, s);
-    }
+    if (c->wd_nb == 6) *rc = u8 ? launch_wide_steps<6, true>(c, feats, N, hv, s) : launch_wide_steps<6, false>(c, feats, N, hv, s);
+    else *rc = u8 ? launch_wide_steps<8, true>(c, feats, N, hv, s) : launch_wide_steps<8, false>(c, feats, N, hv, s);
     return true;
 }
 

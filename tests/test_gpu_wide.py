@@ -114,3 +114,25 @@ def test_encode_wide_is_left_to_the_other_kernels_where_it_does_not_fit():
     rows = np.arange(0, 40000, 61)
     assert np.array_equal(got[rows], _oracle(wl, x[rows]))
     ctx.close()
+
+
+@pytest.mark.parametrize("cfg,D,F,L,N,wide", [
+    (2, 16384, 256, 64, 32768 - 5, 0),    # the LDS holds two groups; the other kernel's blocks share a unit
+    (3, 16384, 256, 200, 16384, 0),       # the same of bytes and eight planes
+    (2, 9900, 256, 64, 32768, 1),         # six steps where the other kernel takes four, about 4900 columns
+    (2, 12000, 256, 64, 32768 - 31, 0),   # ... 6000 columns
+    (2, 14500, 128, 64, 32768 - 1, 0),    # four steps against two
+    (4, 8000, 128, 256, 32768, 1),        # eight planes, about 3800 columns
+    (4, 10000, 128, 256, 32768 - 77, 0),  # ... 4800
+    (2, 16384, 200, 64, 32768, 1),        # the same steps either way
+])
+def test_encode_wide_or_two_blocks_a_unit(cfg, D, F, L, N, wide):
+    wl = make_workload(cfg, seed=D + F + L, D=D, F=F, L=L)
+    x = _rows(wl, N)
+    ctx = _ctx(wl)
+    ctx.hdc_profile_enable(True)
+    got = _encode(ctx, x)
+    assert (ctx.hdc_profile_read("encode_wide")[1], ctx.hdc_profile_read("encode_contract")[1]) == (wide, 1 - wide)
+    rows = np.unique(np.concatenate([np.arange(0, 70), np.arange(N - 70, N), np.arange(0, N, 61)]))
+    assert np.array_equal(got[rows], _oracle(wl, x[rows]))
+    ctx.close()
