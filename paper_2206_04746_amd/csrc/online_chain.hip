@@ -568,6 +568,16 @@ __device__ __noinline__ void walk_block(const int16_t *prod, bool halves, const 
     __syncthreads();
 }
 
+// What walk_subs keeps in LDS.
+template <int CPW, int WAVES>
+struct ChainShared {
+    double best[2][WAVES][kSub];
+    double cosy[2][kSub];
+    int pred[CPW > 1 ? 2 : 1][CPW > 1 ? WAVES : 1][kSub];
+    OnlineWeight rec[kChainBlock];
+    uint2 list[WAVES][kChainBlock];   // a wave's own: weight and place of the samples that name its class
+};
+
 // One workgroup; wave w has classes w CPW .. w CPW + CPW - 1, lane m of it sample m of the sub-block.
 //
 // Sub-block after sub-block: the samples' weights k_n,c (nonzero for the label's class and a wrong
@@ -592,89 +602,22 @@ __device__ __noinline__ void walk_block(const int16_t *prod, bool halves, const 
 // zero, which is no longer nothing then, and the order of the classes matters to a comparison.  A block that
 // starts from such rows is walked sample by sample (walk_block), and so is every block if the learning rate
 // could make a weight overflow; else a weight, at most 2 or twice the rate, stays finite.
-template <int CPW, bool BATCH>
-__global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
-    const int16_t *__restrict__ gram, const double *__restrict__ part, int slices, int nb, int batch,
-    const int32_t *__restrict__ labels, const double *__restrict__ normpart, int G, int C, int D, float lr,
-    double inv_root_d, OnlineWeight *__restrict__ out, double *grown, bool ahead, BlockBefore before_it) {
-    if (blockIdx.x) {
-        update_rows<BATCH>((int)blockIdx.x - 1, before_it.col, before_it.ld, before_it.nb, batch, before_it.recs, before_it.acc, D, C, G,
-                           before_it.normpart);
-        return;
-    }
-    constexpr int kKept = CPW == 1 ? 24 : CPW == 2 ? 12 : 4;   // list entries of a class whose products stay in registers
-    extern __shared__ __align__(16) int16_t prod[];   // the tiles of the block's sub-blocks
-    __shared__ double s_best[2][kChainMaxWaves][kSub];
-    __shared__ double s_cosy[2][kSub];
-    __shared__ int s_pred[CPW > 1 ? 2 : 1][CPW > 1 ? kChainMaxWaves : 1][kSub];
-    __shared__ OnlineWeight s_rec[kChainBlock];
-    __shared__ int s_odd[kChainMaxWaves];   // a wave's rows are not finite
-    __shared__ uint2 s_list[kChainMaxWaves][kChainBlock];   // a wave's own: weight and place of the samples that name its class
+//
+// HALVES: the tiles are what online_gram_kernel leaves for this kernel, else for online_wide_kernel.  WARM: the passes of
+// a sub-block begin from the weights in s.rec, not from zero (they end in the same place).  `start`: dot products against
+// the rows at the block's start (used up).  `norm`: squared norms there, then at its end.
+template <int CPW, bool BATCH, bool HALVES, bool WARM, int WAVES>
+__device__ __forceinline__ void walk_subs(const int16_t *prod, int nb, int batch, int C, int D, float lr, double inv_root_d,
+                                          int (&label)[kSubs], double (&start)[CPW][kSubs], double (&norm)[CPW], ChainShared<CPW, WAVES> &s,
+                                          OnlineWeight *__restrict__ out) {
+    constexpr int kKept = CPW == 1 || WAVES <= kWideWaves ? 24 : CPW == 2 ? 12 : 4;   // list entries of a class whose products stay in registers
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int subs = (nb + kSub - 1) / kSub;
     const int used = (C + CPW - 1) / CPW;   // waves that have classes
-    constexpr int kCopies = kTiles * kTile * 2 / 16 / (kChainMaxWaves * kWave);
-    uint4 copy[kCopies];
-    const int units = subs * (subs + 1) / 2 * (kTile * 2 / 16);
-#pragma unroll
-    for (int u = 0; u < kCopies; ++u)
-        copy[u] = reinterpret_cast<const uint4 *>(gram)[min(tid + u * kChainMaxWaves * kWave, units - 1)];
-    double nrm[CPW], nrm_fb[CPW];   // squared norms before the sub-block; and where the batch that runs into it began
-    double at_start[CPW];           // before the block
-    double start[CPW][kSubs];       // dot products against the rows at the block's start
-    int label[kSubs];
-    bool odd_rows = false;
-#pragma unroll
-    for (int j = 0; j < kSubs; ++j) {
-        const int y = labels[min(j * kSub + lane, nb - 1)];
-        label[j] = j * kSub + lane < nb && y >= 0 && y < C ? y : -1;
-    }
-#pragma unroll
-    for (int k = 0; k < CPW; ++k) {
-        const int c = wave * CPW + k;
-        nrm[k] = nrm_fb[k] = at_start[k] = 0.0;
-#pragma unroll
-        for (int j = 0; j < kSubs; ++j) start[k][j] = 0.0;
-        if (c < C) {
-            double s = 0.0;
-            for (int g0 = 0; g0 < G; g0 += 4 * kWave) {
-                double p[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) p[i] = normpart[(int64_t)c * G + min(g0 + i * kWave + lane, G - 1)];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) s += g0 + i * kWave + lane < G ? p[i] : 0.0;
-            }
-            double x[kSlices + 1][kSubs];
-#pragma unroll
-            for (int i = 0; i <= kSlices; ++i)
-#pragma unroll
-                for (int j = 0; j < kSubs; ++j)
-                    x[i][j] = part[((int64_t)min(i, slices - 1) * C + c) * kChainBlock + j * kSub + lane];
-#pragma unroll
-            for (int i = 0; i <= kSlices; ++i)
-#pragma unroll
-                for (int j = 0; j < kSubs; ++j) start[k][j] += i < slices ? x[i][j] : 0.0;
-            nrm[k] = nrm_fb[k] = lane_f64(lane_prefix(s), kWave - 1) + (ahead ? grown[c] : 0.0);
-            at_start[k] = nrm[k];
-            odd_rows |= !(nrm[k] < __builtin_inf());
-        }
-    }
-    if (lane == 0) s_odd[wave] = odd_rows;
-#pragma unroll
-    for (int u = 0; u < kCopies; ++u)
-        if (tid + u * kChainMaxWaves * kWave < units)
-            reinterpret_cast<uint4 *>(prod)[tid + u * kChainMaxWaves * kWave] = copy[u];
-    __syncthreads();
-    if (wave >= used) return;   // (an ended wave takes no part in later barriers)
-    if (__builtin_expect(__ballot(lane < used && s_odd[lane]) != 0 || !(fabsf(lr) < kTameRate), 0)) {   // the same in every wave
-        walk_block<CPW, BATCH>(prod, true, part, slices, nb, batch, labels, normpart, ahead ? grown : nullptr, grown, G, C, D, lr,
-                               inv_root_d, s_rec, s_cosy[0]);
-        for (int n = tid; n < nb; n += used * kWave) out[n] = s_rec[n];
-        return;
-    }
     const int odd = D & 1;
     const double dd = (double)D;
+    auto whole = [&](int16_t g) { return HALVES ? 2 * (int)g + odd : (int)g; };
 
     // adds w_i <s_i, s_lane> over the listed samples i < lane of the diagonal tile to `all`, and to `some` where i < lim
     auto walk = [&](uint64_t list, double w, const int16_t *tile, int lim, double &all, double &some) {
@@ -690,7 +633,7 @@ __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
                 list &= list - 1;
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) g[u] = 2 * (int)tile[at[u] * kSub + lane] + odd;
+            for (int u = 0; u < U; ++u) g[u] = whole(tile[at[u] * kSub + lane]);
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 if (BATCH) some = fma(v[u], (double)(at[u] < lim ? g[u] : 0), some);
@@ -699,6 +642,9 @@ __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
         }
     };
 
+    double nrm[CPW], nrm_fb[CPW];
+#pragma unroll
+    for (int k = 0; k < CPW; ++k) nrm[k] = nrm_fb[k] = norm[k];
     int buf = 0;
     for (int j = 0; j < subs; ++j) {
         const int m0 = j * kSub, m = m0 + lane;
@@ -724,11 +670,11 @@ __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
                 const int c = wave * CPW + k;
                 int entries = 0;
                 for (int a = 0; a < j; ++a) {
-                    const OnlineWeight r = s_rec[a * kSub + lane];
+                    const OnlineWeight r = s.rec[a * kSub + lane];
                     const float w = r.y == c ? r.w_y : r.pred == c ? -r.w_p : 0.0f;
                     const uint64_t list = __ballot(w != 0.0f);
                     const int at = entries + __popcll(list & ((1ull << lane) - 1));
-                    if (w != 0.0f) s_list[wave][at] = make_uint2(__float_as_uint(w), (uint32_t)(a * kSub + lane));
+                    if (w != 0.0f) s.list[wave][at] = make_uint2(__float_as_uint(w), (uint32_t)(a * kSub + lane));
                     entries += __popcll(list);
                 }
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -738,9 +684,9 @@ __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
                     uint2 x[8];
                     int g[8];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) x[u] = s_list[wave][min(e + u, entries - 1)];
+                    for (int u = 0; u < 8; ++u) x[u] = s.list[wave][min(e + u, entries - 1)];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) g[u] = 2 * (int)tiles[x[u].y * kSub] + odd;
+                    for (int u = 0; u < 8; ++u) g[u] = whole(tiles[x[u].y * kSub]);
 #pragma unroll
                     for (int u = 0; u < 8; ++u) {
                         const double v = e + u < entries ? (double)__uint_as_float(x[u].x) : 0.0;
@@ -756,6 +702,12 @@ __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
         const int16_t *diag = prod + (j * (j + 1) / 2 + j) * kTile;
         float wy = 0.0f, wp = 0.0f;
         int pred = -1;
+        if constexpr (WARM) {
+            const OnlineWeight r = s.rec[m];
+            wy = r.w_y;
+            wp = r.w_p;
+            pred = r.pred;
+        }
         double before[CPW] = {}, total[CPW] = {};   // what the sub-block adds to the squared norms, before each sample and in all
         uint64_t known[CPW] = {};      // the list whose first products are kept: entry u is sample at[][u]
         int at[CPW][kKept] = {};
@@ -782,7 +734,7 @@ __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
                         }
 #pragma unroll
                         for (int u = q; u < q + 4; ++u) {
-                            const int g = 2 * (int)diag[at[k][u] * kSub + lane] + odd;
+                            const int g = whole(diag[at[k][u] * kSub + lane]);
                             kept[k][u] = (double)(at[k][u] < lane ? g : 0);
                         }
                     }
@@ -822,17 +774,17 @@ __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
                     double nn = nrm[k] + before[k];
                     if (BATCH) nn = fb >= m0 ? nrm[k] + __shfl(before[k], fb - m0, kWave) : nrm_fb[k];
                     const double cs = nn > 0.0 ? dot * refined_rsq(nn) * inv_root_d : 0.0;
-                    if (y == c) s_cosy[buf][lane] = cs;
+                    if (y == c) s.cosy[buf][lane] = cs;
                     if (cs > best) {
                         best = cs;
                         arg = c;
                     }
                 }
             }
-            s_best[buf][wave][lane] = best;
-            if constexpr (CPW > 1) s_pred[buf][wave][lane] = arg;
+            s.best[buf][wave][lane] = best;
+            if constexpr (CPW > 1) s.pred[buf][wave][lane] = arg;
             __syncthreads();
-            const double cos_y = s_cosy[buf][lane];
+            const double cos_y = s.cosy[buf][lane];
             best = -4.0;
             arg = 0;
             for (int w0 = 0; w0 < used; w0 += 8) {   // eight waves' bests at a time (the last one repeats: it cannot win twice)
@@ -841,8 +793,8 @@ __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
                     p[u] = min(w0 + u, used - 1);
-                    v[u] = s_best[buf][p[u]][lane];
-                    if constexpr (CPW > 1) p[u] = s_pred[buf][p[u]][lane];
+                    v[u] = s.best[buf][p[u]][lane];
+                    if constexpr (CPW > 1) p[u] = s.pred[buf][p[u]][lane];
                 }
                 const double top = fmax(fmax(fmax(v[0], v[1]), fmax(v[2], v[3])), fmax(fmax(v[4], v[5]), fmax(v[6], v[7])));
                 int first = p[7];
@@ -881,11 +833,92 @@ __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
         }
         if (wave == 0) {
             const OnlineWeight r = {y, pred, wy, wp};
-            s_rec[m] = r;
+            s.rec[m] = r;
             if (m < nb) out[m] = r;
         }
         __syncthreads();
     }
+#pragma unroll
+    for (int k = 0; k < CPW; ++k) norm[k] = nrm[k];
+}
+
+template <int CPW, bool BATCH>
+__global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
+    const int16_t *__restrict__ gram, const double *__restrict__ part, int slices, int nb, int batch,
+    const int32_t *__restrict__ labels, const double *__restrict__ normpart, int G, int C, int D, float lr,
+    double inv_root_d, OnlineWeight *__restrict__ out, double *grown, bool ahead, BlockBefore before_it) {
+    if (blockIdx.x) {
+        update_rows<BATCH>((int)blockIdx.x - 1, before_it.col, before_it.ld, before_it.nb, batch, before_it.recs, before_it.acc, D, C, G,
+                           before_it.normpart);
+        return;
+    }
+    extern __shared__ __align__(16) int16_t prod[];   // the tiles of the block's sub-blocks
+    __shared__ ChainShared<CPW, kChainMaxWaves> s;
+    __shared__ int s_odd[kChainMaxWaves];   // a wave's rows are not finite
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int subs = (nb + kSub - 1) / kSub;
+    const int used = (C + CPW - 1) / CPW;   // waves that have classes
+    constexpr int kCopies = kTiles * kTile * 2 / 16 / (kChainMaxWaves * kWave);
+    uint4 copy[kCopies];
+    const int units = subs * (subs + 1) / 2 * (kTile * 2 / 16);
+#pragma unroll
+    for (int u = 0; u < kCopies; ++u)
+        copy[u] = reinterpret_cast<const uint4 *>(gram)[min(tid + u * kChainMaxWaves * kWave, units - 1)];
+    double nrm[CPW];   // squared norms before the sub-block; and where the batch that runs into it began
+    double at_start[CPW];           // before the block
+    double start[CPW][kSubs];       // dot products against the rows at the block's start
+    int label[kSubs];
+    bool odd_rows = false;
+#pragma unroll
+    for (int j = 0; j < kSubs; ++j) {
+        const int y = labels[min(j * kSub + lane, nb - 1)];
+        label[j] = j * kSub + lane < nb && y >= 0 && y < C ? y : -1;
+    }
+#pragma unroll
+    for (int k = 0; k < CPW; ++k) {
+        const int c = wave * CPW + k;
+        nrm[k] = at_start[k] = 0.0;
+#pragma unroll
+        for (int j = 0; j < kSubs; ++j) start[k][j] = 0.0;
+        if (c < C) {
+            double sum = 0.0;
+            for (int g0 = 0; g0 < G; g0 += 4 * kWave) {
+                double p[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) p[i] = normpart[(int64_t)c * G + min(g0 + i * kWave + lane, G - 1)];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) sum += g0 + i * kWave + lane < G ? p[i] : 0.0;
+            }
+            double x[kSlices + 1][kSubs];
+#pragma unroll
+            for (int i = 0; i <= kSlices; ++i)
+#pragma unroll
+                for (int j = 0; j < kSubs; ++j)
+                    x[i][j] = part[((int64_t)min(i, slices - 1) * C + c) * kChainBlock + j * kSub + lane];
+#pragma unroll
+            for (int i = 0; i <= kSlices; ++i)
+#pragma unroll
+                for (int j = 0; j < kSubs; ++j) start[k][j] += i < slices ? x[i][j] : 0.0;
+            nrm[k] = lane_f64(lane_prefix(sum), kWave - 1) + (ahead ? grown[c] : 0.0);
+            at_start[k] = nrm[k];
+            odd_rows |= !(nrm[k] < __builtin_inf());
+        }
+    }
+    if (lane == 0) s_odd[wave] = odd_rows;
+#pragma unroll
+    for (int u = 0; u < kCopies; ++u)
+        if (tid + u * kChainMaxWaves * kWave < units)
+            reinterpret_cast<uint4 *>(prod)[tid + u * kChainMaxWaves * kWave] = copy[u];
+    __syncthreads();
+    if (wave >= used) return;   // (an ended wave takes no part in later barriers)
+    if (__builtin_expect(__ballot(lane < used && s_odd[lane]) != 0 || !(fabsf(lr) < kTameRate), 0)) {   // the same in every wave
+        walk_block<CPW, BATCH>(prod, true, part, slices, nb, batch, labels, normpart, ahead ? grown : nullptr, grown, G, C, D, lr,
+                               inv_root_d, s.rec, s.cosy[0]);
+        for (int n = tid; n < nb; n += used * kWave) out[n] = s.rec[n];
+        return;
+    }
+    walk_subs<CPW, BATCH, true, false, kChainMaxWaves>(prod, nb, batch, C, D, lr, inv_root_d, label, start, nrm, s, out);
 #pragma unroll
     for (int k = 0; k < CPW; ++k)
         if (lane == 0 && wave * CPW + k < C) grown[wave * CPW + k] = nrm[k] - at_start[k];
@@ -937,6 +970,17 @@ __device__ __forceinline__ void each(F &&f) {
     }
 }
 
+// Where about half the predictions are wrong a block needs 30 to 70 passes, nearly as many as its sub-blocks together,
+// and each costs up to twice as much (the lists of wrong ones).  From more wrong ones than this of 64 in half its
+// sub-blocks, or after so many passes, a block is finished by walk_subs, from the weights as they are.  Microseconds for
+// 2000 samples, whole passes only / this / online_chain_kernel:
+//   labels at random, samples 10 % from their prototype, D = 10000: 2 classes 2643 1774 1864, 6 1668 1035 1083,
+//   8 1295 829 857, 10 1457 1014 895, 12 1214 942 859, 16 1164 843 855; half of them at random, 30 %: 2 404 410 641, 6 513 485 491,
+//   8 545 489 486, 16 746 641 670; right labels, 45 %, D = 1000: 6 411 375 441, 16 826 637 642
+// Nine to twelve classes are two a wave on five or six waves here, where the other kernel has a wave for each: with 28
+// instead of 36, half the labels at random, 10 classes 645 for 596 and 12 646 for 610.
+constexpr int kWideMostWrong = 28, kWideMostWrongPaired = 36, kWidePasses = 20;
+
 template <int CPW, int GR>
 __global__ __launch_bounds__(kWideWaves *kWave) void online_wide_kernel(
     const int16_t *__restrict__ gram, const int16_t *__restrict__ image, const WideOrder *__restrict__ order,
@@ -952,7 +996,7 @@ __global__ __launch_bounds__(kWideWaves *kWave) void online_wide_kernel(
     __shared__ uint2 s_wrong[kChainBlock];   // class wrongly predicted, or -1, and its weight
     __shared__ double s_grown[kWideClasses];   // what the block adds to a class's squared norm
     __shared__ int s_odd[kWideWaves];
-    __shared__ int s_any[kSubs][2];          // a sub-block's samples: a weight changed; a prediction is wrong
+    __shared__ int2 s_any[kSubs];            // of a sub-block's samples: whether a weight changed; how many predictions are wrong
     constexpr int kRows = wide_rows(GR);
     const int tid = threadIdx.x, lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1042,6 +1086,7 @@ __global__ __launch_bounds__(kWideWaves *kWave) void online_wide_kernel(
     if (tid < kChainBlock + 2) s_wy[tid] = 0.0;
     if (tid < kChainBlock) s_wrong[tid] = make_uint2(~0u, 0u);   // (past the last sub-block nobody decides)
     if (tid < kWideClasses) s_grown[tid] = 0.0;
+    if (tid < kSubs) s_any[tid] = make_int2(0, 0);   // (past the last sub-block nobody writes)
     if (tid < kSub) s_place[places - 2][tid] = 0.0;
     __syncthreads();
     const int kind = s_odd[lane & (kWideWaves - 1)];
@@ -1050,7 +1095,8 @@ __global__ __launch_bounds__(kWideWaves *kWave) void online_wide_kernel(
 
     float wy = 0.0f, wp = 0.0f;
     int pred = -1;
-    bool wrong_ones = false;
+    bool wrong_ones = false, hard = false;
+    const int most_wrong = C > kWideWaves && C <= 12 ? kWideMostWrongPaired : kWideMostWrong;
     // Predictions and weights from s_cos, after a barrier; false: no weight has changed.  (With guess, labels count as
     // predictions: rows of zeros would say class 0 of every sample.  The passes end in the same place from any start.)
     auto decide = [&](int l, bool guess) __attribute__((always_inline)) {
@@ -1086,14 +1132,13 @@ __global__ __launch_bounds__(kWideWaves *kWave) void online_wide_kernel(
             pred = pred1;
             s_wy[wave * kSub + l] = (double)wy;
             s_wrong[wave * kSub + l] = make_uint2((uint32_t)pred, __float_as_uint(wp));
-            if (l == 0) {
-                s_any[wave][0] = changed != 0;
-                s_any[wave][1] = wrong != 0;
-            }
+            if (l == 0) s_any[wave] = make_int2(changed != 0, __popcll(wrong));
         }
         __syncthreads();
-        const uint64_t any = __ballot(l < 2 * subs && (&s_any[0][0])[l & (2 * kSubs - 1)]);   // the same in every wave
+        const int v = reinterpret_cast<const int *>(s_any)[l & (2 * kSubs - 1)];
+        const uint64_t any = __ballot(v != 0);   // the same in every wave
         wrong_ones = (any & 0xAA) != 0;
+        hard = 2 * __popcll(__ballot(v > most_wrong) & 0xAA) >= subs;
         return (any & 0x55) != 0;
     };
     // the first pass: no sample of the block counts yet
@@ -1131,7 +1176,7 @@ __global__ __launch_bounds__(kWideWaves *kWave) void online_wide_kernel(
     int column[kSubs];   // first tile of a target sub-block; past the last one, of that
 #pragma unroll
     for (int i = 0; i < kSubs; ++i) column[i] = min(i, subs - 1) * (min(i, subs - 1) + 1) / 2 * kTile;
-    for (int pass = 1; going && pass <= nb; ++pass) {
+    for (int pass = 1; going && !hard && pass <= kWidePasses; ++pass) {
         int l = lane;
         asm volatile("" : "+v"(l));   // (addresses are formed anew in a pass: kept over all, they would not fit the registers)
         {
@@ -1227,8 +1272,35 @@ __global__ __launch_bounds__(kWideWaves *kWave) void online_wide_kernel(
         __syncthreads();
         going = decide(l, false);
     }
-    if (wave < subs && wave * kSub + lane < nb) out[wave * kSub + lane] = OnlineWeight{y, pred, wy, wp};
-    if (tid < C) grown[tid] = s_grown[tid];
+    if (__builtin_expect(!going, 1)) {
+        if (wave < subs && wave * kSub + lane < nb) out[wave * kSub + lane] = OnlineWeight{y, pred, wy, wp};
+        if (tid < C) grown[tid] = s_grown[tid];
+        return;
+    }
+    // sub-block after sub-block, from the weights as they are
+    double from[CPW][kSubs], norm[CPW];
+#pragma unroll
+    for (int k = 0; k < CPW; ++k)
+        if (lane == 0 && wave + k * kWideWaves < C) s_grown[wave + k * kWideWaves] = nrm[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < CPW; ++k) {
+        const int c = min(wave * CPW + k, C - 1);
+        norm[k] = s_grown[c];
+#pragma unroll
+        for (int i = 0; i < kSubs; ++i) from[k][i] = start[kSubs * c + i][lane];
+    }
+    __syncthreads();
+    ChainShared<CPW, kWideWaves> &s = reinterpret_cast<ChainShared<CPW, kWideWaves> &>(s_place[0][0]);
+    if (wave < subs) s.rec[wave * kSub + lane] = OnlineWeight{y, pred, wy, wp};
+    __syncthreads();
+    if (wave * CPW >= C) return;
+#pragma unroll
+    for (int i = 0; i < kSubs; ++i) label[i] = i < subs ? s.rec[i * kSub + lane].y : -1;
+    walk_subs<CPW, false, false, true, kWideWaves>(prod, nb, 1, C, D, lr, inv_root_d, label, from, norm, s, out);
+#pragma unroll
+    for (int k = 0; k < CPW; ++k)
+        if (lane == 0 && wave * CPW + k < C) grown[wave * CPW + k] = norm[k] - s_grown[wave * CPW + k];
 }
 
 // ---- host side -------------------------------------------------------------------------------------
@@ -1362,14 +1434,17 @@ static int launch_wide(hdc_ctx_impl *c, const ChainCall &a, hipStream_t s) {
     auto kern = online_wide_kernel<CPW, GR>;
     const int slot = CPW == 1 ? 6 : 7, C = c->p.C, per_place = kSub * (int)sizeof(double);
     const int most = CPW * kWideWaves, cosines = kSubs * (CPW == 1 ? 2 : 1);   // places beside the runs' for a class: cosines, starts
+    auto behind = [&](int classes) {   // the products: the places, or what a walk by sub-blocks keeps there
+        return std::max((wide_places(classes) + cosines * classes) * per_place, (int)sizeof(ChainShared<CPW, kWideWaves>));
+    };
     if (!c->oc_attr_set[slot]) {
         HDC_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    kTiles * kTile * (int)sizeof(int16_t) + (wide_places(most) + cosines * most) * per_place));
+                                    kTiles * kTile * (int)sizeof(int16_t) + behind(most)));
         c->oc_attr_set[slot] = true;
     }
     const int subs = (a.nb + kSub - 1) / kSub;
     hipLaunchKernelGGL(kern, dim3(a.ahead ? 1u + (unsigned)a.G : 1u), dim3(kWideWaves * kWave),
-                       (size_t)(subs * (subs + 1) / 2) * kTile * sizeof(int16_t) + (size_t)(wide_places(C) + cosines * C) * per_place, s,
+                       (size_t)(subs * (subs + 1) / 2) * kTile * sizeof(int16_t) + behind(C), s,
                        c->oc_gram_d + a.b * kTiles * kTile, c->oc_image_d + a.b * kWideImage,
                        static_cast<const WideOrder *>(c->oc_order_d) + a.b, c->oc_part_d, a.slices + (a.ahead ? 1 : 0), a.nb, a.labels,
                        a.norm, a.G, C, c->p.D, a.lr, 1.0 / sqrt((double)c->p.D), a.recs, c->oc_norm_d + (int64_t)C * a.G, a.ahead,

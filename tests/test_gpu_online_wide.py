@@ -42,6 +42,22 @@ def test_blocks_as_a_whole_match_the_oracle(D, C, N, kind):
     ctx.close()
 
 
+# Most predictions wrong, or most of them for long: blocks are finished sub-block after sub-block, and the next block begins
+# from the squared norms that leaves.  One and two classes a wave, some waves without one, a last block of one to four
+# sub-blocks
+@pytest.mark.parametrize("flip,wrong", [(0.1, 1.0), (0.1, 0.7), (0.45, 0.0)])
+@pytest.mark.parametrize("D,C,N", [(1000, 2, 1025), (1001, 3, 600), (999, 8, 700), (2049, 9, 1100), (640, 12, 1500), (3000, 16, 2000)])
+def test_blocks_of_wrong_predictions_match_the_oracle(D, C, N, flip, wrong):
+    rng = np.random.default_rng(D + 10 * C + N)
+    hv, y = clustered(rng, N, D, C, flip)
+    y = np.where(rng.random(N) < wrong, rng.integers(0, C, N), y).astype(np.int32)
+    ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
+    acc = torch.zeros((C, D), dtype=torch.float32, device="cuda")
+    ctx.hdc_train_online(dev_u32(hv), torch.from_numpy(y).cuda(), acc, epochs=2, lr=1.0)
+    assert off(acc, oracle.train_online(hv, y, D, C, epochs=2, lr=1.0)) < TOL
+    ctx.close()
+
+
 def test_more_samples_than_are_held_at_a_time():
     D, C, N = 96, 3, 8192 + 300                    # 32 blocks are held at a time
     hv, y = clustered(np.random.default_rng(1), N, D, C)
