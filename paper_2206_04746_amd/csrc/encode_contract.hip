@@ -160,8 +160,11 @@ typedef uint32_t ct_u32x4 __attribute__((ext_vector_type(4)));
 // Dynamic LDS: the job's bin numbers, a byte each, [sample][KS * 64 + 16] (the 16 spread the rows
 // over the banks), then per (tile, column) the bits of the job's 32 samples [T * 32] (two 16-bit
 // halves, one per lane half).
+// Blocks of eight waves are held to 128 registers a lane, four waves a SIMD, so that two fit a compute unit; at 130, what
+// chains of four steps and eight planes take by themselves, every second block waited (at 128 two registers go to memory:
+// 20000 samples, 200 features, 128 levels in a circle, D = 16000 152 -> 103 us, D = 4000 57 -> 38).
 template <int KS, int NB, bool kU8, int NW, bool kChain>
-__global__ __launch_bounds__(NW *kWave) void encode_contract_kernel(
+__global__ __launch_bounds__(NW *kWave, NW == kCtWaves ? 4 : 3) void encode_contract_kernel(
     const void *__restrict__ feats, int64_t N, int F, int L, const float *__restrict__ lo,
     const float *__restrict__ scale, int W, int split, const CtRanges range_tile,
     const uint32_t *__restrict__ bt, const uint32_t *__restrict__ src_of, const float *__restrict__ kc,
@@ -452,7 +455,7 @@ static size_t contract_lds(const hdc_ctx_impl *c, int v, bool planes) {
     return (size_t)kCtSamples * (c->ct_steps * 64 + 16) + (planes ? (size_t)c->ct_steps * 2 * kWave * 16 : 0) + (size_t)c->ct_range_max[v] * 32 * 4;
 }
 
-// Blocks of eight waves have at most 128 registers a lane: two share a compute unit where its LDS holds both.  A block
+// Two blocks of eight waves share a compute unit where its LDS holds both (their registers do).  A block
 // is a chain of phases that leave the unit idle in places (20000 samples, D = 10000, 64 levels: 200 features, one
 // block a unit 56.2 us, two 42.4; 31 features 46.6, two and one step instead of two 31.9).
 constexpr int kCtMostSharedSteps = 4;

@@ -202,6 +202,8 @@ def test_encode_tables_whose_every_dimension_flips_once_take_the_contraction():
     (2, 1024, 63, 100, 16417, False), (2, 1000, 31, 2, 17003, False), (2, 2500, 256, 32, 17003, False), (2, 4000, 60, 8, 17003, True),
     # columns of 32 samples that the LDS holds once a compute unit, not twice; rows split over blocks
     (2, 32768, 40, 16, 4001, False), (2, 20000, 64, 64, 9001, False), (2, 16384, 129, 256, 8257, False),
+    # chains in four steps of eight planes, floats and bytes, one job a block and more
+    (2, 4000, 255, 66, 8193, True), (3, 4000, 225, 66, 17003, True), (2, 8000, 200, 66, 9001, True), (2, 16000, 129, 66, 16417, True),
 ])
 def test_encode_contraction_of_few_features_with_two_blocks_a_compute_unit(cfg, D, F, L, N, circle):
     wl = make_workload(cfg, seed=D + F + L, D=D, F=F, L=L, n_train=N)
