@@ -174,7 +174,7 @@ int hdc_binarize_classical(hdc_ctx *ctx, const int32_t *acc_dev, const int64_t *
  * method in 64 bits for it, but a prediction between cosines that agree this closely (rows that
  * repeated samples have made proportional, for instance) may be another one than a walk by samples
  * takes.  The first call, whatever its size, allocates
- * context-owned scratch (10 MB + 8192 rows, at most 64 MB of them) unless hdc_reserve has done so;
+ * context-owned scratch (20 MB + 16384 rows, at most 64 MB of them, and up to 2.5 MB at the largest C and D) unless hdc_reserve has done so;
  * later calls only enqueue on `stream`.  Where the scratch cannot be had - memory is short, or the
  * first call is being captured into a graph - and D <= 32768, the call goes sample by sample
  * without any, which is slower; beyond D = 32768 that is HDC_ENOMEM or HDC_EHIP.

@@ -59,7 +59,7 @@ def test_blocks_of_wrong_predictions_match_the_oracle(D, C, N, flip, wrong):
 
 
 def test_more_samples_than_are_held_at_a_time():
-    D, C, N = 96, 3, 8192 + 300                    # 32 blocks are held at a time
+    D, C, N = 96, 3, 16384 + 300                   # 64 blocks are held at a time
     hv, y = clustered(np.random.default_rng(1), N, D, C)
     ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
     acc = torch.zeros((C, D), dtype=torch.float32, device="cuda")
