@@ -316,7 +316,8 @@ typedef enum {
     HDC_K_ONLINE_BWD = 6, /* batch sums + accumulator update of hdc_train_online_batched, by batch or block */
     HDC_K_ENCODE_CONTRACT = 7, /* the contraction form of hdc_encode (quantises, bundles and spreads in one kernel) */
     HDC_K_ENCODE_WIDE = 8,     /* the contraction form of hdc_encode for long streams (jobs of 64 or 128 samples) */
-    HDC_K_COUNT = 9
+    HDC_K_ONLINE_WIDE = 9,     /* the calls among those of HDC_K_ONLINE whose blocks are walked as a whole, one entry a call */
+    HDC_K_COUNT = 10
 } hdc_kernel_id;
 #define HDC_PROFILE_SLOTS 512
 int hdc_profile_enable(hdc_ctx *ctx, int enable);

@@ -1514,11 +1514,12 @@ static int walk_blocks(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *label
                        int batch, float *acc, hipStream_t s) {
     const int C = c->p.C, D = c->p.D, W = c->W;
     const int G = (D + kWave - 1) / kWave;
+    const bool wide = !BATCH && wide_takes(c, N, epochs, lr);
     ProfScope walk(c, HDC_K_ONLINE, s, !BATCH);   // a walk by samples as a whole; of batches each block's three steps
+    ProfScope which(c, HDC_K_ONLINE_WIDE, s, wide);
     int rc = launch_norm(c, acc, G, s);
     if (rc != HDC_OK) return rc;
     const int block = kChainBlock / batch * batch;   // whole batches
-    const bool wide = !BATCH && wide_takes(c, N, epochs, lr);
     const int64_t ld = held_samples(G), held = std::min(ld / block, kHeldBlocks) * block;
     int norm_at = 0;   // which of the two arrays of squared norms is that of the rows
     for (int32_t e = 0; e < epochs; ++e)

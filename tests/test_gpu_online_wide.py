@@ -1,6 +1,6 @@
 """Per-sample online training with the blocks walked as a whole and a block's row updates beside the next block's
-chain (csrc/online_chain.hip, up to 16 classes and D = 32767, from 129 samples on) against the CPU oracle: where the
-order of the products changes, at the edges of sub-blocks and blocks, and where calls leave it."""
+chain (csrc/online_chain.hip, up to 16 classes and D = 32767, from 129 samples on and 128 (C - 2) + 1 in all epochs) against
+the CPU oracle: where the order of the products changes, at the edges of sub-blocks and blocks, and where calls leave it."""
 import numpy as np
 import pytest
 
@@ -24,6 +24,25 @@ def labels(kind, rng, y, C):
             "blocks": (n // 64 % C).astype(np.int32), "random": rng.integers(0, C, len(y)).astype(np.int32)}[kind]
 
 
+def train(ctx, hv, y, acc, epochs, lr):
+    """One call; says whether it went in blocks that are walked as a whole."""
+    ctx.hdc_profile_enable(True)
+    ctx.hdc_train_online(dev_u32(hv), torch.from_numpy(y).cuda(), acc, epochs=epochs, lr=lr)
+    assert ctx.hdc_profile_read("online")[1] == 1
+    return ctx.hdc_profile_read("online_wide")[1]
+
+
+@pytest.mark.parametrize("C,D,N,epochs,lr,wide", [
+    (2, 64, 128, 9, 1.0, 0), (2, 64, 129, 1, 1.0, 1), (1, 64, 129, 1, 1.0, 1), (16, 64, 896, 2, 1.0, 0), (16, 64, 1793, 1, 1.0, 1),
+    (8, 64, 256, 3, 1.0, 0), (8, 64, 257, 3, 1.0, 1), (17, 64, 4000, 1, 1.0, 0), (3, 32767, 129, 1, 1.0, 1), (3, 32768, 129, 1, 1.0, 0),
+    (3, 64, 300, 1, 0.9e30, 1), (3, 64, 300, 1, 1e30, 0), (3, 64, 300, 1, float("nan"), 0)])
+def test_which_calls_go_in_blocks_walked_as_a_whole(C, D, N, epochs, lr, wide):
+    ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
+    hv, y = np.zeros((N, ctx.W), np.uint32), np.zeros(N, np.int32)
+    assert train(ctx, hv, y, torch.zeros((C, D), dtype=torch.float32, device="cuda"), epochs, lr) == wide
+    ctx.close()
+
+
 # one more than two sub-blocks, edges of three and four, of a block and the next; classes at one and two a wave (four
 # and two rows a group) and past them; smallest D, odd D, the largest and one more
 @pytest.mark.parametrize("kind", ["drawn", "one", "most", "few", "blocks", "random"])
@@ -34,11 +53,11 @@ def test_blocks_as_a_whole_match_the_oracle(D, C, N, kind):
     hv, y = clustered(rng, N, D, C)
     y = labels(kind, rng, y, C)
     ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
-    hvd, yd = dev_u32(hv), torch.from_numpy(y).cuda()
     acc = torch.zeros((C, D), dtype=torch.float32, device="cuda")
+    epochs = max(2, 128 * (C - 2) // N + 1)        # with fewer samples in all they go by sub-blocks
     for calls in (1, 2):                           # the second call goes on from the rows of the first
-        ctx.hdc_train_online(hvd, yd, acc, epochs=2, lr=0.5)
-        assert off(acc, oracle.train_online(hv, y, D, C, epochs=2 * calls, lr=0.5)) < TOL
+        assert train(ctx, hv, y, acc, epochs, 0.5) == (C <= 16 and D <= 32767)
+        assert off(acc, oracle.train_online(hv, y, D, C, epochs=epochs * calls, lr=0.5)) < TOL
     ctx.close()
 
 
@@ -53,8 +72,28 @@ def test_blocks_of_wrong_predictions_match_the_oracle(D, C, N, flip, wrong):
     y = np.where(rng.random(N) < wrong, rng.integers(0, C, N), y).astype(np.int32)
     ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
     acc = torch.zeros((C, D), dtype=torch.float32, device="cuda")
-    ctx.hdc_train_online(dev_u32(hv), torch.from_numpy(y).cuda(), acc, epochs=2, lr=1.0)
+    assert train(ctx, hv, y, acc, 2, 1.0)
     assert off(acc, oracle.train_online(hv, y, D, C, epochs=2, lr=1.0)) < TOL
+    ctx.close()
+
+
+# Rows that are no numbers or infinite from the start, at one and two classes a wave: every block of these is walked
+# sample by sample, the later ones beside the row updates of the block before
+@pytest.mark.parametrize("row,value", [(0, float("nan")), (-1, float("nan")), (0, float("inf")), (1, float("-inf")), (slice(None), float("nan"))])
+@pytest.mark.parametrize("C,N", [(2, 700), (8, 800), (9, 1100), (16, 1900)])
+def test_rows_that_are_not_finite(C, N, row, value):
+    D = 200
+    hv, y = clustered(np.random.default_rng(C), N, D, C)
+    start = np.random.default_rng(6).normal(size=(C, D)).astype(np.float32)
+    start[row, 7] = value
+    ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
+    acc = torch.from_numpy(start.copy()).cuda()
+    assert train(ctx, hv, y, acc, 1, 1.0)
+    got, want = acc.cpu().numpy(), oracle.train_online(hv, y, D, C, epochs=1, lr=1.0, acc=start.copy())
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[np.isinf(want)], want[np.isinf(want)])
+    ok = np.isfinite(want)
+    assert np.array_equal(np.isfinite(got), ok)
+    assert np.max(np.abs(got[ok] - want[ok]), initial=0.0) <= TOL * max(1.0, float(np.max(np.abs(want[ok]), initial=0.0)))
     ctx.close()
 
 
@@ -63,6 +102,6 @@ def test_more_samples_than_are_held_at_a_time():
     hv, y = clustered(np.random.default_rng(1), N, D, C)
     ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
     acc = torch.zeros((C, D), dtype=torch.float32, device="cuda")
-    ctx.hdc_train_online(dev_u32(hv), torch.from_numpy(y).cuda(), acc, epochs=2, lr=1.0)
+    assert train(ctx, hv, y, acc, 2, 1.0)
     assert off(acc, oracle.train_online(hv, y, D, C, epochs=2, lr=1.0)) < 1e-5   # n <= 6000: sqrt(n) 2^-23
     ctx.close()
