@@ -169,8 +169,8 @@ int hdc_binarize_classical(hdc_ctx *ctx, const int32_t *acc_dev, const int64_t *
  * products with the rows at the block's start, then the updates are applied to the rows one by one.
  * The cosines then leave out the fp32 rounding of the u <= 512 updates of a row since the start of
  * the block or the one before: at most u * 2^-24, as a rule sqrt(u) * 2^-24 (largest seen 3e-8 at D = 10000, 6 classes;
- * 3e-7 over D = 33 to 4096 from zero rows; 3e-6 from rows of size 1e6; more while samples drive a
- * row through zero).  They are no further from the
+ * 3e-7 over D = 33 to 4096 from zero rows; 4e-6 from rows of size 1e6; up to 6e-4 for a few while samples
+ * drive a row of many times their size through zero).  They are no further from the
  * method in 64 bits for it, but a prediction between cosines that agree this closely (rows that
  * repeated samples have made proportional, for instance) may be another one than a walk by samples
  * takes.  The first call, whatever its size, allocates

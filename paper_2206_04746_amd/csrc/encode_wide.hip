@@ -80,12 +80,17 @@ constexpr size_t kWdLdsLimit = 160 * 1024;
 // Two groups a job leave four waves alone on a unit: 65536 samples, D = 16384, 256 features 263 / 149, the same of 256
 // levels 397 / 187; tables that vary in every dimension, D = 10000, 31 features 162 / 96, 200 features 204 / 142; and
 // beyond six steps, where its blocks are one a unit.
+// Six steps in two groups are walked here, though the other kernel is the faster one for most such models, by 1.12 to 1.5
+// times over 315 calls measured (65536 samples, D = 16384, 342 features: 32 levels 250 / 195, 64 273 / 218, 256 426 / 284;
+// 200000 samples 780 / 599, 847 / 676, 1340 / 876); this one is where it has to split the words for its number of tiles:
+// 256 levels, every dimension varying, D = 13000 488 / 544, 16384 506 / 616.
 constexpr int kWdStepsOfTwo = 6;
 // Where the threshold needs slots that the last step does not have (128 or 256 features), a third or half of the matrix
 // instructions are for it.  From some number of varying dimensions on that is not made up for: 65536 samples, 256 features,
 // D = 9000 105 / 107, 10000 106 / 107 (262144 samples: 369 / 423), 11000 131 / 108, 13000 150 / 126; 128 features,
 // 10000 88 / 86, 14500 137 / 98; 256 levels, 256 features, 8500 175 / 172, 9300 206 / 175, 128 features, 8500 131 / 138,
-// 10000 162 / 140.
+// 10000 162 / 140.  Models of as many steps here as there stay, though some are as much as 9 % slower here: 220 features, D = 10000
+// 98 / 118, 12000 125 / 119, 14500 148 / 137, 16384 130 / 155 (200000 samples: 274 / 332, 355 / 337, 420 / 394, 398 / 440).
 constexpr int kWdMostExtra6 = 5400, kWdMostExtra8 = 4500;   // columns, up to 64 levels and beyond
 
 // ---- host: tables of the model (built in contract_tables.h) ------------------------------------

@@ -7,25 +7,27 @@
 // and the whole chain can be walked on the scalar products of the samples with one another, which
 // do not depend on the rows.  Four kernels:
 //   online_gram_kernel   once per call: <s_n, s_m> of all pairs of a block
-//   online_dots_kernel   per block: <acc_c, s_m> against the rows at the block's start (fp64)
-//   online_chain_kernel  per block, one workgroup: cosines, predictions and weights of all samples
-//   online_rows_kernel   per block: the updates applied to the rows element by element, in sample
-//                        order, one fp32 rounding per update (per batch: one per batch), and the rows'
-//                        new squared norms
+//   online_dots_kernel   per block: <acc_c, s_m> against the rows as they stand (fp64), which do not hold the
+//                        block before yet: what that adds comes from the samples' products
+//   online_chain_kernel  per block, one workgroup: cosines, predictions and weights of all samples; its other
+//                        workgroups apply the updates of the block before to the rows element by element, in
+//                        sample order, one fp32 rounding per update (per batch: one per batch), and form the
+//                        rows' new squared norms
+//   online_rows_kernel   the same updates for the last block (for every one, before the next, where a weight could overflow)
 // Per-sample calls of up to 16 classes take online_wide_kernel for the chain, which walks the block as a whole, with the
-// row updates of the block before as its other workgroups (wide_takes, walk_wide).
-// The dot products stay fp64 sums of the same fp32 rows and fp32 weights.  Inside a block they leave
-// out the fp32 rounding of the u updates of a row made since the block began (walk_wide: since the one before did): at most 2^-24 of an element each,
-// so u 2^-24 of a cosine at the very most and about sqrt(u) 2^-24 as a rule: largest 3e-8 at 561 features, 6
-// classes, D = 10000; 3e-7 over D = 33 to 4096, 1 to 16 classes and samples 2 to 35 % from their prototype; 3e-6
-// where rows of size 1e6 are trained on; up to 4e-4 for a cosine or two where samples drive a row through zero.
-// That is no distance from the method: against the method in 64 bits the walk by samples, which rounds the rows at
-// every step, is as far off (largest over those models, walk and blocks: cosines 2.8e-7 and 3.4e-7, rows relative
-// 2-norm 1.4e-6 and 1.3e-6 from zero rows; 1.4e-5 and 1.2e-5, 2.9e-5 both from rows of 1e6; 5.6e-4 and 2.1e-4,
-// 5.3e-6 and 5.4e-6 through zero; walk_wide on the GPU, 1 to 16 classes, D = 1000 to 12000, 1000 to 1500 samples: rows
-// 1.43e-7 to 5.47e-7 where blocks that begin from their own rows are 1.42e-7 to 5.46e-7 off, largest differences alike
-// in four digits).  But the two forms may part where two cosines agree that closely, also where samples that repeat
-// make rows proportional.
+// row updates of the block before as its other workgroups (wide_takes).
+// The dot products stay fp64 sums of the same fp32 rows and fp32 weights.  They leave out the fp32 rounding of the u <= 512
+// updates of a row made since the block before began: at most 2^-24 of an element each, so u 2^-24 of a cosine at the very
+// most and about sqrt(u) 2^-24 as a rule.  Largest over 36 to 180 models each, D = 33 to 4096, 1 to 16 classes, 1200 samples
+// up to 35 % from their prototype: 2.6e-7 from zero rows (2.5e-8 at D = 10000, 6 classes), 3.4e-6 from rows of size 1e6; 7.1e-6
+// and 5.6e-4 for a few cosines where samples drive rows of up to 80 and of up to 1000 times their prototype through zero
+// (with only the updates since the block itself began: 2.0e-7, 1.8e-6, 7.1e-6, 1.2e-4).
+// That is no distance from the method.  Against the method in 64 bits (largest over the same models, the walk by samples,
+// which rounds the rows at every step / this): cosines 2.3e-7 / 1.7e-7, 7.6e-6 / 5.0e-6, 5.2e-6 / 6.5e-7, 3.6e-4 / 1.2e-4;
+// rows, relative 2-norm, 1.1e-6 / 9.3e-7, 1.8e-5 / 1.8e-5, 2.0e-6 / 1.5e-6, and 6.5e-6 / 1.3e-5 through zero from 1000 prototypes
+// (in the geometric mean 9.4e-7 / 1.2e-6).  On the GPU, 1 to 16 classes, D = 1000 to 12000, 1000 to 1500 samples from zero rows:
+// rows 1.43e-7 to 5.47e-7, blocks that begin from their own rows 1.42e-7 to 5.46e-7.  But the two forms may part where two
+// cosines agree that closely, also where samples that repeat make rows proportional.
 //
 // Walking the chain sample after sample on one workgroup took 3.6 us per sample (two block barriers
 // and a block-wide sum for each).
@@ -927,8 +929,9 @@ __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
 // ---- the chain of a whole block at once ------------------------------------------------------------
 // One workgroup, per sample (not in batches), up to 16 classes.  The same fixed point as in online_chain_kernel, over all
 // samples of a block together: four or five passes settle 256 samples where the sub-blocks one after another take
-// sixteen (from rows of zeros nine to twenty where those take 24 to 37).  7352 samples x 3 epochs, 6 classes,
-// D = 10000: 29.2 us a block -> 14.3, of which five are spent before the first pass.
+// sixteen (from rows of zeros nine to twenty where those take 24 to 37; what predictions that are wrong make of it is told at
+// kWideMostWrong).  7352 samples x 3 epochs, 6 classes, D = 10000: 29.2 us a block -> 16.4 with the rows of the block before
+// beside it, of which five are spent before the first pass.
 //
 // A pass takes the block's whole triangle of products, 640 rows of 64 (source sample x targets of a sub-block).  They
 // stay in registers for all passes, as fp64: eight waves of up to 92 rows, listed sub-block after sub-block and class
@@ -1322,13 +1325,14 @@ bool online_chain_takes(const hdc_ctx_impl *c) { return c->p.C <= 4 * kChainMaxW
 // classes, the longer the list of samples that name one; at two and four classes a wave the passes spill; at large
 // D a batch costs more, a block hardly.  1020 samples, time of the blocks over that of the batches, at 32, 42, 51, 64
 // and 85 samples a batch:
-//   C = 1:  D = 1000 0.94 1.27 1.45 1.46 2.09   10000 0.77 1.03 1.19 1.20 1.74   40000 0.49 0.67 0.79 0.84 1.07
-//   C = 2:  D = 1000 0.68 0.90 1.04 1.08 1.54    4000 0.61 0.83 0.95 0.99 1.40   40000 0.39 0.53 0.63 0.67 0.87
-//   C = 4:  D = 1000 0.53 0.72 0.82 0.88 1.25    4000 0.46 0.63 0.72 0.79 1.10   10000 0.37 0.52 0.59 0.65 0.90
-//   C = 10: D = 1000 0.38 0.57 0.63 0.66 0.95    4000 0.35 0.53 0.57 0.62 0.88   10000 0.31 0.45 0.51 0.54 0.78
-//   C = 33: D = 1000 0.55 0.79 0.87 0.91 1.30    4000 0.52 0.75 0.81 0.84 1.22   10000 0.38 0.54 0.60 0.63 0.88
-// The line below leaves 10 of 3180 calls measured on both sides (1 to 64 classes, D = 100 to 65535, 4 to 1500 samples,
-// batches of 1 to 85) more than 5 % slower than the other way, the worst 9 %.
+//   C = 1:  D = 1000 0.74 0.96 1.12 1.05 1.52   10000 0.71 0.95 1.03 1.01 1.39   40000 0.62 0.92 0.92 1.11 1.27
+//   C = 2:  D = 1000 0.59 0.79 0.90 0.85 1.24    4000 0.57 0.75 0.84 0.85 1.17   40000 0.51 0.73 0.79 0.84 1.03
+//   C = 4:  D = 1000 0.49 0.66 0.73 0.78 1.04    4000 0.48 0.63 0.72 0.76 1.02   10000 0.45 0.58 0.66 0.71 0.96
+//   C = 10: D = 1000 0.37 0.53 0.59 0.60 0.86    4000 0.36 0.53 0.59 0.60 0.87   10000 0.34 0.49 0.55 0.56 0.78
+//   C = 33: D = 1000 0.54 0.74 0.83 0.83 1.17    4000 0.55 0.77 0.83 0.84 1.19   10000 0.43 0.59 0.67 0.68 0.94
+// The line below was drawn when a block was three launches, and is on the careful side of two: of 3128 calls it decides (1 to
+// 64 classes, D = 100 to 65535, 4 to 1500 samples, batches of 1 to 85) 14 are more than 5 % faster in batches, the worst
+// 1.21 times, and 194 more than 5 % faster in blocks, the worst 1.7 times.
 static double batches_per_block(int C, int D) {
     if (D < 512 && C <= 10) return C == 1 ? 4.0 : C <= 4 ? 3.2 : 2.0;   // few dimensions: the passes settle sooner
     const double small = C == 1 ? 7.0 : C == 2 ? 4.7 : C <= 5 ? 3.9 : C <= 16 ? 3.05 : 3.7;
@@ -1336,7 +1340,8 @@ static double batches_per_block(int C, int D) {
 }
 
 // A block that is not full costs a third of a full one and its share of the rest; but a call costs two
-// batches more, a last block of a few samples (260 at 85 a batch) as much as any.
+// batches more, a last block of a few samples (260 at 85 a batch) as much as any.  (Of 723 calls of two or three batches, or
+// of so few a block, 601 would be more than 5 % faster in blocks, half of them 1.2 times and more.)
 bool online_chain_pays(const hdc_ctx_impl *c, int64_t N, int64_t batch) {
     if (3 * batch > kChainBlock) return false;   // (two batches a block or one: not measured)
     const int64_t block = kChainBlock / batch * batch, batches = (N + batch - 1) / batch, rest = N % block;
@@ -1348,9 +1353,11 @@ bool online_chain_pays(const hdc_ctx_impl *c, int64_t N, int64_t batch) {
 // that can make a weight overflow leaves the walk sample by sample, and that to the other kernel.  The first blocks of a
 // zero model take more passes the more classes, and long lists of one to three classes are what the sub-blocks pay for.
 // Time by sub-blocks over time of this way, samples 10 and 30 % from their prototype, every tenth label at random, D = 1000:
-//   C = 1:  129 samples 1.55 1.53, 520 2.45 2.60    C = 3: 129 0.98 1.08, 520 1.31 1.45    C = 5: 200 1.07 1.03, 385 1.14 1.12
-//   C = 8:  300 0.88 0.98, 520 0.99 1.10, 769 1.07 1.19    C = 12: 520 0.93 1.01, 1281 1.08 1.21    C = 16: 520 0.86 0.93, 1793 1.10 1.17
-// and, 2000 samples, 6 classes, D = 10000: 1.65 without false labels, 1.01 with half of them, 0.93 with labels at random.
+//   C = 1:  129 samples 1.41 1.40, 520 2.15 2.12    C = 3: 129 1.08 1.07, 520 1.20 1.25    C = 5: 200 1.02 1.15, 385 1.03 1.10
+//   C = 8:  300 0.90 0.88, 520 0.94 0.97, 769 1.00 1.03    C = 12: 520 0.98 1.06, 1281 1.07 1.16    C = 16: 520 0.96 1.04, 1025 1.02 1.13,
+//   1793 1.09 1.19
+// and, 2000 samples, 6 classes, D = 10000: 1.42 without false labels, 1.20 with a third of them false, 1.01 with half of them or
+// with labels at random; 10 classes 1.36, 1.11, 0.92, 0.89 (two classes a wave on five waves: at kWideMostWrong).
 static bool wide_takes(const hdc_ctx_impl *c, int64_t N, int32_t epochs, float lr) {
     const int C = c->p.C;
     return C <= kWideClasses && c->p.D <= 32767 && N > 2 * kSub && N * epochs > 2 * kSub * (C - 2) && fabsf(lr) < kTameRate;

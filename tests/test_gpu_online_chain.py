@@ -56,9 +56,9 @@ def test_blocks_match_the_oracle(D, C, N, batch):
 
 
 # Samples close to their prototypes (weights next to zero, and the roundings of a row's updates alike), and rows that
-# are large to begin with.  What a cosine leaves out is at most half a unit of every element for each of the u <= 256
-# updates of the row in the block, u 2^-24 of the row, and a weight moves by as much; N weights of random sign, and
-# an element's own rounding.
+# are large to begin with.  What a cosine leaves out is at most half a unit of every element for each of the u updates of
+# the row in the block and the one before, u 2^-24 of the row, and a weight moves by as much; N weights of random sign, and
+# an element's own rounding.  (u <= 512, of which the classes share: 256 is asked for.)
 @pytest.mark.parametrize("batch", [0, 20])
 @pytest.mark.parametrize("size", [0.0, 1.0, 1e3, 1e6])
 @pytest.mark.parametrize("D,C,flip", [(64, 1, 0.05), (100, 2, 0.02), (1024, 5, 0.02), (1000, 17, 0.1), (4096, 3, 0.35)])
