@@ -41,6 +41,11 @@ def test_contraction_blocks_of_eight_waves_fit_a_compute_unit_twice(kernels):
         assert f["vgpr_count"] <= 128 and f["agpr_count"] == 0, (name, f)
 
 
+def test_cosines_are_finished_by_eight_waves_a_simd(kernels):
+    for name, f in of(kernels, "cosine_finish_kernel|online_weights_kernel").items():
+        assert f["vgpr_count"] <= 64 and f["private_segment_fixed_size"] == 0, (name, f)
+
+
 def test_whole_block_walk_of_online_training_does_not_spill(kernels):
     for name, f in of(kernels, "online_wide_kernel").items():
         assert f["private_segment_fixed_size"] == 0 and f["vgpr_count"] <= 256, (name, f)
