@@ -977,12 +977,13 @@ __device__ __forceinline__ void each(F &&f) {
 // and each costs up to twice as much (the lists of wrong ones).  From more wrong ones than this of 64 in half its
 // sub-blocks, or after so many passes, a block is finished by walk_subs, from the weights as they are.  Microseconds for
 // 2000 samples, whole passes only / this / online_chain_kernel:
-//   labels at random, samples 10 % from their prototype, D = 10000: 2 classes 2643 1774 1864, 6 1668 1035 1083,
-//   8 1295 829 857, 10 1457 1014 895, 12 1214 942 859, 16 1164 843 855; half of them at random, 30 %: 2 404 410 641, 6 513 485 491,
-//   8 545 489 486, 16 746 641 670; right labels, 45 %, D = 1000: 6 411 375 441, 16 826 637 642
-// Nine to twelve classes are two a wave on five or six waves here, where the other kernel has a wave for each: with 28
-// instead of 36, half the labels at random, 10 classes 645 for 596 and 12 646 for 610.
-constexpr int kWideMostWrong = 28, kWideMostWrongPaired = 36, kWidePasses = 20;
+//   labels at random, samples 10 % from their prototype, D = 10000: 2 classes 2652 1812 1867, 3 3117 1736 1782,
+//   6 1667 1036 1073, 8 1297 834 846, 10 1462 1016 885, 12 1215 941 847, 16 1168 844 843; half of them at random, 30 %:
+//   2 406 409 640, 3 384 386 528, 6 512 480 486, 8 547 492 481, 10 664 663 599, 16 748 640 662; right labels, 45 %, D = 1000:
+//   3 311 311 454, 6 416 377 436, 12 655 596 552, 16 827 659 630
+// (Nine to twelve classes are two a wave on five or six waves here, where the other kernel has a wave for each.)  24, 28, 36
+// and 44 instead of 32, over 56 such calls for each of 2 to 16 classes: in the mean within 1 % of this, and 2 % and 5 % slower.
+constexpr int kWideMostWrong = 32, kWidePasses = 20;
 
 template <int CPW, int GR>
 __global__ __launch_bounds__(kWideWaves *kWave) void online_wide_kernel(
@@ -1099,7 +1100,6 @@ __global__ __launch_bounds__(kWideWaves *kWave) void online_wide_kernel(
     float wy = 0.0f, wp = 0.0f;
     int pred = -1;
     bool wrong_ones = false, hard = false;
-    const int most_wrong = C > kWideWaves && C <= 12 ? kWideMostWrongPaired : kWideMostWrong;
     // Predictions and weights from s_cos, after a barrier; false: no weight has changed.  (With guess, labels count as
     // predictions: rows of zeros would say class 0 of every sample.  The passes end in the same place from any start.)
     auto decide = [&](int l, bool guess) __attribute__((always_inline)) {
@@ -1141,7 +1141,7 @@ __global__ __launch_bounds__(kWideWaves *kWave) void online_wide_kernel(
         const int v = reinterpret_cast<const int *>(s_any)[l & (2 * kSubs - 1)];
         const uint64_t any = __ballot(v != 0);   // the same in every wave
         wrong_ones = (any & 0xAA) != 0;
-        hard = 2 * __popcll(__ballot(v > most_wrong) & 0xAA) >= subs;
+        hard = 2 * __popcll(__ballot(v > kWideMostWrong) & 0xAA) >= subs;
         return (any & 0x55) != 0;
     };
     // the first pass: no sample of the block counts yet
@@ -1358,9 +1358,17 @@ bool online_chain_pays(const hdc_ctx_impl *c, int64_t N, int64_t batch) {
 //   1793 1.09 1.19
 // and, 2000 samples, 6 classes, D = 10000: 1.42 without false labels, 1.20 with a third of them false, 1.01 with half of them or
 // with labels at random; 10 classes 1.36, 1.11, 0.92, 0.89 (two classes a wave on five waves: at kWideMostWrong).
+// A block costs as much whatever part of it has samples: five classes and more go this way if a first block is two thirds
+// full, nine and more if all are on the average.  8 epochs, D = 64 to 10000, every tenth or third label at random, time this way
+// over time by sub-blocks (over time by sub-blocks with three launches a block):
+//   6 classes: 129 samples 0.95 to 1.09, 200 0.79 to 0.96, 300 0.91 to 1.07 (0.84 to 1.01), 400 0.83 to 0.96
+//   8 classes: 129 1.05 to 1.13, 200 0.92 to 0.97, 300 1.01 to 1.13 (0.92 to 1.08), 400 0.90 to 0.99
+//   10 classes: 129 1.02 to 1.15, 200 0.87 to 1.02, 300 1.01 to 1.16 (0.95 to 1.13), 400 0.86 to 1.05
 static bool wide_takes(const hdc_ctx_impl *c, int64_t N, int32_t epochs, float lr) {
     const int C = c->p.C;
-    return C <= kWideClasses && c->p.D <= 32767 && N > 2 * kSub && N * epochs > 2 * kSub * (C - 2) && fabsf(lr) < kTameRate;
+    const int64_t blocks = (N + kChainBlock - 1) / kChainBlock;
+    return C <= kWideClasses && c->p.D <= 32767 && N > 2 * kSub && N * epochs > 2 * kSub * (C - 2) &&
+           (C <= 4 || 3 * N >= 2 * kChainBlock * (C <= kWideWaves ? 1 : blocks)) && fabsf(lr) < kTameRate;
 }
 
 int reserve_online_chain(hdc_ctx_impl *c) {
