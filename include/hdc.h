@@ -165,16 +165,18 @@ int hdc_binarize_classical(hdc_ctx *ctx, const int32_t *acc_dev, const int64_t *
  * epochs >= 0; lr is the paper's learning rate gamma.  Beyond D = 32768 the call runs
  * hdc_train_online_batched with batches of one sample (the same method).
  * Up to C = 64 and D = 65535, calls of more than a few samples are worked off in blocks of 256
- * samples: the chain is walked on the samples' scalar products with one another and the dot
- * products with the rows at the block's start, then the updates are applied to the rows one by one.
- * The cosines then leave out the fp32 rounding of the u <= 512 updates of a row since the start of
- * the block or the one before: at most u * 2^-24, as a rule sqrt(u) * 2^-24 (largest seen 3e-8 at D = 10000, 6 classes;
- * 3e-7 over D = 33 to 4096 from zero rows; 4e-6 from rows of size 1e6; up to 6e-4 for a few while samples
- * drive a row of many times their size through zero).  They are no further from the
- * method in 64 bits for it, but a prediction between cosines that agree this closely (rows that
+ * samples, of more than 1024 samples and up to C = 32 in blocks of 2048: the chain is walked on the
+ * samples' scalar products with one another and the dot products with the rows at the block's start,
+ * then the updates are applied to the rows one by one.  The cosines then leave out the fp32 rounding
+ * of the updates of a row since the start of the block (of 256: or of the one before), u of them: as
+ * a rule sqrt(u) * 2^-24 (largest seen 3e-8 at D = 10000, 6 classes; 3e-7 over D = 33 to 4096 from
+ * zero rows; 4e-6 from rows of size 1e6; up to 6e-4 for a few while samples drive a row of many
+ * times their size through zero).  They are no further from the method in 64 bits for it, but a
+ * prediction between cosines that agree this closely (rows that
  * repeated samples have made proportional, for instance) may be another one than a walk by samples
  * takes.  The first call, whatever its size, allocates
- * context-owned scratch (20 MB + 16384 rows, at most 64 MB of them, and up to 2.5 MB at the largest C and D) unless hdc_reserve has done so;
+ * context-owned scratch (20 MB + 16384 rows, at most 64 MB of them, and up to 2.5 MB at the largest C and D; up to C = 32 another
+ * 36 MB and 1 MB a class, without which calls of more than 1024 samples go in blocks of 256) unless hdc_reserve has done so;
  * later calls only enqueue on `stream`.  Where the scratch cannot be had - memory is short, or the
  * first call is being captured into a graph - and D <= 32768, the call goes sample by sample
  * without any, which is slower; beyond D = 32768 that is HDC_ENOMEM or HDC_EHIP.
@@ -192,7 +194,8 @@ int hdc_train_online(hdc_ctx *ctx, const uint32_t *hv_dev, const int32_t *labels
  *                                     -float(lr*(1 - cos_pred)) * s for c == pred != y
  * (fp64 sums) and acc[c] = float(double(acc[c]) + delta[c]), one rounding per element and
  * batch.  batch >= 1; a batch larger than N is one batch per epoch.  Small batches (up to 85 samples,
- * fewer for few dimensions and for one or two classes; C <= 64, D <= 65535) are worked off several at a time as described for hdc_train_online.  Other arguments, layout
+ * fewer for few dimensions and for one or two classes; C <= 64, D <= 65535; up to 256 in calls of more than
+ * 1024 samples, C <= 32) are worked off several at a time as described for hdc_train_online.  Other arguments, layout
  * and the treatment of out-of-range labels are those of hdc_train_online.  The first call, and one
  * with a larger batch (min(batch, N)) than any before it, allocates device memory owned by the
  * context (HDC_ENOMEM if that fails) and therefore synchronises the device; other calls only
@@ -317,7 +320,8 @@ typedef enum {
     HDC_K_ENCODE_CONTRACT = 7, /* the contraction form of hdc_encode (quantises, bundles and spreads in one kernel) */
     HDC_K_ENCODE_WIDE = 8,     /* the contraction form of hdc_encode for long streams (jobs of 64 or 128 samples) */
     HDC_K_ONLINE_WIDE = 9,     /* the calls among those of HDC_K_ONLINE whose blocks are walked as a whole, one entry a call */
-    HDC_K_COUNT = 10
+    HDC_K_ONLINE_SPREAD = 10,  /* the calls of both online trainers that go in blocks of up to 2048 samples, one entry a call */
+    HDC_K_COUNT = 11
 } hdc_kernel_id;
 #define HDC_PROFILE_SLOTS 512
 int hdc_profile_enable(hdc_ctx *ctx, int enable);

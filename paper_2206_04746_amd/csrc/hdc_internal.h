@@ -106,6 +106,17 @@ struct hdc_ctx_impl {
     double *oc_norm_d;    // [C][ceil(D/64)] the other squared-norm partials, and [C] what a block adds to them
     bool oc_attr_set[8];  // dynamic-LDS limit of online_chain_kernel / online_wide_kernel raised, by variant
 
+    // Scratch of the trainer of long sets (online_spread.hip), allocated with the one above.
+    bool os_ready;
+    char *os_mem_d;       // the allocation that holds what follows
+    size_t os_mem_bytes;
+    int16_t *os_strips_d; // [blocks][triangle of strips of 16 columns] products of the samples of a block
+    double *os_part_d;    // [slices][C][2048] partial dot products of a block
+    void *os_rec_d;       // [2048] weight records of a block
+    void *os_slots_d;     // [passes][words] what its workgroups tell one another; zero between calls
+    int *os_state_d;      // [2] workgroups that have begun (zero between calls), slots in use
+    bool os_attr_set[6];  // dynamic-LDS limit of online_spread_kernel and online_update_kernel raised, by variant
+
     // hdc_encode_sparse (allocated and derived on its first call)
     bool sp_ready;
     uint32_t *sp_b_d;       // [slices][Fp][64] item ^ level 0 (of the compact tables when `compact`)

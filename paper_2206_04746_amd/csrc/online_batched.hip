@@ -1027,7 +1027,8 @@ int launch_train_online_batched(hdc_ctx_impl *c, const uint32_t *hv, const int32
     const FwdShape f = fwd_shape(C, G);
     if (batch > N) batch = N;
     int rc = HDC_OK;
-    if (online_chain_pays(c, N, batch) && online_chain_ready(c, s, &rc)) {
+    const bool pays = online_chain_pays(c, N, batch);
+    if ((pays || online_spread_pays(c, N, batch)) && online_chain_ready(c, s, &rc) && (pays || online_spread_takes(c, N, lr, batch, false))) {
         // a shorter call with the same batch goes in pieces: their scratch, too, belongs to this call
         if (batch > c->ob_blocks_batch && !stream_captured(s)) {
             rc = reserve_pieces(c, batch);

@@ -32,10 +32,8 @@
 // Walking the chain sample after sample on one workgroup took 3.6 us per sample (two block barriers
 // and a block-wide sum for each).
 #include <algorithm>
-#include <type_traits>
 
-#include "hdc_internal.h"
-#include "online_weight.h"
+#include "online_lanes.h"
 
 namespace hdc {
 
@@ -73,17 +71,6 @@ struct WideOrder {                       // of a block, from its labels
 constexpr int kWideImage = kWideWaves * kWideRows * kSub;
 __host__ __device__ constexpr int wide_place(int row, int lane) {   // row: 96 wave + its row
     return ((row >> 3) * kSub + lane) * 8 + (row & 7);
-}
-
-// Sum over the lanes up to this one.
-__device__ __forceinline__ int lane_sum(int v) {
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);    // row_shr:1, 2, 4, 8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15, 31
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);
-    return v;
 }
 
 // Writes the order of one block (256 threads).  A list: the samples of a class among those up to the end of a target
@@ -195,7 +182,9 @@ typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-template <bool WIDE>
+enum class Products { kTiles, kWide, kStrips };   // for online_chain_kernel, online_wide_kernel, online_spread_kernel
+
+template <Products FOR>
 __global__ __launch_bounds__(kGramWaves *kWave) void online_gram_kernel(const uint64_t *__restrict__ col, int64_t ld,
                                                                         int64_t N, int D, int G, int block,
                                                                         int16_t *__restrict__ gram,
@@ -203,7 +192,8 @@ __global__ __launch_bounds__(kGramWaves *kWave) void online_gram_kernel(const ui
                                                                         int16_t *__restrict__ image, int16_t *__restrict__ pairs) {
     __shared__ int sum[kSub][kGramPitch];
     __shared__ int ones[2][kSub];
-    const bool pair = (int)blockIdx.x >= kTiles;   // sub-block a of this block, b of the next one
+    constexpr bool WIDE = FOR == Products::kWide;
+    const bool pair = FOR != Products::kStrips && (int)blockIdx.x >= kTiles;   // sub-block a of this block, b of the next one
     int a, b = 0;
     if (pair) {
         a = ((int)blockIdx.x - kTiles) / kSubs;
@@ -269,6 +259,20 @@ __global__ __launch_bounds__(kGramWaves *kWave) void online_gram_kernel(const ui
             for (int k = 0; k < 16; ++k)   // register k: row 8 (k / 4) + 4 half + k % 4, column r
                 atomicAdd(&sum[32 * i + 8 * (k / 4) + 4 * half + k % 4][32 * j + r], (int)dot[i][j][k]);
     __syncthreads();
+    if constexpr (FOR == Products::kStrips) {   // eight of a row to a thread: 16 samples' columns after one another, by rows
+        static_assert(kTile == 8 * kGramWaves * kWave, "a thread to eight products");
+        const int u = t >> 3, v = 8 * (t & 7), n = a * kSub + u, strip = (b * kSub + v) / kStripCols;
+        u32x4 out;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int lo = (D >> 1) - ones[0][u] - ones[1][v + 2 * k] + 2 * sum[u][v + 2 * k];
+            const int hi = (D >> 1) - ones[0][u] - ones[1][v + 2 * k + 1] + 2 * sum[u][v + 2 * k + 1];
+            out[k] = (uint32_t)(uint16_t)lo | (uint32_t)hi << 16;
+        }
+        if (n < kStripCols * (strip + 1))
+            *reinterpret_cast<u32x4 *>(gram + (int64_t)blockIdx.y * kSpanProducts + strip_start(strip) + n * kStripCols + (v & 8)) = out;
+        return;
+    }
     int16_t *out = pair ? pairs + ((int64_t)blockIdx.y * kSubs * kSubs + ((int)blockIdx.x - kTiles)) * kTile
                         : gram + ((int64_t)blockIdx.y * kTiles + blockIdx.x) * kTile;
     for (int i = t; i < kTile; i += kGramWaves * kWave) {
@@ -324,7 +328,7 @@ __global__ __launch_bounds__(kDotWaves *kWave) void online_dots_kernel(const uin
                                                                        const float *__restrict__ acc, int D, int C,
                                                                        int slice, int slices, const int16_t *__restrict__ pairs,
                                                                        const OnlineWeight *__restrict__ recs, int before,
-                                                                       double *__restrict__ part) {
+                                                                       double *__restrict__ part, int span) {
     __shared__ __align__(16) double red[kDotWaves][256];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
     const int q = lane >> 4, i = lane & 15;
@@ -333,9 +337,9 @@ __global__ __launch_bounds__(kDotWaves *kWave) void online_dots_kernel(const uin
     const int c = blockIdx.z * 16 + i;
     const uint16_t *h = reinterpret_cast<const uint16_t *>(col) + 4 * (int64_t)n + q;   // this lane's 16 bits of a group
     const float *row = acc + (int64_t)(c < C ? c : C - 1) * D;
-    const int span = slice / kDotWaves;   // a multiple of 64
-    const int lo = blockIdx.x * slice + wave * span;
-    const int hi = lo + span < D ? lo + span : D;
+    const int share = slice / kDotWaves;   // a multiple of 64
+    const int lo = blockIdx.x * slice + wave * share;
+    const int hi = lo + share < D ? lo + share : D;
     f64x4 sum = {0.0, 0.0, 0.0, 0.0};
     if ((int)blockIdx.x == slices) sum = add_block_before(pairs, recs, before, D, &red[0][0]);   // (lo is past D)
     for (int d0 = lo; d0 < hi; d0 += kWave) {
@@ -367,39 +371,8 @@ __global__ __launch_bounds__(kDotWaves *kWave) void online_dots_kernel(const uin
         double s = 0.0;
 #pragma unroll
         for (int w = 0; w < kDotWaves; ++w) s += red[w][(t & 15) * 16 + (t >> 4)];
-        if (cc < C) part[((int64_t)blockIdx.x * C + cc) * kChainBlock + m] = s;
+        if (cc < C && m < span) part[((int64_t)blockIdx.x * C + cc) * span + m] = s;
     }
-}
-
-// ---- lanes ------------------------------------------------------------------------------------------
-__device__ __forceinline__ float lane_f32(float v, int i) {
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), i));
-}
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_add(double v) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xF, ROWS == 0xF);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xF, ROWS == 0xF);
-    return v + __hiloint2double(hi, lo);
-}
-// Inclusive sum over the lanes: four shifts within a row of 16, then the row totals.
-__device__ __forceinline__ double lane_prefix(double v) {
-    v = dpp_add<0x111, 0xF>(v);   // row_shr:1
-    v = dpp_add<0x112, 0xF>(v);
-    v = dpp_add<0x114, 0xF>(v);
-    v = dpp_add<0x118, 0xF>(v);
-    v = dpp_add<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
-    v = dpp_add<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
-    return v;
-}
-__device__ __forceinline__ double lane_f64(double v, int i) {
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), i),
-                            __builtin_amdgcn_readlane(__double2loint(v), i));
-}
-// The value of the lane before (lane 0: zero).
-__device__ __forceinline__ double lane_before(double v) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xF, 0xF, true);   // wave_shr:1
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xF, 0xF, true);
-    return __hiloint2double(hi, lo);
 }
 
 // ---- the rows ------------------------------------------------------------------------------------
@@ -491,84 +464,16 @@ struct BlockBefore {
 };
 
 // ---- the chain -----------------------------------------------------------------------------------
-__device__ __forceinline__ double refined_rsq(double nn) {
-    double r = __builtin_amdgcn_rsq(nn);
-    r = r * fma(-0.5 * nn * r, r, 1.5);
-    return r * fma(-0.5 * nn * r, r, 1.5);
-}
-
-// The samples of a block one after another: a wave's lanes deal the samples before among them for each of
-// its classes, and the decision is taken class by class, as in the kernels that walk sample by sample
-// (BATCH: as in the batched trainer, which passes over classes whose cosine is no number).  cosv: [C] in LDS.
-template <int CPW, bool BATCH>
-__device__ __noinline__ void walk_block(const int16_t *prod, bool halves, const double *__restrict__ part, int slices, int nb, int batch,
-                           const int32_t *__restrict__ labels, const double *__restrict__ normpart, const double *before,
-                           double *grown, int G, int C, int D, float lr, double inv_root_d, OnlineWeight *rec, double *cosv) {
-    const int tid = threadIdx.x, lane = tid & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    double nrm[CPW], frozen[CPW], at_start[CPW];   // squared norms now, where the batch began, where the block did
-    for (int k = 0; k < CPW; ++k) {
-        const int c = wave * CPW + k;
-        double s = 0.0;
-        for (int g = lane; g < G && c < C; g += kWave) s += normpart[(int64_t)c * G + g];
-        nrm[k] = frozen[k] = lane_f64(lane_prefix(s), kWave - 1) + (before && c < C ? before[c] : 0.0);
-        at_start[k] = nrm[k];
+// The product of samples n < m from a block's tiles, which hold them whole or as online_gram_kernel's halves.
+struct TileProduct {
+    const int16_t *prod;
+    int odd;
+    bool halves;
+    __device__ int operator()(int n, int m) const {
+        const int b = m / kSub, g = prod[b * (b + 1) / 2 * kTile + n * kSub + m % kSub];
+        return halves ? 2 * g + odd : g;
     }
-    for (int m = 0; m < nb; ++m) {
-        const int first = BATCH ? m / batch * batch : m, b = m / kSub;
-        const int16_t *tiles = prod + b * (b + 1) / 2 * kTile + m % kSub;   // row n is product (n, m)
-        int y = labels[m];
-        y = y >= 0 && y < C ? y : -1;
-        double all[CPW];
-        __syncthreads();   // the record before is there, cosv has been read
-#pragma unroll
-        for (int k = 0; k < CPW; ++k) {
-            const int c = wave * CPW + k;
-            if (first == m) frozen[k] = nrm[k];
-            if (c >= C) continue;
-            double start = 0.0, old = 0.0, own = 0.0;
-            for (int i = 0; i < slices; ++i) start += part[((int64_t)i * C + c) * kChainBlock + m];
-            for (int n = lane; n < m; n += kWave) {
-                const OnlineWeight r = rec[n];
-                const double g = (double)(halves ? 2 * (int)tiles[n * kSub] + (D & 1) : (int)tiles[n * kSub]);
-                const double term = r.y == c ? (double)r.w_y * g : r.pred == c ? -(double)r.w_p * g : 0.0;
-                (n < first ? old : own) += term;
-            }
-            const double dot = start + lane_f64(lane_prefix(old), kWave - 1);
-            all[k] = dot + lane_f64(lane_prefix(own), kWave - 1);
-            const double nn = frozen[k];
-            if (lane == 0) cosv[c] = nn <= 0.0 ? 0.0 : dot * refined_rsq(nn) * inv_root_d;
-        }
-        __syncthreads();
-        int pred = BATCH ? -1 : 0;
-        double best = BATCH ? -2.0 : cosv[0];
-        for (int c = BATCH ? 0 : 1; c < C; ++c) {
-            const double v = cosv[c];
-            if (v > best) {
-                best = v;
-                pred = c;
-            }
-        }
-        OnlineWeight r = {y, -1, 0.0f, 0.0f};
-        if (y >= 0) {
-            r.w_y = (float)(1.0 - cosv[y]);
-            if (pred >= 0 && pred != y) {
-                r.pred = pred;
-                r.w_p = (float)((double)lr * (1.0 - best));
-            }
-        }
-        if (tid == 0) rec[m] = r;
-#pragma unroll
-        for (int k = 0; k < CPW; ++k) {
-            const int c = wave * CPW + k;
-            const double w = r.y == c ? (double)r.w_y : r.pred == c ? -(double)r.w_p : 0.0;
-            if (c < C && (r.y == c || r.pred == c)) nrm[k] += w * (2.0 * all[k] + w * (double)D);
-        }
-    }
-    for (int k = 0; k < CPW && grown; ++k)
-        if (lane == 0 && wave * CPW + k < C) grown[wave * CPW + k] = nrm[k] - at_start[k];
-    __syncthreads();
-}
+};
 
 // What walk_subs keeps in LDS.
 template <int CPW, int WAVES>
@@ -915,7 +820,7 @@ __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
     __syncthreads();
     if (wave >= used) return;   // (an ended wave takes no part in later barriers)
     if (__builtin_expect(__ballot(lane < used && s_odd[lane]) != 0 || !(fabsf(lr) < kTameRate), 0)) {   // the same in every wave
-        walk_block<CPW, BATCH>(prod, true, part, slices, nb, batch, labels, normpart, ahead ? grown : nullptr, grown, G, C, D, lr,
+        walk_block<CPW, BATCH>(TileProduct{prod, D & 1, true}, part, kChainBlock, slices, nb, batch, labels, normpart, ahead ? grown : nullptr, grown, G, C, D, lr,
                                inv_root_d, s.rec, s.cosy[0]);
         for (int n = tid; n < nb; n += used * kWave) out[n] = s.rec[n];
         return;
@@ -945,33 +850,6 @@ __global__ __launch_bounds__(kChainMaxWaves *kWave) void online_chain_kernel(
 // from LDS, as the list changes from pass to pass.
 //
 // All of it has to stay within 256 registers: a kernel that spills waits 4 us longer for its launch.
-
-// acc += w of lane (16 k + I) x g, in every row of 16 lanes k, for GR rows.  (Such a broadcast wants two wait states
-// after a vector write of its operand; five after one of the execution mask by the vector unit, of which there is none.)
-template <int I, int GR>
-__device__ __forceinline__ void add_rows(double &acc, double w, const double *g) {
-    if constexpr (GR == 4)
-        asm volatile("s_nop 1\n\t"
-                     "v_fmac_f64_dpp %0, %1, %2 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
-                     "v_fmac_f64_dpp %0, %1, %3 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
-                     "v_fmac_f64_dpp %0, %1, %4 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n\t"
-                     "v_fmac_f64_dpp %0, %1, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
-                     : "+v"(acc) : "v"(w), "v"(g[0]), "v"(g[1]), "v"(g[2]), "v"(g[3]), "n"(I), "n"(I + 1), "n"(I + 2), "n"(I + 3));
-    else
-        asm volatile("s_nop 1\n\t"
-                     "v_fmac_f64_dpp %0, %1, %2 row_newbcast:%4 row_mask:0xf bank_mask:0xf\n\t"
-                     "v_fmac_f64_dpp %0, %1, %3 row_newbcast:%5 row_mask:0xf bank_mask:0xf"
-                     : "+v"(acc) : "v"(w), "v"(g[0]), "v"(g[1]), "n"(I), "n"(I + 1));
-}
-
-// f(0), f(1) ... f(N - 1) with the number as a type
-template <int N, int I = 0, typename F>
-__device__ __forceinline__ void each(F &&f) {
-    if constexpr (I < N) {
-        f(std::integral_constant<int, I>{});
-        each<N, I + 1>(f);
-    }
-}
 
 // Where about half the predictions are wrong a block needs 30 to 70 passes, nearly as many as its sub-blocks together,
 // and each costs up to twice as much (the lists of wrong ones).  From more wrong ones than this of 64 in half its
@@ -1170,7 +1048,7 @@ __global__ __launch_bounds__(kWideWaves *kWave) void online_wide_kernel(
     if (__builtin_expect(strange, 0)) {
         __syncthreads();
         OnlineWeight *rec = reinterpret_cast<OnlineWeight *>(&s_place[0][0]);   // (4 KB of at least 7)
-        walk_block<CPW, false>(prod, false, part, CPW == 1 ? slices : 1, nb, 1, labels, normpart, ahead ? grown : nullptr, grown, G, C, D,
+        walk_block<CPW, false>(TileProduct{prod, 0, false}, part, kChainBlock, CPW == 1 ? slices : 1, nb, 1, labels, normpart, ahead ? grown : nullptr, grown, G, C, D,
                                lr, inv_root_d, rec, s_wy);
         for (int n = tid; n < nb; n += kWideWaves * kWave) out[n] = rec[n];
         return;
@@ -1314,9 +1192,29 @@ static int chain_slice(int D) {   // dimensions of a slice: up to ten slices, wh
 }
 
 // Samples whose columns are held at a time: within 64 MB.
-static int64_t held_samples(int G) {
+int64_t held_samples(int G) {
     const int64_t fit = ((int64_t)64 << 20) / ((int64_t)G * (int64_t)sizeof(uint64_t)) / kSub * kSub;
     return std::min(fit, kHeldBlocks * kChainBlock);
+}
+
+void launch_columns(hdc_ctx_impl *c, const uint32_t *hv, int64_t n, int64_t ld, hipStream_t s) {
+    const int G = (c->p.D + kWave - 1) / kWave;
+    hipLaunchKernelGGL(online_columns_kernel<false>, dim3((unsigned)((n + kSub - 1) / kSub), (unsigned)((G + kColGroups - 1) / kColGroups)),
+                       dim3(256), 0, s, hv, n, c->W, c->last_word_mask, G, ld, c->oc_col_d, nullptr, c->p.C, nullptr);
+}
+
+void launch_strips(hdc_ctx_impl *c, int64_t n, int64_t ld, int block, int16_t *strips, hipStream_t s) {
+    const int subs = (int)((std::min<int64_t>(n, block) + kSub - 1) / kSub);
+    hipLaunchKernelGGL(online_gram_kernel<Products::kStrips>, dim3((unsigned)(subs * (subs + 1) / 2), (unsigned)((n + block - 1) / block)),
+                       dim3(kGramWaves * kWave), 0, s, c->oc_col_d, ld, n, c->p.D, (c->p.D + kWave - 1) / kWave, block, strips, nullptr,
+                       nullptr, nullptr);
+}
+
+void launch_dots(hdc_ctx_impl *c, const uint64_t *col, int64_t ld, int nb, const float *acc, int slice, double *part, int span,
+                 hipStream_t s) {
+    const int C = c->p.C, D = c->p.D, slices = (D + slice - 1) / slice;
+    hipLaunchKernelGGL(online_dots_kernel, dim3((unsigned)slices, (unsigned)((nb + 15) / 16), (unsigned)((C + 15) / 16)),
+                       dim3(kDotWaves * kWave), 0, s, col, ld, nb, acc, D, C, slice, slices, nullptr, nullptr, 0, part, span);
 }
 
 bool online_chain_takes(const hdc_ctx_impl *c) { return c->p.C <= 4 * kChainMaxWaves && c->p.D <= 65535; }
@@ -1410,6 +1308,7 @@ bool online_chain_ready(hdc_ctx_impl *c, hipStream_t s, int *rc) {
     *rc = HDC_OK;
     if (!online_chain_takes(c)) return false;
     if (!c->oc_ready && !stream_captured(s)) *rc = reserve_online_chain(c);
+    if (*rc == HDC_OK && c->oc_ready && !c->os_ready && !stream_captured(s)) *rc = reserve_online_spread(c);
     if (*rc == HDC_ENOMEM) *rc = HDC_OK;
     return c->oc_ready;
 }
@@ -1493,7 +1392,7 @@ static int walk_held(hdc_ctx_impl *c, const int32_t *labels, int64_t N, float lr
             hipLaunchKernelGGL(online_dots_kernel,
                                dim3((unsigned)(slices + (ahead ? 1 : 0)), (unsigned)((nb + 15) / 16), (unsigned)((C + 15) / 16)),
                                dim3(kDotWaves * kWave), 0, s, col, ld, nb, acc, D, C, slice, slices,
-                               ahead ? c->oc_pairs_d + (b - 1) * kSubs * kSubs * kTile : nullptr, recs_before, block, c->oc_part_d);
+                               ahead ? c->oc_pairs_d + (b - 1) * kSubs * kSubs * kTile : nullptr, recs_before, block, c->oc_part_d, kChainBlock);
         }
         HDC_HIP(hipGetLastError());
         const ChainCall a = {b, slices, nb, batch, G, labels + b * block, lr, norm[*norm_at], ahead,
@@ -1549,7 +1448,7 @@ static int walk_blocks(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *label
                 HDC_HIP(hipGetLastError());
                 if (hn > 1 || wide) {
                     const int subs = (int)((std::min<int64_t>(hn, block) + kSub - 1) / kSub);
-                    hipLaunchKernelGGL(wide ? online_gram_kernel<true> : online_gram_kernel<false>,
+                    hipLaunchKernelGGL(wide ? online_gram_kernel<Products::kWide> : online_gram_kernel<Products::kTiles>,
                                        dim3((unsigned)(subs * (subs + 1) / 2 + (blocks > 1 ? (kTiles - subs * (subs + 1) / 2) + kSubs * kSubs : 0)), blocks),
                                        dim3(kGramWaves * kWave), 0, s, c->oc_col_d, ld, hn, D, G, block, c->oc_gram_d, order,
                                        c->oc_image_d, c->oc_pairs_d);
@@ -1564,6 +1463,9 @@ static int walk_blocks(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *label
 
 int launch_online_chain(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *labels, int64_t N, int32_t epochs,
                         float lr, int64_t batch, bool per_sample, float *acc, hipStream_t s) {
+    if (online_spread_takes(c, N, lr, batch, per_sample))
+        return per_sample ? launch_online_spread<false>(c, hv, labels, N, epochs, lr, 1, acc, s)
+                          : launch_online_spread<true>(c, hv, labels, N, epochs, lr, (int)batch, acc, s);
     return per_sample ? walk_blocks<false>(c, hv, labels, N, epochs, lr, 1, acc, s)
                       : walk_blocks<true>(c, hv, labels, N, epochs, lr, (int)batch, acc, s);
 }

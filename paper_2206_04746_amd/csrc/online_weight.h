@@ -47,4 +47,28 @@ bool online_chain_ready(hdc_ctx_impl *c, hipStream_t s, int *rc);
 int launch_online_chain(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *labels, int64_t N, int32_t epochs,
                         float lr, int64_t batch, bool per_sample, float *acc, hipStream_t s);
 
+
+// Calls of many samples in blocks of kSpan, each block's chain spread over kSpan / kStripCols workgroups
+// (online_spread.hip).
+constexpr int kSpan = 2048;         // most samples of a block
+constexpr int kStripCols = 16;      // samples of a workgroup
+// Products of a block's samples: strip after strip of 16 columns, of each the rows of the samples up to its last one.
+__host__ __device__ constexpr int strip_start(int strip) { return kStripCols * kStripCols * strip * (strip + 1) / 2; }
+constexpr int kSpanProducts = strip_start(kSpan / kStripCols);
+bool online_spread_pays(const hdc_ctx_impl *c, int64_t N, int64_t batch);   // in batches: worth asking for scratch
+bool online_spread_takes(const hdc_ctx_impl *c, int64_t N, float lr, int64_t batch, bool per_sample);
+int reserve_online_spread(hdc_ctx_impl *c);
+template <bool BATCH>
+int launch_online_spread(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *labels, int64_t N, int32_t epochs, float lr,
+                         int batch, float *acc, hipStream_t s);
+
+// Steps of both forms of the block-wise walk (online_chain.hip): the samples' bits by dimension groups (col[group][ld]),
+// the products of `blocks` blocks of up to kSpan samples in strips, and partial dot products part[slice][class][span] of
+// nb samples with the rows.
+int64_t held_samples(int G);
+void launch_columns(hdc_ctx_impl *c, const uint32_t *hv, int64_t n, int64_t ld, hipStream_t s);
+void launch_strips(hdc_ctx_impl *c, int64_t n, int64_t ld, int block, int16_t *strips, hipStream_t s);
+void launch_dots(hdc_ctx_impl *c, const uint64_t *col, int64_t ld, int nb, const float *acc, int slice, double *part, int span,
+                 hipStream_t s);
+
 }  // namespace hdc

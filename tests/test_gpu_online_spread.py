@@ -1,0 +1,150 @@
+"""Online training of more than 1024 samples in blocks of up to 2048, each block's chain spread over a workgroup per 16
+samples (csrc/online_spread.hip), per sample and in batches, against the CPU oracle: at the edges of workgroups and blocks,
+of the class lists, where batches begin inside a workgroup or end with one, and where predictions are mostly wrong, so that
+the workgroups finish a block one after another."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+import oracle  # noqa: E402
+from workloads import make_workload  # noqa: E402
+
+from test_gpu_online_batched import clustered  # noqa: E402
+from test_gpu_online_chain import TOL, off  # noqa: E402
+from test_gpu_online_wide import labels  # noqa: E402
+from test_gpu_parity import dev_u32, make_ctx  # noqa: E402
+
+
+def train(ctx, hvd, yd, acc, batch, epochs, lr=1.0):
+    """One call (batch 0: hdc_train_online); says whether it went in blocks of 2048."""
+    ctx.hdc_profile_enable(True)
+    if batch:
+        ctx.hdc_train_online_batched(hvd, yd, acc, batch, epochs=epochs, lr=lr)
+    else:
+        ctx.hdc_train_online(hvd, yd, acc, epochs=epochs, lr=lr)
+    return ctx.hdc_profile_read("online_spread")[1]
+
+
+def want(hv, y, D, C, batch, epochs, lr=1.0, acc=None):
+    if batch:
+        return oracle.train_online_batched(hv, y, D, C, batch, epochs=epochs, lr=lr, acc=acc)
+    return oracle.train_online(hv, y, D, C, epochs=epochs, lr=lr, acc=acc)
+
+
+# one workgroup more than 1024 samples, edges of a workgroup's 16 samples, of a block and the next; classes at one and two a
+# wave and the most of them; small, odd and large D
+@pytest.mark.parametrize("batch", [0, 1, 7, 16, 17, 64, 85, 200])
+@pytest.mark.parametrize("D,C,N", [(64, 1, 1025), (1000, 2, 1040), (1001, 5, 2047), (2049, 16, 2048), (640, 17, 2049), (640, 32, 2200),
+                                   (10000, 6, 2600), (333, 9, 4097)])
+def test_long_calls_match_the_oracle(D, C, N, batch):
+    rng = np.random.default_rng(D + 10 * C + N)
+    hv, y = clustered(rng, N, D, C)
+    y[N // 2] = C                                  # out of range: skipped
+    hv[N - 1], y[N - 1] = hv[0], y[0]              # the same sample twice
+    ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
+    hvd, yd = dev_u32(hv), torch.from_numpy(y).cuda()
+    acc = torch.zeros((C, D), dtype=torch.float32, device="cuda")
+    for calls in (1, 2):                           # the second call goes on from the rows of the first
+        assert train(ctx, hvd, yd, acc, batch, 1, 0.5) == (C <= 16 or not 0 < batch < 16)
+        assert off(acc, want(hv, y, D, C, batch, calls, 0.5)) < TOL
+    ctx.close()
+
+
+# all samples of one class (its list runs through every row of lanes), hardly any valid, classes in runs
+@pytest.mark.parametrize("kind", ["one", "most", "few", "blocks"])
+@pytest.mark.parametrize("batch", [0, 40])
+@pytest.mark.parametrize("D,C,N", [(1000, 4, 2100), (512, 16, 1500), (512, 20, 2500)])
+def test_long_calls_of_uneven_classes(D, C, N, batch, kind):
+    rng = np.random.default_rng(D + C + N)
+    hv, y = clustered(rng, N, D, C)
+    y = labels(kind, rng, y, C)
+    ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
+    acc = torch.zeros((C, D), dtype=torch.float32, device="cuda")
+    assert train(ctx, dev_u32(hv), torch.from_numpy(y).cuda(), acc, batch, 2)
+    assert off(acc, want(hv, y, D, C, batch, 2)) < TOL
+    ctx.close()
+
+
+# Wrong predictions: some (listed beside the right ones), and so many that workgroups go on alone; one to eight classes to a
+# row of lanes; batches that fill workgroups, cross them, and several to a workgroup
+@pytest.mark.parametrize("flip,wrong", [(0.1, 1.0), (0.1, 0.5), (0.1, 0.2), (0.45, 0.0)])
+@pytest.mark.parametrize("batch", [0, 10, 16, 64, 100])
+@pytest.mark.parametrize("D,C,N", [(1000, 2, 2048), (999, 6, 3000), (640, 12, 2100), (512, 24, 2100)])
+def test_long_calls_of_wrong_predictions(D, C, N, batch, flip, wrong):
+    rng = np.random.default_rng(D + 10 * C + N)
+    hv, y = clustered(rng, N, D, C, flip)
+    y = np.where(rng.random(N) < wrong, rng.integers(0, C, N), y).astype(np.int32)
+    ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
+    hvd, yd = dev_u32(hv), torch.from_numpy(y).cuda()
+    acc = torch.zeros((C, D), dtype=torch.float32, device="cuda")
+    train(ctx, hvd, yd, acc, batch, 1)
+    assert off(acc, want(hv, y, D, C, batch, 1)) < TOL
+    again = torch.zeros_like(acc)                  # the same bits every time
+    train(ctx, hvd, yd, again, batch, 1)
+    assert torch.equal(acc, again)
+    ctx.close()
+
+
+@pytest.mark.parametrize("batch", [0, 20])
+@pytest.mark.parametrize("row,value", [(0, float("nan")), (1, float("inf"))])
+@pytest.mark.parametrize("C", [3, 20])
+def test_long_calls_from_rows_that_are_not_finite(C, row, value, batch):
+    D, N = 200, 2100
+    hv, y = clustered(np.random.default_rng(C), N, D, C)
+    start = np.random.default_rng(6).normal(size=(C, D)).astype(np.float32)
+    start[row, 7] = value
+    ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
+    hvd, yd, acc = dev_u32(hv), torch.from_numpy(y).cuda(), torch.from_numpy(start.copy()).cuda()
+    assert train(ctx, hvd, yd, acc, batch, 1)
+    if batch:    # (against calls of one batch each: the oracle takes class 0 here as well)
+        single = torch.from_numpy(start.copy()).cuda()
+        for n in range(0, N, batch):
+            ctx.hdc_train_online_batched(hvd[n:n + batch], yd[n:n + batch], single, batch, epochs=1, lr=1.0)
+        expected = single.cpu().numpy()
+    else:
+        expected = want(hv, y, D, C, 0, 1, acc=start.copy())
+    got, ok = acc.cpu().numpy(), np.isfinite(expected)
+    assert np.array_equal(np.isnan(got), np.isnan(expected)) and np.array_equal(got[np.isinf(expected)], expected[np.isinf(expected)])
+    assert np.max(np.abs(got[ok] - expected[ok]), initial=0.0) <= TOL * max(1.0, float(np.max(np.abs(expected[ok]), initial=0.0)))
+    ctx.close()
+
+
+@pytest.mark.parametrize("wrong", [0.0, 1.0])
+def test_long_calls_replayed_from_a_graph(wrong):
+    D, C, N = 1000, 5, 2500
+    rng = np.random.default_rng(2)
+    hv, y = clustered(rng, N, D, C, 0.1)
+    y = np.where(rng.random(N) < wrong, rng.integers(0, C, N), y).astype(np.int32)
+    ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
+    hvd, yd = dev_u32(hv), torch.from_numpy(y).cuda()
+    acc = torch.zeros((C, D), dtype=torch.float32, device="cuda")
+    eager = torch.zeros_like(acc)
+    ctx.hdc_train_online(hvd[:5], yd[:5], eager, epochs=1, lr=1.0)     # scratch is set up here
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        acc.zero_()
+        ctx.hdc_train_online(hvd, yd, acc, epochs=2, lr=1.0)
+    for k in range(3):
+        hvd.copy_(hvd.roll(17, dims=0))
+        yd.copy_(yd.roll(17, dims=0))
+        graph.replay()
+        eager.zero_()
+        ctx.hdc_train_online(hvd, yd, eager, epochs=2, lr=1.0)
+        torch.cuda.synchronize()
+        assert torch.equal(acc, eager), k
+    ctx.close()
+
+
+@pytest.mark.parametrize("C,N,batch,lr,spread", [
+    (2, 1024, 0, 1.0, 0), (2, 1025, 0, 1.0, 1), (32, 2000, 0, 1.0, 1), (33, 2000, 0, 1.0, 0), (3, 2000, 256, 1.0, 1), (3, 2000, 257, 1.0, 0),
+    (17, 2000, 15, 1.0, 0), (17, 2000, 16, 1.0, 1), (3, 2000, 0, 1e30, 0), (3, 2000, 0, float("nan"), 0)])
+def test_which_calls_go_in_blocks_of_2048(C, N, batch, lr, spread):
+    ctx = make_ctx(make_workload(1, D=64, C=C, F=3, L=2))
+    hvd = torch.zeros((N, ctx.W), dtype=torch.int32, device="cuda")
+    yd = torch.zeros(N, dtype=torch.int32, device="cuda")
+    assert train(ctx, hvd, yd, torch.zeros((C, 64), dtype=torch.float32, device="cuda"), batch, 1, lr) == spread
+    ctx.close()
