@@ -2,14 +2,14 @@
 //
 // With the class accumulators frozen over a batch, the chain of hdc_train_online breaks into
 // three data-parallel steps per batch:
-//   forward   dot[n][c] = <acc[c], s_n>   for every sample of the batch        (C x D x B FMAs)
+//   forward   dot[n][c] = <acc[c], s_n>   for every sample of the batch        (or row_dots.hip)
 //   weights   cosines, prediction and the two fp32 weights of each sample      (tiny)
 //   backward  delta[c][d] = sum over the batch of the weighted +-s_n, then
 //             acc = float(double(acc) + delta) and the new squared norms       (<= 2 x D x B adds)
-// All sums are fp64.  Dimensions sit on lanes in both big steps (64 consecutive dimensions of a
+// All sums of the backward step are fp64.  Dimensions sit on lanes there (64 consecutive dimensions of a
 // sample are exactly one 64-bit lane mask, so the +-1 of a lane is one v_cndmask on the mask);
-// fp64 FMA on the vector unit has the same peak as the fp64 matrix path on this chip, so there
-// is nothing to gain from MFMA here.
+// fp64 FMA on the vector unit has the same peak as the fp64 matrix path on this chip.
+#include <algorithm>
 #include <type_traits>
 
 #include "hdc_internal.h"
@@ -18,7 +18,6 @@
 namespace hdc {
 
 typedef const uint32_t __attribute__((address_space(4))) *kptr_u32;
-
 typedef const OnlineWeight __attribute__((address_space(4))) *kptr_w;
 
 constexpr int kFwdWaves = 4;     // waves per forward block
@@ -937,30 +936,44 @@ static FwdShape fwd_shape(int C, int G) {
     return f;
 }
 
+constexpr int kDotSlices = 40;   // at most (finish_cosines reads them all)
+
+// Slices of partial dot products at most, whichever way a call takes.
+static int fwd_slices(int C, int D) { return std::max(fwd_shape(C, (D + kWave - 1) / kWave).slices, row_dots_slices(D, kDotSlices)); }
+
 // Most samples one forward launch takes: bounds the partial-dot-product scratch to 256 MB.
-static int64_t fwd_sub_batch(const FwdShape &f, int C, int64_t limit) {
-    int64_t sb = (int64_t)(256u << 20) / ((int64_t)f.slices * C * (int64_t)sizeof(double));
+static int64_t fwd_sub_batch(int C, int D, int64_t limit) {
+    int64_t sb = (int64_t)(256u << 20) / ((int64_t)fwd_slices(C, D) * C * (int64_t)sizeof(double));
     if (sb > 8192) sb = 8192;
     if (sb < 64) sb = 64;
     return sb > limit ? limit : sb;
 }
 
-static int launch_fwd(hdc_ctx_impl *c, const FwdShape &f, const uint32_t *rows, int64_t nb, const float *acc,
-                      bool norms, hipStream_t s) {
+// Partial dot products of nb samples, *slices of them: in fp64 where there is little to do, because the digits of row_dots.hip take their
+// time whatever comes of them.  Cosine inference, fp64 form / digits, us a call:
+//   D = 1000, 6 classes: 300 samples 8.3 8.9, 2947 9.7 9.0   10000, 6: 16 9.7 10.6, 300 11.9 11.1, 2947 25.3 14.0   10000, 10: 300 13.5 14.0,
+//   2947 37.9 18.5   1000, 26: 300 10.7 15.9, 2947 17.4 16.5   10000, 26: 16 14.7 20.4, 300 22.0 20.8, 2947 77.9 33.1   500, 200: 300 30.3 35.2,
+//   2947 53.3 38.7   5000, 200: 16 43.5 48.3, 300 65.5 51.5, 20000 1289 390
+// (up to eight classes two digits share a tile of columns, which is half the work on both sides).
+static int launch_fwd(hdc_ctx_impl *c, const uint32_t *rows, int64_t nb, const float *acc, bool norms, int *slices, hipStream_t s) {
+    const int C = c->p.C, D = c->p.D;
+    ProfScope prof(c, HDC_K_ONLINE_FWD, s);
+    double *norm = norms ? c->ob_norm_d : nullptr;
+    if (nb * C * D >= (C <= 8 ? 12000000 : 60000000)) return launch_row_dots(c, rows, nb, acc, c->ob_part_d, nb * C, C, 1, norm, kDotSlices, slices, s);
+    const FwdShape f = fwd_shape(C, (D + kWave - 1) / kWave);
+    *slices = f.slices;
     // about four waves per SIMD when there is that much work; whole trips per wave
     int64_t spw = (nb * f.slices * f.chunks + 4095) / 4096;
     spw = (spw + f.ns - 1) / f.ns * f.ns;
     if (spw > 64) spw = 64;
     const int64_t tiles = (nb + kFwdWaves * spw - 1) / (kFwdWaves * spw);
     const dim3 grid((unsigned)f.slices, (unsigned)f.chunks, (unsigned)(tiles + (norms ? 1 : 0)));
-    double *norm = norms ? c->ob_norm_d : nullptr;
-    ProfScope prof(c, HDC_K_ONLINE_FWD, s);
     if (f.wide)
-        hipLaunchKernelGGL((online_fwd_kernel<4, 8>), grid, dim3(kFwdWaves * kWave), 0, s, rows, nb, acc, c->p.D,
-                           c->W, c->p.C, (int)spw, c->ob_part_d, norm);
+        hipLaunchKernelGGL((online_fwd_kernel<4, 8>), grid, dim3(kFwdWaves * kWave), 0, s, rows, nb, acc, D, c->W, C, (int)spw, c->ob_part_d,
+                           norm);
     else
-        hipLaunchKernelGGL((online_fwd_kernel<2, 16>), grid, dim3(kFwdWaves * kWave), 0, s, rows, nb, acc, c->p.D,
-                           c->W, c->p.C, (int)spw, c->ob_part_d, norm);
+        hipLaunchKernelGGL((online_fwd_kernel<2, 16>), grid, dim3(kFwdWaves * kWave), 0, s, rows, nb, acc, D, c->W, C, (int)spw, c->ob_part_d,
+                           norm);
     HDC_HIP(hipGetLastError());
     return HDC_OK;
 }
@@ -977,11 +990,10 @@ int launch_norm(hdc_ctx_impl *c, const float *acc, int G, hipStream_t s) {
 static int reserve_pieces(hdc_ctx_impl *c, int64_t batch) {
     const int C = c->p.C, D = c->p.D;
     const int G = (D + kWave - 1) / kWave;
-    const FwdShape f = fwd_shape(C, G);
-    const int64_t sb = fwd_sub_batch(f, C, batch);
+    const int64_t sb = fwd_sub_batch(C, D, batch);
     const int64_t ld = (sb + kTileSamples - 1) / kTileSamples * kTileSamples;
     HDC_HIP(hipSetDevice(c->device));
-    int rc = grow(&c->ob_part_d, &c->ob_part_bytes, (size_t)f.slices * sb * C * sizeof(double));
+    int rc = grow(&c->ob_part_d, &c->ob_part_bytes, (size_t)fwd_slices(C, D) * sb * C * sizeof(double));
     if (rc == HDC_OK) rc = grow(&c->ob_wts_d, &c->ob_wts_bytes, (size_t)ld * sizeof(OnlineWeight));
     if (rc == HDC_OK) rc = grow(&c->ob_col_d, &c->ob_col_bytes, (size_t)(G + 3) * ld * sizeof(uint64_t));
     const int cb = bwd_dense_width(C);
@@ -1011,11 +1023,10 @@ int reserve_online_batched(hdc_ctx_impl *c, int64_t batch) {
 
 // Scratch of hdc_search_cosine for calls of up to `queries` queries.
 int reserve_search_cosine(hdc_ctx_impl *c, int64_t queries) {
-    const int C = c->p.C, G = (c->p.D + kWave - 1) / kWave;
-    const FwdShape f = fwd_shape(C, G);
-    const int64_t sb = fwd_sub_batch(f, C, queries);
+    const int C = c->p.C, D = c->p.D, G = (D + kWave - 1) / kWave;
+    const int64_t sb = fwd_sub_batch(C, D, queries);
     HDC_HIP(hipSetDevice(c->device));
-    int rc = grow(&c->ob_part_d, &c->ob_part_bytes, (size_t)f.slices * sb * C * sizeof(double));
+    int rc = grow(&c->ob_part_d, &c->ob_part_bytes, (size_t)fwd_slices(C, D) * sb * C * sizeof(double));
     if (rc == HDC_OK) rc = grow(&c->ob_norm_d, &c->ob_norm_bytes, (size_t)C * G * sizeof(double));
     return rc;
 }
@@ -1024,7 +1035,6 @@ int launch_train_online_batched(hdc_ctx_impl *c, const uint32_t *hv, const int32
                                 int32_t epochs, float lr, int64_t batch, float *acc, hipStream_t s) {
     const int C = c->p.C, D = c->p.D, W = c->W;
     const int G = (D + kWave - 1) / kWave;
-    const FwdShape f = fwd_shape(C, G);
     if (batch > N) batch = N;
     int rc = HDC_OK;
     const bool pays = online_chain_pays(c, N, batch);
@@ -1041,7 +1051,7 @@ int launch_train_online_batched(hdc_ctx_impl *c, const uint32_t *hv, const int32
 
     // A batch is worked off in pieces of at most `sb` samples (forward, weights, backward each);
     // sb bounds the scratch: partial dot products and transposed masks.
-    const int64_t sb = fwd_sub_batch(f, C, batch);
+    const int64_t sb = fwd_sub_batch(C, D, batch);
     const int cb = bwd_dense_width(C);
     rc = reserve_pieces(c, batch);
     if (rc != HDC_OK) return rc;
@@ -1069,14 +1079,15 @@ int launch_train_online_batched(hdc_ctx_impl *c, const uint32_t *hv, const int32
             for (int64_t s0 = 0; s0 < B; s0 += sb) {
                 const int64_t nb = s0 + sb < B ? sb : B - s0;
                 const uint32_t *rows = hv + (b0 + s0) * W;
-                rc = launch_fwd(c, f, rows, nb, acc, false, s);
+                int slices;
+                rc = launch_fwd(c, rows, nb, acc, false, &slices, s);
                 if (rc != HDC_OK) return rc;
                 const int64_t ld_used = (nb + kTileSamples - 1) / kTileSamples * kTileSamples;
                 const int cp = cosine_group(C);
                 const int wblocks = (int)((ld_used + 256 / cp - 1) / (256 / cp));
                 const int tblocks = (int)(ld_used / kTileSamples) * ttiles;
                 hipLaunchKernelGGL(online_weights_kernel, dim3((unsigned)(wblocks + tblocks)), dim3(256),
-                                   (size_t)C * sizeof(double), s, c->ob_part_d, f.slices, nb, labels + b0 + s0,
+                                   (size_t)C * sizeof(double), s, c->ob_part_d, slices, nb, labels + b0 + s0,
                                    c->ob_norm_d, G, C, root_d, lr, static_cast<OnlineWeight *>(c->ob_wts_d),
                                    cb && !bwd_by_lists(C, nb) ? c->ob_coef_d : nullptr, cb, cp, wblocks, rows, W,
                                    c->ob_col_d, ld_used,
@@ -1094,18 +1105,18 @@ int launch_search_cosine(hdc_ctx_impl *c, const uint32_t *hv, int64_t N, const f
                          int32_t *pred, hipStream_t s) {
     const int C = c->p.C, D = c->p.D, W = c->W;
     const int G = (D + kWave - 1) / kWave;
-    const FwdShape f = fwd_shape(C, G);
-    const int64_t sb = fwd_sub_batch(f, C, N);
+    const int64_t sb = fwd_sub_batch(C, D, N);
     int rc = reserve_search_cosine(c, N);
     if (rc != HDC_OK) return rc;
     const double root_d = sqrt((double)D);
     for (int64_t n0 = 0; n0 < N; n0 += sb) {
         const int64_t nb = n0 + sb < N ? sb : N - n0;
-        rc = launch_fwd(c, f, hv + n0 * W, nb, acc, n0 == 0, s);
+        int slices;
+        rc = launch_fwd(c, hv + n0 * W, nb, acc, n0 == 0, &slices, s);
         if (rc != HDC_OK) return rc;
         const int cp = cosine_group(C);
         hipLaunchKernelGGL(cosine_finish_kernel, dim3((unsigned)((nb + 256 / cp - 1) / (256 / cp))), dim3(256),
-                           (size_t)C * sizeof(double), s, c->ob_part_d, f.slices, nb, c->ob_norm_d, G, C, root_d, cp,
+                           (size_t)C * sizeof(double), s, c->ob_part_d, slices, nb, c->ob_norm_d, G, C, root_d, cp,
                            cos_out ? cos_out + n0 * C : nullptr, pred + n0);
         HDC_HIP(hipGetLastError());
     }

@@ -1210,13 +1210,6 @@ void launch_strips(hdc_ctx_impl *c, int64_t n, int64_t ld, int block, int16_t *s
                        nullptr, nullptr);
 }
 
-void launch_dots(hdc_ctx_impl *c, const uint64_t *col, int64_t ld, int nb, const float *acc, int slice, double *part, int span,
-                 hipStream_t s) {
-    const int C = c->p.C, D = c->p.D, slices = (D + slice - 1) / slice;
-    hipLaunchKernelGGL(online_dots_kernel, dim3((unsigned)slices, (unsigned)((nb + 15) / 16), (unsigned)((C + 15) / 16)),
-                       dim3(kDotWaves * kWave), 0, s, col, ld, nb, acc, D, C, slice, slices, nullptr, nullptr, 0, part, span);
-}
-
 bool online_chain_takes(const hdc_ctx_impl *c) { return c->p.C <= 4 * kChainMaxWaves && c->p.D <= 65535; }
 
 // A block of 256 samples costs as much as this many batches the other way, three launches each.  The fewer the
@@ -1269,7 +1262,7 @@ static bool wide_takes(const hdc_ctx_impl *c, int64_t N, int32_t epochs, float l
            (C <= 4 || 3 * N >= 2 * kChainBlock * (C <= kWideWaves ? 1 : blocks)) && fabsf(lr) < kTameRate;
 }
 
-int reserve_online_chain(hdc_ctx_impl *c) {
+static int reserve_blocks(hdc_ctx_impl *c) {
     if (c->oc_ready) return HDC_OK;
     const int C = c->p.C, D = c->p.D;
     const int G = (D + kWave - 1) / kWave, slice = chain_slice(D), slices = (D + slice - 1) / slice;
@@ -1304,11 +1297,21 @@ int reserve_online_chain(hdc_ctx_impl *c) {
     return rc;
 }
 
+// (Long calls go in blocks of 256 where the memory for longer ones cannot be had.)
+int reserve_online_chain(hdc_ctx_impl *c) {
+    if (c->oc_ready && c->os_ready) return HDC_OK;
+    int rc = reserve_blocks(c);
+    if (rc == HDC_OK) {
+        rc = reserve_online_spread(c);
+        if (rc == HDC_ENOMEM) rc = HDC_OK;
+    }
+    return rc;
+}
+
 bool online_chain_ready(hdc_ctx_impl *c, hipStream_t s, int *rc) {
     *rc = HDC_OK;
     if (!online_chain_takes(c)) return false;
     if (!c->oc_ready && !stream_captured(s)) *rc = reserve_online_chain(c);
-    if (*rc == HDC_OK && c->oc_ready && !c->os_ready && !stream_captured(s)) *rc = reserve_online_spread(c);
     if (*rc == HDC_ENOMEM) *rc = HDC_OK;
     return c->oc_ready;
 }

@@ -18,6 +18,7 @@ namespace {
 
 constexpr int kOwn = kStripCols;          // samples of a workgroup: a lane to each in every row of 16 lanes
 constexpr int kGroups = kSpan / kOwn;     // most workgroups of a block
+constexpr int kDotSlices = 20;           // of the dot products, at most
 constexpr int kWaves = 16, kThreads = kWaves * kWave;
 constexpr int kHearing = 8, kHeard = kSpan / (kHearing * kWave);   // waves that wait for other workgroups' weights, words of a lane
 constexpr int kLists = 4 * kWaves;        // a row of 16 lanes takes one list of sources
@@ -312,11 +313,11 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
 #pragma unroll
     for (int k = 0; k < CPW; ++k) {
         const int c = min(own_class + k * kWaves, C - 1);
-        double p[3], dot = 0.0;     // (up to kSlices, a quarter to a row of lanes)
+        double p[5], dot = 0.0;     // (kDotSlices at most, a quarter to a row of lanes)
 #pragma unroll
-        for (int i = 0; i < 3; ++i) p[i] = part[((int64_t)min(4 * i + q, slices - 1) * C + c) * kSpan + n0 + l];
+        for (int i = 0; i < 5; ++i) p[i] = part[((int64_t)min(4 * i + q, slices - 1) * C + c) * kSpan + n0 + l];
 #pragma unroll
-        for (int i = 0; i < 3; ++i) dot += 4 * i + q < slices ? p[i] : 0.0;
+        for (int i = 0; i < 5; ++i) dot += 4 * i + q < slices ? p[i] : 0.0;
         start[k] = sum_rows(dot);
         nrm[k] = sum_lanes(nrm[k]);
         if (own_class + k * kWaves < C) {
@@ -584,7 +585,7 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
             break;
         }
         if (s.parting[r & 1]) break;
-        parting = r + 1 == kRounds || (r >= kTryRounds && 3 * s.flips[r & 1] > n0 && n0 >= 4 * kWave);
+        parting = r + 1 == kRounds || (r >= kTryRounds && 2 * s.flips[r & 1] > n0 && n0 >= 4 * kWave);
         wrong_ones = s.wrong[r & 1] != 0;
         if (wrong_ones)
             for (int v = wave; v < classes; v += kWaves) {
@@ -1029,11 +1030,6 @@ __global__ __launch_bounds__(kUpdateWaves *kWave) void online_update_kernel(cons
     }
 }
 
-int spread_slice(int D) {   // dimensions of a slice of the dot products: up to ten, whole groups of 64 per wave
-    constexpr int kUnit = 8 * kWave;
-    return ((D + 9) / 10 + kUnit - 1) / kUnit * kUnit;
-}
-
 constexpr float kTameSpread = 1e30f;   // a learning rate below which no weight overflows
 
 int64_t held_spans(int G) { return std::max<int64_t>(1, std::min<int64_t>(8, held_samples(G) / kSpan)); }
@@ -1058,7 +1054,8 @@ int launch_spread(hdc_ctx_impl *c, const int16_t *strips, int slices, int nb, in
 // What a call needs beside the blocks' scratch (reserve_online_chain).
 int reserve_online_spread(hdc_ctx_impl *c) {
     if (c->os_ready || c->p.C > kMaxClasses) return HDC_OK;
-    const int C = c->p.C, D = c->p.D, G = (D + kWave - 1) / kWave, slice = spread_slice(D), slices = (D + slice - 1) / slice;
+    const int C = c->p.C, D = c->p.D, G = (D + kWave - 1) / kWave;
+    const int slices = row_dots_slices(D, kDotSlices);
     const size_t slot_bytes = (size_t)kRounds * slot_words(C) * sizeof(Word);
     struct { void **at; size_t bytes; } parts[] = {
         {(void **)&c->os_slots_d, slot_bytes + 256},
@@ -1096,7 +1093,7 @@ template <bool BATCH>
 int launch_online_spread(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *labels, int64_t N, int32_t epochs, float lr, int batch,
                          float *acc, hipStream_t s) {
     const int C = c->p.C, D = c->p.D, W = c->W, G = (D + kWave - 1) / kWave;
-    const int slice = spread_slice(D), slices = (D + slice - 1) / slice;
+    int slices;
     ProfScope walk(c, HDC_K_ONLINE, s, !BATCH);   // a walk by samples as a whole; of batches each block's three steps
     ProfScope which(c, HDC_K_ONLINE_WIDE, s, !BATCH && C <= 16), spread(c, HDC_K_ONLINE_SPREAD, s);
     int rc = launch_norm(c, acc, G, s);
@@ -1117,9 +1114,9 @@ int launch_online_spread(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *lab
                 const uint64_t *col = c->oc_col_d + b0;
                 {
                     ProfScope prof(c, HDC_K_ONLINE_FWD, s, BATCH);
-                    launch_dots(c, col, ld, nb, acc, slice, c->os_part_d, kSpan, s);
+                    rc = launch_row_dots(c, hv + (h0 + b0) * W, nb, acc, c->os_part_d, (int64_t)C * kSpan, 1, kSpan, nullptr, kDotSlices, &slices, s);
                 }
-                HDC_HIP(hipGetLastError());
+                if (rc != HDC_OK) return rc;
                 {
                     ProfScope prof(c, HDC_K_ONLINE, s, BATCH);
                     const int16_t *strips = c->os_strips_d + b0 / block * kSpanProducts;

@@ -48,6 +48,12 @@ int launch_online_chain(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *labe
                         float lr, int64_t batch, bool per_sample, float *acc, hipStream_t s);
 
 
+// Partial dot products of nb samples with the rows (row_dots.hip), part[slice * stride + n * step_n + class * step_c], and, where
+// normpart is given, the rows' squared-norm partials.  *slices: how many there are, row_dots_slices at most.
+int row_dots_slices(int D, int most);
+int launch_row_dots(hdc_ctx_impl *c, const uint32_t *hv, int64_t nb, const float *acc, double *part, int64_t stride, int64_t step_n,
+                    int64_t step_c, double *normpart, int most, int *slices, hipStream_t s);
+
 // Calls of many samples in blocks of kSpan, each block's chain spread over kSpan / kStripCols workgroups
 // (online_spread.hip).
 constexpr int kSpan = 2048;         // most samples of a block
@@ -62,13 +68,10 @@ template <bool BATCH>
 int launch_online_spread(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *labels, int64_t N, int32_t epochs, float lr,
                          int batch, float *acc, hipStream_t s);
 
-// Steps of both forms of the block-wise walk (online_chain.hip): the samples' bits by dimension groups (col[group][ld]),
-// the products of `blocks` blocks of up to kSpan samples in strips, and partial dot products part[slice][class][span] of
-// nb samples with the rows.
+// Steps of both forms of the block-wise walk (online_chain.hip): the samples' bits by dimension groups (col[group][ld])
+// and the products of a block's samples in strips.
 int64_t held_samples(int G);
 void launch_columns(hdc_ctx_impl *c, const uint32_t *hv, int64_t n, int64_t ld, hipStream_t s);
 void launch_strips(hdc_ctx_impl *c, int64_t n, int64_t ld, int block, int16_t *strips, hipStream_t s);
-void launch_dots(hdc_ctx_impl *c, const uint64_t *col, int64_t ld, int nb, const float *acc, int slice, double *part, int span,
-                 hipStream_t s);
 
 }  // namespace hdc
