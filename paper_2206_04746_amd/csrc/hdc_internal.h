@@ -115,7 +115,7 @@ struct hdc_ctx_impl {
     void *os_rec_d;       // [2048] weight records of a block
     void *os_slots_d;     // [passes][words] what its workgroups tell one another; zero between calls
     int *os_state_d;      // [2] workgroups that have begun (zero between calls), slots in use
-    bool os_attr_set[6];  // dynamic-LDS limit of online_spread_kernel and online_update_kernel raised, by variant
+    bool os_attr_set[4];  // dynamic-LDS limit of online_spread_kernel raised, by variant
 
     // hdc_encode_sparse (allocated and derived on its first call)
     bool sp_ready;

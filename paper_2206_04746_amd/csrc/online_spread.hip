@@ -935,88 +935,172 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
 }
 
 // ---- the rows ------------------------------------------------------------------------------------
-// A block per group of 64 dimensions, waves deal the classes among them.  A lane keeps one element of a row in a register
-// and takes the updates that name its class in sample order, one fp32 add each (in batches an fp64 sum a batch and one
-// rounding).  The updates are listed first: then 64 of them at a time lie in the lanes' registers, and the loop over them
-// is nothing but lane reads of fixed lanes.  The block clears its share of the slots, too.
-constexpr int kUpdateWaves = 16;
+// A block per group of 64 dimensions, class c is wave c % 16's.  A lane keeps one element of a row in a register and takes the
+// updates that name its class in sample order, one fp32 add each (in batches an fp64 sum a batch and one rounding).
+// The chain of additions is what bounds it, so all else is kept off it: the block lists the updates class after
+// class (as the workgroups of the chain do the samples before), a wave takes 64 of them at a time, turns their
+// 64 x 64 bits so that a lane has those of its dimension, and an update is three instructions, the last of which reads its weight from another
+// lane and adds it: a shift, the sign put on 1.0, a multiply-add (exact: the product is +-weight).  The block clears its share of the slots, too.
+struct UpdateShared {
+    uint2 list[2 * kSpan];             // sample, weight: class after class
+    uint16_t count[kSpan / kWave][kMaxClasses];
+    int total[kMaxClasses];
+};
+
+// A 64 x 64 matrix of bits, row i in lane i's (lo, hi), turned: column i.
+__device__ __forceinline__ void transpose_bits(uint32_t &lo, uint32_t &hi) {
+    const int lane = threadIdx.x & (kWave - 1);
+    {
+        const auto h = __builtin_amdgcn_permlane32_swap(lo, hi, false, false);   // rows 0 to 31; 32 to 63: of dimensions 0 to 31 in the lower lanes
+        lo = h[0];
+        hi = h[1];
+    }
+    const uint32_t pick16 = lane & 16 ? 0x07060302u : 0x05040100u, pick8 = lane & 8 ? 0x03070105u : 0x06020400u;
+    uint32_t *const half[2] = {&lo, &hi};
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        uint32_t x = *half[i];
+        const auto h = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        x = __builtin_amdgcn_perm(h[1], h[0], pick16);
+        const uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x128, 0xF, 0xF, true);   // row_ror:8
+        x = __builtin_amdgcn_perm(y, x, pick8);
+        auto step = [&](uint32_t other, int width, uint32_t keep) {   // the lane that differs in bit `width`
+            const bool up = lane & width;
+            const uint32_t moved = up ? other >> width : other << width, mask = up ? ~keep : keep;
+            x = (x & mask) | (moved & ~mask);
+        };
+        const int mirrored = __builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xF, 0xF, true);           // row_half_mirror: lane ^ 7
+        step((uint32_t)__builtin_amdgcn_update_dpp(0, mirrored, 0x1B, 0xF, 0xF, true), 4, 0x0F0F0F0Fu);   // quad_perm 3,2,1,0: lane ^ 3
+        step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, true), 2, 0x33333333u);     // quad_perm 2,3,0,1
+        step((uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, true), 1, 0x55555555u);     // quad_perm 1,0,3,2
+        *half[i] = x;
+    }
+}
+
+// a += w of lane (16 j + I) x s, in every row of 16 lanes j.
+template <int I>
+__device__ __forceinline__ void add_update(float &a, float w, float s) {
+    asm volatile("s_nop 1\n\t"
+                 "v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(a) : "v"(w), "v"(s), "n"(I));
+}
 
 template <bool BATCH>
-__global__ __launch_bounds__(kUpdateWaves *kWave) void online_update_kernel(const uint64_t *__restrict__ col, int64_t ld, int nb, int batch,
-                                                                            const OnlineWeight *__restrict__ recs, float *acc, int D, int C,
-                                                                            int G, double *__restrict__ normpart, Word *__restrict__ slots,
-                                                                            int *__restrict__ state) {
-    extern __shared__ uint2 lists[];    // [waves][kSpan]: sample, weight
-    const int tid = threadIdx.x, lane = tid & (kWave - 1), g = blockIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = blockDim.x >> 6;
+__global__ __launch_bounds__(kThreads) void online_update_kernel(const uint64_t *__restrict__ col, int64_t ld, int nb, int batch,
+                                                                 const OnlineWeight *__restrict__ recs, float *acc, int D, int C, int G,
+                                                                 double *__restrict__ normpart, Word *__restrict__ slots, int *__restrict__ state) {
+    __shared__ UpdateShared s;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), l = lane & 15, g = blockIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    OnlineWeight r[2];   // of samples tid and tid + kThreads
+#pragma unroll
+    for (int u = 0; u < 2; ++u) r[u] = recs[min(tid + u * kThreads, nb - 1)];
+    const int d = g * kWave + lane;
+    float first = 0.0f;  // the element of the wave's first class
+    if (d < D && wave < C) first = acc[(int64_t)wave * D + d];
+    reinterpret_cast<uint32_t *>(&s.count[0][0])[tid & (kSpan / kWave * kMaxClasses / 2 - 1)] = 0;
     {
         const int64_t words = slot_words(C), used = min(state[1], kRounds - 1) * words, end = (kRounds - 1) * words - used;   // and the last one
-        for (int64_t i = (int64_t)blockIdx.x * blockDim.x + tid; i < used + words; i += (int64_t)gridDim.x * blockDim.x)
+        for (int64_t i = (int64_t)blockIdx.x * kThreads + tid; i < used + words; i += (int64_t)gridDim.x * kThreads)
             slots[i < used ? i : i + end] = 0;
         if (blockIdx.x == 0 && tid == 0) state[0] = 0;
     }
-    uint2 *list = lists + wave * kSpan;
-    const int d = g * kWave + lane;
-    for (int c = wave; c < C; c += waves) {
-        int entries = 0;
-        for (int n0 = 0; n0 < nb; n0 += 4 * kWave) {
-            OnlineWeight r[4];
+    __syncthreads();
+    // numbers within a class's list, of both classes a sample may name
+    int rank[2][2], key[2][2];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) r[u] = recs[min(n0 + u * kWave + lane, nb - 1)];
+    for (int u = 0; u < 2; ++u) {
+        const bool in = tid + u * kThreads < nb;
+        key[u][0] = in && r[u].y >= 0 && r[u].w_y != 0.0f ? r[u].y : -1;
+        key[u][1] = in && r[u].pred >= 0 && r[u].w_p != 0.0f ? r[u].pred : -1;
+        uint64_t named[2] = {__ballot(key[u][0] >= 0), __ballot(key[u][1] >= 0)}, with[2][2] = {{named[0], named[1]}, {named[0], named[1]}};
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int n = n0 + u * kWave + lane;
-                const float w = r[u].y == c ? r[u].w_y : r[u].pred == c ? -r[u].w_p : 0.0f;
-                const uint64_t named = __ballot(w != 0.0f && n < nb);
-                if (w != 0.0f && n < nb) list[entries + __popcll(named & ((1ull << lane) - 1))] = make_uint2((uint32_t)n, __float_as_uint(w));
-                entries += __popcll(named);
+        for (int b = 0; b < 5; ++b)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const uint64_t m = __ballot(key[u][j] >> b & 1);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) with[i][j] &= key[u][i] >> b & 1 ? m : ~m;
             }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint64_t same = with[i][0] | with[i][1];   // samples that name the class
+            rank[u][i] = __popcll(same & ((1ull << lane) - 1));
+            if (key[u][i] >= 0 && rank[u][i] == 0) s.count[wave + u * kWaves][key[u][i]] = (uint16_t)__popcll(same);
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        float a = d < D ? acc[(int64_t)c * D + d] : 0.0f;
+    }
+    __syncthreads();
+    for (int c = wave; c < C; c += kWaves) {
+        const int x = lane < kSpan / kWave ? s.count[lane][c] : 0, sum = lane_sum(x);
+        if (lane < kSpan / kWave) s.count[lane][c] = (uint16_t)(sum - x);
+        if (lane == kWave - 1) s.total[c] = sum;
+    }
+    __syncthreads();
+    const int total = lane < C ? s.total[lane] : 0, end = lane_sum(total);
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int at = __shfl(end - total, max(key[u][i], 0), kWave);
+            if (key[u][i] >= 0)
+                s.list[at + s.count[wave + u * kWaves][key[u][i]] + rank[u][i]] =
+                    make_uint2((uint32_t)(tid + u * kThreads), __float_as_uint(i ? -r[u].w_p : r[u].w_y));
+        }
+    __syncthreads();
+    for (int c = wave; c < C; c += kWaves) {
+        const int entries = __builtin_amdgcn_readlane(total, c);
+        const uint2 *list = s.list + __builtin_amdgcn_readlane(end, c) - entries;
+        float a = c == wave ? first : d < D ? acc[(int64_t)c * D + d] : 0.0f;
         double delta = 0.0;
-        auto fetch = [&](int e0, uint2 &x, uint64_t &bits) {   // past the end weight 0
-            const int e = min(e0 + lane, entries - 1);
-            x = list[e];
-            bits = col[(int64_t)g * ld + x.x];
-            if (e0 + lane >= entries) x.y = 0;
-        };
-        uint2 x = make_uint2(0, 0);
         uint64_t bits = 0;
-        if (entries) fetch(0, x, bits);
+        if (entries) bits = col[(int64_t)g * ld + list[min(lane, entries - 1)].x];
         for (int e0 = 0; e0 < entries; e0 += kWave) {
-            const uint2 now = x;
-            const uint64_t sign = bits;
-            if (e0 + kWave < entries) fetch(e0 + kWave, x, bits);
-            const int lo = (int)(uint32_t)sign, hi = (int)(uint32_t)(sign >> 32);
+            uint32_t lo = ~(uint32_t)bits, hi = ~(uint32_t)(bits >> 32);   // set: subtract
+            if (e0 + kWave < entries) bits = col[(int64_t)g * ld + list[min(e0 + kWave + lane, entries - 1)].x];
+            float w[4];   // 16 entries in every row of lanes; past the end weight 0
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint2 x = list[min(e0 + 16 * i + l, entries - 1)];
+                w[i] = e0 + 16 * i + l < entries ? __uint_as_float(x.y) : 0.0f;
+            }
             uint64_t ends = 0;     // (batches) entries after which another batch begins
             if (BATCH) {
-                const int after = e0 + lane + 1 < entries ? (int)list[e0 + lane + 1].x / batch : -1;
-                ends = __ballot((int)now.x / batch != after && e0 + lane < entries);
+                const int e = min(e0 + lane, entries - 1);
+                ends = __ballot(e0 + lane < entries && (e + 1 == entries || (int)list[e].x / batch != (int)list[min(e + 1, entries - 1)].x / batch));
             }
+            transpose_bits(lo, hi);
+            each<4>([&](auto i_) {
+                constexpr int i = decltype(i_)::value;
+                if (e0 + 16 * i < entries) {   // uniform
+                    const uint32_t m = i < 2 ? lo : hi;
+                    if constexpr (BATCH) {
+                        const double w64 = (double)w[i];
+                        const uint32_t stops = (uint32_t)(ends >> (16 * i));
+                        each<4>([&](auto j_) {
+                            constexpr int j = 4 * decltype(j_)::value;
+                            double x[4];
 #pragma unroll
-            for (int u0 = 0; u0 < kWave; u0 += 8) {
-                if (e0 + u0 < entries) {   // uniform
-#pragma unroll
-                    for (int u = u0; u < u0 + 8; ++u) {
-                        const uint64_t mask = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(lo, u) |
-                                              (uint64_t)(uint32_t)__builtin_amdgcn_readlane(hi, u) << 32;
-                        const float v = lane_f32(__uint_as_float(now.y), u);
-                        const float t = __builtin_amdgcn_inverse_ballot_w64(mask) ? v : -v;
-                        if constexpr (BATCH) {
-                            delta += (double)t;
-                            if (ends >> u & 1) {   // uniform
-                                a = (float)((double)a + delta);
-                                delta = 0.0;
-                            }
-                        } else {
-                            a = __fadd_rn(a, t);
-                        }
+                            for (int u = 0; u < 4; ++u)
+                                x[u] = __hiloint2double((int)((m << (31 - (16 * (i & 1) + j + u)) & 0x80000000u) | 0x3FF00000u), 0);
+                            if (stops >> j & 15)
+                                each<4>([&](auto u_) {
+                                    constexpr int u = decltype(u_)::value;
+                                    add_rows<j + u, 1>(delta, w64, x + u);
+                                    if (stops >> (j + u) & 1) {   // uniform
+                                        a = (float)((double)a + delta);
+                                        delta = 0.0;
+                                    }
+                                });
+                            else
+                                add_rows<j, 4>(delta, w64, x);
+                        });
+                    } else {
+                        each<16>([&](auto u_) {
+                            constexpr int u = decltype(u_)::value;
+                            add_update<u>(a, w[i], __uint_as_float((m << (31 - (16 * (i & 1) + u)) & 0x80000000u) | 0x3F800000u));
+                        });
                     }
                 }
-            }
+            });
         }
         double p = 0.0;
         if (d < D) {
@@ -1025,8 +1109,6 @@ __global__ __launch_bounds__(kUpdateWaves *kWave) void online_update_kernel(cons
         }
         p = lane_prefix(p);
         if (lane == kWave - 1) normpart[(int64_t)c * G + g] = p;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();   // the list is rewritten for the next class
     }
 }
 
@@ -1126,15 +1208,9 @@ int launch_online_spread(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *lab
                 if (rc != HDC_OK) return rc;
                 {
                     ProfScope prof(c, HDC_K_ONLINE_BWD, s, BATCH);
-                    const int waves = std::min(std::max(C, 4), 8);
-                    if (!c->os_attr_set[4 + BATCH]) {
-                        HDC_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(online_update_kernel<BATCH>),
-                                                    hipFuncAttributeMaxDynamicSharedMemorySize, 8 * kSpan * (int)sizeof(uint2)));
-                        c->os_attr_set[4 + BATCH] = true;
-                    }
-                    hipLaunchKernelGGL(online_update_kernel<BATCH>, dim3((unsigned)G), dim3((unsigned)(waves * kWave)), (size_t)waves * kSpan * sizeof(uint2), s,
-                                       col, ld, nb, batch, static_cast<const OnlineWeight *>(c->os_rec_d), acc, D, C, G, c->ob_norm_d,
-                                       (Word *)c->os_slots_d, c->os_state_d);
+                    hipLaunchKernelGGL(online_update_kernel<BATCH>, dim3((unsigned)G), dim3(kThreads), 0, s, col, ld, nb, batch,
+                                       static_cast<const OnlineWeight *>(c->os_rec_d), acc, D, C, G, c->ob_norm_d, (Word *)c->os_slots_d,
+                                       c->os_state_d);
                 }
                 HDC_HIP(hipGetLastError());
             }
