@@ -28,7 +28,9 @@ constexpr int kListGroups = kSteps / kRunGroup;
 constexpr int kNone = kSpan;              // a source that is none: its weight is zero
 constexpr int kMaxClasses = 32;
 constexpr int kRounds = 49;               // slots: passes that the workgroups take together, at most, and one for the end
-constexpr int kTryRounds = 4;             // passes after which predictions that still change say that it takes many
+// Where most predictions still change after this pass they are mostly wrong, and a pass settles few samples.  (From zero rows of related classes
+// they change later, a third of them and for some passes only: 2048 samples, 6 classes 18 passes, 110 us against 510 one after another.)
+constexpr int kTryRounds = 4;
 constexpr int kSpinLimit = 1 << 24;       // loads of one word before a wait is given up (never: see wait_for)
 static_assert(kOwn * (kGroups - 1) + (kRunGroup - 1) * 2 * kMaxClasses <= kLists * kSteps, "room in the lists");
 
@@ -371,6 +373,67 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
         return;
     }
     const bool zero_model = __ballot(lane < kWaves && !s.zero[lane & (kWaves - 1)]) == 0;
+    bool changed = false, parting = false; // (the deciding wave's) a weight, in this pass; this workgroup goes on alone
+    const int decider = kWaves - 1;
+    // Weights from the cosines.  (guess: labels count as predictions, where rows of zeros would say class 0 of every sample.
+    // The passes end in the same place from any start.)
+    auto decide = [&](bool guess) {
+        const int2 of = s.own_class[l];
+        const double2 w = s.own_w[l];
+        const double cos_y = s.cosine[max(of.x, 0)][l];
+        double best = -4.0;
+        int arg = 0;
+        for (int c0 = 0; c0 < C; c0 += 8) {   // eight at a time (the last one repeats: it cannot win twice)
+            double v[8];
+            int at[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                v[u] = s.cosine[min(c0 + u, C - 1)][l];
+                at[u] = c0 + u;
+            }
+#pragma unroll
+            for (int step = 1; step < 8; step *= 2)
+#pragma unroll
+                for (int u = 0; u < 8; u += 2 * step) {
+                    const bool other = v[u + step] > v[u];
+                    v[u] = other ? v[u + step] : v[u];
+                    at[u] = other ? at[u + step] : at[u];
+                }
+            const bool better = v[0] > best;
+            best = better ? v[0] : best;
+            arg = better ? at[0] : arg;
+        }
+        const bool wrong = (of.x >= 0) & (arg != of.x) & !guess;
+        const double wy = of.x >= 0 ? (double)(float)(1.0 - cos_y) : 0.0, wp = wrong ? -(double)(float)((double)lr * (1.0 - best)) : 0.0;
+        const int pred = wrong ? arg : -1;
+        changed = __ballot(wy != w.x || wp != w.y || pred != of.y) != 0;
+        if (lane < kOwn) {
+            s.own_class[l] = make_int2(of.x, pred);
+            s.own_w[l] = make_double2(wy, wp);
+        }
+        if (lane == 0) s.own_changed = changed;
+    };
+    auto tell_weights = [&](Word *slot) {
+        const int pred = s.own_class[l].y;
+        const double2 w = s.own_w[l];
+        if (lane < kOwn) {
+            if (pred >= 0) tell(slot + kSpan + n0 + l, 1ull << 32 | __float_as_uint((float)-w.y));
+            tell(slot + n0 + l, 1ull << 63 | (Word)((changed ? 0x100 : 0) | (parting ? 0x200 : 0)) << 32 | (Word)(pred + 1) << 32 | __float_as_uint((float)w.x));
+        }
+    };
+    const int64_t words = slot_words(C);
+    // The first pass: no sample of the block counts yet.  Told before the lists are made, it is there when they are.
+#pragma unroll
+    for (int k = 0; k < CPW; ++k)
+        if (own_class + k * kWaves < C && q == 0) s.cosine[own_class + k * kWaves][l] = cosine_of(start[k], nrm[k], inv_root_d);
+    __syncthreads();
+    if (wave == decider) {
+        decide(zero_model);
+        changed = true;
+        if (lane == 0) s.own_changed = 1;
+        tell_weights(slots);
+    }
+
     for (int v = wave; v < classes; v += kWaves) {
         const int x = lane < kSpan / kWave ? sort.count[lane][v] : 0, sum = lane_sum(x);
         if (lane < kSpan / kWave) sort.count[lane][v] = (uint16_t)(sum - x);
@@ -449,7 +512,6 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
     const double dd = (double)D;
 
     // ---- passes, all workgroups together
-    bool changed = false, parting = false; // (the deciding wave's) a weight, in this pass; this workgroup goes on alone
     double grown[CPW][2] = {};             // of workgroups lane and lane + 64, as last heard
     double open[CPW] = {};                 // (batches) of the one the open batch begins in, up to there
     const int open_group = first_open / kOwn;
@@ -457,67 +519,7 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
     int wrong_per = 1;
     bool wrong_ones = false;
     int front = 0;                         // workgroups before this one are done: their weights have stopped changing
-    const int decider = kWaves - 1;
     auto wrong_key = [&](int n, int wrong) { return max(wrong, 0) + (BATCH && n >= first_open ? C : 0); };
-    // Weights from the cosines.  (guess: labels count as predictions, where rows of zeros would say class 0 of every sample.
-    // The passes end in the same place from any start.)
-    auto decide = [&](bool guess) {
-        const int2 of = s.own_class[l];
-        const double2 w = s.own_w[l];
-        const double cos_y = s.cosine[max(of.x, 0)][l];
-        double best = -4.0;
-        int arg = 0;
-        for (int c0 = 0; c0 < C; c0 += 8) {   // eight at a time (the last one repeats: it cannot win twice)
-            double v[8];
-            int at[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                v[u] = s.cosine[min(c0 + u, C - 1)][l];
-                at[u] = c0 + u;
-            }
-#pragma unroll
-            for (int step = 1; step < 8; step *= 2)
-#pragma unroll
-                for (int u = 0; u < 8; u += 2 * step) {
-                    const bool other = v[u + step] > v[u];
-                    v[u] = other ? v[u + step] : v[u];
-                    at[u] = other ? at[u + step] : at[u];
-                }
-            const bool better = v[0] > best;
-            best = better ? v[0] : best;
-            arg = better ? at[0] : arg;
-        }
-        const bool wrong = (of.x >= 0) & (arg != of.x) & !guess;
-        const double wy = of.x >= 0 ? (double)(float)(1.0 - cos_y) : 0.0, wp = wrong ? -(double)(float)((double)lr * (1.0 - best)) : 0.0;
-        const int pred = wrong ? arg : -1;
-        changed = __ballot(wy != w.x || wp != w.y || pred != of.y) != 0;
-        if (lane < kOwn) {
-            s.own_class[l] = make_int2(of.x, pred);
-            s.own_w[l] = make_double2(wy, wp);
-        }
-        if (lane == 0) s.own_changed = changed;
-    };
-    auto tell_weights = [&](Word *slot) {
-        const int pred = s.own_class[l].y;
-        const double2 w = s.own_w[l];
-        if (lane < kOwn) {
-            if (pred >= 0) tell(slot + kSpan + n0 + l, 1ull << 32 | __float_as_uint((float)-w.y));
-            tell(slot + n0 + l, 1ull << 63 | (Word)((changed ? 0x100 : 0) | (parting ? 0x200 : 0)) << 32 | (Word)(pred + 1) << 32 | __float_as_uint((float)w.x));
-        }
-    };
-    const int64_t words = slot_words(C);
-    // the first pass: no sample of the block counts yet
-#pragma unroll
-    for (int k = 0; k < CPW; ++k)
-        if (own_class + k * kWaves < C && q == 0) s.cosine[own_class + k * kWaves][l] = cosine_of(start[k], nrm[k], inv_root_d);
-    __syncthreads();
-    if (wave == decider) {
-        decide(zero_model);
-        changed = true;
-        if (lane == 0) s.own_changed = 1;
-        tell_weights(slots);
-    }
-
     bool done = false;
     int r = 1;
     for (; r < kRounds; ++r) {
@@ -585,7 +587,7 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
             break;
         }
         if (s.parting[r & 1]) break;
-        parting = r + 1 == kRounds || (r >= kTryRounds && 2 * s.flips[r & 1] > n0 && n0 >= 4 * kWave);
+        parting = r + 1 == kRounds || (r == kTryRounds && 2 * s.flips[r & 1] > n0 && n0 >= 4 * kWave);
         wrong_ones = s.wrong[r & 1] != 0;
         if (wrong_ones)
             for (int v = wave; v < classes; v += kWaves) {
