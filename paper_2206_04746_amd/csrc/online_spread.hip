@@ -979,6 +979,10 @@ __device__ __forceinline__ void transpose_bits(uint32_t &lo, uint32_t &hi) {
     }
 }
 
+__device__ __forceinline__ uint32_t signed_one(uint32_t bits, uint32_t sign, uint32_t one) {
+    return __builtin_amdgcn_bitop3_b32(bits, sign, one, 0xEA);   // bits & sign | one
+}
+
 // a += w of lane (16 j + I) x s, in every row of 16 lanes j.
 template <int I>
 __device__ __forceinline__ void add_update(float &a, float w, float s) {
@@ -1048,6 +1052,9 @@ __global__ __launch_bounds__(kThreads) void online_update_kernel(const uint64_t 
                     make_uint2((uint32_t)(tid + u * kThreads), __float_as_uint(i ? -r[u].w_p : r[u].w_y));
         }
     __syncthreads();
+    uint32_t sign = 0x80000000u, one = BATCH ? 0x3FF00000u : 0x3F800000u;   // 1.0's upper word, 1.0f
+    asm volatile("" : "+v"(sign), "+v"(one));   // (in registers: an instruction takes one constant at most)
+    const uint32_t inverse = ((1u << 20) + batch - 1) / batch;   // samples' batches: numbers below 2048, by up to 512
     for (int c = wave; c < C; c += kWaves) {
         const int entries = __builtin_amdgcn_readlane(total, c);
         const uint2 *list = s.list + __builtin_amdgcn_readlane(end, c) - entries;
@@ -1067,7 +1074,8 @@ __global__ __launch_bounds__(kThreads) void online_update_kernel(const uint64_t 
             uint64_t ends = 0;     // (batches) entries after which another batch begins
             if (BATCH) {
                 const int e = min(e0 + lane, entries - 1);
-                ends = __ballot(e0 + lane < entries && (e + 1 == entries || (int)list[e].x / batch != (int)list[min(e + 1, entries - 1)].x / batch));
+                const uint32_t here = list[e].x * inverse >> 20, after = list[min(e + 1, entries - 1)].x * inverse >> 20;
+                ends = __ballot(e0 + lane < entries && (e + 1 == entries || here != after));
             }
             transpose_bits(lo, hi);
             each<4>([&](auto i_) {
@@ -1082,12 +1090,13 @@ __global__ __launch_bounds__(kThreads) void online_update_kernel(const uint64_t 
                             double x[4];
 #pragma unroll
                             for (int u = 0; u < 4; ++u)
-                                x[u] = __hiloint2double((int)((m << (31 - (16 * (i & 1) + j + u)) & 0x80000000u) | 0x3FF00000u), 0);
+                                x[u] = __hiloint2double((int)signed_one(m << (31 - (16 * (i & 1) + j + u)), sign, one), 0);
                             if (stops >> j & 15)
                                 each<4>([&](auto u_) {
                                     constexpr int u = decltype(u_)::value;
                                     add_rows<j + u, 1>(delta, w64, x + u);
                                     if (stops >> (j + u) & 1) {   // uniform
+                                        asm volatile("");         // (a branch: selects would be on every addition's way)
                                         a = (float)((double)a + delta);
                                         delta = 0.0;
                                     }
@@ -1098,7 +1107,7 @@ __global__ __launch_bounds__(kThreads) void online_update_kernel(const uint64_t 
                     } else {
                         each<16>([&](auto u_) {
                             constexpr int u = decltype(u_)::value;
-                            add_update<u>(a, w[i], __uint_as_float((m << (31 - (16 * (i & 1) + u)) & 0x80000000u) | 0x3F800000u));
+                            add_update<u>(a, w[i], __uint_as_float(signed_one(m << (31 - (16 * (i & 1) + u)), sign, one)));
                         });
                     }
                 }
