@@ -7,7 +7,7 @@
 // at random 8; with all of them, where predictions are mostly wrong, 140 to 170, which is fewer by the sample than blocks
 // of 256 take).  So a pass is spread over the chip and the block made long:
 //   online_gram_kernel   once per call: <s_n, s_m> of all pairs of a block, in strips of 16 columns
-//   online_dots_kernel   per block: <acc_c, s_m> against the rows as they stand
+//   row_dots_kernel      per block: <acc_c, s_m> against the rows as they stand
 //   online_spread_kernel per block: cosines, predictions and weights of all samples
 //   online_update_kernel per block: the updates, element by element in sample order, and the rows' squared norms
 #include "online_lanes.h"
@@ -28,9 +28,6 @@ constexpr int kListGroups = kSteps / kRunGroup;
 constexpr int kNone = kSpan;              // a source that is none: its weight is zero
 constexpr int kMaxClasses = 32;
 constexpr int kRounds = 49;               // slots: passes that the workgroups take together, at most, and one for the end
-// Where most predictions still change after this pass they are mostly wrong, and a pass settles few samples.  (From zero rows of related classes
-// they change later, a third of them and for some passes only: 2048 samples, 6 classes 18 passes, 110 us against 510 one after another.)
-constexpr int kTryRounds = 4;
 constexpr int kSpinLimit = 1 << 24;       // loads of one word before a wait is given up (never: see wait_for)
 static_assert(kOwn * (kGroups - 1) + (kRunGroup - 1) * 2 * kMaxClasses <= kLists * kSteps, "room in the lists");
 
@@ -587,7 +584,14 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
             break;
         }
         if (s.parting[r & 1]) break;
-        parting = r + 1 == kRounds || (r == kTryRounds && 2 * s.flips[r & 1] > n0 && n0 >= 4 * kWave);
+        // Where most predictions change at the second or third pass they are mostly wrong, and a pass settles few samples: the
+        // workgroups go on one after another (no passes tried: 1585 us; all of them first, 1685: 4000 samples of 6 classes,
+        // labels at random).  From zero rows of classes that are like one another predictions change from the fourth pass on,
+        // and settle by the eighteenth: 110 us for the first 2048 samples, 510 one workgroup after another.  They change among
+        // the earliest first, so that few samples before a workgroup say nothing (9 classes, 2197 samples, D = 2115: 310 us, and
+        // 775 where a workgroup after 256 samples asked at the fourth pass).
+        parting = r + 1 == kRounds || (r == 2 && 4 * s.flips[0] > 3 * n0 && n0 >= 4 * kWave) ||
+                  (r == 3 && 2 * s.flips[1] > n0 && n0 >= 8 * kWave);
         wrong_ones = s.wrong[r & 1] != 0;
         if (wrong_ones)
             for (int v = wave; v < classes; v += kWaves) {
@@ -1172,14 +1176,20 @@ int reserve_online_spread(hdc_ctx_impl *c) {
     return HDC_OK;
 }
 
-// Calls of more samples than a few blocks of 256 hold; in batches those that a call of three launches a batch is slower at, and, of
-// more than 16 classes, batches of at least a workgroup's samples.
+// Calls of more samples than a few blocks of 256 hold (batch 0: per sample).  A batch costs three launches of its own otherwise,
+// about 14 us, and here a call about 100 us and each block 70, whatever the batch: so many batches it must have.  (Here against
+// three launches a batch, us, D = 2000 and 3 classes: 2000 samples in 16 batches 170 and 204, in 11 178 and 148; 8000 in 32 378
+// and 466; 4000 in 16 234 and 230; 1100 in 18, of 12 classes, 184 and 173.)  With more than 16 classes a wave takes two, and batches
+// are those that fill a workgroup (1000 dimensions, 32 classes, 4100 samples in batches of 5: 2092 as before).
 bool online_spread_pays(const hdc_ctx_impl *c, int64_t N, int64_t batch) {
-    return c->p.C <= kMaxClasses && c->p.D <= 65535 && N > 1024 && batch <= 256 && (c->p.C <= kWaves || batch >= kOwn);
+    if (c->p.C > kMaxClasses || c->p.D > 65535 || N <= 1024) return false;
+    if (batch == 0) return true;
+    const bool few = c->p.C <= kWaves;
+    return batch <= 256 && N >= (few ? 1280 : 1536) && N >= (8 + 5 * ((N + kSpan - 1) / kSpan)) * batch && (few || batch >= kOwn);
 }
 
 bool online_spread_takes(const hdc_ctx_impl *c, int64_t N, float lr, int64_t batch, bool per_sample) {
-    return c->os_ready && online_spread_pays(c, N, per_sample ? kOwn : batch) && fabsf(lr) < kTameSpread;
+    return c->os_ready && online_spread_pays(c, N, per_sample ? 0 : batch) && fabsf(lr) < kTameSpread;
 }
 
 template <bool BATCH>

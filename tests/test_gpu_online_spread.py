@@ -28,6 +28,12 @@ def train(ctx, hvd, yd, acc, batch, epochs, lr=1.0):
     return ctx.hdc_profile_read("online_spread")[1]
 
 
+def goes(C, N, batch):
+    """In blocks of 2048: per sample, and where there are enough batches for what a block costs."""
+    few = C <= 16
+    return batch == 0 or (batch <= 256 and N >= max(1280 if few else 1536, (8 + 5 * -(-N // 2048)) * batch) and (few or batch >= 16))
+
+
 def want(hv, y, D, C, batch, epochs, lr=1.0, acc=None):
     if batch:
         return oracle.train_online_batched(hv, y, D, C, batch, epochs=epochs, lr=lr, acc=acc)
@@ -36,8 +42,8 @@ def want(hv, y, D, C, batch, epochs, lr=1.0, acc=None):
 
 # one workgroup more than 1024 samples, edges of a workgroup's 16 samples, of a block and the next; classes at one and two a
 # wave and the most of them; small, odd and large D
-@pytest.mark.parametrize("batch", [0, 1, 7, 16, 17, 64, 85, 200])
-@pytest.mark.parametrize("D,C,N", [(64, 1, 1025), (1000, 2, 1040), (1001, 5, 2047), (2049, 16, 2048), (640, 17, 2049), (640, 32, 2200),
+@pytest.mark.parametrize("batch", [0, 1, 7, 16, 17, 64, 85, 160])
+@pytest.mark.parametrize("D,C,N", [(64, 1, 1025), (1000, 2, 1296), (1001, 5, 2047), (2049, 16, 2048), (640, 17, 2049), (640, 32, 2200),
                                    (10000, 6, 2600), (333, 9, 4097)])
 def test_long_calls_match_the_oracle(D, C, N, batch):
     rng = np.random.default_rng(D + 10 * C + N)
@@ -48,7 +54,7 @@ def test_long_calls_match_the_oracle(D, C, N, batch):
     hvd, yd = dev_u32(hv), torch.from_numpy(y).cuda()
     acc = torch.zeros((C, D), dtype=torch.float32, device="cuda")
     for calls in (1, 2):                           # the second call goes on from the rows of the first
-        assert train(ctx, hvd, yd, acc, batch, 1, 0.5) == (C <= 16 or not 0 < batch < 16)
+        assert train(ctx, hvd, yd, acc, batch, 1, 0.5) == goes(C, N, batch)
         assert off(acc, want(hv, y, D, C, batch, calls, 0.5)) < TOL
     ctx.close()
 
@@ -140,7 +146,8 @@ def test_long_calls_replayed_from_a_graph(wrong):
 
 
 @pytest.mark.parametrize("C,N,batch,lr,spread", [
-    (2, 1024, 0, 1.0, 0), (2, 1025, 0, 1.0, 1), (32, 2000, 0, 1.0, 1), (33, 2000, 0, 1.0, 0), (3, 2000, 256, 1.0, 1), (3, 2000, 257, 1.0, 0),
+    (2, 1024, 0, 1.0, 0), (2, 1025, 0, 1.0, 1), (32, 2000, 0, 1.0, 1), (33, 2000, 0, 1.0, 0), (3, 2000, 153, 1.0, 1), (3, 2000, 154, 1.0, 0), (3, 1279, 2, 1.0, 0),
+    (3, 1280, 2, 1.0, 1), (17, 1535, 16, 1.0, 0), (17, 1536, 16, 1.0, 1), (1, 7168, 256, 1.0, 1), (1, 7167, 256, 1.0, 0), (1, 8000, 257, 1.0, 0),
     (17, 2000, 15, 1.0, 0), (17, 2000, 16, 1.0, 1), (3, 2000, 0, 1e30, 0), (3, 2000, 0, float("nan"), 0)])
 def test_which_calls_go_in_blocks_of_2048(C, N, batch, lr, spread):
     ctx = make_ctx(make_workload(1, D=64, C=C, F=3, L=2))
