@@ -68,11 +68,12 @@ __global__ __launch_bounds__(kWave) void base_planes_kernel(const uint32_t *__re
 // parallel rows: qa[n][k] = bin * 256 (u16, the byte offset of the bin's row in the LDS slice, as
 // the dense kernel's quantiser writes it) and fb[n][k] = f * 256 (the byte offset of the feature's
 // row in a slice of b).  The list is padded with (feature 0, bin 0) entries - which add exactly the
-// 1 that is taken back for every entry - to a multiple of 16; blocks[n] = entries / 16.
+// 1 that is taken back for every entry - to a multiple of 16; blocks[n] = entries / 16.  Above bit 16 of it: how many of these blocks of 16, the first ones,
+// name features below `near` only.
 constexpr int kListWaves = 4;
 template <bool kU8>
 __global__ __launch_bounds__(kListWaves *kWave) void sparse_lists_kernel(
-    const void *__restrict__ feats, int64_t N, int F, int Fp, int L, const float *__restrict__ lo,
+    const void *__restrict__ feats, int64_t N, int F, int Fp, int L, int near, const float *__restrict__ lo,
     const float *__restrict__ scale, uint16_t *__restrict__ qa, uint32_t *__restrict__ fb,
     uint32_t *__restrict__ blocks) {
     const int lane = threadIdx.x & (kWave - 1);
@@ -80,7 +81,7 @@ __global__ __launch_bounds__(kListWaves *kWave) void sparse_lists_kernel(
     if (n >= N) return;
     uint16_t *qrow = qa + n * Fp;
     uint32_t *frow = fb + n * Fp;
-    int listed = 0;
+    int listed = 0, near_listed = 0;
     constexpr int kAhead = 8;   // feature chunks of 64 whose values are fetched together
     for (int f0 = 0; f0 < F; f0 += kAhead * kWave) {
         // all loads first, at clamped indices (what is fetched for f >= F is dropped below)
@@ -115,6 +116,7 @@ __global__ __launch_bounds__(kListWaves *kWave) void sparse_lists_kernel(
                 frow[k] = (uint32_t)f * (kSliceWords * 4u);
             }
             listed += __popcll(hits);
+            near_listed += __popcll(__ballot(bin != 0 && f < near));
         }
     }
     const int padded = (listed + 15) & ~15;   // <= Fp, which is a multiple of 16 and >= F
@@ -122,7 +124,9 @@ __global__ __launch_bounds__(kListWaves *kWave) void sparse_lists_kernel(
         qrow[listed + lane] = 0;
         frow[listed + lane] = 0;
     }
-    if (lane == 0) blocks[n] = (uint32_t)(padded >> 4);
+    // (with no far entry the padding, of feature 0, is near as well)
+    const int near_blocks = near > 0 ? (near_listed == listed ? padded : near_listed) >> 4 : 0;
+    if (lane == 0) blocks[n] = (uint32_t)(padded >> 4) | (uint32_t)near_blocks << 16;
 }
 
 // ---- bundling -------------------------------------------------------------------------------------
@@ -131,14 +135,23 @@ __global__ __launch_bounds__(kListWaves *kWave) void sparse_lists_kernel(
 // blocks, samples dealt round-robin to the waves.  Rows of b come from global memory (L1 / L2, the
 // table is a few hundred KB): one 64-bit add per listed entry forms the lane's address from the
 // wave-uniform row offset.  (Buffer loads that take the row offset as their scalar offset need no
-// such add but measured 9 % slower: the kernel is bound by the issue of these loads, about one per
-// 5 clocks per CU, not by the vector ALU.)  The rows of the next block of 16 entries are requested
-// before the current block is bundled.
+// such add but measured 9 % slower.)  The rows of the next block of 16 entries are requested before
+// the current block is bundled.
+// What bounds it: these row loads, about 10 clocks per entry and slice on a CU, where the vector ALU
+// takes five.  With 16 waves to a block and one block to a CU the first rows of b (`near`: what e
+// leaves of the 160 KB) lie in LDS as well, and the blocks of entries that name only these are bundled
+// from there, at the vector ALU's rate.  60000 samples, D = 10000, us with and without: 400 features
+// (all near) 270 and 306, 100 features 126 and 151, 784 with L = 64 464 and 493, with L = 256 (384 near)
+// 671 and 689.  (Every other wave far entries first, to use both paths at any time: 37 scalar registers
+// spilled and 784 us in place of 580 for the kernel.)
+constexpr int kNearWaves = 16;
+constexpr size_t kLds = 160 * 1024;
+constexpr int kNearSamples = 8;   // a wave, at least: 6000 samples of 784 features, L = 64, take 75 us so and 73 otherwise, 12000 119 and 122
 template <int P, int WAVES>
 __global__ __launch_bounds__(WAVES *kWave) void encode_sparse_kernel(
     const uint16_t *__restrict__ qa, const uint32_t *__restrict__ fb, const uint32_t *__restrict__ blocks,
     const uint32_t *__restrict__ b, const uint32_t *__restrict__ e, const uint32_t *__restrict__ base,
-    uint32_t *__restrict__ hv, int N, int Fp, int L, int W) {
+    uint32_t *__restrict__ hv, int N, int Fp, int L, int near, int W) {
     static_assert(P >= 8, "planes 1..4 take the tree, plane 5 its carry");
     extern __shared__ uint32_t lv[];
     const int slice = blockIdx.x;
@@ -148,7 +161,12 @@ __global__ __launch_bounds__(WAVES *kWave) void encode_sparse_kernel(
         const uint32_t *src = e + (size_t)slice * L * kSliceWords;
         for (int i = threadIdx.x; i < L * kSliceWords; i += WAVES * kWave) lv[i] = src[i];
     }
+    if (WAVES == kNearWaves) {   // and the first rows of b
+        const uint32_t *src = b + (size_t)slice * Fp * kSliceWords;
+        for (int i = threadIdx.x; i < near * kSliceWords; i += WAVES * kWave) lv[L * kSliceWords + i] = src[i];
+    }
     __syncthreads();
+    const uint32_t near_col = (uint32_t)(L * kSliceWords + lane) * 4u;
 
     // this lane's column of this slice of b; a listed row offset f * 256 (f < F) stays inside it
     const char *bcol = reinterpret_cast<const char *>(b + (size_t)slice * Fp * kSliceWords + lane);
@@ -161,7 +179,8 @@ __global__ __launch_bounds__(WAVES *kWave) void encode_sparse_kernel(
     for (int n = (int)blockIdx.y * WAVES + wave; n < N; n += stride) {
         const_u32_ptr qrow = (const_u32_ptr)(uintptr_t)(qa + (int64_t)n * Fp);
         const_u32_ptr frow = (const_u32_ptr)(uintptr_t)(fb + (int64_t)n * Fp);
-        const int nb = (int)((const_u32_ptr)(uintptr_t)blocks)[n];
+        const uint32_t counts = ((const_u32_ptr)(uintptr_t)blocks)[n];
+        const int nb = (int)(counts & 0xffffu), near_nb = WAVES == kNearWaves ? (int)(counts >> 16) : 0;
 
         // counters start at base - 16 * nb (mod 2^P): add the wave-uniform constant plane by plane
         uint32_t pl[P];
@@ -208,21 +227,55 @@ __global__ __launch_bounds__(WAVES *kWave) void encode_sparse_kernel(
             ripple<5, P>(pl, Tree<4, 0>::run(pl + 1, c2));
         };
 
-        if (nb > 0) {
+        // the same from the rows in LDS
+        auto request_near = [&](const uint32_t (&so)[16], uint32_t (&w)[16]) {
+#pragma unroll
+            for (int j = 0; j < 16; ++j)
+                w[j] = *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(lv) + (near_col + so[j]));
+        };
+        if (WAVES == kNearWaves && near_nb > 0) {
+            uint32_t w[16], so_a[16], so_b[16], qa_[8], qb_[8], x[16];
+            offsets_of(0, so_a);
+            bins_of(0, qa_);
+            offsets_of(1, so_b);
+            bins_of(1, qb_);
+            pin_schedule();
+            for (int blk = 0; blk < near_nb; blk += 2) {
+                wait_scalar_loads();
+                request_near(so_a, w);
+                pin_schedule();
+                gather16(x, qa_);
+                offsets_of(blk + 2, so_a);
+                bins_of(blk + 2, qa_);
+                pin_schedule();
+                bundle(x, w);
+                if (blk + 1 < near_nb) {
+                    wait_scalar_loads();
+                    request_near(so_b, w);
+                    pin_schedule();
+                    gather16(x, qb_);
+                    offsets_of(blk + 3, so_b);
+                    bins_of(blk + 3, qb_);
+                    pin_schedule();
+                    bundle(x, w);
+                }
+            }
+        }
+        if (nb > near_nb) {
             // Two blocks per trip (A even, B odd), nothing conditional inside.  Everything a block
             // needs is asked for a block or more ahead: its row offsets two blocks ahead (scalar
             // loads), its rows of b one block ahead (buffer loads at those offsets), its bin
             // offsets two blocks ahead.  Scalar loads are issued right after a gather has waited
             // on the LDS counter, so the next such wait finds them long done.
             uint32_t wa[16], wb[16], so_a[16], so_b[16], qa_[8], qb_[8], x[16];
-            offsets_of(0, so_a);
-            offsets_of(1, so_b);
-            bins_of(0, qa_);
-            bins_of(1, qb_);
+            int blk = near_nb;
+            offsets_of(blk, so_a);
+            offsets_of(blk + 1, so_b);
+            bins_of(blk, qa_);
+            bins_of(blk + 1, qb_);
             request(so_a, wa);              // (waits for so_a)
-            offsets_of(2, so_a);
+            offsets_of(blk + 2, so_a);
             pin_schedule();
-            int blk = 0;
             for (; blk + 1 < nb; blk += 2) {
                 wait_scalar_loads();
                 request(so_b, wb);          // rows of block blk + 1
@@ -248,12 +301,12 @@ __global__ __launch_bounds__(WAVES *kWave) void encode_sparse_kernel(
 }
 
 typedef void (*sparse_fn)(const uint16_t *, const uint32_t *, const uint32_t *, const uint32_t *, const uint32_t *,
-                          const uint32_t *, uint32_t *, int, int, int, int);
+                          const uint32_t *, uint32_t *, int, int, int, int, int);
 struct SparseVariant {
     sparse_fn fn;
     int P, waves;
 };
-#define HDC_SPARSE(P) {encode_sparse_kernel<P, 4>, P, 4}, {encode_sparse_kernel<P, 8>, P, 8}
+#define HDC_SPARSE(P) {encode_sparse_kernel<P, 4>, P, 4}, {encode_sparse_kernel<P, 8>, P, 8}, {encode_sparse_kernel<P, kNearWaves>, P, kNearWaves}
 static const SparseVariant kSparse[] = {HDC_SPARSE(8), HDC_SPARSE(10), HDC_SPARSE(12), HDC_SPARSE(16)};
 #undef HDC_SPARSE
 
@@ -330,13 +383,22 @@ int launch_encode_sparse(hdc_ctx_impl *c, const void *feats, int64_t N, uint32_t
     if (compact && c->Wc == 0) return launch_encode(c, feats, N, hv, s);
     const int W = compact ? c->Wc : c->W, Wp = compact ? c->Wcp : c->Wp;
     const int nslices = Wp / kSliceWords;
-    const int waves = c->p.L > 128 ? 8 : 4;
+    const int near = min(c->p.F, (int)(kLds / (kSliceWords * 4)) - c->p.L);
+    const bool with_rows = near > 0 && min(N, c->q_rows) >= (int64_t)kNearSamples * (c->num_cus / nslices) * kNearWaves && nslices <= c->num_cus;
+    const int waves = with_rows ? kNearWaves : c->p.L > 128 ? 8 : 4;
     const SparseVariant *v = nullptr;
     for (const SparseVariant &k : kSparse)
         if (k.P == P && k.waves == waves) v = &k;
     if (!v) return HDC_ELIMIT;
-    const size_t lds = (size_t)c->p.L * kSliceWords * sizeof(uint32_t);
-    if (c->sp_bpc == 0) {
+    const size_t lds = (size_t)(c->p.L + (with_rows ? near : 0)) * kSliceWords * sizeof(uint32_t);
+    if (with_rows && !c->sp_near) {
+        hipFuncAttributes attr;
+        HDC_HIP(hipFuncGetAttributes(&attr, reinterpret_cast<const void *>(v->fn)));
+        if (attr.sharedSizeBytes != 0) return HDC_ELIMIT;
+        HDC_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(v->fn), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds));
+        c->sp_near = true;
+    }
+    if (!with_rows && c->sp_bpc == 0) {
         hipFuncAttributes attr;
         HDC_HIP(hipFuncGetAttributes(&attr, reinterpret_cast<const void *>(v->fn)));
         if (attr.sharedSizeBytes != 0) return HDC_ELIMIT;
@@ -354,14 +416,14 @@ int launch_encode_sparse(hdc_ctx_impl *c, const void *feats, int64_t N, uint32_t
             const dim3 grid((unsigned)((n + kListWaves - 1) / kListWaves));
             if (c->p.feat_dtype == HDC_U8)
                 hipLaunchKernelGGL(sparse_lists_kernel<true>, grid, dim3(kListWaves * kWave), 0, s, x, n, c->p.F,
-                                   c->Fp, c->p.L, c->lo_d, c->scale_d, c->q_d, c->sp_fb_d, c->sp_blocks_d);
+                                   c->Fp, c->p.L, with_rows ? near : 0, c->lo_d, c->scale_d, c->q_d, c->sp_fb_d, c->sp_blocks_d);
             else
                 hipLaunchKernelGGL(sparse_lists_kernel<false>, grid, dim3(kListWaves * kWave), 0, s, x, n, c->p.F,
-                                   c->Fp, c->p.L, c->lo_d, c->scale_d, c->q_d, c->sp_fb_d, c->sp_blocks_d);
+                                   c->Fp, c->p.L, with_rows ? near : 0, c->lo_d, c->scale_d, c->q_d, c->sp_fb_d, c->sp_blocks_d);
         }
         uint32_t *out = hv + (size_t)n0 * c->W;
         {
-            int max_waves = (c->num_cus * c->sp_bpc) / nslices * waves;
+            int max_waves = (c->num_cus * (with_rows ? 1 : c->sp_bpc)) / nslices * waves;
             if (max_waves < waves) max_waves = waves;
             const int64_t k = (n + max_waves - 1) / max_waves;   // samples per wave
             const int64_t need_waves = (n + k - 1) / k;
@@ -369,7 +431,7 @@ int launch_encode_sparse(hdc_ctx_impl *c, const void *feats, int64_t N, uint32_t
             ProfScope prof(c, HDC_K_ENCODE, s);
             hipLaunchKernelGGL(v->fn, dim3((unsigned)nslices, (unsigned)per_slice), dim3(waves * kWave), lds, s,
                                c->q_d, c->sp_fb_d, c->sp_blocks_d, c->sp_b_d, c->sp_e_d, c->sp_base_d,
-                               compact ? c->hvc_d : out, (int)n, c->Fp, c->p.L, W);
+                               compact ? c->hvc_d : out, (int)n, c->Fp, c->p.L, with_rows ? near : 0, W);
         }
         if (compact) launch_expand(c, n, out, s);
         HDC_HIP(hipGetLastError());

@@ -125,6 +125,7 @@ struct hdc_ctx_impl {
     uint32_t *sp_fb_d;      // [q_rows][Fp]     listed features' row offsets in a slice of sp_b_d
     uint32_t *sp_blocks_d;  // [q_rows]         16-entry blocks per sample
     int sp_bpc;             // blocks of encode_sparse_kernel a CU holds (0 = not asked yet)
+    bool sp_near = false;   // encode_sparse_kernel with rows of b in LDS may use all of it
 
     // Encoding as a contraction over the features (encode_contract.hip); tables derived at create
     // when the level table is of the shape it needs.

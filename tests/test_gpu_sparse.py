@@ -153,3 +153,34 @@ def test_sparse_encode_argument_errors():
     assert binding.lib.hdc_encode_sparse(ctx._h, None, 4, hv4.data_ptr(), None) == binding.HDC_EINVAL
     assert binding.lib.hdc_encode_sparse(ctx._h, None, -1, None, None) == binding.HDC_EINVAL
     ctx.close()
+
+
+# From 8 samples a wave on the first 640 - L rows of the item table are read from LDS: fewer features than that, as many, one
+# more, and many more; lists that end among these rows, lists beyond them, none.  Against the dense encoder, which is held to the oracle.
+@pytest.mark.parametrize("L,F", [(2, 37), (16, 624), (16, 625), (64, 1300), (256, 383), (256, 384), (256, 400), (256, 784)])
+@pytest.mark.parametrize("dtype", ["u8", "f32"])
+def test_sparse_encode_of_many_samples_matches_the_dense_encoder(dtype, L, F):
+    D, N = 6100, 8 * 256 // 3 * 16 + 77
+    wl = make_workload(1, D=D, C=2, F=F, L=L)
+    rng = np.random.default_rng(L + F)
+    lo, scale = (None, None) if dtype == "u8" else (np.full(F, -1.0), np.full(F, L / 2, dtype=np.float32))
+    from paper_2206_04746_amd import binding
+    ctx = binding.Context(D, F, L, 2, wl.item, wl.level, wl.tie, lo, scale, dtype)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(F)
+    keep = torch.rand((N, F), device="cuda", generator=g) < torch.rand((N, 1), device="cuda", generator=g) ** 3
+    keep[:64] = False
+    keep[64:128, F // 2:] = False
+    keep[128:192, :F - min(F, 20)] = False
+    keep[192:256] = True
+    if dtype == "u8":
+        x = torch.randint(0, 256, (N, F), device="cuda", generator=g, dtype=torch.int32).mul_(keep).to(torch.uint8)
+    else:
+        x = torch.where(keep, torch.rand((N, F), device="cuda", generator=g) * 2.0 - 1.0, -1.0)
+    dense, sparse = (torch.full((N, ctx.W), -1, dtype=torch.int32, device="cuda") for _ in range(2))
+    ctx.hdc_encode(x, dense)
+    ctx.hdc_encode_sparse(x, sparse)
+    assert torch.equal(dense, sparse)
+    some = rng.choice(N, 40, replace=False)
+    assert np.array_equal(sparse[some].cpu().numpy().view(np.uint32), oracle.encode(x[some].cpu().numpy(), D, L, wl.item, wl.level, wl.tie, lo, scale))
+    ctx.close()
