@@ -176,7 +176,7 @@ int hdc_binarize_classical(hdc_ctx *ctx, const int32_t *acc_dev, const int64_t *
  * repeated samples have made proportional, for instance) may be another one than a walk by samples
  * takes.  The first call, whatever its size, allocates
  * context-owned scratch (20 MB + 16384 rows, at most 64 MB of them, and up to 2.5 MB at the largest C and D; up to C = 32 another
- * 36 MB and 1 MB a class, without which calls of more than 1024 samples go in blocks of 256) unless hdc_reserve has done so;
+ * 36 MB and 0.45 MB a class, without which calls of more than 1024 samples go in blocks of 256) unless hdc_reserve has done so;
  * later calls only enqueue on `stream`.  Where the scratch cannot be had - memory is short, or the
  * first call is being captured into a graph - and D <= 32768, the call goes sample by sample
  * without any, which is slower; beyond D = 32768 that is HDC_ENOMEM or HDC_EHIP.
@@ -194,8 +194,8 @@ int hdc_train_online(hdc_ctx *ctx, const uint32_t *hv_dev, const int32_t *labels
  *                                     -float(lr*(1 - cos_pred)) * s for c == pred != y
  * (fp64 sums) and acc[c] = float(double(acc[c]) + delta[c]), one rounding per element and
  * batch.  batch >= 1; a batch larger than N is one batch per epoch.  Small batches (up to 85 samples,
- * fewer for few dimensions and for one or two classes; C <= 64, D <= 65535; up to 256 in calls of more than
- * 1024 samples, C <= 32) are worked off several at a time as described for hdc_train_online.  Other arguments, layout
+ * fewer for few dimensions and for one or two classes; C <= 64, D <= 65535; up to 256 in calls of at least 1280
+ * samples, C <= 32, that have 8 batches and 5 more per 2048 samples) are worked off several at a time as described for hdc_train_online.  Other arguments, layout
  * and the treatment of out-of-range labels are those of hdc_train_online.  The first call, and one
  * with a larger batch (min(batch, N)) than any before it, allocates device memory owned by the
  * context (HDC_ENOMEM if that fails) and therefore synchronises the device; other calls only

@@ -14,7 +14,8 @@
 //                        sample order, one fp32 rounding per update (per batch: one per batch), and form the
 //                        rows' new squared norms
 //   online_rows_kernel   the same updates for the last block (for every one, before the next, where a weight could overflow)
-// Per-sample calls of up to 16 classes take online_wide_kernel for the chain, which walks the block as a whole, with the
+// Calls of more than 1024 samples of up to 32 classes go in blocks of 2048 (online_spread.hip), with their products from
+// online_gram_kernel here in strips of 16 columns.  Other per-sample calls of up to 16 classes take online_wide_kernel for the chain, which walks the block as a whole, with the
 // row updates of the block before as its other workgroups (wide_takes).
 // The dot products stay fp64 sums of the same fp32 rows and fp32 weights.  They leave out the fp32 rounding of the u <= 512
 // updates of a row made since the block before began: at most 2^-24 of an element each, so u 2^-24 of a cosine at the very
