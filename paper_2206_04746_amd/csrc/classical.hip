@@ -717,22 +717,29 @@ __global__ __launch_bounds__(kRowsWaves *kWave) void accumulate_local_kernel(
 }
 
 // ---- small batches: grouping, counting and the update of acc in one launch ----------------------
-// Up to kFusedMaxN rows.  grid = (C, slices of 64 word columns), 16 waves per block.  A block takes
-// class c and one slice: it lists the rows of the class in LDS by itself (every block reads the few
+// Up to kFusedMaxN rows.  grid = (C, slices of 64 word columns, parts), 16 waves per block.  A block takes
+// class c, one slice and a part of all rows (below): it lists the rows of the class in LDS by itself (every block reads the few
 // thousand labels; a wave appends its matches with one LDS atomic), its 16 waves count a sixteenth
 // of those rows each with the same bit-sliced adders as accumulate_kernel (a couple of 8-row
 // batches per wave), the 16 counts are added pairwise through LDS in four rounds, and all waves
 // together turn the planes into integers and add them to acc[c][the slice's 2048 dimensions],
-// which this block alone owns (coalesced 8-byte read-modify-writes, the old values fetched at the
+// which this block alone owns where there is one part (coalesced 8-byte read-modify-writes, the old values fetched at the
 // start).  Three launches and two scratch round trips less than the general path; fourteen
 // planes hold any count up to the row limit, whatever the class sizes.
 constexpr int kFusedMaxN = 8192;
 constexpr int kFusedPlanes = 14;
+constexpr int kAhead = 2;   // batches of 8 rows that a wave has asked for
+// What bounds it: latency, labels, rows, four rounds of sums, one after the other.  With few classes a wave had hundreds of rows to
+// fetch and most of the chip nothing to do, so from 256 rows a class on, on the average, the rows are split among up to 8 blocks a class
+// while there are compute units for them, by their numbers (the lists' order differs from block to block); their sums meet in acc by integer atomics.  Rows, classes, D, us a call before, with rows fetched
+// without conditions and one atomic a wave for the list, and split: 2000, 5, 1024: 8.2, 7.6, 6.5; 7352, 6, 10000: 14.2, 12.1, 7.7;
+// 8000, 2, 10000: 30.9, 26.9, 9.2; 6238, 26, 10000 (not split): 8.6, 7.7.  (A part per 512 rows: 7.8, 8.6, 8.9.)
+constexpr int64_t kPartRows = 256, kFusedParts = 8;
 static_assert(kFusedMaxN < (1 << kFusedPlanes), "a class may hold every row");
 constexpr size_t kFusedSlotWords = (size_t)kAccWaves * kFusedPlanes * kWave;   // one plane set per wave
 
 __global__ __launch_bounds__(kAccWaves *kWave) void accumulate_small_kernel(
-    const uint32_t *__restrict__ hv, const int32_t *__restrict__ labels, int N, int W, int D, int32_t *acc,
+    const uint32_t *__restrict__ hv, const int32_t *__restrict__ labels, int N, int per, int W, int D, int32_t *acc,
     int64_t *class_n) {
     extern __shared__ uint32_t sm[];   // plane sets [16][kFusedPlanes][64], then the row list (u16)
     __shared__ uint32_t count;
@@ -742,31 +749,43 @@ __global__ __launch_bounds__(kAccWaves *kWave) void accumulate_small_kernel(
     const int lane = threadIdx.x & (kWave - 1);
     if (threadIdx.x == 0) count = 0;
     __syncthreads();
+    const int parts = gridDim.z, from = (int)blockIdx.z * per, to = min(from + per, N);
     {   // a thread's labels all at once (the loads are independent), then the appends
         constexpr int kPer = kFusedMaxN / (kAccWaves * kWave);
+        uint64_t hits[kPer];
+        uint32_t n = 0;
         int lab[kPer];
 #pragma unroll
         for (int k = 0; k < kPer; ++k) {
-            const int i = threadIdx.x + k * kAccWaves * kWave;
-            lab[k] = i < N ? labels[i] : -1;
+            const int i = from + threadIdx.x + k * kAccWaves * kWave;
+            lab[k] = i < to ? labels[i] : -1;
         }
 #pragma unroll
         for (int k = 0; k < kPer; ++k) {
-            const bool hit = lab[k] == c;
-            const uint64_t m = __ballot(hit);
-            if (m) {   // uniform: one atomic per wave reserves room for its matches (any order: integer sums)
-                uint32_t base = 0;
-                if (lane == 0) base = atomicAdd(&count, (uint32_t)__popcll(m));
-                base = __builtin_amdgcn_readfirstlane(base);
-                const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                if (hit) list[base + rank] = (uint16_t)(threadIdx.x + k * kAccWaves * kWave);
+            hits[k] = __ballot(lab[k] == c);
+            n += (uint32_t)__popcll(hits[k]);
+        }
+        if (n) {   // uniform: one atomic per wave reserves room for its matches (any order: integer sums)
+            uint32_t base = 0;
+            if (lane == 0) base = atomicAdd(&count, n);
+            base = __builtin_amdgcn_readfirstlane(base);
+#pragma unroll
+            for (int k = 0; k < kPer; ++k) {
+                const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(hits[k] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hits[k], 0u));
+                if (lab[k] == c) list[base + rank] = (uint16_t)(from + threadIdx.x + k * kAccWaves * kWave);
+                base += (uint32_t)__popcll(hits[k]);
             }
         }
     }
     __syncthreads();
     const uint32_t total = count;
     if (total == 0) return;   // uniform
-    if (blockIdx.y == 0 && threadIdx.x == 0) class_n[c] += (int64_t)total;
+    if (blockIdx.y == 0 && threadIdx.x == 0) {
+        if (parts == 1)
+            class_n[c] += (int64_t)total;
+        else
+            atomicAdd(reinterpret_cast<unsigned long long *>(class_n + c), (unsigned long long)total);
+    }
 
     // the two accumulators this lane will add to at the end, on their way while the rows are counted:
     // wave g finishes word columns 4g .. 4g+3 of the slice, lane l bits 2 (l % 16), +1 of column l / 16
@@ -774,17 +793,17 @@ __global__ __launch_bounds__(kAccWaves *kWave) void accumulate_small_kernel(
     const int fbit = (lane & 15) * 2;
     const int64_t fd = (int64_t)fcol * 32 + fbit;
     int32_t *fdst = acc + (int64_t)c * D + fd;
-    const bool pair = (D & 1) == 0 && (reinterpret_cast<uintptr_t>(acc) & 7u) == 0 && fd + 1 < D;
+    const bool pair = parts == 1 && (D & 1) == 0 && (reinterpret_cast<uintptr_t>(acc) & 7u) == 0 && fd + 1 < D;
     int2 old2 = make_int2(0, 0);
     if (pair) {
         old2 = *reinterpret_cast<const int2 *>(fdst);
-    } else {
+    } else if (parts == 1) {
         if (fd < D) old2.x = fdst[0];
         if (fd + 1 < D) old2.y = fdst[1];
     }
 
     const int col = blockIdx.y * kSliceWords + lane;
-    const bool in_range = col < W;
+    const uint32_t *src = hv + min(col, W - 1);   // (what is counted beyond the row's end is not stored)
     const uint32_t rb = ((total + kAccWaves - 1) / kAccWaves + 7) / 8 * 8;
     const uint32_t first = (uint32_t)wave * rb;
     const uint32_t rows = first < total ? min(rb, total - first) : 0u;
@@ -792,15 +811,17 @@ __global__ __launch_bounds__(kAccWaves *kWave) void accumulate_small_kernel(
     uint32_t pl[kFusedPlanes];
 #pragma unroll
     for (int i = 0; i < kFusedPlanes; ++i) pl[i] = 0;
+    // Rows past the last are fetched again and masked when they are counted: with a condition at a load, the next load waits for
+    // it.
+    const uint32_t last = rows ? first + rows - 1 : 0u;
     auto load8 = [&](uint32_t r0, uint32_t(&x)[8]) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            x[j] = 0;
-            if (r0 + j < rows && in_range) x[j] = hv[(int64_t)list[first + r0 + j] * W + col];   // row test: uniform
-        }
+        for (int j = 0; j < 8; ++j) x[j] = src[(int64_t)list[min(first + r0 + j, last)] * W];
     };
-    auto add8 = [&](const uint32_t(&x)[8]) {
+    auto add8 = [&](uint32_t r0, uint32_t(&x)[8]) {
         uint32_t a, b, p, c2a, c2b, c3;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] &= r0 + j < rows ? ~0u : 0u;
         p = pl[0]; a = maj3(p, x[0], x[1]); p = xor3(p, x[0], x[1]);
         b = maj3(p, x[2], x[3]); p = xor3(p, x[2], x[3]); pl[0] = p;
         p = pl[1]; c2a = maj3(p, a, b); pl[1] = xor3(p, a, b);
@@ -815,13 +836,15 @@ __global__ __launch_bounds__(kAccWaves *kWave) void accumulate_small_kernel(
             c3 = t;
         }
     };
-    uint32_t xa[8], xb[8];
-    load8(0, xa);
-    for (uint32_t r0 = 0; r0 < rows; r0 += 16) {
-        load8(r0 + 8, xb);
-        add8(xa);
-        load8(r0 + 16, xa);
-        add8(xb);
+    uint32_t x[kAhead][8];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k) load8(8 * k, x[k]);
+    for (uint32_t r0 = 0; r0 < rows; r0 += 8 * kAhead) {
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            add8(r0 + 8 * k, x[k]);
+            load8(r0 + 8 * (k + kAhead), x[k]);
+        }
     }
 
     // 16 plane sets -> 1: the upper half of the waves still in play parks its planes, the lower
@@ -862,6 +885,9 @@ __global__ __launch_bounds__(kAccWaves *kWave) void accumulate_small_kernel(
     }
     if (pair) {
         *reinterpret_cast<int2 *>(fdst) = make_int2(old2.x + (int)v0, old2.y + (int)v1);
+    } else if (parts > 1) {
+        if (fd < D && v0) atomicAdd(fdst, (int)v0);
+        if (fd + 1 < D && v1) atomicAdd(fdst + 1, (int)v1);
     } else {
         if (fd < D) fdst[0] = old2.x + (int)v0;
         if (fd + 1 < D) fdst[1] = old2.y + (int)v1;
@@ -1106,9 +1132,11 @@ int launch_train_classical(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *l
         if (lds > 64 * 1024)   // (per launch: the limit belongs to the function, and another context may have set a smaller one)
             HDC_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(accumulate_small_kernel),
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        const int64_t slices = c->Wp / kSliceWords;
+        const int64_t parts = max((int64_t)1, min(min(kFusedParts, (N + C * kPartRows - 1) / (C * kPartRows)), c->num_cus / (C * slices)));
         ProfScope prof(c, HDC_K_ACCUMULATE, s);
-        hipLaunchKernelGGL(accumulate_small_kernel, dim3((unsigned)C, (unsigned)(c->Wp / kSliceWords)),
-                           dim3(kAccWaves * kWave), lds, s, hv, labels, (int)N, c->W, c->p.D, acc, class_n);
+        hipLaunchKernelGGL(accumulate_small_kernel, dim3((unsigned)C, (unsigned)slices, (unsigned)parts),
+                           dim3(kAccWaves * kWave), lds, s, hv, labels, (int)N, (int)((N + parts - 1) / parts), c->W, c->p.D, acc, class_n);
         HDC_HIP(hipGetLastError());
         return HDC_OK;
     }
