@@ -1,13 +1,17 @@
-// Dot products of sample bits (+-1) with real class rows, exact to 2^-55 of a slice's largest element: the forward step of
-// cosine inference and of online training (arXiv 2206.04746, Sec. III).
+// Dot products of sample bits (+-1) with real class rows, of a slice rounded once: the forward step of cosine inference and of
+// online training (arXiv 2206.04746, Sec. III).
 //
 // A double-precision product on this chip runs at the vector unit's rate wherever it is sent, 64 times slower than 8-bit whole
 // numbers on the matrix cores.  So a slice of a row (512 dimensions) is turned into whole numbers of 56 bits, relative to its
-// largest element, and those into seven signed digits of 8 bits: sums of +-digit are exact in 32 bits, and the
-// dot product is the digits' sums put together in fp64, one rounding of 2^-53 where an fp64 sum has one per dimension.  An
-// element down to 2^-30 of the slice's largest loses nothing, a smaller one at most 2^-55 of that.  2947 samples, 6 classes, D = 10000: the fp64
-// form took 20 us, this 8 (cosine inference 24.4 and 13.2 with the finish).  What bounds it: bytes made of bits, and a block's own digits
-// before its first product.
+// largest element, and those into seven signed digits of 8 bits: sums of +-digit are exact in 32 bits, and the dot product is
+// the digits' sums put together in fp64, one rounding of 2^-53 where an fp64 sum has one per dimension.  2947 samples, 6 classes,
+// D = 10000: the fp64 form took 20 us, this 8 (cosine inference 25.6 and 14.8 with the finish).  What bounds it: bytes made of bits,
+// and a block's own digits before its first product.
+//
+// Digits hold an element whole if its last bit is no less than 2^-54 of the largest one's power of two: every element down to 2^-30
+// of the largest.  A row of a slice with one that they do not hold, or that is no number or infinite, is summed in fp64 on the
+// matrix cores instead: the same call with one such element takes 26 us, with one in every row of every slice 39 (26 classes: 33.8, 38
+// and 80, and 82 in the fp64 form).
 //
 // grid (slices, tiles of samples, chunks of classes), eight waves.  The block forms the digits of its rows in LDS, in the
 // order in which the matrix instruction takes them; a wave has 16 samples (RT of these), whose bits become bytes of 1 and -1 on the way: a
@@ -17,6 +21,7 @@
 
 #include "hdc_internal.h"
 #include "online_weight.h"
+#include "row_digits.h"
 
 namespace hdc {
 
@@ -24,6 +29,7 @@ namespace {
 
 constexpr int kWaves = 8, kThreads = kWaves * kWave, kDigits = 7;
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef double v4d __attribute__((ext_vector_type(4)));
 
 constexpr int kBlocks = 4, kDims = 128 * kBlocks;   // of a slice
 
@@ -37,10 +43,8 @@ struct Shape {
 
 // Turns the lanes of a row of 16 by N: lane i takes lane i + N.
 template <int N>
-__device__ __forceinline__ double from_lane(double v) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x120 + 16 - N, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x120 + 16 - N, 0xF, 0xF, true);
-    return __hiloint2double(hi, lo);
+__device__ __forceinline__ int from_lane(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, 0x120 + 16 - N, 0xF, 0xF, true);
 }
 
 // part[slice * stride + n * step_n + c * step_c].  The blocks of one tile more, where wanted, form the squared-norm partials.
@@ -50,7 +54,7 @@ __global__ __launch_bounds__(kThreads) void row_dots_kernel(const uint32_t *__re
                                                             int64_t step_c, double *__restrict__ normpart, int G) {
     using S = Shape<P>;
     __shared__ __align__(16) uint32_t digits[kBlocks * 2 * S::kTiles][kWave][4];
-    __shared__ uint32_t largest[2][S::kClasses];
+    __shared__ uint32_t largest[2][S::kClasses];   // element of a slice; bit 31: digits leave out some of an element
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
     const int c0 = blockIdx.z * S::kClasses, slices = (D + kDims - 1) / kDims;
     const int s0 = blockIdx.x * per, s1 = min(s0 + per, slices);
@@ -96,11 +100,15 @@ __global__ __launch_bounds__(kThreads) void row_dots_kernel(const uint32_t *__re
             for (int b = 0; b < kBlocks; ++b) word[t][b] = hv[row[t] + min(d0 / 32 + 4 * b + kg, W - 1)];
         __syncthreads();   // the digits before have been read
         uint32_t *const most = largest[(sl - s0) & 1];
+        uint32_t least = ~0u;   // (a thread's elements are of one class: kThreads is a multiple of a word's units)
 #pragma unroll
         for (int i = 0; i < S::kPerThread; ++i) {
             uint32_t m = 0;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) m = max(m, x[i][j] & 0x7FFFFFFFu);
+            for (int j = 0; j < 4; ++j) {
+                m = max(m, x[i][j] & 0x7FFFFFFFu);
+                least = min(least, (x[i][j] & 0x7FFFFFFFu) - 1);
+            }
             m = max(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0xB1, 0xF, 0xF, true));   // quad_perm 1,0,3,2
             m = max(m, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)m, 0x4E, 0xF, 0xF, true));   // quad_perm 2,3,0,1
             if constexpr (kStep <= 16) m = max(m, (uint32_t)__shfl_xor((int)m, 16, kWave));
@@ -109,20 +117,15 @@ __global__ __launch_bounds__(kThreads) void row_dots_kernel(const uint32_t *__re
         }
         __syncthreads();
         if (tid < S::kClasses) largest[(sl - s0 + 1) & 1][tid] = 0;
+        const int own = tid / 4 % S::kClasses;
+        const uint32_t top_of = most[own] >> 23 & 255;   // (255, with an element that is no number or infinite: digits of no meaning)
+        const double scale = digits_scale(top_of);
 #pragma unroll
         for (int i = 0; i < S::kPerThread; ++i) {
-            const int u = tid + i * kThreads, c = u / 4 % S::kClasses, b = u / (8 * kStep), k = u / (2 * kStep) % 4, r = u / kStep % 2 * 4 + u % 4;
-            // the slice's largest element is below 2^(top - 126): times this, below 2^54
-            const double scale = __builtin_ldexp(1.0, 54 + 126 - max((int)(most[c] >> 23), 1));
+            const int u = tid + i * kThreads, b = u / (8 * kStep), k = u / (2 * kStep) % 4, r = u / kStep % 2 * 4 + u % 4;
             uint32_t lo[4], hi[4];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const double v = (double)__uint_as_float(x[i][j]) * scale, upper = rint(v * 0x1p-32);   // both exact
-                const int64_t low = (int64_t)(int)rint(fma(upper, -0x1p32, v));
-                const uint64_t whole = ((uint64_t)(uint32_t)(int)upper << 32) + (uint64_t)low + 0x80808080808080ull;   // byte k less 128 is digit k
-                lo[j] = (uint32_t)whole ^ 0x80808080u;
-                hi[j] = (uint32_t)(whole >> 32) ^ 0x808080u;
-            }
+            for (int j = 0; j < 4; ++j) digits_of((double)__uint_as_float(x[i][j]) * scale, lo[j], hi[j]);
             // byte k of the four elements into one word
             const uint32_t a01 = __builtin_amdgcn_perm(lo[1], lo[0], 0x05010400), a23 = __builtin_amdgcn_perm(lo[3], lo[2], 0x05010400);
             const uint32_t b01 = __builtin_amdgcn_perm(lo[1], lo[0], 0x07030602), b23 = __builtin_amdgcn_perm(lo[3], lo[2], 0x07030602);
@@ -134,7 +137,18 @@ __global__ __launch_bounds__(kThreads) void row_dots_kernel(const uint32_t *__re
                                      __builtin_amdgcn_perm(f23, f01, 0x05040100), 0u};
 #pragma unroll
             for (int w = 0; w < S::kTiles * P; ++w)   // (an eighth digit, where a tile has room for one, is zero)
-                digits[(b * 2 + r / 4) * S::kTiles + w / P][k * 16 + w % P * S::kClasses + c][r % 4] = out[w];
+                digits[(b * 2 + r / 4) * S::kTiles + w / P][k * 16 + w % P * S::kClasses + own][r % 4] = out[w];
+        }
+        if (__builtin_expect(!digits_hold(least, top_of), 0)) {
+            bool all = true;
+#pragma unroll
+            for (int i = 0; i < S::kPerThread; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const double v = (double)__uint_as_float(x[i][j]) * scale;
+                    all &= v == rint(v);
+                }
+            if (!all) atomicOr(&most[own], 0x80000000u);
         }
         __syncthreads();
         if (idle) continue;
@@ -158,38 +172,65 @@ __global__ __launch_bounds__(kThreads) void row_dots_kernel(const uint32_t *__re
         }
         const int c = col % S::kClasses;
         const uint32_t top = most[c];
-        const double unit = __builtin_ldexp(1.0, max((int)(top >> 23), 1) - 126 - 54);
+        const bool exact = top < 0x7F800000u;
+        const double unit = exact ? __builtin_ldexp(1.0, max((int)(top >> 23), 1) - 126 - 54) : 0.0;
 #pragma unroll
         for (int t = 0; t < RT; ++t)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                double v;
-                if constexpr (P == 1) {   // (sums of 512 digits: two of them go together in 32 bits)
-                    v = (double)sum[t][6][i];
-#pragma unroll
-                    for (int w = 4; w >= 0; w -= 2) v = fma(v, 65536.0, (double)(sum[t][w][i] + 256 * sum[t][w + 1][i]));
+            for (int i = 0; i < 4; ++i) {   // (sums of 512 digits: two of them go together in 32 bits)
+                int s01, s23, s45, s6;
+                if constexpr (P == 1) {
+                    s01 = sum[t][0][i] + 256 * sum[t][1][i], s23 = sum[t][2][i] + 256 * sum[t][3][i];
+                    s45 = sum[t][4][i] + 256 * sum[t][5][i], s6 = sum[t][6][i];
                 } else if constexpr (P == 2) {
-                    v = (double)sum[t][3][i];
-#pragma unroll
-                    for (int w = 2; w >= 0; --w) v = fma(v, 65536.0, (double)sum[t][w][i]);
-                    v = fma(from_lane<8>(v), 256.0, v);
+                    s01 = sum[t][0][i] + 256 * from_lane<8>(sum[t][0][i]), s23 = sum[t][1][i] + 256 * from_lane<8>(sum[t][1][i]);
+                    s45 = sum[t][2][i] + 256 * from_lane<8>(sum[t][2][i]), s6 = sum[t][3][i];
                 } else {
-                    v = fma((double)sum[t][1][i], 4294967296.0, (double)sum[t][0][i]);
-                    v = fma(from_lane<4>(v), 256.0, v);
-                    v = fma(from_lane<8>(v), 65536.0, v);
+                    s01 = sum[t][0][i] + 256 * from_lane<4>(sum[t][0][i]), s45 = sum[t][1][i] + 256 * from_lane<4>(sum[t][1][i]);
+                    s23 = from_lane<8>(s01), s6 = from_lane<8>(sum[t][1][i]);
                 }
-                v *= unit;
-                if (__builtin_expect(top >= 0x7F800000u, 0)) {   // an element that is no number or infinite: one after another
-                    v = 0.0;
-                    const int64_t n = first + (wave * RT + t) * 16 + 4 * kg + i;
-                    if (n < nb && c0 + c < C)
-                        for (int d = d0; d < min(d0 + kDims, D); ++d) {
-                            const double a = (double)acc[(int64_t)(c0 + c) * D + d];
-                            v += hv[n * W + d / 32] >> (d % 32) & 1 ? a : -a;
-                        }
-                }
-                total[t][i] += v;
+                total[t][i] += sum_of_digits(s01, s23, s45, s6) * unit;
             }
+        if (__builtin_expect(__ballot(!exact) != 0, 0)) {   // classes that digits do not hold: in fp64
+            // Lanes of row kg of 16 have words kg, kg + 4 ... of the slice.  What comes out as sample 4 i + kg is to be sample 4 kg + i.
+            const int64_t tile = first + (int64_t)wave * RT * 16 + 4 * (col % 4) + col / 4;
+            const float *const values = acc + (int64_t)min(c0 + c, C - 1) * D;
+            v4d all_of[RT] = {};
+            float x[2][8];   // of eight dimensions, and the next eight
+            uint32_t bits[2][RT];
+            auto ask = [&](int h, float(&to)[8], uint32_t(&word_of)[RT]) {
+                const int d = d0 + 32 * (4 * (h / 4) + kg) + 8 * (h & 3);
+#pragma unroll
+                for (int t = 0; t < RT; ++t) word_of[t] = hv[min(tile + 16 * t, nb - 1) * W + min(d / 32, W - 1)] >> 8 * (h & 3);
+                if (d + 8 <= D) {
+                    __builtin_memcpy(to, values + d, sizeof(to));
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) to[j] = d + j < D ? values[d + j] : 0.0f;
+                }
+            };
+            auto add = [&](const float(&from)[8], const uint32_t(&word_of)[RT]) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const double a = exact || col >= S::kClasses ? 0.0 : (double)from[j];
+#pragma unroll
+                    for (int t = 0; t < RT; ++t)
+                        all_of[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(word_of[t] >> j & 1 ? 1.0 : -1.0, a, all_of[t], 0, 0, 0);
+                }
+            };
+            ask(0, x[0], bits[0]);
+#pragma unroll 1
+            for (int h = 0; h < 4 * kBlocks; h += 2) {
+                ask(h + 1, x[1], bits[1]);
+                add(x[0], bits[0]);
+                ask(h + 2, x[0], bits[0]);   // (past the slice: not used)
+                add(x[1], bits[1]);
+            }
+#pragma unroll
+            for (int t = 0; t < RT; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) total[t][i] += all_of[t][i];
+        }
     }
     // register i of lane 16 q + col: sample 4 q + i
     if (col < S::kClasses && c0 + col < C) {

@@ -1,4 +1,5 @@
-"""Host-side logic of the library that needs no GPU: the table builders of the contraction encoders
+"""Host-side logic of the library that needs no GPU: the digits of class rows (a C++ check program built with the
+sanitizers), the table builders of the contraction encoders
 (a C++ check program built with the sanitizers) and the bit gather / spread helpers with which
 hdc_create packs the varying dimensions and expand_kernel's stage masks are made (a C++ check
 program compiled with the host compiler against bit-by-bit definitions)."""
@@ -27,6 +28,16 @@ def test_contraction_table_builders_under_the_sanitizers(tmp_path):
     src = os.path.join(ROOT, "tests", "host", "contract_tables_check.cpp")
     inc = os.path.join(ROOT, "paper_2206_04746_amd", "csrc")
     subprocess.run(["g++", "-O1", "-g", "-std=c++17", "-Wall", "-Werror", "-fsanitize=address,undefined",
+                    "-fno-sanitize-recover=all", "-I", inc, src, "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.startswith("OK"), r.stdout + r.stderr
+
+
+def test_digits_of_row_elements_under_the_sanitizers(tmp_path):
+    exe = tmp_path / "row_digits_check"
+    src = os.path.join(ROOT, "tests", "host", "row_digits_check.cpp")
+    inc = os.path.join(ROOT, "paper_2206_04746_amd", "csrc")
+    subprocess.run(["g++", "-O1", "-g", "-std=c++17", "-Wall", "-Werror", "-fsanitize=address,undefined,float-cast-overflow",
                     "-fno-sanitize-recover=all", "-I", inc, src, "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0 and r.stdout.startswith("OK"), r.stdout + r.stderr
