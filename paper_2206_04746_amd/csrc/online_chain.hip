@@ -1263,7 +1263,8 @@ static bool wide_takes(const hdc_ctx_impl *c, int64_t N, int32_t epochs, float l
            (C <= 4 || 3 * N >= 2 * kChainBlock * (C <= kWideWaves ? 1 : blocks)) && fabsf(lr) < kTameRate;
 }
 
-static int reserve_blocks(hdc_ctx_impl *c) {
+// (the tests call it, for contexts without the scratch of longer blocks)
+int reserve_online_blocks(hdc_ctx_impl *c) {
     if (c->oc_ready) return HDC_OK;
     const int C = c->p.C, D = c->p.D;
     const int G = (D + kWave - 1) / kWave, slice = chain_slice(D), slices = (D + slice - 1) / slice;
@@ -1301,7 +1302,7 @@ static int reserve_blocks(hdc_ctx_impl *c) {
 // (Long calls go in blocks of 256 where the memory for longer ones cannot be had.)
 int reserve_online_chain(hdc_ctx_impl *c) {
     if (c->oc_ready && c->os_ready) return HDC_OK;
-    int rc = reserve_blocks(c);
+    int rc = reserve_online_blocks(c);
     if (rc == HDC_OK) {
         rc = reserve_online_spread(c);
         if (rc == HDC_ENOMEM) rc = HDC_OK;

@@ -1210,7 +1210,7 @@ int launch_online_spread(hdc_ctx_impl *c, const uint32_t *hv, const int32_t *lab
     const int C = c->p.C, D = c->p.D, W = c->W, G = (D + kWave - 1) / kWave;
     int slices;
     ProfScope walk(c, HDC_K_ONLINE, s, !BATCH);   // a walk by samples as a whole; of batches each block's three steps
-    ProfScope which(c, HDC_K_ONLINE_WIDE, s, !BATCH && C <= 16), spread(c, HDC_K_ONLINE_SPREAD, s);
+    ProfScope spread(c, HDC_K_ONLINE_SPREAD, s);
     int rc = launch_norm(c, acc, G, s);
     if (rc != HDC_OK) return rc;
     const int block = kSpan / batch * batch;   // whole batches

@@ -41,6 +41,7 @@ constexpr int64_t kOnlineWords = 14 * 1024;   // samples x threads whose bit wor
 bool online_chain_takes(const hdc_ctx_impl *c);
 bool online_chain_pays(const hdc_ctx_impl *c, int64_t N, int64_t batch);
 int reserve_online_chain(hdc_ctx_impl *c);
+int reserve_online_blocks(hdc_ctx_impl *c);   // without that of longer blocks (online_spread.hip)
 // Whether a call may go in blocks: a model they take, their scratch there or to be had.  False without an
 // error (*rc HDC_OK) while the stream is captured or memory is short: such a call goes another way.
 bool online_chain_ready(hdc_ctx_impl *c, hipStream_t s, int *rc);

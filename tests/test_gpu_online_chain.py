@@ -8,6 +8,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 import oracle  # noqa: E402
+from paper_2206_04746_amd import binding  # noqa: E402
 from workloads import make_workload  # noqa: E402
 
 from test_gpu_online_batched import clustered  # noqa: E402
@@ -20,6 +21,12 @@ from test_gpu_parity import dev_u32, make_ctx  # noqa: E402
 # such weights of random sign: sqrt(n) 3e-7, whatever its own size (an element next to zero by as much as a large
 # one: hence the bound against the largest), which against rows of size sqrt(n) is 3e-7.  Seven times that.
 TOL = 2e-6
+
+
+def blocks_of_256(ctx):
+    """The context as it is where the scratch of longer blocks could not be had."""
+    assert getattr(binding.lib, "_ZN3hdc21reserve_online_blocksEPNS_12hdc_ctx_implE")(ctx._h) == 0
+    return ctx
 
 
 def off(acc, want):
@@ -132,16 +139,19 @@ def test_rows_and_weights_that_are_not_finite(C, row, value, lr, batch):
     ctx.close()
 
 
-def test_more_samples_than_are_held_at_a_time():
-    D, C, N = 96, 3, 16384 + 300                   # the sample products of 16384 rows are held at a time
+@pytest.mark.parametrize("C,longer", [(3, True), (3, False), (35, True)])
+def test_more_samples_than_are_held_at_a_time(C, longer):
+    D, N = 96, 16384 + 300                         # the sample products of 16384 rows are held at a time
     rng = np.random.default_rng(1)
     wl = make_workload(1, D=D, C=C, F=3, L=2)
     hv, y = clustered(rng, N, D, C)
-    ctx = make_ctx(wl)
+    ctx = make_ctx(wl) if longer else blocks_of_256(make_ctx(wl))
     hvd, yd = dev_u32(hv), torch.from_numpy(y).cuda()
+    ctx.hdc_profile_enable(True)
     for batch in (8, 60):
         acc = torch.zeros((C, D), dtype=torch.float32, device="cuda")
         ctx.hdc_train_online_batched(hvd, yd, acc, batch, epochs=2, lr=1.0)
+        assert ctx.hdc_profile_read("online_spread")[1] == (longer and C <= 32)
         assert off(acc, oracle.train_online_batched(hv, y, D, C, batch, epochs=2, lr=1.0)) < 1e-5   # n <= 11000: sqrt(n) 2^-23
     ctx.close()
 

@@ -25,7 +25,9 @@ def train(ctx, hvd, yd, acc, batch, epochs, lr=1.0):
         ctx.hdc_train_online_batched(hvd, yd, acc, batch, epochs=epochs, lr=lr)
     else:
         ctx.hdc_train_online(hvd, yd, acc, epochs=epochs, lr=lr)
-    return ctx.hdc_profile_read("online_spread")[1]
+    spread = ctx.hdc_profile_read("online_spread")[1]
+    assert not (spread and ctx.hdc_profile_read("online_wide")[1])     # (counts calls in blocks of 256)
+    return spread
 
 
 def goes(C, N, batch):

@@ -1,6 +1,7 @@
 """Per-sample online training with the blocks walked as a whole and a block's row updates beside the next block's
 chain (csrc/online_chain.hip, up to 16 classes and D = 32767, from 129 samples on, 128 (C - 2) + 1 in all epochs, two thirds of a block from 5 classes on, of all blocks from 9 on) against
-the CPU oracle: where the order of the products changes, at the edges of sub-blocks and blocks, and where calls leave it."""
+the CPU oracle: where the order of the products changes, at the edges of sub-blocks and blocks, and where calls leave it.  The
+contexts have no scratch for longer blocks, in which calls of more than 1024 samples go otherwise (test_gpu_online_spread.py)."""
 import numpy as np
 import pytest
 
@@ -12,7 +13,7 @@ import oracle  # noqa: E402
 from workloads import make_workload  # noqa: E402
 
 from test_gpu_online_batched import clustered  # noqa: E402
-from test_gpu_online_chain import TOL, off  # noqa: E402
+from test_gpu_online_chain import TOL, blocks_of_256, off  # noqa: E402
 from test_gpu_parity import dev_u32, make_ctx  # noqa: E402
 
 
@@ -38,7 +39,7 @@ def train(ctx, hv, y, acc, epochs, lr):
     (9, 64, 341, 9, 1.0, 0), (9, 64, 342, 9, 1.0, 1), (9, 64, 513, 9, 1.0, 1), (17, 64, 4000, 1, 1.0, 0), (3, 32767, 129, 1, 1.0, 1), (3, 32768, 129, 1, 1.0, 0),
     (3, 64, 300, 1, 0.9e30, 1), (3, 64, 300, 1, 1e30, 0), (3, 64, 300, 1, float("nan"), 0)])
 def test_which_calls_go_in_blocks_walked_as_a_whole(C, D, N, epochs, lr, wide):
-    ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
+    ctx = blocks_of_256(make_ctx(make_workload(1, D=D, C=C, F=3, L=2)))
     hv, y = np.zeros((N, ctx.W), np.uint32), np.zeros(N, np.int32)
     assert train(ctx, hv, y, torch.zeros((C, D), dtype=torch.float32, device="cuda"), epochs, lr) == wide
     ctx.close()
@@ -53,7 +54,7 @@ def test_blocks_as_a_whole_match_the_oracle(D, C, N, kind):
     rng = np.random.default_rng(D + 10 * C + N)
     hv, y = clustered(rng, N, D, C)
     y = labels(kind, rng, y, C)
-    ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
+    ctx = blocks_of_256(make_ctx(make_workload(1, D=D, C=C, F=3, L=2)))
     acc = torch.zeros((C, D), dtype=torch.float32, device="cuda")
     epochs = max(2, 128 * (C - 2) // N + 1)        # with fewer samples in all they go by sub-blocks
     for calls in (1, 2):                           # the second call goes on from the rows of the first
@@ -71,7 +72,7 @@ def test_blocks_of_wrong_predictions_match_the_oracle(D, C, N, flip, wrong):
     rng = np.random.default_rng(D + 10 * C + N)
     hv, y = clustered(rng, N, D, C, flip)
     y = np.where(rng.random(N) < wrong, rng.integers(0, C, N), y).astype(np.int32)
-    ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
+    ctx = blocks_of_256(make_ctx(make_workload(1, D=D, C=C, F=3, L=2)))
     acc = torch.zeros((C, D), dtype=torch.float32, device="cuda")
     assert train(ctx, hv, y, acc, 2, 1.0)
     assert off(acc, oracle.train_online(hv, y, D, C, epochs=2, lr=1.0)) < TOL
@@ -87,7 +88,7 @@ def test_rows_that_are_not_finite(C, N, row, value):
     hv, y = clustered(np.random.default_rng(C), N, D, C)
     start = np.random.default_rng(6).normal(size=(C, D)).astype(np.float32)
     start[row, 7] = value
-    ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
+    ctx = blocks_of_256(make_ctx(make_workload(1, D=D, C=C, F=3, L=2)))
     acc = torch.from_numpy(start.copy()).cuda()
     assert train(ctx, hv, y, acc, 1, 1.0)
     got, want = acc.cpu().numpy(), oracle.train_online(hv, y, D, C, epochs=1, lr=1.0, acc=start.copy())
@@ -101,7 +102,7 @@ def test_rows_that_are_not_finite(C, N, row, value):
 def test_more_samples_than_are_held_at_a_time():
     D, C, N = 96, 3, 16384 + 300                   # 64 blocks are held at a time
     hv, y = clustered(np.random.default_rng(1), N, D, C)
-    ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
+    ctx = blocks_of_256(make_ctx(make_workload(1, D=D, C=C, F=3, L=2)))
     acc = torch.zeros((C, D), dtype=torch.float32, device="cuda")
     assert train(ctx, hv, y, acc, 2, 1.0)
     assert off(acc, oracle.train_online(hv, y, D, C, epochs=2, lr=1.0)) < 1e-5   # n <= 6000: sqrt(n) 2^-23
