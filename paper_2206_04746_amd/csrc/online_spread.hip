@@ -123,7 +123,7 @@ struct SpreadShared {
     uint8_t key[kLists * kListGroups + 8];// class of a group of sources
     int first_group[2 * kMaxClasses + 1]; // of a class
     int total[2 * kMaxClasses];           // sources of a class
-    int front[2], wrong[2], flips[2];     // first workgroup that a weight of has changed; whether a prediction is wrong; those that have changed
+    int front[2], wrong[2], flips[2];     // first workgroup that a weight of has changed; predictions that are wrong; those that have changed
     int parting[2];                       // whether a workgroup has gone on alone
     int own_changed, number, odd[kWaves], zero[kWaves];
     int2 own_class[kOwn];                 // its own samples: label, class wrongly predicted or -1
@@ -557,7 +557,7 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
                 for (int u = 0; u < kHeard; ++u) missing |= wanted[u] && !v[u];
                 if (!__ballot(missing)) break;
             }
-            int told = group, flips = 0;
+            int told = group, flips = 0, wrong_here = 0;
             bool parts = false;
 #pragma unroll
             for (int u = 0; u < kHeard; ++u) {
@@ -571,17 +571,18 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
                 flips += __popcll(__ballot(wrong + 1 != before[u]));
                 parts |= wanted[u] && (hi & 0x200);
                 rank[u] = -1;
-                if (__ballot(wrong >= 0)) {   // numbers of the samples a class was wrongly predicted for, by the ballots of 64
+                if (const uint64_t any = __ballot(wrong >= 0)) {   // numbers of the samples a class was wrongly predicted for, by the ballots of 64
                     if (wanted[u] && wrong >= 0) s.heard_wp[n] = __uint_as_float((uint32_t)(vp[u] ? vp[u] : wait_for(slot + kSpan + n)));
                     uint64_t same;
                     const int key = wrong_key(n, wrong), k = rank_of(key, wrong >= 0, same);
                     if (wrong >= 0 && k == 0) s.count[wave + u * kHearing][key] = (uint16_t)__popcll(same);
                     if (wrong >= 0) rank[u] = k << 8 | key;
-                    s.wrong[r & 1] = 1;
+                    wrong_here += __popcll(any);
                 }
             }
             if (told < group && lane == 0) atomicMin(&s.front[r & 1], told);
             if (flips && lane == 0) atomicAdd(&s.flips[r & 1], flips);
+            if (wrong_here && lane == 0) atomicAdd(&s.wrong[r & 1], wrong_here);
             if (parts) s.parting[r & 1] = 1;
         }
         __syncthreads();
@@ -591,13 +592,14 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
             break;
         }
         if (s.parting[r & 1]) break;
-        // Where most predictions change at the second or third pass they are mostly wrong, and a pass settles few samples: the
-        // workgroups go on one after another (no passes tried: 1585 us; all of them first, 1685: 4000 samples of 6 classes,
-        // labels at random).  From zero rows of classes that are like one another predictions change from the fourth pass on,
-        // and settle by the eighteenth: 110 us for the first 2048 samples, 510 one workgroup after another.  They change among
-        // the earliest first, so that few samples before a workgroup say nothing (9 classes, 2197 samples, D = 2115: 310 us, and
-        // 775 where a workgroup after 256 samples asked at the fourth pass).
-        parting = r + 1 == kRounds || (r == 2 && 4 * s.flips[0] > 3 * n0 && n0 >= 4 * kWave) ||
+        // Where most predictions change at the second pass and most are wrong then, or half of them change at the third, a pass settles
+        // few samples: the workgroups go on one after another (no passes tried: 1585 us; all of them first, 1685: 4000 samples of 6
+        // classes, labels at random).  From rows that were trained on other labels, or that are none, most predictions change at
+        // the second pass, because they are right then, and few at the third.  From zero rows of classes that are like one another
+        // they change from the fourth pass on, and settle by the eighteenth: 110 us for the first 2048 samples, 510 one workgroup
+        // after another.  They change among the earliest first, so that few samples before a workgroup say nothing (9 classes, 2197
+        // samples, D = 2115: 310 us, and 775 where a workgroup after 256 samples asked at the fourth pass).
+        parting = r + 1 == kRounds || (r == 2 && 4 * s.flips[0] > 3 * n0 && 2 * s.wrong[0] > n0 && n0 >= 4 * kWave) ||
                   (r == 3 && 2 * s.flips[1] > n0 && n0 >= 8 * kWave);
         wrong_ones = s.wrong[r & 1] != 0;
         if (wrong_ones)

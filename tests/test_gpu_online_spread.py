@@ -96,6 +96,51 @@ def test_long_calls_of_wrong_predictions(D, C, N, batch, flip, wrong):
     ctx.close()
 
 
+def starting_rows(kind, rng, hv, y, D, C):
+    """zeros; at random; trained on other labels, of all samples or of half of them"""
+    if kind == "zero":
+        return np.zeros((C, D), dtype=np.float32)
+    if kind == "random":
+        return rng.normal(size=(C, D)).astype(np.float32)
+    named = (y[:200] + 1) % C
+    return oracle.train_online(hv[:200], (named if kind == "other" else np.where(rng.random(200) < 0.5, y[:200], named)).astype(np.int32), D, C, epochs=1, lr=1.0)
+
+
+# Most predictions change at the second pass, because they are right then: the passes go on
+@pytest.mark.parametrize("kind", ["random", "other", "half"])
+@pytest.mark.parametrize("batch", [0, 32])
+@pytest.mark.parametrize("D,C,N", [(1000, 2, 2000), (1000, 6, 2100), (2000, 20, 2048)])
+def test_long_calls_from_rows_that_know_other_labels(D, C, N, batch, kind):
+    rng = np.random.default_rng(D + C + N)
+    hv, y = clustered(rng, N, D, C)
+    start = starting_rows(kind, rng, hv, y, D, C)
+    ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
+    acc = torch.from_numpy(start.copy()).cuda()
+    assert train(ctx, dev_u32(hv), torch.from_numpy(y).cuda(), acc, batch, 1)
+    assert off(acc, want(hv, y, D, C, batch, 1, acc=start.copy())) < TOL
+    ctx.close()
+
+
+def test_rows_that_know_other_labels_take_no_longer_than_zeros():
+    D, C, N = 1000, 6, 2000                        # 145 us either way; 480 from such rows if workgroups go on alone
+    rng = np.random.default_rng(1)
+    hv, y = clustered(rng, N, D, C)
+    ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
+    hvd, yd, took = dev_u32(hv), torch.from_numpy(y).cuda(), {}
+    for kind in ("zero", "other"):
+        start = torch.from_numpy(starting_rows(kind, rng, hv, y, D, C)).cuda()
+        took[kind] = []
+        for _ in range(8):
+            acc, first, last = start.clone(), torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            first.record()
+            ctx.hdc_train_online(hvd, yd, acc, epochs=1, lr=1.0)
+            last.record()
+            torch.cuda.synchronize()
+            took[kind].append(first.elapsed_time(last))
+    ctx.close()
+    assert min(took["other"]) < 2 * min(took["zero"]), took
+
+
 @pytest.mark.parametrize("batch", [0, 20])
 @pytest.mark.parametrize("row,value", [(0, float("nan")), (1, float("inf"))])
 @pytest.mark.parametrize("C", [3, 20])
