@@ -30,7 +30,8 @@ constexpr int kRunGroup = 4;              // a class's sources are filled up to 
 constexpr int kListGroups = kSteps / kRunGroup;
 constexpr int kNone = kSpan;              // a source that is none: its weight is zero
 constexpr int kMaxClasses = 32;
-constexpr int kRounds = 49;               // slots: passes that the workgroups take together, at most, and one for the end
+constexpr int kRounds = 49, kManyRounds = 97;   // passes that the workgroups take together, at most, and one; the second with more than kWaves classes
+__host__ __device__ constexpr int slots_of(int C) { return C <= kWaves ? kRounds : kManyRounds; }   // the last one for the end
 constexpr int kSpinLimit = 1 << 24;       // loads of one word before a wait is given up (never: see wait_for)
 static_assert(kOwn * (kGroups - 1) + (kRunGroup - 1) * 2 * kMaxClasses <= kLists * kSteps, "room in the lists");
 
@@ -426,6 +427,12 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
         }
     };
     const int64_t words = slot_words(C);
+    // One wave takes long for its 16 samples with two classes a wave, and the more classes the sooner passes settle (24, labels at
+    // random, 67 passes of 2048 samples; 6, 270).  4000 samples, D = 2000, us, one workgroup after another, by passes, blocks of 256:
+    // 17 classes 2391, 2154, 1770; 24 2343, 1717, 1692, six tenths at random 2096, 1335, 1556; 32 2309, 1442, 1802.  In batches a workgroup
+    // has no samples of its own to settle (24 classes, batches of 32, at random: 924, 1407, 1001).
+    constexpr bool kPassesOnly = CPW == 2 && !BATCH;
+    constexpr int kPasses = kPassesOnly ? kManyRounds : kRounds;
     // The first pass: no sample of the block counts yet.  Told before the lists are made, it is there when they are.
 #pragma unroll
     for (int k = 0; k < CPW; ++k)
@@ -526,7 +533,7 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
     auto wrong_key = [&](int n, int wrong) { return max(wrong, 0) + (BATCH && n >= first_open ? C : 0); };
     bool done = false;
     int r = 1;
-    for (; r < kRounds; ++r) {
+    for (; r < kPasses; ++r) {
         asm volatile("" : "+v"(tid));   // (addresses are formed anew in a pass: kept over all, they would not fit the registers)
         lane = tid & (kWave - 1), l = lane & (kOwn - 1), q = lane / kOwn;
         Word *slot = slots + (r - 1) * words;
@@ -599,8 +606,8 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
         // they change from the fourth pass on, and settle by the eighteenth: 110 us for the first 2048 samples, 510 one workgroup
         // after another.  They change among the earliest first, so that few samples before a workgroup say nothing (9 classes, 2197
         // samples, D = 2115: 310 us, and 775 where a workgroup after 256 samples asked at the fourth pass).
-        parting = r + 1 == kRounds || (r == 2 && 4 * s.flips[0] > 3 * n0 && 2 * s.wrong[0] > n0 && n0 >= 4 * kWave) ||
-                  (r == 3 && 2 * s.flips[1] > n0 && n0 >= 8 * kWave);
+        parting = r + 1 == kPasses || (!kPassesOnly && ((r == 2 && 4 * s.flips[0] > 3 * n0 && 2 * s.wrong[0] > n0 && n0 >= 4 * kWave) ||
+                                                        (r == 3 && 2 * s.flips[1] > n0 && n0 >= 8 * kWave)));
         wrong_ones = s.wrong[r & 1] != 0;
         if (wrong_ones)
             for (int v = wave; v < classes; v += kWaves) {
@@ -774,11 +781,11 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
         __syncthreads();
         if (wave == decider) {
             decide(false);
-            if (r + 1 < kRounds) tell_weights(slots + r * words);
+            if (r + 1 < kPasses) tell_weights(slots + r * words);
         }
         if (parting) break;
     }
-    Word *slot = slots + (kRounds - 1) * words;   // the last one: weights and squared norms for good
+    Word *slot = slots + (slots_of(C) - 1) * words;   // the last one: weights and squared norms for good
     if (done) {
         if (wave == decider) {
             changed = parting = false;
@@ -917,7 +924,7 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
                 }
             }
         }
-        if (group == groups - 1 && tid == 0) state[1] = kRounds;
+        if (group == groups - 1 && tid == 0) state[1] = kPasses;
         return;
     }
     if (wave) return;
@@ -946,7 +953,7 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
         tell(norms + group, norm_word(s.mine[lane].x));
         if (BATCH) tell(norms + (int64_t)C * kGroups + group, norm_word(s.mine[lane].y));
     }
-    if (group == groups - 1 && lane == 0) state[1] = kRounds;
+    if (group == groups - 1 && lane == 0) state[1] = kPasses;
 }
 
 // ---- the rows ------------------------------------------------------------------------------------
@@ -1023,7 +1030,7 @@ __global__ __launch_bounds__(kThreads) void online_update_kernel(const uint64_t 
     if (d < D && wave < C) first = acc[(int64_t)wave * D + d];
     reinterpret_cast<uint32_t *>(&s.count[0][0])[tid & (kSpan / kWave * kMaxClasses / 2 - 1)] = 0;
     {
-        const int64_t words = slot_words(C), used = min(state[1], kRounds - 1) * words, end = (kRounds - 1) * words - used;   // and the last one
+        const int64_t words = slot_words(C), last = (slots_of(C) - 1) * words, used = min(state[1] * words, last), end = last - used;   // and the last one
         for (int64_t i = (int64_t)blockIdx.x * kThreads + tid; i < used + words; i += (int64_t)gridDim.x * kThreads)
             slots[i < used ? i : i + end] = 0;
         if (blockIdx.x == 0 && tid == 0) state[0] = 0;
@@ -1167,7 +1174,7 @@ int reserve_online_spread(hdc_ctx_impl *c) {
     if (c->os_ready || c->p.C > kMaxClasses) return HDC_OK;
     const int C = c->p.C, D = c->p.D, G = (D + kWave - 1) / kWave;
     const int slices = row_dots_slices(D, kDotSlices);
-    const size_t slot_bytes = (size_t)kRounds * slot_words(C) * sizeof(Word);
+    const size_t slot_bytes = (size_t)slots_of(C) * slot_words(C) * sizeof(Word);
     struct { void **at; size_t bytes; } parts[] = {
         {(void **)&c->os_slots_d, slot_bytes + 256},
         {(void **)&c->os_strips_d, (size_t)held_spans(G) * kSpanProducts * sizeof(int16_t)},

@@ -141,6 +141,21 @@ def test_rows_that_know_other_labels_take_no_longer_than_zeros():
     assert min(took["other"]) < 2 * min(took["zero"]), took
 
 
+# With more than 16 classes passes go on, 96 of them (24 classes: 70 are enough; 17 of few dimensions: 110 to 150 would be)
+@pytest.mark.parametrize("D,C,N", [(512, 24, 2048), (200, 17, 2100), (64, 18, 2048)])
+def test_long_calls_of_many_classes_and_random_labels(D, C, N):
+    rng = np.random.default_rng(D + C)
+    hv, y = clustered(rng, N, D, C)
+    y = rng.integers(0, C, N).astype(np.int32)
+    ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
+    hvd, yd, rows = dev_u32(hv), torch.from_numpy(y).cuda(), []
+    for _ in range(2):                             # the second call finds the words as the first one found them
+        rows.append(torch.zeros((C, D), dtype=torch.float32, device="cuda"))
+        assert train(ctx, hvd, yd, rows[-1], 0, 1)
+    assert torch.equal(rows[0], rows[1]) and off(rows[0], want(hv, y, D, C, 0, 1)) < TOL
+    ctx.close()
+
+
 @pytest.mark.parametrize("batch", [0, 20])
 @pytest.mark.parametrize("row,value", [(0, float("nan")), (1, float("inf"))])
 @pytest.mark.parametrize("C", [3, 20])
