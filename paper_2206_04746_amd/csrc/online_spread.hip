@@ -173,27 +173,38 @@ __device__ __forceinline__ void add_own(double (&acc)[CL < 2 ? 2 : CL], const do
                          : "v"(w[k]), "v"(w[k + 1]), "v"(g[0]), "v"(g[1]), "v"(g[2]), "v"(g[3]), "n"(I), "n"(I + 1), "n"(I + 2), "n"(I + 3));
 }
 
-// One wave finds the fixed point of a workgroup's samples by itself.  Row q of lanes has classes q, q + 4 ... q + 4 CL - 4 and,
+// One wave finds the fixed point of a workgroup's samples by itself: a chain of dependent instructions, five to seven passes of about 900
+// clocks where labels are at random, so nothing is read again in a pass that fits the registers (4000 samples of 6 classes, D = 2000, labels
+// at random: 1604 us with LDS reads in every pass and products made after the last weights were heard, 1449 now).  Row q of lanes has classes q, q + 4 ... q + 4 CL - 4 and,
 // for more classes than that, those 4 CL further on; what the samples before add to the dot products lies in tail and head (all
 // of it; what counts in batches), the squared norms in wrong_tail and wrong_head.
 template <int CL, int CHUNKS, bool BATCH>
-__device__ __forceinline__ void settle_own(SpreadShared &s, int n0, int fb, int next_fb, int C, int odd, double dd, float lr, double inv_root_d) {
+__device__ __forceinline__ void settle_own(SpreadShared &s, const double (&product)[kOwn], int n0, int fb, int next_fb, int C, double dd, float lr,
+                                           double inv_root_d) {
     const int lane = threadIdx.x & (kWave - 1), l = lane & (kOwn - 1), q = lane / kOwn;
     int2 of = s.own_class[l];
     double2 own = s.own_w[l];
-    double product[kOwn];
     const int before_batch = fb - n0;   // (batches) own samples that count
+    // What the samples before add: in registers for all passes, where there is room (a pass then stores nothing), else asked for when a
+    // pass begins, or where it is used.
+    constexpr bool kHold = CHUNKS == 1 && !BATCH, kAsk = CHUNKS == 1 && BATCH;
+    double every_before[CL], counts_before[CL], norm[CL], norm_open[CL], grown[CL];
+    auto load_before = [&](int h, int k) {
+        const int at = min(4 * (CL * h + k) + q, C - 1);
+        every_before[k] = s.tail[at][l];
+        norm[k] = s.wrong_tail[at][0];
+        if (BATCH) counts_before[k] = s.head[at][l], norm_open[k] = s.wrong_head[at][0];
+    };
 #pragma unroll
-    for (int u = 0; u < kOwn; ++u) {
-        const double g = (double)(2 * (int)s.strip[(n0 + u) * kOwn + l] + odd);
-        product[u] = u < l ? g : 0.0;
-    }
+    for (int k = 0; kHold && k < CL; ++k) load_before(0, k);
     for (int pass = 0; pass < kOwn + 2; ++pass) {   // (16 settle them, one more finds nothing changed)
         double best = -4.0, cos_y = 0.0;
         int arg = kMaxClasses;
 #pragma unroll
         for (int h = 0; h < CHUNKS; ++h) {
             double w[CL], every[CL < 2 ? 2 : CL] = {}, dot[CL < 2 ? 2 : CL] = {};
+#pragma unroll
+            for (int k = 0; kAsk && k < CL; ++k) load_before(0, k);
 #pragma unroll
             for (int k = 0; k < CL; ++k) {
                 const int c = 4 * (CL * h + k) + q;
@@ -212,16 +223,19 @@ __device__ __forceinline__ void settle_own(SpreadShared &s, int n0, int fb, int 
             if (CL == 1) every[0] += every[1], dot[0] += dot[1];
 #pragma unroll
             for (int k = 0; k < CL; ++k) {
-                const int c = 4 * (CL * h + k) + q, at = min(c, C - 1);
-                const double all = every[k] + s.tail[at][l], counts = BATCH ? dot[k] + s.head[at][l] : all;
+                const int c = 4 * (CL * h + k) + q;
+                if (CHUNKS > 1) load_before(h, k);
+                const double all = every[k] + every_before[k], counts = BATCH ? dot[k] + counts_before[k] : all;
                 const double run = row_prefix(w[k] * fma(w[k], dd, 2.0 * all)), before = row_before(run);
-                const double base = s.wrong_tail[at][0];
-                double nn = base + before;
+                double nn = norm[k] + before;
                 if (BATCH) {
                     const double at_fb = __shfl(before, kOwn * q + min(max(fb - n0, 0), kOwn - 1), kWave);
-                    nn = fb >= n0 ? base + at_fb : s.wrong_head[at][0];
+                    nn = fb >= n0 ? norm[k] + at_fb : norm_open[k];
                 }
-                s.cosine[c][l] = run;   // (32 classes there)
+                if (kHold)
+                    grown[k] = run;
+                else
+                    s.cosine[c][l] = run;   // (32 classes there)
                 const double cs = cosine_of(counts, nn, inv_root_d);
                 const bool better = (c < C) & (cs > best);
                 best = better ? cs : best;
@@ -248,6 +262,10 @@ __device__ __forceinline__ void settle_own(SpreadShared &s, int n0, int fb, int 
         own = make_double2(wy, wp);
         of.y = pred;
         if (!moved) break;
+    }
+    if constexpr (kHold) {
+#pragma unroll
+        for (int k = 0; k < CL; ++k) s.cosine[4 * k + q][l] = grown[k];
     }
     if (q == 0) {
         s.own_class[l] = of;
@@ -883,6 +901,17 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
             }
         }
     }
+    // The settling wave's products of the 16 samples with one another, on their way while others wait for the last weights: it has
+    // class 15, so none of its own with fewer.
+    constexpr int kSettler = kWaves - 1 - kHearing;
+    double product[kOwn] = {};
+    if (wave == kSettler && !one_batch) {
+#pragma unroll
+        for (int u = 0; u < kOwn; ++u) {
+            const double g = (double)whole(s.strip[(n0 + u) * kOwn + l]);
+            product[u] = u < l ? g : 0.0;
+        }
+    }
     __syncthreads();
     if (one_batch) {   // no sample of its own counts: cosines at once; then what it adds to the squared norms
         for (int c = wave; c < C; c += kWaves)
@@ -927,16 +956,16 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
         if (group == groups - 1 && tid == 0) state[1] = kPasses;
         return;
     }
-    if (wave) return;
+    if (wave != kSettler) return;
     if constexpr (CPW == 2) {
-        settle_own<BATCH ? 2 : 4, BATCH ? 4 : 2, BATCH>(s, n0, fb, next_fb, C, odd, dd, lr, inv_root_d);
+        settle_own<BATCH ? 2 : 4, BATCH ? 4 : 2, BATCH>(s, product, n0, fb, next_fb, C, dd, lr, inv_root_d);
     } else {
         if (C <= 4)
-            settle_own<1, 1, BATCH>(s, n0, fb, next_fb, C, odd, dd, lr, inv_root_d);
+            settle_own<1, 1, BATCH>(s, product, n0, fb, next_fb, C, dd, lr, inv_root_d);
         else if (C <= 8)
-            settle_own<2, 1, BATCH>(s, n0, fb, next_fb, C, odd, dd, lr, inv_root_d);
+            settle_own<2, 1, BATCH>(s, product, n0, fb, next_fb, C, dd, lr, inv_root_d);
         else
-            settle_own<BATCH ? 2 : 4, BATCH ? 2 : 1, BATCH>(s, n0, fb, next_fb, C, odd, dd, lr, inv_root_d);
+            settle_own<BATCH ? 2 : 4, BATCH ? 2 : 1, BATCH>(s, product, n0, fb, next_fb, C, dd, lr, inv_root_d);
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
