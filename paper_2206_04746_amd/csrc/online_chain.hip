@@ -467,6 +467,7 @@ struct BlockBefore {
 // ---- the chain -----------------------------------------------------------------------------------
 // The product of samples n < m from a block's tiles, which hold them whole or as online_gram_kernel's halves.
 struct TileProduct {
+    static constexpr bool kPanels = false;
     const int16_t *prod;
     int odd;
     bool halves;

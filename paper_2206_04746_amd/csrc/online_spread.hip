@@ -137,9 +137,12 @@ struct SortShared {                       // lies over tail and head
 };
 static_assert(sizeof(SortShared) <= sizeof(double) * kOwn * (kLists + 2 * kMaxClasses), "");
 static_assert(sizeof(SpreadShared) <= 160 * 1024, "LDS of a compute unit");
-static_assert(sizeof(OnlineWeight) * kSpan <= sizeof(int16_t) * kSpan * kOwn, "records of a walk by samples");
+// a walk by samples: their records in what the passes sum, its panels' sums in the strip
+static_assert(sizeof(OnlineWeight) * kSpan <= offsetof(SpreadShared, cosine) - offsetof(SpreadShared, word), "");
+static_assert(sizeof(double) * kMaxClasses * kPanel <= sizeof(int16_t) * kSpan * kOwn, "");
 
 struct StripProduct {
+    static constexpr bool kPanels = true;
     const int16_t *strips;
     int odd;
     __device__ int operator()(int n, int m) const {
@@ -388,9 +391,9 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
     if (__builtin_expect(__ballot(lane < kWaves && s.odd[lane & (kWaves - 1)]) != 0, 0)) {   // rows that are not finite: the same everywhere
         if (group) return;
         __syncthreads();
-        OnlineWeight *rec = reinterpret_cast<OnlineWeight *>(s.strip);
+        OnlineWeight *rec = reinterpret_cast<OnlineWeight *>(s.word);
         walk_block<CPW, BATCH>(StripProduct{strips, odd}, part, kSpan, slices, nb, batch, labels, normpart, nullptr, nullptr, G, C, D,
-                               lr, inv_root_d, rec, &s.cosine[0][0]);
+                               lr, inv_root_d, rec, &s.cosine[0][0], reinterpret_cast<double *>(s.strip));
         for (int n = tid; n < nb; n += kThreads) out[n] = rec[n];
         if (tid == 0) state[1] = 0;
         return;

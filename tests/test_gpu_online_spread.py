@@ -13,7 +13,7 @@ import oracle  # noqa: E402
 from workloads import make_workload  # noqa: E402
 
 from test_gpu_online_batched import clustered  # noqa: E402
-from test_gpu_online_chain import TOL, off  # noqa: E402
+from test_gpu_online_chain import TOL, blocks_of_256, off  # noqa: E402
 from test_gpu_online_wide import labels  # noqa: E402
 from test_gpu_parity import dev_u32, make_ctx  # noqa: E402
 
@@ -156,9 +156,10 @@ def test_long_calls_of_many_classes_and_random_labels(D, C, N):
     ctx.close()
 
 
-@pytest.mark.parametrize("batch", [0, 20])
+# (panels of 256 samples, of 240, 195 and 200 in batches; the last block of one panel)
+@pytest.mark.parametrize("batch", [0, 20, 65, 100])
 @pytest.mark.parametrize("row,value", [(0, float("nan")), (1, float("inf"))])
-@pytest.mark.parametrize("C", [3, 20])
+@pytest.mark.parametrize("C", [3, 20, 32])
 def test_long_calls_from_rows_that_are_not_finite(C, row, value, batch):
     D, N = 200, 2100
     hv, y = clustered(np.random.default_rng(C), N, D, C)
@@ -178,6 +179,30 @@ def test_long_calls_from_rows_that_are_not_finite(C, row, value, batch):
     assert np.array_equal(np.isnan(got), np.isnan(expected)) and np.array_equal(got[np.isinf(expected)], expected[np.isinf(expected)])
     assert np.max(np.abs(got[ok] - expected[ok]), initial=0.0) <= TOL * max(1.0, float(np.max(np.abs(expected[ok]), initial=0.0)))
     ctx.close()
+
+
+@pytest.mark.parametrize("batch", [0, 32])
+def test_rows_that_are_not_finite_take_no_longer_than_in_blocks_of_256(batch):
+    D, C, N = 500, 6, 2048                         # 4 ms either way; 10 where each sample was added to by all before it
+    hv, y = clustered(np.random.default_rng(C), N, D, C)
+    hvd, yd, took = dev_u32(hv), torch.from_numpy(y).cuda(), []
+    start = torch.full((C, D), 1.0, device="cuda")
+    start[1, 7] = float("inf")
+    for ctx in (blocks_of_256(make_ctx(make_workload(1, D=D, C=C, F=3, L=2))), make_ctx(make_workload(1, D=D, C=C, F=3, L=2))):
+        times = []
+        for _ in range(4):
+            acc, first, last = start.clone(), torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            first.record()
+            if batch:
+                ctx.hdc_train_online_batched(hvd, yd, acc, batch, epochs=1, lr=1.0)
+            else:
+                ctx.hdc_train_online(hvd, yd, acc, epochs=1, lr=1.0)
+            last.record()
+            torch.cuda.synchronize()
+            times.append(first.elapsed_time(last))
+        took.append(min(times))
+        ctx.close()
+    assert took[1] < 1.5 * took[0], took
 
 
 @pytest.mark.parametrize("wrong", [0.0, 1.0])
