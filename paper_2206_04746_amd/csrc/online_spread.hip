@@ -33,6 +33,10 @@ constexpr int kMaxClasses = 32;
 constexpr int kRounds = 49, kManyRounds = 97;   // passes that the workgroups take together, at most, and one; the second with more than kWaves classes
 __host__ __device__ constexpr int slots_of(int C) { return C <= kWaves ? kRounds : kManyRounds; }   // the last one for the end
 constexpr int kSpinLimit = 1 << 24;       // loads of one word before a wait is given up (never: see wait_for)
+// What such a word of a sample counts as: a weight that is no number, with no prediction and nothing changed; a squared norm's word of 0
+// is no number as it is.  The rows say so then.
+constexpr unsigned long long kLost = 0x7FC00000ull;
+static_assert((kLost & 0x7FFFFFFFull) > 0x7F800000ull && kLost >> 32 == 0, "no number, and nothing beside it");
 static_assert(kOwn * (kGroups - 1) + (kRunGroup - 1) * 2 * kMaxClasses <= kLists * kSteps, "room in the lists");
 
 // ---- what workgroups tell one another ------------------------------------------------------------
@@ -93,7 +97,7 @@ __device__ __forceinline__ double sum_lanes(double v) {
 __device__ __forceinline__ double cosine_of(double dot, double nn, double inv_root_d) {
     double c = dot * refined_rsq(nn) * inv_root_d;
     asm volatile("" : "+v"(c));
-    return nn > 0.0 ? c : 0.0;
+    return nn <= 0.0 ? 0.0 : c;
 }
 
 // How many lanes before this one have the same key (0 to 63), of those that have any; which lanes do.
@@ -573,7 +577,8 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
                 vp[u] = 0;
                 before[u] = (int)(last >> 32 & 0xFF);
             }
-            for (int i = 0; i < kSpinLimit; ++i) {
+            int tries = 0;
+            for (; tries < kSpinLimit; ++tries) {
                 bool missing = false;
 #pragma unroll
                 for (int u = 0; u < kHeard; ++u)
@@ -585,6 +590,10 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
                 for (int u = 0; u < kHeard; ++u) missing |= wanted[u] && !v[u];
                 if (!__ballot(missing)) break;
             }
+            if (__builtin_expect(tries == kSpinLimit, 0))
+#pragma unroll
+                for (int u = 0; u < kHeard; ++u)
+                    if (!v[u]) v[u] = kLost;
             int told = group, flips = 0, wrong_here = 0;
             bool parts = false;
 #pragma unroll
@@ -600,7 +609,10 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
                 parts |= wanted[u] && (hi & 0x200);
                 rank[u] = -1;
                 if (const uint64_t any = __ballot(wrong >= 0)) {   // numbers of the samples a class was wrongly predicted for, by the ballots of 64
-                    if (wanted[u] && wrong >= 0) s.heard_wp[n] = __uint_as_float((uint32_t)(vp[u] ? vp[u] : wait_for(slot + kSpan + n)));
+                    if (wanted[u] && wrong >= 0) {
+                        if (!vp[u]) vp[u] = wait_for(slot + kSpan + n);
+                        s.heard_wp[n] = __uint_as_float((uint32_t)(vp[u] ? vp[u] : kLost));
+                    }
                     uint64_t same;
                     const int key = wrong_key(n, wrong), k = rank_of(key, wrong >= 0, same);
                     if (wrong >= 0 && k == 0) s.count[wave + u * kHearing][key] = (uint16_t)__popcll(same);
@@ -831,6 +843,7 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
     const int last = one_batch ? open_group + within : group;   // workgroups before this one do
     const int turn = (l + 4 * q) & (kOwn - 1);       // lanes 0 to 3 of a row: its four samples
     double old[CPW] = {}, late[CPW] = {};
+    bool lost = false;   // a wait was given up
     auto add = [&](int j, double (&norm)[CPW], double (&norm_open)[CPW], bool ask_norm) {
         const int n = j * kOwn + turn;
         double p[4];
@@ -842,7 +855,8 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
             const bool norms = ask_norm;
             Word vp = 0, vn[CPW] = {};
             v = 0;
-            for (int i = 0; i < kSpinLimit; ++i) {   // all that is to come at once
+            int tries = 0;
+            for (; tries < kSpinLimit; ++tries) {   // all that is to come at once
                 if (!v) v = look(slot + n);
                 if (!vp) vp = look(slot + kSpan + n);
                 bool missing = !v || (((uint32_t)(v >> 32) & 0xFF) && !vp);
@@ -856,6 +870,7 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
                 if (!__ballot(missing)) break;
                 if (group - j > 8) __builtin_amdgcn_s_sleep(8);
             }
+            lost |= tries == kSpinLimit;
             wp = __uint_as_float((uint32_t)vp);
 #pragma unroll
             for (int k = 0; k < CPW; ++k)
@@ -885,6 +900,9 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
             norm_open[k] = start_norm + sum_lanes((lane < known ? grown[k][0] : 0.0) + (lane + kWave < known ? grown[k][1] : 0.0));
         }
         for (int j = 0; j < last; ++j) add(j, norm, norm_open, !one_batch || j < open_group);
+        if (__builtin_expect(lost, 0))
+#pragma unroll
+            for (int k = 0; k < CPW; ++k) old[k] = __builtin_nan("");
 #pragma unroll
         for (int k = 0; k < CPW; ++k) {
             const int c = own_class + k * kWaves;
@@ -931,6 +949,9 @@ __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *
         if (own_class < C) {
             double unused[CPW];
             for (int j = last; j < group; ++j) add(j, unused, unused, false);
+            if (__builtin_expect(lost, 0))
+#pragma unroll
+                for (int k = 0; k < CPW; ++k) old[k] = __builtin_nan("");
 #pragma unroll
             for (int k = 0; k < CPW; ++k) {
                 const int c = own_class + k * kWaves;
