@@ -61,6 +61,46 @@ def test_long_calls_match_the_oracle(D, C, N, batch):
     ctx.close()
 
 
+def packed(rng, N, D, C):
+    """clustered() for many dimensions: an eighth of the bits differ from the class's"""
+    words = lambda n: rng.integers(0, 1 << 32, (n, (D + 31) // 32), dtype=np.uint32)  # noqa: E731
+    y = rng.integers(0, C, N).astype(np.int32)
+    hv = words(C)[y] ^ (words(N) & words(N) & words(N))
+    if D % 32:
+        hv[:, -1] &= np.uint32((1 << (D % 32)) - 1)
+    return hv, y
+
+
+# Slices of more than 512 dimensions' worth of partial sums (D > 10240), squared norms of more than 256 groups (16384), per sample up to D = 32768
+# and in batches to 65535, where products reach the limits of 16 bits: equal samples and ones that differ in every bit
+@pytest.mark.parametrize("batch", [0, 1, 40])
+@pytest.mark.parametrize("D,C,N", [(10241, 3, 1300), (20001, 20, 1600), (32767, 2, 1290), (40000, 2, 1281), (65535, 3, 1300)])
+def test_long_calls_of_many_dimensions(D, C, N, batch):
+    rng = np.random.default_rng(D)
+    hv, y = packed(rng, N, D, C)
+    hv[700], y[700] = hv[3], y[3]
+    hv[1200], y[1200] = ~hv[5], (y[5] + 1) % C
+    hv[1201], y[1201] = ~hv[1199], (y[1199] + 1) % C
+    if D % 32:
+        hv[:, -1] &= np.uint32((1 << (D % 32)) - 1)
+    ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
+    acc = torch.zeros((C, D), dtype=torch.float32, device="cuda")
+    assert train(ctx, dev_u32(hv), torch.from_numpy(y).cuda(), acc, batch, 2) == goes(C, N, batch)
+    assert off(acc, want(hv, y, D, C, batch, 2)) < TOL
+    ctx.close()
+
+
+# 16384 samples are held at a time, 8192 at the largest D: products are made again every epoch
+@pytest.mark.parametrize("D,C,N,batch", [(96, 3, 16384 + 300, 0), (96, 3, 16384 + 300, 100), (65535, 2, 8192 + 40, 25)])
+def test_long_calls_of_more_samples_than_are_held(D, C, N, batch):
+    hv, y = packed(np.random.default_rng(D), N, D, C)
+    ctx = make_ctx(make_workload(1, D=D, C=C, F=3, L=2))
+    acc = torch.zeros((C, D), dtype=torch.float32, device="cuda")
+    assert train(ctx, dev_u32(hv), torch.from_numpy(y).cuda(), acc, batch, 2)
+    assert off(acc, want(hv, y, D, C, batch, 2)) < 1e-5   # n <= 11000: sqrt(n) 2^-23
+    ctx.close()
+
+
 # all samples of one class (its list runs through every row of lanes), hardly any valid, classes in runs
 @pytest.mark.parametrize("kind", ["one", "most", "few", "blocks"])
 @pytest.mark.parametrize("batch", [0, 40])

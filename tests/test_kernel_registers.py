@@ -46,6 +46,11 @@ def test_cosines_are_finished_by_eight_waves_a_simd(kernels):
         assert f["vgpr_count"] <= 64 and f["private_segment_fixed_size"] == 0, (name, f)
 
 
+def test_passes_of_online_training_by_samples_do_not_spill(kernels):
+    for name, f in of(kernels, r"online_spread_kernelILi\dELb0E").items():    # (in batches 18 and 49 registers do)
+        assert f["private_segment_fixed_size"] == 0 and f["vgpr_count"] <= 128, (name, f)
+
+
 def test_whole_block_walk_of_online_training_does_not_spill(kernels):
     for name, f in of(kernels, "online_wide_kernel").items():
         assert f["private_segment_fixed_size"] == 0 and f["vgpr_count"] <= 256, (name, f)
