@@ -329,7 +329,7 @@ __global__ __launch_bounds__(kDotWaves *kWave) void online_dots_kernel(const uin
                                                                        const float *__restrict__ acc, int D, int C,
                                                                        int slice, int slices, const int16_t *__restrict__ pairs,
                                                                        const OnlineWeight *__restrict__ recs, int before,
-                                                                       double *__restrict__ part, int span) {
+                                                                       double *__restrict__ part) {
     __shared__ __align__(16) double red[kDotWaves][256];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
     const int q = lane >> 4, i = lane & 15;
@@ -372,7 +372,7 @@ __global__ __launch_bounds__(kDotWaves *kWave) void online_dots_kernel(const uin
         double s = 0.0;
 #pragma unroll
         for (int w = 0; w < kDotWaves; ++w) s += red[w][(t & 15) * 16 + (t >> 4)];
-        if (cc < C && m < span) part[((int64_t)blockIdx.x * C + cc) * span + m] = s;
+        if (cc < C) part[((int64_t)blockIdx.x * C + cc) * kChainBlock + m] = s;
     }
 }
 
@@ -1398,7 +1398,7 @@ static int walk_held(hdc_ctx_impl *c, const int32_t *labels, int64_t N, float lr
             hipLaunchKernelGGL(online_dots_kernel,
                                dim3((unsigned)(slices + (ahead ? 1 : 0)), (unsigned)((nb + 15) / 16), (unsigned)((C + 15) / 16)),
                                dim3(kDotWaves * kWave), 0, s, col, ld, nb, acc, D, C, slice, slices,
-                               ahead ? c->oc_pairs_d + (b - 1) * kSubs * kSubs * kTile : nullptr, recs_before, block, c->oc_part_d, kChainBlock);
+                               ahead ? c->oc_pairs_d + (b - 1) * kSubs * kSubs * kTile : nullptr, recs_before, block, c->oc_part_d);
         }
         HDC_HIP(hipGetLastError());
         const ChainCall a = {b, slices, nb, batch, G, labels + b * block, lr, norm[*norm_at], ahead,
