@@ -166,8 +166,8 @@ int hdc_binarize_classical(hdc_ctx *ctx, const int32_t *acc_dev, const int64_t *
  * hdc_train_online_batched with batches of one sample (the same method).
  * Up to C = 64 and D = 65535, calls of more than a few samples are worked off in blocks of 256
  * samples, of more than 1024 samples and up to C = 32 in blocks of 2048: the chain is walked on the
- * samples' scalar products with one another and the dot products with the rows at the block's start,
- * then the updates are applied to the rows one by one.  The cosines then leave out the fp32 rounding
+ * samples' scalar products with one another and the dot products with the rows at the block's start
+ * (of 2048: over 512 dimensions rounded once, as in hdc_search_cosine), then the updates are applied to the rows one by one.  The cosines then leave out the fp32 rounding
  * of the updates of a row since the start of the block (of 256: or of the one before), u of them: as
  * a rule sqrt(u) * 2^-24 (largest seen 3e-8 at D = 10000, 6 classes; 3e-7 over D = 33 to 4096 from
  * zero rows; 4e-6 from rows of size 1e6; up to 6e-4 for a few while samples drive a row of many
@@ -194,7 +194,7 @@ int hdc_train_online(hdc_ctx *ctx, const uint32_t *hv_dev, const int32_t *labels
  *   delta[c] = sum over the batch of  +float(1 - cos_y) * s         for c == y
  *                                     -float(lr*(1 - cos_pred)) * s for c == pred != y
  * (fp64 sums) and acc[c] = float(double(acc[c]) + delta[c]), one rounding per element and
- * batch.  batch >= 1; a batch larger than N is one batch per epoch.  Small batches (up to 85 samples,
+ * batch.  The dot products of a batch of many samples are formed as in hdc_search_cosine.  batch >= 1; a batch larger than N is one batch per epoch.  Small batches (up to 85 samples,
  * fewer for few dimensions and for one or two classes; C <= 64, D <= 65535; up to 256 in calls of at least 1280
  * samples, C <= 32, that have 8 batches and 5 more per 2048 samples) are worked off several at a time as described for hdc_train_online.  Other arguments, layout
  * and the treatment of out-of-range labels are those of hdc_train_online.  The first call, and one

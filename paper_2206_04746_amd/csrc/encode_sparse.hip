@@ -141,8 +141,8 @@ __global__ __launch_bounds__(kListWaves *kWave) void sparse_lists_kernel(
 // takes five.  With 16 waves to a block and one block to a CU the first rows of b (`near`: what e
 // leaves of the 160 KB) lie in LDS as well, and the blocks of entries that name only these are bundled
 // from there, at the vector ALU's rate.  60000 samples, D = 10000, us with and without: 400 features
-// (all near) 270 and 306, 100 features 126 and 151, 784 with L = 64 464 and 493, with L = 256 (384 near)
-// 671 and 689.  (Every other wave far entries first, to use both paths at any time: 37 scalar registers
+// (all near) 267 and 303, 100 features 128 and 150, 784 with L = 64 471 and 491, with L = 256 (384 near)
+// 666 and 698, of which little is left (730 and 737 with the accumulation) where other kernels run in between.  (Every other wave far entries first, to use both paths at any time: 37 scalar registers
 // spilled and 784 us in place of 580 for the kernel.)
 constexpr int kNearWaves = 16;
 constexpr size_t kLds = 160 * 1024;

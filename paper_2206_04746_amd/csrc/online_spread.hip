@@ -3,15 +3,15 @@
 //
 // online_chain.hip tells how a block's chain is a triangular fixed point on the samples' scalar products with one
 // another.  How many passes it takes hardly depends on the block's length: five or six settle 2048 samples as they do
-// 256, because one sample moves the cosines of the others little (from rows of zeros 11 to 17; with a third of the labels
-// at random 8; with all of them, where predictions are mostly wrong, 140 to 170, which is fewer by the sample than blocks
-// of 256 take).  So a pass is spread over the chip and the block made long:
+// 256, because one sample moves the cosines of the others little (from rows of zeros 9 to 19, for 2 to 24 classes; with a third of
+// the labels at random 8 to 11, from zeros 14 to 26; with all of them, where predictions are mostly wrong, 170 to 270 for 6 classes, 67
+// for 24).  So a pass is spread over the chip and the block made long:
 //   online_gram_kernel   once per call: <s_n, s_m> of all pairs of a block, in strips of 16 columns
 //   row_dots_kernel      per block: <acc_c, s_m> against the rows as they stand
 //   online_spread_kernel per block: cosines, predictions and weights of all samples
 //   online_update_kernel per block: the updates, element by element in sample order, and the rows' squared norms
-// 7352 samples, 6 classes, D = 10000, us, with blocks of 256 on one workgroup and now: three epochs 2003 and 763, one in
-// batches of 64 879 and 449.  The rows come out as near the method in 64 bits: relative 2-norm 0.97e-7 to 1.39e-6 over ten models of
+// 7352 samples, 6 classes, D = 10000, us, with blocks of 256 on one workgroup and now: three epochs 2003 and 775, one in
+// batches of 64 879 and 450.  The rows come out as near the method in 64 bits: relative 2-norm 0.97e-7 to 1.39e-6 over ten models of
 // 2 to 16 classes, D = 500 to 4000, rows of up to 1e6 to begin with, between 1.6 % nearer and 0.5 % farther than blocks of 256.
 #include "online_lanes.h"
 
@@ -289,6 +289,7 @@ __device__ __forceinline__ void settle_own(SpreadShared &s, const double (&produ
 // one wave, 9 clocks each.  16 samples a workgroup, because a row of 16 lanes then holds one list's sources against all of them,
 // and 2048 samples are half the chip's compute units, one workgroup each for the products in LDS.  6 classes, D = 10000: 136 us for a
 // block from zero rows, 27 to 30 for one of settled rows, where eight blocks of 256 took 131 us.
+// In batches 18 vector registers (48 with two classes a wave) are in scratch; settled blocks take 37 to 60 us there.
 // Class c is wave (c + 8) % 16's: the first waves are busy with what they hear, the last one decides.
 template <int CPW, bool BATCH>
 __global__ __launch_bounds__(kThreads) void online_spread_kernel(const int16_t *__restrict__ strips, const double *__restrict__ part,
@@ -1132,7 +1133,7 @@ __global__ __launch_bounds__(kThreads) void online_update_kernel(const uint64_t 
     __syncthreads();
     uint32_t sign = 0x80000000u, one = BATCH ? 0x3FF00000u : 0x3F800000u;   // 1.0's upper word, 1.0f
     asm volatile("" : "+v"(sign), "+v"(one));   // (in registers: an instruction takes one constant at most)
-    const uint32_t inverse = ((1u << 20) + batch - 1) / batch;   // samples' batches: numbers below 2048, by up to 512
+    const uint32_t inverse = ((1u << 20) + batch - 1) / batch;   // samples' batches: numbers below 2048, divided by up to 256 (right up to 512)
     for (int c = wave; c < C; c += kWaves) {
         const int entries = __builtin_amdgcn_readlane(total, c);
         const uint2 *list = s.list + __builtin_amdgcn_readlane(end, c) - entries;
