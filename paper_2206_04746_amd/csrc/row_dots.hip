@@ -8,7 +8,7 @@
 // D = 10000: the fp64 form took 20 us, this 8 (cosine inference 25.6 and 14.8 with the finish).  What bounds it: bytes made of bits,
 // and a block's own digits before its first product.
 //
-// Digits hold an element whole if its last bit is no less than 2^-54 of the largest one's power of two: every element down to 2^-30
+// Digits hold an element whole if its last bit is no less than 2^-53 of the largest one's power of two: every element down to 2^-30
 // of the largest.  A row of a slice with one that they do not hold, or that is no number or infinite, is summed in fp64 on the
 // matrix cores instead: the same call with one such element takes 26 us, with one in every row of every slice 39 (26 classes: 33.8, 38
 // and 80, and 82 in the fp64 form).
